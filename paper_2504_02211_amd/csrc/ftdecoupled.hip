@@ -192,10 +192,8 @@ __global__ __launch_bounds__(256) void ftdec_transpose_v(const uint16_t* __restr
   }
 }
 
-__global__ void ftdec_reset(int32_t* counters, uint32_t* resmax, int n, unsigned long long* retried) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) { counters[i] = 0; resmax[i] = 0u; }
-  if (i == 0) *retried = 0ull;
+__global__ void ftdec_reset(int32_t* s_count, unsigned long long* retried) {
+  if (threadIdx.x == 0) { *s_count = 0; *retried = 0ull; }
 }
 
 }  // namespace ftdec
@@ -204,16 +202,20 @@ using namespace ftdec;
 
 struct ftdec_ctx {
   ftdec_config cfg;
-  int BH = 0, N = 0, Np = 0, d = 0, Tm = 0, Tn1 = 0;
+  int BH = 0, N = 0, Np = 0, d = 0, Tn1 = 0;
+  int slots1 = 0, slots2 = 0;    // report slots per head of the two GEMMs (allocated)
+  int used1 = 0, used2 = 0;      // ... in use by the last call
+  uint32_t ring_n = 0;
   // device
   float* S = nullptr;
   _Float16* P = nullptr;
   _Float16* vt = nullptr;
   uint16_t* wc1 = nullptr;       // [BH][Tn1][32][d]
   uint16_t* wc2 = nullptr;       // [BH][1][32][Np]
-  ftgemm_event* g_events = nullptr;   // [2*BH][cap]
-  int32_t* counters = nullptr;        // [2*BH] GEMM logs, [2*BH] the softmax log
-  uint32_t* resmax = nullptr;         // [2*BH + 1]
+  ftgemm_event* g_events = nullptr;   // [2*BH][ring_n] event rings of the GEMMs
+  uint32_t* cursors = nullptr;        // [2*BH]
+  ftgemm::GSlot* g_slots = nullptr;   // [BH][slots1], then [BH][slots2]
+  int32_t* s_count = nullptr;         // the softmax log's counter
   ftdec_event* s_events = nullptr;
   unsigned long long* retried = nullptr;
   ftgemm::GFault* d_gfaults = nullptr;
@@ -224,7 +226,7 @@ struct ftdec_ctx {
   int64_t bytes_total = 0, bytes_sp = 0;
   size_t softmax_lds = 0;
   std::vector<ftdec_event> events;
-  std::vector<int32_t> h_counters;
+  std::vector<ftgemm::GSlot> h_slots;
   std::vector<ftgemm_event> h_gev;
   hipStream_t last_stream = nullptr;
   bool ran = false, timing = false;
@@ -248,7 +250,7 @@ static int dfail(ftdec_ctx* c, int code, const std::string& msg) {
 static void drelease(ftdec_ctx* c) {
   if (!c) return;
   (void)hipFree(c->S); (void)hipFree(c->P); (void)hipFree(c->vt); (void)hipFree(c->wc1); (void)hipFree(c->wc2);
-  (void)hipFree(c->g_events); (void)hipFree(c->counters); (void)hipFree(c->resmax); (void)hipFree(c->s_events);
+  (void)hipFree(c->g_events); (void)hipFree(c->cursors); (void)hipFree(c->g_slots); (void)hipFree(c->s_count); (void)hipFree(c->s_events);
   (void)hipFree(c->retried); (void)hipFree(c->d_gfaults); (void)hipFree(c->d_sfaults);
   if (c->h_gfaults) (void)hipHostFree(c->h_gfaults);
   if (c->h_sfaults) (void)hipHostFree(c->h_sfaults);
@@ -282,8 +284,10 @@ extern "C" int ftdec_create(const ftdec_config* cfg, ftdec_ctx** out) {
   if (!(e.eps_dmr > 0.f)) e.eps_dmr = 1.0f / 4096.0f;
   if (e.max_events <= 0) e.max_events = 4096;
   c->BH = e.batch * e.heads; c->N = e.seq; c->Np = (e.seq + 7) & ~7; c->d = e.head_dim;
-  c->Tm = (c->N + ftgemm::GBM - 1) / ftgemm::GBM;
   c->Tn1 = (c->N + ftgemm::GBN - 1) / ftgemm::GBN;
+  c->slots1 = std::max(ftgemm::gemm_slots(c->N, c->N, ftgemm::gemm_plan(c->N, c->N, c->d, c->BH, false, false)), ftgemm::gemm_slots(c->N, c->N, ftgemm::gemm_plan(c->N, c->N, c->d, c->BH, true, false)));
+  c->slots2 = std::max(ftgemm::gemm_slots(c->N, c->d, ftgemm::gemm_plan(c->N, c->d, c->Np, c->BH, false, false)), ftgemm::gemm_slots(c->N, c->d, ftgemm::gemm_plan(c->N, c->d, c->Np, c->BH, true, false)));
+  c->ring_n = ftgemm::ring_size(e.max_events);
   c->fault_cap = 1 << 16;
   hipError_t he = hipSetDevice(e.device);
   if (he != hipSuccess) { int rc = dfail(nullptr, FTDEC_EHIP, std::string("hipSetDevice: ") + hipGetErrorString(he)); delete c; return rc; }
@@ -291,8 +295,8 @@ extern "C" int ftdec_create(const ftdec_config* cfg, ftdec_ctx** out) {
   struct { void** p; size_t bytes; bool sp; } allocs[] = {
       {(void**)&c->S, BH * N * N * 4, true}, {(void**)&c->P, BH * N * Np * 2, true}, {(void**)&c->vt, BH * d * Np * 2, false},
       {(void**)&c->wc1, BH * c->Tn1 * ftgemm::GCK * d * 2, false}, {(void**)&c->wc2, BH * ftgemm::GCK * Np * 2, false},
-      {(void**)&c->g_events, 2 * BH * cap * sizeof(ftgemm_event), false}, {(void**)&c->counters, (2 * BH + 1) * 4, false},
-      {(void**)&c->resmax, (2 * BH + 1) * 4, false}, {(void**)&c->s_events, cap * sizeof(ftdec_event), false},
+      {(void**)&c->g_events, 2 * BH * c->ring_n * sizeof(ftgemm_event), false}, {(void**)&c->cursors, 2 * BH * 4, false},
+      {(void**)&c->g_slots, BH * (c->slots1 + c->slots2) * sizeof(ftgemm::GSlot), false}, {(void**)&c->s_count, 4, false}, {(void**)&c->s_events, cap * sizeof(ftdec_event), false},
       {(void**)&c->retried, 8, false}, {(void**)&c->d_gfaults, sizeof(ftgemm::GFault) * c->fault_cap, false},
       {(void**)&c->d_sfaults, sizeof(SFault) * c->fault_cap, false}};
   for (auto& al : allocs) {
@@ -308,8 +312,8 @@ extern "C" int ftdec_create(const ftdec_config* cfg, ftdec_ctx** out) {
   }
   he = hipHostMalloc((void**)&c->h_gfaults, sizeof(ftgemm::GFault) * c->fault_cap, hipHostMallocDefault);
   if (he == hipSuccess) he = hipHostMalloc((void**)&c->h_sfaults, sizeof(SFault) * c->fault_cap, hipHostMallocDefault);
-  if (he == hipSuccess) he = ftgemm::gemm_allow_lds(c->d);
-  if (he == hipSuccess) he = ftgemm::gemm_allow_lds(c->Np);
+  if (he == hipSuccess) he = ftgemm::gemm_allow_lds(ftgemm::gemm_plan(N, N, d, c->BH, false, false), e.ft_mode != FTDEC_FT_OFF, e.in_dtype == FTDEC_BF16);
+  if (he == hipSuccess) he = ftgemm::gemm_allow_lds(ftgemm::gemm_plan(N, d, Np, c->BH, false, false), e.ft_mode != FTDEC_FT_OFF, false);
   // the softmax row is staged in LDS when it fits next to the reduction scratch
   c->softmax_lds = N * 4 <= 32 * 1024 ? N * 4 : 0;
   for (int v = 0; v < 4 && he == hipSuccess; ++v)
@@ -386,10 +390,11 @@ extern "C" int ftdec_forward(ftdec_ctx* c, const void* q, const void* k, const v
     DHIP_TRY(c, hipStreamSynchronize(st));     // the staging buffers may be rewritten by the next call
   }
 
-  const int n_cnt = 2 * BH + 1;
-  ftdec_reset<<<(n_cnt + 255) / 256, 256, 0, st>>>(c->counters, c->resmax, n_cnt, c->retried);
+  ftdec_reset<<<1, 64, 0, st>>>(c->s_count, c->retried);
   if (c->timing) DHIP_TRY(c, hipEventRecord(c->ev[0], st));
-  const size_t cap = e.max_events;
+  // (with a fault list every head runs the injecting tile shape, so that all slots have one stride)
+  const ftgemm::GPlan plan1 = ftgemm::gemm_plan(N, N, d, BH, n_g > 0, false), plan2 = ftgemm::gemm_plan(N, d, Np, BH, n_g > 0, false);
+  c->used1 = ftgemm::gemm_slots(N, N, plan1); c->used2 = ftgemm::gemm_slots(N, d, plan2);
   auto gemm_args = [&](int which, int bh) {
     ftgemm::GArgs a;
     std::memset(&a, 0, sizeof a);
@@ -398,10 +403,12 @@ extern "C" int ftdec_forward(ftdec_ctx* c, const void* q, const void* k, const v
     const int slot = which * BH + bh;
     a.faults = c->d_gfaults + g_off[slot];
     a.n_faults = g_off[slot + 1] - g_off[slot];
-    a.events = c->g_events + (size_t)slot * cap;
-    a.ev_count = c->counters + slot;
-    a.max_events = e.max_events;
-    a.resmax = c->resmax + slot;
+    a.events = c->g_events + (size_t)slot * c->ring_n;
+    a.cursor = c->cursors + slot;
+    a.ring_mask = c->ring_n - 1;
+    const int per_head = which ? c->used2 : c->used1;
+    a.slots = c->g_slots + (which ? (size_t)BH * c->slots1 : 0) + (size_t)bh * per_head;
+    if (!n_g) { a.bs_events = c->ring_n; a.bs_slots = per_head; }
     return a;
   };
 
@@ -415,13 +422,13 @@ extern "C" int ftdec_forward(ftdec_ctx* c, const void* q, const void* k, const v
     ftgemm::GArgs a = gemm_args(0, bh);
     a.x = q16 + (size_t)bh * N * d; a.w = k16 + (size_t)bh * N * d; a.wc = c->wc1 + (size_t)bh * wc1_stride;
     a.y = c->S + (size_t)bh * N * N;
-    a.M = N; a.N = N; a.K = d; a.Tm = c->Tm; a.Tn = c->Tn1;
+    a.M = N; a.N = N; a.K = d;
     if (!n_g) {
-      a.bs_x = a.bs_w = (long long)N * d; a.bs_wc = wc1_stride; a.bs_y_bytes = (long long)N * N * 4; a.bs_events = (long long)cap;
+      a.bs_x = a.bs_w = (long long)N * d; a.bs_wc = wc1_stride; a.bs_y_bytes = (long long)N * N * 4;
       a.skip_upper = e.causal;      // score tiles above the diagonal are never read by the softmax (with a fault
                                     // list the matrix is computed in full: a fault may name any score)
     }
-    DHIP_TRY(c, ftgemm::gemm_launch(a, ft, a.n_faults > 0, bf, st, n_g ? 1 : BH));
+    DHIP_TRY(c, ftgemm::gemm_launch(a, ft, n_g > 0, bf, plan1, st, n_g ? 1 : BH));
   }
   if (c->timing) DHIP_TRY(c, hipEventRecord(c->ev[1], st));
 
@@ -433,7 +440,7 @@ extern "C" int ftdec_forward(ftdec_ctx* c, const void* q, const void* k, const v
     a.eps = e.eps_dmr;
     a.use_lds = c->softmax_lds ? 1 : 0;
     a.faults = c->d_sfaults; a.n_faults = n_s;
-    a.events = c->s_events; a.ev_count = c->counters + 2 * BH; a.max_events = e.max_events;
+    a.events = c->s_events; a.ev_count = c->s_count; a.max_events = e.max_events;
     a.retried = c->retried;
     hipLaunchKernelGGL(select_softmax(ft, n_s > 0), dim3(N, BH), dim3(256), c->softmax_lds, st, a);
     DHIP_TRY(c, hipGetLastError());
@@ -451,13 +458,12 @@ extern "C" int ftdec_forward(ftdec_ctx* c, const void* q, const void* k, const v
     ftgemm::GArgs a = gemm_args(1, bh);
     a.x = p16 + (size_t)bh * N * Np; a.w = vt16 + (size_t)bh * d * Np; a.wc = c->wc2 + (size_t)bh * wc2_stride;
     a.y = reinterpret_cast<float*>(o) + (size_t)bh * N * d;
-    a.M = N; a.N = d; a.K = Np; a.Tm = c->Tm; a.Tn = 1;
+    a.M = N; a.N = d; a.K = Np;
     if (!n_g) {
       a.bs_x = (long long)N * Np; a.bs_w = (long long)d * Np; a.bs_wc = wc2_stride; a.bs_y_bytes = (long long)N * d * 4;
-      a.bs_events = (long long)cap;
       a.k_lower = e.causal;         // P is lower-triangular: keys beyond a tile's last query contribute nothing
     }
-    DHIP_TRY(c, ftgemm::gemm_launch(a, ft, a.n_faults > 0, false, st, n_g ? 1 : BH));
+    DHIP_TRY(c, ftgemm::gemm_launch(a, ft, n_g > 0, false, plan2, st, n_g ? 1 : BH));
   }
   if (c->timing) DHIP_TRY(c, hipEventRecord(c->ev[3], st));
   c->last_stream = st;
@@ -472,24 +478,27 @@ extern "C" int ftdec_report(ftdec_ctx* c, ftdec_report_view* out) {
   DHIP_TRY(c, hipSetDevice(e.device));
   DHIP_TRY(c, hipStreamSynchronize(c->last_stream));
   const int BH = c->BH, cap = e.max_events;
-  c->h_counters.resize(2 * (size_t)BH + 1);
-  DHIP_TRY(c, hipMemcpy(c->h_counters.data(), c->counters, c->h_counters.size() * 4, hipMemcpyDeviceToHost));
   unsigned long long retried = 0;
   DHIP_TRY(c, hipMemcpy(&retried, c->retried, 8, hipMemcpyDeviceToHost));
   c->events.clear();
   int dropped = 0;
-  for (int slot = 0; slot < 2 * BH; ++slot) {
-    const int count = c->h_counters[slot], stored = std::min(count, cap);
-    dropped += count - stored;
-    if (!stored) continue;
-    c->h_gev.resize(stored);
-    DHIP_TRY(c, hipMemcpy(c->h_gev.data(), c->g_events + (size_t)slot * cap, sizeof(ftgemm_event) * stored, hipMemcpyDeviceToHost));
-    const int bh = slot % BH;
-    for (const ftgemm_event& g : c->h_gev)
-      c->events.push_back(ftdec_event{bh / e.heads, bh % e.heads, slot < BH ? FTDEC_ST_GEMM1 : FTDEC_ST_GEMM2, g.row, g.col, g.action});
+  for (int which = 0; which < 2; ++which) {
+    const int per_head = which ? c->used2 : c->used1;
+    c->h_slots.resize((size_t)BH * per_head);
+    DHIP_TRY(c, hipMemcpy(c->h_slots.data(), c->g_slots + (which ? (size_t)BH * c->slots1 : 0), c->h_slots.size() * sizeof(ftgemm::GSlot), hipMemcpyDeviceToHost));
+    for (int bh = 0; bh < BH; ++bh) {
+      const ftgemm::GSlot* sl = c->h_slots.data() + (size_t)bh * per_head;
+      c->h_gev.clear();
+      DHIP_TRY(c, ftgemm::gemm_fetch_events(sl, per_head, c->g_events + ((size_t)which * BH + bh) * c->ring_n, c->ring_n, cap, c->h_gev));
+      dropped += (int)(ftgemm::gemm_stats(sl, per_head).events - (long long)c->h_gev.size());
+      for (const ftgemm_event& g : c->h_gev)
+        c->events.push_back(ftdec_event{bh / e.heads, bh % e.heads, which ? FTDEC_ST_GEMM2 : FTDEC_ST_GEMM1, g.row, g.col, g.action});
+    }
   }
   {
-    const int count = c->h_counters[2 * BH], stored = std::min(count, cap);
+    int32_t count = 0;
+    DHIP_TRY(c, hipMemcpy(&count, c->s_count, sizeof count, hipMemcpyDeviceToHost));
+    const int stored = std::min(count, cap);
     dropped += count - stored;
     const size_t base = c->events.size();
     c->events.resize(base + stored);

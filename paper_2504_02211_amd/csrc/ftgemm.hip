@@ -4,6 +4,7 @@
 #include "ftgemm_main.h"
 
 #include <algorithm>
+#include <cmath>
 #include <cstdio>
 #include <cstring>
 #include <new>
@@ -14,13 +15,18 @@ using namespace ftgemm;
 
 struct ftgemm_ctx {
   ftgemm_config cfg;          // effective configuration
-  int Tm = 0, Tn = 0;
+  int Tn = 0;
+  void* scratch = nullptr;    // the device buffers below, in one allocation
   uint16_t* wc = nullptr;     // [Tn][32][k] checksum rows of the weights (input type)
   const void* encoded_w = nullptr;
   GFault* d_faults = nullptr;
-  ftgemm_event* d_events = nullptr;
-  int32_t* d_ev_count = nullptr;
-  uint32_t* d_resmax = nullptr;
+  ftgemm_event* d_events = nullptr;   // ring, never cleared: the slots say which entries a call wrote
+  uint32_t* d_cursor = nullptr;
+  GSlot* d_slots = nullptr;
+  float4v* ws = nullptr;              // shares of a split contraction
+  uint32_t ring_n = 0;
+  int n_slots = 0, last_slots = 0;
+  std::vector<GSlot> slots;
   GFault* h_faults = nullptr; // pinned staging
   int fault_cap = 0;
   std::vector<ftgemm_event> events;
@@ -47,47 +53,125 @@ static int gfail(ftgemm_ctx* c, int code, const std::string& msg) {
 
 static void grelease(ftgemm_ctx* c) {
   if (!c) return;
-  (void)hipFree(c->wc); (void)hipFree(c->d_faults); (void)hipFree(c->d_events);
-  (void)hipFree(c->d_ev_count); (void)hipFree(c->d_resmax);
+  (void)hipFree(c->scratch);
   if (c->h_faults) (void)hipHostFree(c->h_faults);
   for (hipEvent_t e : c->ev) if (e) (void)hipEventDestroy(e);
   delete c;
 }
 
-typedef void (*gemm_fn)(const GArgs);
-
-template <bool BF, bool RAG> static gemm_fn select_gemm_t(bool ft, bool inject) {
-  if (ft) return inject ? ftgemm_main<true, true, BF, RAG> : ftgemm_main<true, false, BF, RAG>;
-  return inject ? ftgemm_main<false, true, BF, RAG> : ftgemm_main<false, false, BF, RAG>;
-}
-// ragged: k is not a multiple of the kernel's K step
-static gemm_fn select_gemm(bool ft, bool inject, bool bf, bool ragged) {
-  if (ragged) return bf ? select_gemm_t<true, true>(ft, inject) : select_gemm_t<false, true>(ft, inject);
-  return bf ? select_gemm_t<true, false>(ft, inject) : select_gemm_t<false, false>(ft, inject);
-}
-static size_t gemm_lds(bool ft) { return ft ? GStage<true>::LDS_TOTAL : GStage<false>::LDS_TOTAL; }
-
 namespace ftgemm {
-hipError_t gemm_allow_lds(int k) {
-  for (int v = 0; v < 8; ++v) {
-    hipError_t he = hipFuncSetAttribute((const void*)select_gemm((v & 1) != 0, (v & 2) != 0, (v & 4) != 0, k % GBK != 0),
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)gemm_lds((v & 1) != 0));
+
+template <class T> static constexpr TileInfo info_of() { return TileInfo{T::BM, T::BF, T::NW * 64, {T::template lds<false>(), T::template lds<true>()}}; }
+static constexpr TileInfo TILES[N_TILES] = {info_of<TileWide>(), info_of<TileHalf>(), info_of<TileQuarter>(),
+                                            info_of<TileStrip>(), info_of<TileNarrow>(), info_of<TileSlim>()};
+
+static gemm_fn tile_kernel(int tile, bool ft, bool inject, bool bf16) {
+  return bf16 ? tile_kernel_bf16(tile, ft, inject) : tile_kernel_f16(tile, ft, inject);
+}
+
+hipError_t gemm_allow_lds(GPlan plan, bool ft, bool bf16) {
+  for (int inject = 0; inject < 2; ++inject) {
+    const int tile = inject ? (int)TILE_QUARTER : plan.tile;
+    hipError_t he = hipFuncSetAttribute((const void*)tile_kernel(tile, ft, inject != 0, bf16), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                        TILES[tile].lds[ft]);
     if (he != hipSuccess) return he;
   }
   return hipSuccess;
 }
+
 hipError_t gemm_launch_encode_w(const uint16_t* w, uint16_t* wc, int n, int k, bool bf16, hipStream_t st, int batch,
                                 long long bs_w, long long bs_wc) {
-  dim3 grid((n + GBN - 1) / GBN, (k / 8 + 31) / 32, batch);
+  dim3 grid((n + GBN - 1) / GBN, (k / 8 + 7) / 8, batch);
   if (bf16) ftgemm_encode_w<true><<<grid, 256, 0, st>>>(w, wc, n, k, bs_w, bs_wc);
   else ftgemm_encode_w<false><<<grid, 256, 0, st>>>(w, wc, n, k, bs_w, bs_wc);
   return hipGetLastError();
 }
-hipError_t gemm_launch(const GArgs& a, bool ft, bool inject, bool bf16, hipStream_t st, int batch) {
-  gemm_fn f = select_gemm(ft, inject, bf16, a.K % GBK != 0);
-  hipLaunchKernelGGL(f, dim3(a.Tm * a.Tn, batch), dim3(GWAVES * 64), gemm_lds(ft), st, a);
+
+int gemm_slots(long long m, long long n, GPlan plan) {
+  const int bm = plan.parts > 1 ? TileFinish::BM : TILES[plan.tile].bm;
+  return (int)((m + bm - 1) / bm * ((n + GBN - 1) / GBN));
+}
+
+static int ws_tokens_of(long long m, GPlan plan) {
+  const int bm = TILES[plan.tile].bm;
+  return (int)((m + bm - 1) / bm * (bm / 16));
+}
+
+size_t gemm_workspace(long long m, long long n, GPlan plan) {
+  if (plan.parts <= 1) return 0;
+  return (size_t)plan.parts * ws_tokens_of(m, plan) * ((n + GBN - 1) / GBN) * WS_BLOCKS * 64 * sizeof(float4v);
+}
+
+// The tile shape and the split of K with the least expected time.  Microseconds, from timings of every
+// shape at 1..16384 tokens, 64..16384 features, K 64..8192: a round of tiles (one per CU) costs `fixed` and
+// `step` per 64 columns of K, the latter up to (1 + load) times as much when every CU is busy (L2 traffic,
+// power); a split adds the second launch and a pass of the shares through memory.  Wide tiles move the
+// fewest bytes per product, narrow ones fill the chip: 4096^3 takes 136 / 152 / 188 / 257 us with tiles of
+// 256 / 128 / 64 / 32 tokens, 1024 x 1024 x 1024 takes 31 / 23 / 17 / 13, 128 x 1024 x 8192 takes
+// 161 / 110 / 70 / 56 unsplit and 18.5 with 32-token tiles split eight ways.
+GPlan gemm_plan(long long m, long long n, long long k, int batch, bool inject, bool may_split) {
+  if (inject) return {TILE_QUARTER, 1};
+  if (n <= 64) return {TILE_SLIM, 1};
+  if (n <= 128) return {TILE_NARROW, 1};
+  static constexpr struct { int tile; double fixed, step, load; } COST[] = {
+      {TILE_WIDE, 5.5, 1.18, 0.67}, {TILE_HALF, 3.7, 0.8, 0.36}, {TILE_QUARTER, 2.5, 0.5, 0.36}, {TILE_STRIP, 1.5, 0.4, 0.18}};
+  constexpr double CUS = 256.0, LAUNCH = 4.5, MEMORY = 5e6;           // bytes per microsecond
+  const long long steps = (k + 63) / 64, tn = (n + GBN - 1) / GBN;
+  GPlan best{TILE_WIDE, 1};
+  double best_us = 0.0;
+  for (const auto& c : COST)
+    for (int parts = 1; parts <= 16 && (parts == 1 || (may_split && 2 * parts <= steps)); parts *= 2) {
+      const GPlan plan{c.tile, parts};
+      const double groups = (double)((m + TILES[c.tile].bm - 1) / TILES[c.tile].bm * tn) * batch * parts;
+      const double rounds = std::ceil(groups / CUS), busy = std::min(1.0, groups / CUS);
+      double us = LAUNCH + rounds * (c.fixed + (double)((steps + parts - 1) / parts) * c.step * (1.0 + c.load * busy));
+      if (parts > 1) us += LAUNCH + 2.0 * (double)gemm_workspace(m, n, plan) / MEMORY;
+      if (best_us == 0.0 || us < best_us) { best = plan; best_us = us; }
+    }
+  return best;
+}
+
+hipError_t gemm_launch(GArgs a, bool ft, bool inject, bool bf16, GPlan plan, hipStream_t st, int batch) {
+  const TileInfo& ti = TILES[plan.tile];
+  a.Tm = (a.M + ti.bm - 1) / ti.bm;
+  a.Tn = (a.N + GBN - 1) / GBN;
+  a.parts = plan.parts;
+  a.ws_tokens = ws_tokens_of(a.M, plan);
+  hipLaunchKernelGGL(tile_kernel(plan.tile, ft, inject, bf16), dim3(a.Tm * a.Tn, batch, plan.parts), dim3(ti.threads), ti.lds[ft], st, a);
+  hipError_t he = hipGetLastError();
+  if (he != hipSuccess || plan.parts <= 1) return he;
+  hipLaunchKernelGGL((bf16 ? finish_kernel_bf16 : finish_kernel_f16)(ft), dim3((a.M + TileFinish::BM - 1) / TileFinish::BM * a.Tn),
+                     dim3(TileFinish::NW * 64), ft ? TileFinish::lds<true>() : TileFinish::lds<false>(), st, a);
   return hipGetLastError();
 }
+
+GStats gemm_stats(const GSlot* slots, int n_slots) {
+  GStats s{0, 0.f};
+  for (int i = 0; i < n_slots; ++i) { s.events += slots[i].n; s.stat = std::max(s.stat, slots[i].stat); }
+  return s;
+}
+
+hipError_t gemm_fetch_events(const GSlot* slots, int n_slots, const ftgemm_event* ring, uint32_t ring_n, int max_events,
+                             std::vector<ftgemm_event>& out) {
+  const GStats st = gemm_stats(slots, n_slots);
+  if (!st.events) return hipSuccess;
+  std::vector<ftgemm_event> all(ring_n);
+  hipError_t he = hipMemcpy(all.data(), ring, sizeof(ftgemm_event) * ring_n, hipMemcpyDeviceToHost);
+  if (he != hipSuccess) return he;
+  // end of this call's entries: the runs of a call are contiguous as a whole, counted without wrapping
+  bool any = false;
+  uint32_t end = 0;
+  for (int i = 0; i < n_slots; ++i)
+    if (slots[i].n) {
+      const uint32_t e = slots[i].first + (uint32_t)slots[i].n;
+      if (!any || (int32_t)(e - end) > 0) end = e;
+      any = true;
+    }
+  const uint32_t keep = (uint32_t)std::min<long long>(std::min<long long>(st.events, max_events), ring_n);
+  for (uint32_t at = end - keep; at != end; ++at) out.push_back(all[at & (ring_n - 1)]);
+  return hipSuccess;
+}
+
 }  // namespace ftgemm
 
 extern "C" int ftgemm_create(const ftgemm_config* cfg, ftgemm_ctx** out) {
@@ -104,8 +188,8 @@ extern "C" int ftgemm_create(const ftgemm_config* cfg, ftgemm_ctx** out) {
   if (cfg->fold_tokens != 0 && cfg->fold_tokens != 1) return gfail(nullptr, FTGEMM_EINVAL, "fold_tokens must be 0 or 1");
   // with fold_tokens the kernel runs the transposed problem: its tokens are the weight rows, its features the token rows
   const long long km = cfg->fold_tokens ? cfg->n : cfg->m, kn = cfg->fold_tokens ? cfg->m : cfg->n;
-  const long long tm = (km + GBM - 1) / GBM, tn = (kn + GBN - 1) / GBN;
-  if (tm * tn > 0x7FFFFFFFll) return gfail(nullptr, FTGEMM_EUNSUPPORTED, "too many output tiles");
+  const long long tn = (kn + GBN - 1) / GBN;
+  if ((km + TILES[TILE_STRIP].bm - 1) / TILES[TILE_STRIP].bm * tn > 0x7FFFFFFFll) return gfail(nullptr, FTGEMM_EUNSUPPORTED, "too many output tiles");
   // the per-lane load offsets are 32-bit: 256 rows of k fp16 values must fit
   if ((long long)cfg->k * 2 * 256 > 0x7FFFFFFFll) return gfail(nullptr, FTGEMM_EUNSUPPORTED, "k too large");
 
@@ -118,7 +202,6 @@ extern "C" int ftgemm_create(const ftgemm_config* cfg, ftgemm_ctx** out) {
   if (!(e.tau_rel > 0.f)) e.tau_rel = 1.0f / 32768.0f;
   if (!(e.tau_abs >= 0.f)) e.tau_abs = 0.f;
   if (e.max_events <= 0) e.max_events = 65536;
-  c->Tm = (int)tm;
   c->Tn = (int)tn;
   c->fault_cap = 1 << 16;
 
@@ -134,17 +217,22 @@ extern "C" int ftgemm_create(const ftgemm_config* cfg, ftgemm_ctx** out) {
       return rc_;                                                                                         \
     }                                                                                                     \
   } while (0)
-  const size_t n_wc = (size_t)c->Tn * GCK * e.k;
-  GCREATE_TRY(hipMalloc((void**)&c->wc, n_wc * 2));
-  GCREATE_TRY(hipMalloc((void**)&c->d_faults, sizeof(GFault) * c->fault_cap));
-  GCREATE_TRY(hipMalloc((void**)&c->d_events, sizeof(ftgemm_event) * (size_t)e.max_events));
-  GCREATE_TRY(hipMalloc((void**)&c->d_ev_count, sizeof(int32_t)));
-  GCREATE_TRY(hipMalloc((void**)&c->d_resmax, sizeof(uint32_t)));
+  c->ring_n = ring_size(e.max_events);
+  const GPlan plan = gemm_plan(km, kn, e.k, 1, false, true);
+  c->n_slots = std::max(gemm_slots(km, kn, plan), gemm_slots(km, kn, gemm_plan(km, kn, e.k, 1, true, false)));
+  // one allocation for all of the device scratch: each hipMalloc costs tens of microseconds.  Only the
+  // cursor has to start from a value: checksum rows are written before they are read.
+  struct { void** at; size_t bytes, from; } parts[] = {
+      {(void**)&c->wc, (size_t)c->Tn * GCK * e.k * 2, 0}, {(void**)&c->d_faults, sizeof(GFault) * c->fault_cap, 0},
+      {(void**)&c->d_events, sizeof(ftgemm_event) * (size_t)c->ring_n, 0}, {(void**)&c->d_cursor, sizeof(uint32_t), 0},
+      {(void**)&c->d_slots, sizeof(GSlot) * (size_t)c->n_slots, 0}, {(void**)&c->ws, gemm_workspace(km, kn, plan), 0}};
+  size_t total = 0;
+  for (auto& p : parts) { p.from = total; total += (p.bytes + 255) & ~(size_t)255; }
+  GCREATE_TRY(hipMalloc(&c->scratch, total));
+  for (auto& p : parts) *p.at = static_cast<char*>(c->scratch) + p.from;
   GCREATE_TRY(hipHostMalloc((void**)&c->h_faults, sizeof(GFault) * c->fault_cap, hipHostMallocDefault));
-  GCREATE_TRY(hipMemset(c->wc, 0, n_wc * 2));
-  GCREATE_TRY(hipMemset(c->d_ev_count, 0, sizeof(int32_t)));
-  GCREATE_TRY(hipMemset(c->d_resmax, 0, sizeof(uint32_t)));
-  GCREATE_TRY(gemm_allow_lds(e.k));
+  GCREATE_TRY(hipMemset(c->d_cursor, 0, sizeof(uint32_t)));
+  GCREATE_TRY(gemm_allow_lds(plan, e.ft_mode != FTGEMM_FT_OFF, e.in_dtype == FTGEMM_BF16));
   GCREATE_TRY(hipDeviceSynchronize());
 #undef GCREATE_TRY
   *out = c;
@@ -164,10 +252,7 @@ extern "C" int ftgemm_encode_weights(ftgemm_ctx* c, const void* w, void* hip_str
   if (e.fold_tokens) return FTGEMM_OK;      // the checksums are those of x, taken inside every forward
   GHIP_TRY(c, hipSetDevice(e.device));
   hipStream_t st = (hipStream_t)hip_stream;
-  dim3 grid(c->Tn, (e.k / 8 + 31) / 32);
-  if (e.in_dtype == FTGEMM_BF16) ftgemm_encode_w<true><<<grid, 256, 0, st>>>(reinterpret_cast<const uint16_t*>(w), c->wc, e.n, e.k);
-  else ftgemm_encode_w<false><<<grid, 256, 0, st>>>(reinterpret_cast<const uint16_t*>(w), c->wc, e.n, e.k);
-  GHIP_TRY(c, hipGetLastError());
+  GHIP_TRY(c, gemm_launch_encode_w(reinterpret_cast<const uint16_t*>(w), c->wc, e.n, e.k, e.in_dtype == FTGEMM_BF16, st));
   c->encoded_w = w;
   return FTGEMM_OK;
 }
@@ -198,34 +283,29 @@ extern "C" int ftgemm_forward(ftgemm_ctx* c, const void* x, const void* w, void*
     GHIP_TRY(c, hipMemcpyAsync(c->d_faults, c->h_faults, sizeof(GFault) * n_faults, hipMemcpyHostToDevice, st));
     GHIP_TRY(c, hipStreamSynchronize(st));   // the staging buffer may be rewritten by the next call
   }
-  ftgemm_reset<<<1, 64, 0, st>>>(c->d_ev_count, c->d_resmax);
-
-  if (ft && tr) {
-    // tensor checksums of this call's token rows (eq. (13), (14) on x)
-    dim3 grid(c->Tn, (e.k / 8 + 31) / 32);
-    if (e.in_dtype == FTGEMM_BF16) ftgemm_encode_w<true><<<grid, 256, 0, st>>>(reinterpret_cast<const uint16_t*>(x), c->wc, e.m, e.k);
-    else ftgemm_encode_w<false><<<grid, 256, 0, st>>>(reinterpret_cast<const uint16_t*>(x), c->wc, e.m, e.k);
-    GHIP_TRY(c, hipGetLastError());
-  }
+  const bool bf = e.in_dtype == FTGEMM_BF16;
+  // fold_tokens: tensor checksums of this call's token rows (eq. (13), (14) on x)
+  if (ft && tr) GHIP_TRY(c, gemm_launch_encode_w(reinterpret_cast<const uint16_t*>(x), c->wc, e.m, e.k, bf, st));
   GArgs a;
   a.x = reinterpret_cast<const uint16_t*>(tr ? w : x);
   a.w = reinterpret_cast<const uint16_t*>(tr ? x : w);
   a.wc = c->wc;
   a.y = y; a.out_dtype = e.out_dtype;
-  a.M = tr ? e.n : e.m; a.N = tr ? e.m : e.n; a.K = e.k; a.Tm = c->Tm; a.Tn = c->Tn;
+  a.M = tr ? e.n : e.m; a.N = tr ? e.m : e.n; a.K = e.k; a.Tm = a.Tn = 0;
   a.transposed = tr ? 1 : 0;
-  a.bs_x = a.bs_w = a.bs_wc = a.bs_y_bytes = a.bs_events = 0;
+  a.bs_x = a.bs_w = a.bs_wc = a.bs_y_bytes = a.bs_events = a.bs_slots = 0;
   a.skip_upper = 0; a.k_lower = 0;
   a.tau_rel = e.tau_rel; a.tau_abs = e.tau_abs;
   a.correct = e.ft_mode == FTGEMM_FT_CORRECT ? 1 : 0;
   a.faults = c->d_faults; a.n_faults = n_faults;
-  a.events = c->d_events; a.ev_count = c->d_ev_count; a.max_events = e.max_events;
-  a.resmax = c->d_resmax;
-  gemm_fn f = select_gemm(ft, n_faults > 0, e.in_dtype == FTGEMM_BF16, e.k % GBK != 0);
+  a.events = c->d_events; a.cursor = c->d_cursor; a.ring_mask = c->ring_n - 1;
+  a.slots = c->d_slots;
+  a.ws = c->ws;
+  const GPlan plan = gemm_plan(a.M, a.N, a.K, 1, n_faults > 0, true);
   if (c->timing) GHIP_TRY(c, hipEventRecord(c->ev[0], st));
-  hipLaunchKernelGGL(f, dim3(c->Tm * c->Tn), dim3(GWAVES * 64), gemm_lds(ft), st, a);
-  GHIP_TRY(c, hipGetLastError());
+  GHIP_TRY(c, gemm_launch(a, ft, n_faults > 0, bf, plan, st));
   if (c->timing) GHIP_TRY(c, hipEventRecord(c->ev[1], st));
+  c->last_slots = gemm_slots(a.M, a.N, plan);
   c->last_stream = st;
   c->ran = true;
   return FTGEMM_OK;
@@ -237,23 +317,19 @@ extern "C" int ftgemm_report(ftgemm_ctx* c, ftgemm_report_view* out) {
   const ftgemm_config& e = c->cfg;
   GHIP_TRY(c, hipSetDevice(e.device));
   GHIP_TRY(c, hipStreamSynchronize(c->last_stream));
-  int32_t count = 0;
-  uint32_t rm = 0;
-  GHIP_TRY(c, hipMemcpy(&count, c->d_ev_count, sizeof count, hipMemcpyDeviceToHost));
-  GHIP_TRY(c, hipMemcpy(&rm, c->d_resmax, sizeof rm, hipMemcpyDeviceToHost));
-  const int stored = std::min(count, e.max_events);
-  c->events.resize(stored);
-  if (stored) GHIP_TRY(c, hipMemcpy(c->events.data(), c->d_events, sizeof(ftgemm_event) * stored, hipMemcpyDeviceToHost));
+  c->slots.resize(c->last_slots);
+  GHIP_TRY(c, hipMemcpy(c->slots.data(), c->d_slots, sizeof(GSlot) * c->slots.size(), hipMemcpyDeviceToHost));
+  const GStats stats = gemm_stats(c->slots.data(), (int)c->slots.size());
+  c->events.clear();
+  GHIP_TRY(c, gemm_fetch_events(c->slots.data(), (int)c->slots.size(), c->d_events, c->ring_n, e.max_events, c->events));
   std::sort(c->events.begin(), c->events.end(), [](const ftgemm_event& p, const ftgemm_event& q) {
     if (p.row != q.row) return p.row < q.row;
     return p.col < q.col;
   });
-  out->n_events = stored;
-  out->n_events_dropped = count - stored;
+  out->n_events = (int32_t)c->events.size();
+  out->n_events_dropped = (int32_t)(stats.events - (long long)c->events.size());
   out->events = c->events.data();
-  float rmf;
-  std::memcpy(&rmf, &rm, sizeof rmf);
-  out->residual_max = rmf;
+  out->residual_max = stats.stat;
   return FTGEMM_OK;
 }
 

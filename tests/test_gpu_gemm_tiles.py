@@ -1,0 +1,81 @@
+"""Every tile shape and the split of the K dimension of the linear layer's kernel, at sizes with
+remainders in tokens, features and K.  Verification is exercised without the injector: one element of
+one weight row is changed after its checksums were taken, which shifts one output of every token by a
+known amount; every token must be reported at that column and restored from the checksum of the
+unchanged weights.  Reference: the product in fp64 on the device.  Tolerance as in test_gpu_gemm.py:
+fp32 accumulation over k <= 4096 terms of outputs of order one, 1e-4; a value restored from bf16 words
+(16 bits) 4e-3."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_2504_02211_amd import ftgemm
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [(1, 70, 72), (130, 33, 200),              # all features in one narrow tile
+          (37, 1000, 1024), (40, 601, 2056),        # 32-token tiles, K split over workgroups
+          (700, 1000, 1024), (31, 300, 64),         # 32-token tiles
+          (2049, 1030, 72), (2000, 1999, 512),      # 64-token tiles
+          (1000, 8000, 136),                        # 128-token tiles
+          (4097, 2050, 264), (3000, 3000, 72)]      # 256-token tiles
+
+
+@pytest.mark.parametrize("m,n,k", SHAPES)
+@pytest.mark.parametrize("dtype,fold", [(ftgemm.F16, False), (ftgemm.BF16, True)])
+def test_tile_shapes(m, n, k, dtype, fold):
+    print(f"[gemm tiles] m={m} n={n} k={k} dtype={dtype} fold_tokens={fold}", flush=True)
+    tt = torch.float16 if dtype == ftgemm.F16 else torch.bfloat16
+    g = torch.Generator(device="cuda")
+    g.manual_seed(m + 3 * n + 7 * k)
+    x = torch.randn((m, k), generator=g, device="cuda").to(tt)
+    w = (torch.randn((n, k), generator=g, device="cuda") * k ** -0.5).to(tt)
+    for out in (ftgemm.F32, dtype):
+        y = torch.full((m, n), float("nan"), dtype=torch.float32 if out == ftgemm.F32 else tt, device="cuda")
+        ctx = ftgemm.FtGemm(m, n, k, out_dtype=out, in_dtype=dtype, fold_tokens=fold)
+        ctx.encode_weights(w)
+        ctx.forward(x, w, y)
+        rep = ctx.report()
+        ctx.close()
+        want = x.double() @ w.double().t()
+        tol = 1e-4 if out == ftgemm.F32 else (2.0 ** -10 if dtype == ftgemm.F16 else 2.0 ** -7)
+        assert rep.n_events == 0 and rep.n_events_dropped == 0
+        assert bool(((y.double() - want).abs() <= tol * want.abs().clamp(min=1.0)).all())
+
+
+@pytest.mark.parametrize("m,n,k", SHAPES)
+@pytest.mark.parametrize("dtype,correct", [(ftgemm.F16, True), (ftgemm.BF16, True), (ftgemm.F16, False)])
+def test_location_and_repair_in_every_tile_shape(m, n, k, dtype, correct):
+    print(f"[gemm tiles repair] m={m} n={n} k={k} dtype={dtype} correct={correct}", flush=True)
+    tt = torch.float16 if dtype == ftgemm.F16 else torch.bfloat16
+    g = torch.Generator(device="cuda")
+    g.manual_seed(m + 5 * n + 11 * k)
+    x = torch.randn((m, k), generator=g, device="cuda").to(tt)
+    x[:, 3] = 1.0
+    w = (torch.randn((n, k), generator=g, device="cuda") * k ** -0.5).to(tt)
+    want = x.double() @ w.double().t()
+    y = torch.full((m, n), float("nan"), dtype=torch.float32, device="cuda")
+    ctx = ftgemm.FtGemm(m, n, k, in_dtype=dtype, ft_mode=ftgemm.FT_CORRECT if correct else ftgemm.FT_DETECT)
+    ctx.encode_weights(w)
+    cols = sorted({0, n // 2, n - 1})
+    for col in cols:
+        was = w[col, 3].clone()
+        w[col, 3] = was + 8.0                                  # every output of this feature moves by 8 (exact to the type's rounding)
+        shift = float(w[col, 3].double() - was.double())
+        ctx.forward(x, w, y)
+        rep = ctx.report()
+        w[col, 3] = was
+        assert rep.n_events_dropped == 0
+        assert rep.event_list() == [(r, col, int(correct)) for r in range(m)]
+        expect = want.clone()
+        if not correct:
+            expect[:, col] += shift
+        err = (y.double() - expect).abs()
+        assert float(err.max()) <= (1e-4 if dtype == ftgemm.F16 else 4e-3)
+    # the same context without a fault: nothing of the earlier calls is left in its report
+    ctx.forward(x, w, y)
+    rep = ctx.report()
+    ctx.close()
+    assert rep.n_events == 0 and float((y.double() - want).abs().max()) <= 1e-4
+    assert np.isfinite(rep.residual_max)
