@@ -281,6 +281,7 @@ static hipError_t launch_pass(const ftattn_config& e, const Geometry& g, const B
   KArgs a;
   a.q = q; a.q_bf16 = bf; a.kc = b.kc; a.vt = b.vt; a.o = o; a.out_dtype = e.out_dtype;
   a.N = N; a.H = e.heads; a.Ti = g.Ti; a.Tj = g.Tj;
+  a.head_group = head_group(D, ft, g.BH, g.Ti);
   a.scale = e.softmax_scale;
   a.scale_log2 = e.softmax_scale * 1.4426950408889634f;
   a.eps1 = e.eps1;

@@ -49,6 +49,7 @@ struct KArgs {
   void* o;                 // [BH][N][D], fp32 / fp16 / bf16
   int32_t out_dtype;
   int32_t N, H, Ti, Tj;
+  int32_t head_group;      // (causal) heads whose row tiles are issued together, see causal_row_tile
   float scale;             // sigma
   float scale_log2;        // sigma * log2(e)
   float eps1, tau_fast, tau_o, delta_l;
