@@ -32,6 +32,11 @@ struct Buffers {
   uint32_t* range_next = nullptr;     // the word the next call sets: cleared by this call
 };
 
+// Offsets in the block a report reads: event count, recheck count, two range words used in turn by
+// consecutive calls, residual maxima.  One block, so that a report is one copy behind one wait: with a
+// copy for each it took about 90 us of host time.
+constexpr size_t STAT_EVENTS = 0, STAT_RECHECK = 8, STAT_RANGE = 16, STAT_RESMAX = 256;
+
 struct ftattn_ctx {
   ftattn_config cfg;          // effective configuration
   Geometry geo;
@@ -41,15 +46,14 @@ struct ftattn_ctx {
   DevFault* d_faults = nullptr;
   int32_t* d_fault_off = nullptr;
   ftattn_event* d_events = nullptr;
-  int32_t* d_ev_count = nullptr;
-  unsigned long long* d_recheck = nullptr;
-  uint32_t* d_resmax = nullptr;
-  uint32_t* d_range = nullptr;        // two words, used in turn by consecutive calls
+  unsigned char* d_stat = nullptr;    // counters and residual maxima of the report, one block (STAT_*)
   unsigned calls = 0;
   int fault_cap = 0;
   // pinned host staging
   DevFault* h_faults = nullptr;
   int32_t* h_fault_off = nullptr;
+  unsigned char* h_stat = nullptr;    // where a report finds a copy of d_stat
+  size_t stat_bytes = 0;
   // report storage
   std::vector<ftattn_event> events;
   std::vector<uint8_t> tile_flags, rowtile_flags;
@@ -79,10 +83,10 @@ static int fail(ftattn_ctx* c, int code, const std::string& msg) {
 static void release(ftattn_ctx* c) {
   if (!c) return;
   (void)hipFree(c->kc); (void)hipFree(c->vt); (void)hipFree(c->d_faults);
-  (void)hipFree(c->d_fault_off); (void)hipFree(c->d_events); (void)hipFree(c->d_ev_count);
-  (void)hipFree(c->d_recheck); (void)hipFree(c->d_resmax); (void)hipFree(c->d_range);
+  (void)hipFree(c->d_fault_off); (void)hipFree(c->d_events); (void)hipFree(c->d_stat);
   if (c->h_faults) (void)hipHostFree(c->h_faults);
   if (c->h_fault_off) (void)hipHostFree(c->h_fault_off);
+  if (c->h_stat) (void)hipHostFree(c->h_stat);
   for (hipEvent_t e : c->ev) if (e) (void)hipEventDestroy(e);
   delete c;
 }
@@ -227,19 +231,15 @@ extern "C" int ftattn_create(const ftattn_config* cfg, ftattn_ctx** out) {
   CREATE_TRY(hipMalloc((void**)&c->d_faults, sizeof(DevFault) * c->fault_cap));
   CREATE_TRY(hipMalloc((void**)&c->d_fault_off, sizeof(int32_t) * (n_rt + 1)));
   CREATE_TRY(hipMalloc((void**)&c->d_events, sizeof(ftattn_event) * (size_t)e.max_events));
-  CREATE_TRY(hipMalloc((void**)&c->d_ev_count, sizeof(int32_t)));
-  CREATE_TRY(hipMalloc((void**)&c->d_recheck, sizeof(unsigned long long)));
-  CREATE_TRY(hipMalloc((void**)&c->d_resmax, sizeof(uint32_t) * n_rt * 4));
-  CREATE_TRY(hipMalloc((void**)&c->d_range, sizeof(uint32_t) * 2));
-  CREATE_TRY(hipMemset(c->d_range, 0, sizeof(uint32_t) * 2));
+  c->stat_bytes = STAT_RESMAX + sizeof(uint32_t) * n_rt * 4;
+  CREATE_TRY(hipMalloc((void**)&c->d_stat, c->stat_bytes));
+  CREATE_TRY(hipMemset(c->d_stat, 0, c->stat_bytes));
+  CREATE_TRY(hipHostMalloc((void**)&c->h_stat, c->stat_bytes, hipHostMallocDefault));
   CREATE_TRY(hipHostMalloc((void**)&c->h_faults, sizeof(DevFault) * c->fault_cap, hipHostMallocDefault));
   CREATE_TRY(hipHostMalloc((void**)&c->h_fault_off, sizeof(int32_t) * (n_rt + 1), hipHostMallocDefault));
   // the checksum rows of the encoded tiles are never written when ft_mode is OFF; keep them defined
   CREATE_TRY(hipMemset(c->kc, 0, g.n_kc * 2));
   CREATE_TRY(hipMemset(c->vt, 0, g.n_vt * 2));
-  CREATE_TRY(hipMemset(c->d_ev_count, 0, sizeof(int32_t)));
-  CREATE_TRY(hipMemset(c->d_recheck, 0, sizeof(unsigned long long)));
-  CREATE_TRY(hipMemset(c->d_resmax, 0, sizeof(uint32_t) * n_rt * 4));
   {
     hipError_t le = allow_lds(e.head_dim, e.per_step, e.stride, why, e.rescale_margin > 0.f);
     if (le != hipSuccess) {
@@ -355,8 +355,12 @@ extern "C" int ftattn_forward(ftattn_ctx* c, const void* q, const void* k, const
 
   Buffers bufs;
   bufs.kc = c->kc; bufs.vt = c->vt; bufs.faults = c->d_faults; bufs.fault_off = n_faults > 0 ? c->d_fault_off : nullptr;
-  bufs.events = c->d_events; bufs.ev_count = c->d_ev_count; bufs.recheck = c->d_recheck; bufs.resmax = c->d_resmax;
-  bufs.range = c->d_range + (c->calls & 1u); bufs.range_next = c->d_range + ((c->calls + 1u) & 1u);
+  bufs.events = c->d_events;
+  bufs.ev_count = (int32_t*)(c->d_stat + STAT_EVENTS);
+  bufs.recheck = (unsigned long long*)(c->d_stat + STAT_RECHECK);
+  bufs.resmax = (uint32_t*)(c->d_stat + STAT_RESMAX);
+  uint32_t* range = (uint32_t*)(c->d_stat + STAT_RANGE);
+  bufs.range = range + (c->calls & 1u); bufs.range_next = range + ((c->calls + 1u) & 1u);
   hipError_t le = launch_pass(e, c->geo, bufs, q, k, v, o, n_faults > 0, st, c->timing ? c->ev : nullptr);
   if (le != hipSuccess) return fail(c, FTATTN_EHIP, std::string("launch: ") + hipGetErrorString(le));
   c->last_stream = st;
@@ -370,11 +374,14 @@ extern "C" int ftattn_report(ftattn_ctx* c, ftattn_report_view* out) {
   if (!c->ran) return fail(c, FTATTN_EINVAL, "no forward call to report on");
   const ftattn_config& e = c->cfg;
   HIP_TRY(c, hipSetDevice(e.device));
+  HIP_TRY(c, hipMemcpyAsync(c->h_stat, c->d_stat, c->stat_bytes, hipMemcpyDeviceToHost, c->last_stream));
   HIP_TRY(c, hipStreamSynchronize(c->last_stream));
   int32_t count = 0;
   unsigned long long recheck = 0;
-  HIP_TRY(c, hipMemcpy(&count, c->d_ev_count, sizeof count, hipMemcpyDeviceToHost));
-  HIP_TRY(c, hipMemcpy(&recheck, c->d_recheck, sizeof recheck, hipMemcpyDeviceToHost));
+  uint32_t range = 0;
+  std::memcpy(&count, c->h_stat + STAT_EVENTS, sizeof count);
+  std::memcpy(&recheck, c->h_stat + STAT_RECHECK, sizeof recheck);
+  std::memcpy(&range, c->h_stat + STAT_RANGE + sizeof range * ((c->calls - 1u) & 1u), sizeof range);
   int stored = std::min(count, e.max_events);
   c->events.resize(stored);
   if (stored) HIP_TRY(c, hipMemcpy(c->events.data(), c->d_events, sizeof(ftattn_event) * stored, hipMemcpyDeviceToHost));
@@ -399,7 +406,7 @@ extern "C" int ftattn_report(ftattn_ctx* c, ftattn_report_view* out) {
   if (count > stored)
     for (auto& f : c->rowtile_flags) f |= FTATTN_RF_EVENT_OVERFLOW;
   c->resmax.resize(n_rt * 4);
-  HIP_TRY(c, hipMemcpy(c->resmax.data(), c->d_resmax, sizeof(float) * n_rt * 4, hipMemcpyDeviceToHost));
+  std::memcpy(c->resmax.data(), c->h_stat + STAT_RESMAX, sizeof(float) * n_rt * 4);
   out->n_events = stored;
   out->n_events_dropped = count - stored;
   out->events = c->events.data();
@@ -409,8 +416,6 @@ extern "C" int ftattn_report(ftattn_ctx* c, ftattn_report_view* out) {
   out->rowtile_flags = c->rowtile_flags.data();
   out->residual_max = c->resmax.data();
   out->recheck_entries = (int64_t)recheck;
-  uint32_t range = 0;
-  HIP_TRY(c, hipMemcpy(&range, c->d_range + ((c->calls - 1u) & 1u), sizeof range, hipMemcpyDeviceToHost));
   out->range_flags = (int32_t)range;
   return FTATTN_OK;
 }
