@@ -169,6 +169,179 @@ __global__ __launch_bounds__(256) void ftdec_softmax(const SArgs a) {
   }
 }
 
+// The same for rows of at most 256 * CH scores: a wave per row, four rows per workgroup, and the row in
+// registers from the one read of S to the one write of P.  Lane l holds the scores 256 c + 4 l .. + 3
+// of chunk c; chunks beyond the row's last valid score are skipped (wave-uniform), so a causal row
+// pays for its own length only.  S has rows of N floats, 16 bytes at a time from any multiple of 4 bytes.
+// Bound: memory (S once, P once; 268 + 134 MB for the lower half of 32 x 2048 x 2048).  There a workgroup
+// per row with eight barriers and four passes over LDS took 223 us, this takes 100.  Rows beyond 4096
+// scores do not fit a wave's registers and keep the workgroup-per-row kernel.
+typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef _Float16 half4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ float wave_max(float v) {
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) v = __builtin_fmaxf(v, __shfl_xor(v, off));
+  return v;
+}
+__device__ __forceinline__ float wave_sum(float v) {
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off);
+  return v;
+}
+
+// fp16(v[x] * f), product and conversion in one instruction with one rounding (the compiler takes a
+// product, rounded to fp32, and a packed conversion)
+__device__ __forceinline__ half4 scaled_to_fp16(const float (&v)[4], float f) {
+  uint32_t lo, hi;
+  asm("v_fma_mixlo_f16 %0, %1, %2, 0" : "=v"(lo) : "v"(v[0]), "v"(f));
+  asm("v_fma_mixhi_f16 %0, %1, %2, 0" : "+v"(lo) : "v"(v[1]), "v"(f));
+  asm("v_fma_mixlo_f16 %0, %1, %2, 0" : "=v"(hi) : "v"(v[2]), "v"(f));
+  asm("v_fma_mixhi_f16 %0, %1, %2, 0" : "+v"(hi) : "v"(v[3]), "v"(f));
+  typedef uint32_t uint2v __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(half4, uint2v{lo, hi});
+}
+
+// f(0) .. f(E - 1) with the index as a constant from the start.  (Loops over the registers of a row are
+// unrolled only after the row has become one wide vector, which is then copied whole around every load.)
+template <int I> struct index_t { static constexpr int value = I; };
+template <int E, int I = 0, class F> __device__ __forceinline__ void each(const F& f) {
+  if constexpr (I < E) {
+    f(index_t<I>{});
+    each<E, I + 1>(f);
+  }
+}
+
+template <bool FT, bool INJ, int CH>
+__global__ __launch_bounds__(256) void ftdec_softmax_wave(const SArgs a) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int N = a.N, row = blockIdx.x * 4 + wave, bh = blockIdx.y;
+  if (row >= N) return;
+  const int nvalid = a.causal ? row + 1 : N;
+  const float* src = a.S + ((size_t)bh * N + row) * N + 4 * lane;
+  _Float16* dst = a.P + ((size_t)bh * N + row) * a.Np + 4 * lane;
+  int f0 = 0, f1 = 0;             // faults of this row: [f0, f1)
+  if (INJ) {
+    const int key = bh * N + row;
+    int lo = 0, hi = a.n_faults;
+    while (lo < hi) { const int mid = (lo + hi) >> 1; if (a.faults[mid].key < key) lo = mid + 1; else hi = mid; }
+    f0 = lo;
+    while (lo < a.n_faults && a.faults[lo].key == key) ++lo;
+    f1 = lo;
+  }
+  const float sl2 = a.scale_log2;
+  // (causal: GEMM II stops at the last query of the row's 256-query tile; the weights beyond are never read)
+  const int jend = a.causal && (row / 256 + 1) * 256 < a.Np ? (row / 256 + 1) * 256 : a.Np;
+  for (int attempt = 0; attempt < 3; ++attempt) {
+    float s[CH][4];
+    // the lane's scores of chunk c are valid below left - 256 c (formed here: the masks of all chunks would
+    // otherwise be kept in scalar registers across the attempts, more than there are)
+    int left = nvalid - 4 * lane;
+    asm volatile("" : "+v"(left));
+    // the first attempt's faults (a soft error does not repeat)
+    auto inject = [&](const int stage, const int col, float v) __attribute__((always_inline)) -> float {
+      if (INJ && attempt == 0)
+        for (int f = f0; f < f1; ++f)
+          if (a.faults[f].stage == stage && a.faults[f].col == col) v = flip(v, a.faults[f].bit);
+      return v;
+    };
+    // ---- the row, and its maximum, twice
+    each<CH>([&](auto ci) __attribute__((always_inline)) {
+      constexpr int c = decltype(ci)::value;
+      float4u q = (float4u)(-__builtin_inff());
+      if (256 * c + 256 <= nvalid) q = *reinterpret_cast<const float4u*>(src + 256 * c);
+      else if (256 * c < nvalid) {
+        // (in place of a score beyond the last valid one that one is read again)
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+          const bool ok = left > 256 * c + x;
+          const float t = src[ok ? 256 * c + x : left - 1];
+          q[x] = ok ? t : -__builtin_inff();
+        }
+      }
+      s[c][0] = q[0]; s[c][1] = q[1]; s[c][2] = q[2]; s[c][3] = q[3];
+    });
+    float ma = -__builtin_inff(), mb = -__builtin_inff();
+    each<CH>([&](auto ci) __attribute__((always_inline)) {
+      constexpr int c = decltype(ci)::value;
+      if (256 * c < nvalid)
+        each<4>([&](auto xi) __attribute__((always_inline)) {
+          const float v = s[c][decltype(xi)::value];
+          ma = __builtin_fmaxf(ma, v);
+          if (FT) mb = __builtin_fmaxf(mb, opaque(v));
+        });
+    });
+    ma = wave_max(ma);
+    if (FT) mb = wave_max(mb);
+    const float na = -ma * sl2, nb = -mb * sl2;
+    // ---- exponentials, twice; eq. (11).  s becomes DMR(e): zero, and equal, beyond the last valid score
+    // (unless no score of the row is a number, and then the valid ones fail as well)
+    float sum = 0.f;
+    uint32_t bad[(CH + 7) / 8] = {};        // a bit per score of the lane
+    each<CH>([&](auto ci) __attribute__((always_inline)) {
+      constexpr int c = decltype(ci)::value;
+      if (256 * c < nvalid) {
+        each<4>([&](auto xi) __attribute__((always_inline)) {
+          constexpr int x = decltype(xi)::value;
+          const float v = s[c][x];
+          float e = inject(FTDEC_ST_EXP, 256 * c + 4 * lane + x, ex2(__builtin_fmaf(v, sl2, na)));
+          if (FT) {
+            const float eb = ex2(__builtin_fmaf(opaque(v), sl2, nb));
+            bad[c / 8] |= __builtin_fabsf(e - eb) < a.eps ? 0u : 1u << (4 * (c % 8) + x);
+            e = 0.5f * (e + eb);
+          }
+          sum += e;
+          s[c][x] = e;
+        });
+        if (FT) asm volatile("" : "+v"(bad[c / 8]));
+      }
+    });
+    uint32_t any = 0u;
+    each<(CH + 7) / 8>([&](auto bi) __attribute__((always_inline)) { any |= bad[decltype(bi)::value]; });
+    if (FT && __builtin_amdgcn_ballot_w64(any != 0u) != 0ull) {
+      each<(CH + 7) / 8>([&](auto bi) __attribute__((always_inline)) {
+        constexpr int b = decltype(bi)::value;
+        for (uint32_t m = bad[b]; m; m &= m - 1) {
+          const int k = __builtin_ctz(m), col = 256 * (8 * b + (k >> 2)) + 4 * lane + (k & 3);
+          if (col < nvalid) log_softmax_event(a, bh, FTDEC_ST_EXP, row, col);
+        }
+      });
+      if (lane == 0) atomicAdd(a.retried, 1ull);
+      continue;
+    }
+    const float inv = 1.0f / wave_sum(sum);
+    // ---- normalised weights; eq. (12)
+    float psum = 0.f;
+    each<CH>([&](auto ci) __attribute__((always_inline)) {
+      constexpr int c = decltype(ci)::value;
+      if (256 * c < jend) {
+        half4 h = (half4)(_Float16)0.f;
+        if (256 * c < nvalid) {
+          each<4>([&](auto xi) __attribute__((always_inline)) {
+            constexpr int x = decltype(xi)::value;
+            if (INJ) {
+              const float p = inject(FTDEC_ST_PNORM, 256 * c + 4 * lane + x, s[c][x] * inv);
+              psum += p;
+              h[x] = (_Float16)p;
+            } else if (FT) {
+              psum = __builtin_fmaf(s[c][x], inv, psum);
+            }
+          });
+          if (!INJ) h = scaled_to_fp16(s[c], inv);
+        }
+        if (256 * c + 4 * lane < jend) *reinterpret_cast<half4*>(dst + 256 * c) = h;      // (jend is a multiple of 8)
+      }
+    });
+    if (!FT) break;
+    psum = wave_sum(psum);
+    if (__builtin_fabsf(psum - 1.0f) < a.eps) break;
+    if (lane == 0) {
+      log_softmax_event(a, bh, FTDEC_ST_PNORM, row, -1);
+      atomicAdd(a.retried, 1ull);
+    }
+  }
+}
+
 // V [N][d] (fp16 or bf16 patterns) -> V^T [d][Np] in fp16, columns beyond N zero.  One workgroup per 64 keys.
 __global__ __launch_bounds__(256) void ftdec_transpose_v(const uint16_t* __restrict__ v, _Float16* __restrict__ vt, int N, int Np,
                                                          int d, int bf16) {
@@ -259,6 +432,16 @@ static void drelease(ftdec_ctx* c) {
 }
 
 typedef void (*softmax_fn)(const SArgs);
+// chunks of 256 scores a wave holds in registers for rows of N scores, or 0: the row is too long
+static int softmax_chunks(int N) { return N <= 512 ? 2 : N <= 1024 ? 4 : N <= 2048 ? 8 : N <= 4096 ? 16 : 0; }
+template <int CH> static softmax_fn pick_wave(bool ft, bool inject) {
+  if (ft) return inject ? ftdec_softmax_wave<true, true, CH> : ftdec_softmax_wave<true, false, CH>;
+  return inject ? ftdec_softmax_wave<false, true, CH> : ftdec_softmax_wave<false, false, CH>;
+}
+static softmax_fn select_softmax_wave(int chunks, bool ft, bool inject) {
+  return chunks == 2 ? pick_wave<2>(ft, inject) : chunks == 4 ? pick_wave<4>(ft, inject)
+         : chunks == 8 ? pick_wave<8>(ft, inject) : pick_wave<16>(ft, inject);
+}
 static softmax_fn select_softmax(bool ft, bool inject) {
   if (ft) return inject ? ftdec_softmax<true, true> : ftdec_softmax<true, false>;
   return inject ? ftdec_softmax<false, true> : ftdec_softmax<false, false>;
@@ -442,7 +625,10 @@ extern "C" int ftdec_forward(ftdec_ctx* c, const void* q, const void* k, const v
     a.faults = c->d_sfaults; a.n_faults = n_s;
     a.events = c->s_events; a.ev_count = c->s_count; a.max_events = e.max_events;
     a.retried = c->retried;
-    hipLaunchKernelGGL(select_softmax(ft, n_s > 0), dim3(N, BH), dim3(256), c->softmax_lds, st, a);
+    if (const int ch = softmax_chunks(N))
+      hipLaunchKernelGGL(select_softmax_wave(ch, ft, n_s > 0), dim3((N + 3) / 4, BH), dim3(256), 0, st, a);
+    else
+      hipLaunchKernelGGL(select_softmax(ft, n_s > 0), dim3(N, BH), dim3(256), c->softmax_lds, st, a);
     DHIP_TRY(c, hipGetLastError());
   }
   if (c->timing) DHIP_TRY(c, hipEventRecord(c->ev[2], st));

@@ -1,0 +1,56 @@
+"""The row softmax of the decoupled scheme at the edges of its register chunks (256 scores) and of the row
+lengths at which it changes shape (512, 1024, 2048, 4096 scores), odd lengths among them: output against
+attention in fp64 on the device, and one fault per stage of the softmax in the first and last chunk of a
+row, found in that row and repaired.  Tolerance as in test_gpu_decoupled.py: 2e-3 absolute, 1e-3 relative."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_2504_02211_amd import ftdecoupled
+
+pytestmark = pytest.mark.gpu
+
+ST_EXP, ST_PNORM = 1, 2
+
+
+@pytest.mark.parametrize("seq", [1, 3, 64, 255, 256, 257, 512, 513, 1023, 1025, 2047, 2048, 2050, 4095, 4096, 4097])
+@pytest.mark.parametrize("causal", [False, True])
+def test_rows(seq, causal):
+    print(f"[decoupled rows] seq {seq} causal {causal}", flush=True)
+    shape = (1, 2, seq, 64)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seq)
+    q, k, v = (torch.randn(shape, generator=g, device="cuda").half() for _ in range(3))
+    s = torch.matmul(q.double(), k.double().transpose(-1, -2).contiguous()) * 64 ** -0.5
+    if causal:
+        s.masked_fill_(~torch.ones((seq, seq), dtype=torch.bool, device="cuda").tril(), float("-inf"))
+    want = torch.matmul(torch.softmax(s, -1), v.double())
+    o = torch.full(shape, float("nan"), dtype=torch.float32, device="cuda")
+    stream = torch.cuda.current_stream().cuda_stream
+
+    def check():
+        diff = o.double() - want
+        assert float(diff.abs().max()) <= 2e-3 and float(diff.norm() / want.norm()) <= 1e-3
+
+    for mode in (ftdecoupled.FT_CORRECT, ftdecoupled.FT_OFF):
+        ctx = ftdecoupled.FtDecoupled(*shape, 0, causal, ft_mode=mode)
+        o.fill_(float("nan"))
+        ctx.forward(q, k, v, o, None, stream)
+        rep = ctx.report()
+        assert rep.n_events == 0 and rep.retried_rows == 0
+        check()
+        if mode == ftdecoupled.FT_CORRECT:
+            # sign bit of the row's first and last exponential (2 e > eps for e > 1/8192: the scores are of order
+            # one) and the top exponent bit of its last weight (p < 1 becomes p * 2^128)
+            r = seq - 1
+            faults = [(0, 0, ST_EXP, r, 0, 31), (0, 1, ST_PNORM, r, seq - 1, 30)]
+            if seq > 1:
+                faults.append((0, 0, ST_EXP, r, seq - 1, 31))
+            o.fill_(float("nan"))
+            ctx.forward(q, k, v, o, np.array(faults, np.int32), stream)
+            rep = ctx.report()
+            assert rep.event_set() == {(0, 0, ST_EXP, r, f[4]) for f in faults if f[2] == ST_EXP} | {(0, 1, ST_PNORM, r, -1)}
+            assert rep.retried_rows == 2
+            check()
+        ctx.close()
