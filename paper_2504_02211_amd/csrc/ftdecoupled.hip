@@ -342,31 +342,46 @@ __global__ __launch_bounds__(256) void ftdec_softmax_wave(const SArgs a) {
   }
 }
 
-// V [N][d] (fp16 or bf16 patterns) -> V^T [d][Np] in fp16, columns beyond N zero.  One workgroup per 64 keys.
+// V [N][d] (fp16 or bf16 patterns) -> V^T [d][Np] in fp16, columns beyond N zero.  One workgroup per 64 keys
+// and 64 features: 16 bytes per lane from memory, transposed through LDS (rows of 33 words: the eight keys
+// a lane gathers, and the 16 lanes of a row, fall on banks of their own), 16 bytes per lane back.  The
+// first workgroup also clears the counters of the softmax log.  Bound: memory, one read and one write of V;
+// 2 x 16 x 2048 x 128 took 24.3 us with 2 bytes per lane, and the reset was a launch of its own.
 __global__ __launch_bounds__(256) void ftdec_transpose_v(const uint16_t* __restrict__ v, _Float16* __restrict__ vt, int N, int Np,
-                                                         int d, int bf16) {
-  __shared__ _Float16 tile[64][257];
-  const int bh = blockIdx.y, k0 = blockIdx.x * 64, tid = threadIdx.x;
+                                                         int d, int bf16, int32_t* s_count, unsigned long long* retried) {
+  typedef uint16_t u16x8 __attribute__((ext_vector_type(8)));
+  typedef _Float16 half8 __attribute__((ext_vector_type(8)));
+  typedef _Float16 half2v __attribute__((ext_vector_type(2)));
+  __shared__ __attribute__((aligned(16))) _Float16 tile[64][66];
+  const int bh = blockIdx.y, k0 = blockIdx.x * 64, f0 = blockIdx.z * 64, tid = threadIdx.x;
+  if (tid == 0 && blockIdx.x == 0 && bh == 0 && f0 == 0) { *s_count = 0; *retried = 0ull; }
   const uint16_t* src = v + (size_t)bh * N * d;
   _Float16* dst = vt + (size_t)bh * d * Np;
-  for (int e = tid; e < 64 * d; e += 256) {
-    const int r = e / d, f = e % d, key = k0 + r;
-    float x = 0.f;
-    if (key < N) {
-      const uint16_t u = src[(size_t)key * d + f];
-      x = bf16 ? __builtin_bit_cast(float, (uint32_t)u << 16) : (float)__builtin_bit_cast(_Float16, u);
+#pragma unroll
+  for (int e = tid; e < 64 * 8; e += 256) {
+    const int r = e >> 3, c = (e & 7) * 8, key = k0 + r;
+    u16x8 u = (u16x8)(uint16_t)0;
+    if (key < N && f0 + c < d) u = *reinterpret_cast<const u16x8*>(src + (size_t)key * d + f0 + c);      // (d is a multiple of 8)
+#pragma unroll
+    for (int x = 0; x < 8; x += 2) {
+      half2v h;
+#pragma unroll
+      for (int y = 0; y < 2; ++y) {
+        const uint16_t w = u[x + y];
+        h[y] = bf16 ? (_Float16)__builtin_bit_cast(float, (uint32_t)w << 16) : __builtin_bit_cast(_Float16, w);
+      }
+      *reinterpret_cast<half2v*>(&tile[r][c + x]) = h;
     }
-    tile[r][f] = (_Float16)x;
   }
   __syncthreads();
-  for (int e = tid; e < 64 * d; e += 256) {
-    const int f = e / 64, r = e % 64, key = k0 + r;
-    if (key < Np) dst[(size_t)f * Np + key] = tile[r][f];
+#pragma unroll
+  for (int e = tid; e < 64 * 8; e += 256) {
+    const int f = e >> 3, r = (e & 7) * 8, key = k0 + r;
+    half8 h;
+#pragma unroll
+    for (int x = 0; x < 8; ++x) h[x] = tile[r + x][f];
+    if (f0 + f < d && key < Np) *reinterpret_cast<half8*>(dst + (size_t)(f0 + f) * Np + key) = h;      // (Np is a multiple of 8)
   }
-}
-
-__global__ void ftdec_reset(int32_t* s_count, unsigned long long* retried) {
-  if (threadIdx.x == 0) { *s_count = 0; *retried = 0ull; }
 }
 
 }  // namespace ftdec
@@ -573,8 +588,10 @@ extern "C" int ftdec_forward(ftdec_ctx* c, const void* q, const void* k, const v
     DHIP_TRY(c, hipStreamSynchronize(st));     // the staging buffers may be rewritten by the next call
   }
 
-  ftdec_reset<<<1, 64, 0, st>>>(c->s_count, c->retried);
   if (c->timing) DHIP_TRY(c, hipEventRecord(c->ev[0], st));
+  ftdec_transpose_v<<<dim3((Np + 63) / 64, BH, (d + 63) / 64), 256, 0, st>>>(reinterpret_cast<const uint16_t*>(v), c->vt, N, Np, d, bf ? 1 : 0,
+                                                                            c->s_count, c->retried);
+  DHIP_TRY(c, hipGetLastError());
   // (with a fault list every head runs the injecting tile shape, so that all slots have one stride)
   const ftgemm::GPlan plan1 = ftgemm::gemm_plan(N, N, d, BH, n_g > 0, false), plan2 = ftgemm::gemm_plan(N, d, Np, BH, n_g > 0, false);
   c->used1 = ftgemm::gemm_slots(N, N, plan1); c->used2 = ftgemm::gemm_slots(N, d, plan2);
@@ -634,8 +651,6 @@ extern "C" int ftdec_forward(ftdec_ctx* c, const void* q, const void* k, const v
   if (c->timing) DHIP_TRY(c, hipEventRecord(c->ev[2], st));
 
   // ---- 3. ABFT-GEMM II: O = P V per head (tokens = queries, weight rows = the features of V^T)
-  ftdec_transpose_v<<<dim3((Np + 63) / 64, BH), 256, 0, st>>>(reinterpret_cast<const uint16_t*>(v), c->vt, N, Np, d, bf ? 1 : 0);
-  DHIP_TRY(c, hipGetLastError());
   const uint16_t* vt16 = reinterpret_cast<const uint16_t*>(c->vt);
   const uint16_t* p16 = reinterpret_cast<const uint16_t*>(c->P);
   const long long wc2_stride = (long long)ftgemm::GCK * Np;
