@@ -679,13 +679,16 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : 2) void ft
             asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(dev_max) : "v"(dv[2]), "v"(dv[3]));
           }
         }
-        else if (!INJ && (PS == 0 || LAZY)) {
+        else if (!INJ && (PS == 0 || LAZY) && (CAUSAL || D == 128)) {
           // ============ masked tile: is there anything for the exact re-evaluation below to report?  With
           // every exponential equal to its second evaluation its lambda is -sigma*R1, so the tile passes
           // there exactly if it passes here.  (Every row tile ends in masked key tiles when causal; the
           // exact path costs about four times as many instructions, with a branch per element: 8 x 16 x 2048 x 64
           // took 201 us with it on every masked tile and 195 with this filter, 4 x 32 x 4096 x 128 976 and 938.
-          // The kernels with the injection code have no registers left for it and take the exact path.)
+          // The kernels with the injection code have no registers left for it and take the exact path.
+          // Without a causal mask only the last key tile can be masked, and at head_dim 64 the filter's registers
+          // and code cost the others more than that tile gains: 8 x 16 x 2048 x 64 takes 286 us without it and 291
+          // with it, 2047 keys 292 and 295, 16 x 12 x 512 x 64 54.2 and 55.4, 333 keys 41.1 and 40.7.)
           bool bad = false;
           uint32_t diff = 0u;
 #pragma unroll

@@ -54,3 +54,33 @@ def test_rows(seq, causal):
             assert rep.retried_rows == 2
             check()
         ctx.close()
+
+
+@pytest.mark.parametrize("batch,heads,seq,head_dim,causal", [
+    (1, 2, 1, 8, False), (2, 1, 63, 40, True), (1, 3, 65, 72, False), (2, 2, 70, 200, True), (1, 1, 129, 256, False),   # V^T remainders
+    (3, 3, 1024, 128, True), (1, 5, 2048, 64, True), (2, 2, 512, 256, True)])                                          # XCD ranges moved per head
+@pytest.mark.parametrize("bf16", [False, True])
+def test_heads_and_features(batch, heads, seq, head_dim, causal, bf16):
+    """V^T in blocks of 64 keys and 64 features, with remainders in both, and every tile of every head computed
+    once where the XCD ranges move on per head.  Same tolerance (V and O as above, P in fp16)."""
+    print(f"[decoupled heads] {batch} x {heads} x {seq} x {head_dim} causal {causal} bf16 {bf16}", flush=True)
+    shape = (batch, heads, seq, head_dim)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seq + head_dim)
+    tt = torch.bfloat16 if bf16 else torch.float16
+    q, k, v = (torch.randn(shape, generator=g, device="cuda").to(tt) for _ in range(3))
+    o = torch.full(shape, float("nan"), dtype=torch.float32, device="cuda")
+    ctx = ftdecoupled.FtDecoupled(*shape, 1 if bf16 else 0, causal)
+    ctx.forward(q, k, v, o, None, torch.cuda.current_stream().cuda_stream)
+    rep = ctx.report()
+    ctx.close()
+    assert rep.n_events == 0 and rep.retried_rows == 0
+    mask = torch.ones((seq, seq), dtype=torch.bool, device="cuda").tril()
+    for b in range(batch):
+        for h in range(heads):
+            s = (q[b, h].double() @ k[b, h].double().t().contiguous()) * head_dim ** -0.5
+            if causal:
+                s.masked_fill_(~mask, float("-inf"))
+            want = torch.softmax(s, -1) @ v[b, h].double()
+            diff = o[b, h].double() - want
+            assert float(diff.abs().max()) <= 2e-3 and float(diff.norm() / want.norm()) <= 1e-3
