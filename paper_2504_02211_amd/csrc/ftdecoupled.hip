@@ -151,7 +151,7 @@ __global__ __launch_bounds__(256) void ftdec_softmax(const SArgs a) {
           for (int f = f0; f < f1; ++f)
             if (a.faults[f].stage == FTDEC_ST_EXP && a.faults[f].col == j) ea = flip(ea, a.faults[f].bit);
         const float e = FT ? 0.5f * (ea + ex2(__builtin_fmaf(opaque(s), sl2, nb))) : ea;
-        p = e * inv;
+        p = opaque(e * inv);            // (one value for the sum and the store, as below)
         if (INJ && attempt == 0)
           for (int f = f0; f < f1; ++f)
             if (a.faults[f].stage == FTDEC_ST_PNORM && a.faults[f].col == j) p = flip(p, a.faults[f].bit);
@@ -188,18 +188,6 @@ __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off);
   return v;
-}
-
-// fp16(v[x] * f), product and conversion in one instruction with one rounding (the compiler takes a
-// product, rounded to fp32, and a packed conversion)
-__device__ __forceinline__ half4 scaled_to_fp16(const float (&v)[4], float f) {
-  uint32_t lo, hi;
-  asm("v_fma_mixlo_f16 %0, %1, %2, 0" : "=v"(lo) : "v"(v[0]), "v"(f));
-  asm("v_fma_mixhi_f16 %0, %1, %2, 0" : "+v"(lo) : "v"(v[1]), "v"(f));
-  asm("v_fma_mixlo_f16 %0, %1, %2, 0" : "=v"(hi) : "v"(v[2]), "v"(f));
-  asm("v_fma_mixhi_f16 %0, %1, %2, 0" : "+v"(hi) : "v"(v[3]), "v"(f));
-  typedef uint32_t uint2v __attribute__((ext_vector_type(2)));
-  return __builtin_bit_cast(half4, uint2v{lo, hi});
 }
 
 // f(0) .. f(E - 1) with the index as a constant from the start.  (Loops over the registers of a row are
@@ -310,7 +298,10 @@ __global__ __launch_bounds__(256) void ftdec_softmax_wave(const SArgs a) {
       continue;
     }
     const float inv = 1.0f / wave_sum(sum);
-    // ---- normalised weights; eq. (12)
+    // ---- normalised weights; eq. (12).  The weight that is summed and the one that is stored are one value:
+    // without `opaque` the product is contracted into the sum and into the conversion, each with a
+    // multiplication of its own, and the sum says nothing of what is stored (a pass over 2 x 16 x 2048 x 128,
+    // causal: 306 us contracted, 310 like this).
     float psum = 0.f;
     each<CH>([&](auto ci) __attribute__((always_inline)) {
       constexpr int c = decltype(ci)::value;
@@ -319,15 +310,10 @@ __global__ __launch_bounds__(256) void ftdec_softmax_wave(const SArgs a) {
         if (256 * c < nvalid) {
           each<4>([&](auto xi) __attribute__((always_inline)) {
             constexpr int x = decltype(xi)::value;
-            if (INJ) {
-              const float p = inject(FTDEC_ST_PNORM, 256 * c + 4 * lane + x, s[c][x] * inv);
-              psum += p;
-              h[x] = (_Float16)p;
-            } else if (FT) {
-              psum = __builtin_fmaf(s[c][x], inv, psum);
-            }
+            const float p = opaque(inject(FTDEC_ST_PNORM, 256 * c + 4 * lane + x, s[c][x] * inv));
+            if (FT) psum += p;
+            h[x] = (_Float16)p;
           });
-          if (!INJ) h = scaled_to_fp16(s[c], inv);
         }
         if (256 * c + 4 * lane < jend) *reinterpret_cast<half4*>(dst + 256 * c) = h;      // (jend is a multiple of 8)
       }

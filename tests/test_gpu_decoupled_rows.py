@@ -84,3 +84,27 @@ def test_heads_and_features(batch, heads, seq, head_dim, causal, bf16):
             want = torch.softmax(s, -1) @ v[b, h].double()
             diff = o[b, h].double() - want
             assert float(diff.abs().max()) <= 2e-3 and float(diff.norm() / want.norm()) <= 1e-3
+
+
+@pytest.mark.parametrize("seq", [40, 700, 1500, 3000, 4097])
+def test_weights_do_not_depend_on_the_fault_list(seq):
+    """The kernel that calls without a fault list run stores the weight that it sums for eq. (12), as the
+    injecting one does, whose faults show that the sum covers it: faults that are found and evaluated again
+    leave the output of the fault-free call, bit for bit.  (A product contracted into the conversion to fp16
+    rounds once instead of twice, which changes the last digit of about one weight in 2^13.)"""
+    print(f"[decoupled weights] seq {seq}", flush=True)
+    shape = (1, 4, seq, 64)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seq + 1)
+    q, k, v = (torch.randn(shape, generator=g, device="cuda").half() for _ in range(3))
+    outs = []
+    stream = torch.cuda.current_stream().cuda_stream
+    for faults in (None, np.array([(0, 1, ST_EXP, seq // 2, 3, 31), (0, 2, ST_PNORM, seq - 1, 5, 30)], np.int32)):
+        ctx = ftdecoupled.FtDecoupled(*shape, 0, False)
+        o = torch.full(shape, float("nan"), dtype=torch.float32, device="cuda")
+        ctx.forward(q, k, v, o, faults, stream)
+        rep = ctx.report()
+        assert rep.retried_rows == (0 if faults is None else 2)
+        ctx.close()
+        outs.append(o)
+    assert torch.equal(outs[0], outs[1])
