@@ -374,11 +374,14 @@ __global__ __launch_bounds__(256) void ftdec_transpose_v(const uint16_t* __restr
 
 using namespace ftdec;
 
+// Counters that a report goes by, all written by the kernels of a call (also where the call is the replay of a
+// captured one): report slots per head of the two GEMMs, the softmax log's counter, rows evaluated again.
+struct DStat { int32_t slots[2], s_count, pad; unsigned long long retried; };
+
 struct ftdec_ctx {
   ftdec_config cfg;
   int BH = 0, N = 0, Np = 0, d = 0, Tn1 = 0;
   int slots1 = 0, slots2 = 0;    // report slots per head of the two GEMMs (allocated)
-  int used1 = 0, used2 = 0;      // ... in use by the last call
   uint32_t ring_n = 0;
   // device
   float* S = nullptr;
@@ -389,9 +392,8 @@ struct ftdec_ctx {
   ftgemm_event* g_events = nullptr;   // [2*BH][ring_n] event rings of the GEMMs
   uint32_t* cursors = nullptr;        // [2*BH]
   ftgemm::GSlot* g_slots = nullptr;   // [BH][slots1], then [BH][slots2]
-  int32_t* s_count = nullptr;         // the softmax log's counter
+  DStat* stat = nullptr;
   ftdec_event* s_events = nullptr;
-  unsigned long long* retried = nullptr;
   ftgemm::GFault* d_gfaults = nullptr;
   SFault* d_sfaults = nullptr;
   ftgemm::GFault* h_gfaults = nullptr;   // pinned
@@ -424,8 +426,8 @@ static int dfail(ftdec_ctx* c, int code, const std::string& msg) {
 static void drelease(ftdec_ctx* c) {
   if (!c) return;
   (void)hipFree(c->S); (void)hipFree(c->P); (void)hipFree(c->vt); (void)hipFree(c->wc1); (void)hipFree(c->wc2);
-  (void)hipFree(c->g_events); (void)hipFree(c->cursors); (void)hipFree(c->g_slots); (void)hipFree(c->s_count); (void)hipFree(c->s_events);
-  (void)hipFree(c->retried); (void)hipFree(c->d_gfaults); (void)hipFree(c->d_sfaults);
+  (void)hipFree(c->g_events); (void)hipFree(c->cursors); (void)hipFree(c->g_slots); (void)hipFree(c->stat); (void)hipFree(c->s_events);
+  (void)hipFree(c->d_gfaults); (void)hipFree(c->d_sfaults);
   if (c->h_gfaults) (void)hipHostFree(c->h_gfaults);
   if (c->h_sfaults) (void)hipHostFree(c->h_sfaults);
   for (hipEvent_t e : c->ev) if (e) (void)hipEventDestroy(e);
@@ -480,8 +482,8 @@ extern "C" int ftdec_create(const ftdec_config* cfg, ftdec_ctx** out) {
       {(void**)&c->S, BH * N * N * 4, true}, {(void**)&c->P, BH * N * Np * 2, true}, {(void**)&c->vt, BH * d * Np * 2, false},
       {(void**)&c->wc1, BH * c->Tn1 * ftgemm::GCK * d * 2, false}, {(void**)&c->wc2, BH * ftgemm::GCK * Np * 2, false},
       {(void**)&c->g_events, 2 * BH * c->ring_n * sizeof(ftgemm_event), false}, {(void**)&c->cursors, 2 * BH * 4, false},
-      {(void**)&c->g_slots, BH * (c->slots1 + c->slots2) * sizeof(ftgemm::GSlot), false}, {(void**)&c->s_count, 4, false}, {(void**)&c->s_events, cap * sizeof(ftdec_event), false},
-      {(void**)&c->retried, 8, false}, {(void**)&c->d_gfaults, sizeof(ftgemm::GFault) * c->fault_cap, false},
+      {(void**)&c->g_slots, BH * (c->slots1 + c->slots2) * sizeof(ftgemm::GSlot), false}, {(void**)&c->stat, sizeof(DStat), false}, {(void**)&c->s_events, cap * sizeof(ftdec_event), false},
+      {(void**)&c->d_gfaults, sizeof(ftgemm::GFault) * c->fault_cap, false},
       {(void**)&c->d_sfaults, sizeof(SFault) * c->fault_cap, false}};
   for (auto& al : allocs) {
     he = hipMalloc(al.p, al.bytes);
@@ -576,11 +578,10 @@ extern "C" int ftdec_forward(ftdec_ctx* c, const void* q, const void* k, const v
 
   if (c->timing) DHIP_TRY(c, hipEventRecord(c->ev[0], st));
   ftdec_transpose_v<<<dim3((Np + 63) / 64, BH, (d + 63) / 64), 256, 0, st>>>(reinterpret_cast<const uint16_t*>(v), c->vt, N, Np, d, bf ? 1 : 0,
-                                                                            c->s_count, c->retried);
+                                                                            &c->stat->s_count, &c->stat->retried);
   DHIP_TRY(c, hipGetLastError());
   // (with a fault list every head runs the injecting tile shape, so that all slots have one stride)
   const ftgemm::GPlan plan1 = ftgemm::gemm_plan(N, N, d, BH, n_g > 0, false), plan2 = ftgemm::gemm_plan(N, d, Np, BH, n_g > 0, false);
-  c->used1 = ftgemm::gemm_slots(N, N, plan1); c->used2 = ftgemm::gemm_slots(N, d, plan2);
   auto gemm_args = [&](int which, int bh) {
     ftgemm::GArgs a;
     std::memset(&a, 0, sizeof a);
@@ -592,7 +593,8 @@ extern "C" int ftdec_forward(ftdec_ctx* c, const void* q, const void* k, const v
     a.events = c->g_events + (size_t)slot * c->ring_n;
     a.cursor = c->cursors + slot;
     a.ring_mask = c->ring_n - 1;
-    const int per_head = which ? c->used2 : c->used1;
+    const int per_head = which ? ftgemm::gemm_slots(N, d, plan2) : ftgemm::gemm_slots(N, N, plan1);
+    a.n_slots = &c->stat->slots[which];
     a.slots = c->g_slots + (which ? (size_t)BH * c->slots1 : 0) + (size_t)bh * per_head;
     if (!n_g) { a.bs_events = c->ring_n; a.bs_slots = per_head; }
     return a;
@@ -626,8 +628,8 @@ extern "C" int ftdec_forward(ftdec_ctx* c, const void* q, const void* k, const v
     a.eps = e.eps_dmr;
     a.use_lds = c->softmax_lds ? 1 : 0;
     a.faults = c->d_sfaults; a.n_faults = n_s;
-    a.events = c->s_events; a.ev_count = c->s_count; a.max_events = e.max_events;
-    a.retried = c->retried;
+    a.events = c->s_events; a.ev_count = &c->stat->s_count; a.max_events = e.max_events;
+    a.retried = &c->stat->retried;
     if (const int ch = softmax_chunks(N))
       hipLaunchKernelGGL(select_softmax_wave(ch, ft, n_s > 0), dim3((N + 3) / 4, BH), dim3(256), 0, st, a);
     else
@@ -665,12 +667,13 @@ extern "C" int ftdec_report(ftdec_ctx* c, ftdec_report_view* out) {
   DHIP_TRY(c, hipSetDevice(e.device));
   DHIP_TRY(c, hipStreamSynchronize(c->last_stream));
   const int BH = c->BH, cap = e.max_events;
-  unsigned long long retried = 0;
-  DHIP_TRY(c, hipMemcpy(&retried, c->retried, 8, hipMemcpyDeviceToHost));
+  DStat stat;
+  DHIP_TRY(c, hipMemcpy(&stat, c->stat, sizeof stat, hipMemcpyDeviceToHost));
   c->events.clear();
   int dropped = 0;
   for (int which = 0; which < 2; ++which) {
-    const int per_head = which ? c->used2 : c->used1;
+    const int per_head = stat.slots[which];
+    if (!per_head) continue;       // (captured, and never run)
     c->h_slots.resize((size_t)BH * per_head);
     DHIP_TRY(c, hipMemcpy(c->h_slots.data(), c->g_slots + (which ? (size_t)BH * c->slots1 : 0), c->h_slots.size() * sizeof(ftgemm::GSlot), hipMemcpyDeviceToHost));
     for (int bh = 0; bh < BH; ++bh) {
@@ -683,10 +686,8 @@ extern "C" int ftdec_report(ftdec_ctx* c, ftdec_report_view* out) {
     }
   }
   {
-    int32_t count = 0;
-    DHIP_TRY(c, hipMemcpy(&count, c->s_count, sizeof count, hipMemcpyDeviceToHost));
-    const int stored = std::min(count, cap);
-    dropped += count - stored;
+    const int stored = std::min(stat.s_count, cap);
+    dropped += stat.s_count - stored;
     const size_t base = c->events.size();
     c->events.resize(base + stored);
     if (stored) DHIP_TRY(c, hipMemcpy(c->events.data() + base, c->s_events, sizeof(ftdec_event) * stored, hipMemcpyDeviceToHost));
@@ -701,7 +702,7 @@ extern "C" int ftdec_report(ftdec_ctx* c, ftdec_report_view* out) {
   out->n_events = (int32_t)c->events.size();
   out->n_events_dropped = dropped;
   out->events = c->events.data();
-  out->retried_rows = (int64_t)retried;
+  out->retried_rows = (int64_t)stat.retried;
   return FTDEC_OK;
 }
 

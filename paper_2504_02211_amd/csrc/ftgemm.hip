@@ -22,11 +22,13 @@ struct ftgemm_ctx {
   GFault* d_faults = nullptr;
   ftgemm_event* d_events = nullptr;   // ring, never cleared: the slots say which entries a call wrote
   uint32_t* d_cursor = nullptr;
-  GSlot* d_slots = nullptr;
+  int32_t* d_n_slots = nullptr;       // slots the last launch to run has written ...
+  GSlot* d_slots = nullptr;           // ... and these, SLOTS_AT bytes behind, so that a report is one copy
   float4v* ws = nullptr;              // shares of a split contraction
   uint32_t ring_n = 0;
-  int n_slots = 0, last_slots = 0;
-  std::vector<GSlot> slots;
+  int n_slots = 0;                    // allocated
+  int last_slots = 0;                 // what the last call made here writes (a graph's replay may write another number)
+  std::vector<GSlot> slots;           // d_n_slots and d_slots of a report (GSlot holds SLOTS_AT bytes as a whole number)
   GFault* h_faults = nullptr; // pinned staging
   int fault_cap = 0;
   std::vector<ftgemm_event> events;
@@ -35,6 +37,8 @@ struct ftgemm_ctx {
   hipEvent_t ev[2] = {nullptr, nullptr};
   std::string err;
 };
+
+constexpr size_t SLOTS_AT = 2 * sizeof(GSlot);
 
 static thread_local std::string g_gemm_create_err;
 
@@ -221,17 +225,19 @@ extern "C" int ftgemm_create(const ftgemm_config* cfg, ftgemm_ctx** out) {
   const GPlan plan = gemm_plan(km, kn, e.k, 1, false, true);
   c->n_slots = std::max(gemm_slots(km, kn, plan), gemm_slots(km, kn, gemm_plan(km, kn, e.k, 1, true, false)));
   // one allocation for all of the device scratch: each hipMalloc costs tens of microseconds.  Only the
-  // cursor has to start from a value: checksum rows are written before they are read.
+  // cursor and the number of slots have to start from a value: checksum rows are written before they are read.
   struct { void** at; size_t bytes, from; } parts[] = {
       {(void**)&c->wc, (size_t)c->Tn * GCK * e.k * 2, 0}, {(void**)&c->d_faults, sizeof(GFault) * c->fault_cap, 0},
       {(void**)&c->d_events, sizeof(ftgemm_event) * (size_t)c->ring_n, 0}, {(void**)&c->d_cursor, sizeof(uint32_t), 0},
-      {(void**)&c->d_slots, sizeof(GSlot) * (size_t)c->n_slots, 0}, {(void**)&c->ws, gemm_workspace(km, kn, plan), 0}};
+      {(void**)&c->d_n_slots, SLOTS_AT + sizeof(GSlot) * (size_t)c->n_slots, 0}, {(void**)&c->ws, gemm_workspace(km, kn, plan), 0}};
   size_t total = 0;
   for (auto& p : parts) { p.from = total; total += (p.bytes + 255) & ~(size_t)255; }
   GCREATE_TRY(hipMalloc(&c->scratch, total));
   for (auto& p : parts) *p.at = static_cast<char*>(c->scratch) + p.from;
+  c->d_slots = reinterpret_cast<GSlot*>(reinterpret_cast<char*>(c->d_n_slots) + SLOTS_AT);
   GCREATE_TRY(hipHostMalloc((void**)&c->h_faults, sizeof(GFault) * c->fault_cap, hipHostMallocDefault));
   GCREATE_TRY(hipMemset(c->d_cursor, 0, sizeof(uint32_t)));
+  GCREATE_TRY(hipMemset(c->d_n_slots, 0, sizeof(int32_t)));
   GCREATE_TRY(gemm_allow_lds(plan, e.ft_mode != FTGEMM_FT_OFF, e.in_dtype == FTGEMM_BF16));
   GCREATE_TRY(hipDeviceSynchronize());
 #undef GCREATE_TRY
@@ -299,7 +305,7 @@ extern "C" int ftgemm_forward(ftgemm_ctx* c, const void* x, const void* w, void*
   a.correct = e.ft_mode == FTGEMM_FT_CORRECT ? 1 : 0;
   a.faults = c->d_faults; a.n_faults = n_faults;
   a.events = c->d_events; a.cursor = c->d_cursor; a.ring_mask = c->ring_n - 1;
-  a.slots = c->d_slots;
+  a.slots = c->d_slots; a.n_slots = c->d_n_slots;
   a.ws = c->ws;
   const GPlan plan = gemm_plan(a.M, a.N, a.K, 1, n_faults > 0, true);
   if (c->timing) GHIP_TRY(c, hipEventRecord(c->ev[0], st));
@@ -317,11 +323,18 @@ extern "C" int ftgemm_report(ftgemm_ctx* c, ftgemm_report_view* out) {
   const ftgemm_config& e = c->cfg;
   GHIP_TRY(c, hipSetDevice(e.device));
   GHIP_TRY(c, hipStreamSynchronize(c->last_stream));
-  c->slots.resize(c->last_slots);
-  GHIP_TRY(c, hipMemcpy(c->slots.data(), c->d_slots, sizeof(GSlot) * c->slots.size(), hipMemcpyDeviceToHost));
-  const GStats stats = gemm_stats(c->slots.data(), (int)c->slots.size());
+  constexpr int head = SLOTS_AT / sizeof(GSlot);
+  int32_t n = c->last_slots;
+  for (int have = -1; have < n; ) {         // (a second copy only after a replay that wrote more)
+    have = n;
+    c->slots.resize(head + n);
+    GHIP_TRY(c, hipMemcpy(c->slots.data(), c->d_n_slots, sizeof(GSlot) * c->slots.size(), hipMemcpyDeviceToHost));
+    std::memcpy(&n, c->slots.data(), sizeof n);
+  }
+  const GSlot* slots = c->slots.data() + head;
+  const GStats stats = gemm_stats(slots, n);
   c->events.clear();
-  GHIP_TRY(c, gemm_fetch_events(c->slots.data(), (int)c->slots.size(), c->d_events, c->ring_n, e.max_events, c->events));
+  GHIP_TRY(c, gemm_fetch_events(slots, n, c->d_events, c->ring_n, e.max_events, c->events));
   std::sort(c->events.begin(), c->events.end(), [](const ftgemm_event& p, const ftgemm_event& q) {
     if (p.row != q.row) return p.row < q.row;
     return p.col < q.col;

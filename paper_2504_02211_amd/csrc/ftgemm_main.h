@@ -98,6 +98,8 @@ struct GArgs {
   uint32_t* cursor;        // next free entry of the ring, counted without wrapping
   uint32_t ring_mask;
   GSlot* slots;            // one per workgroup (of a problem)
+  int32_t* n_slots;        // how many that is: what a report goes by, because the launch that it reports on may be
+                           // the replay of a captured one, with another tile shape than the host's last call
   // batch of independent products (blockIdx.y): element strides between consecutive problems of x, w,
   // wc, the event rings and the slots, byte stride of y; one cursor per problem.  All zero for a single product.
   long long bs_x, bs_w, bs_wc, bs_y_bytes, bs_events, bs_slots;
@@ -190,6 +192,11 @@ using TileStrip = GTile<32, 256, 2, 4, 64, 3>;
 using TileNarrow = GTile<128, 128, 4, 4, 64, 3>;
 using TileFinish = GTile<16, 256, 1, 4, 64, 1>;      // epilogue only
 using TileSlim = GTile<256, 64, 4, 4, 64, 3>;
+
+__device__ __forceinline__ void write_slot(const GArgs& a, int logical, const GSlot& s) {
+  a.slots[logical] = s;
+  if (logical == 0) *a.n_slots = (int32_t)gridDim.x;
+}
 
 __device__ __forceinline__ void log_gemm_event(const GArgs& a, uint32_t at, int row, int col, float res, int action) {
   ftgemm_event e;
@@ -484,10 +491,10 @@ __device__ __forceinline__ void finish_tile(const GArgs& a, char* smem, float4v 
       float s = shared_stat[0];
 #pragma unroll
       for (int w = 1; w < T::NW; ++w) s = fmax2(s, shared_stat[w]);
-      a.slots[logical] = GSlot{(uint32_t)shared_n[2], shared_n[1], s};
+      write_slot(a, logical, GSlot{(uint32_t)shared_n[2], shared_n[1], s});
     }
   } else if (tid == 0) {
-    a.slots[logical] = GSlot{0u, 0, 0.f};
+    write_slot(a, logical, GSlot{0u, 0, 0.f});
   }
 }
 
@@ -535,7 +542,7 @@ __global__ __launch_bounds__(T::NW * 64, 8 / T::NW) void ftgemm_main(const GArgs
   const int M = a.M, N = a.N, K = a.K;
   const int m0 = tm * T::BM, n0 = tn * GBN;
   if (a.skip_upper && n0 > m0 + T::BM - 1) {          // (the whole workgroup, before any barrier)
-    if (tid == 0) a.slots[logical] = GSlot{0u, 0, 0.f};
+    if (tid == 0) write_slot(a, logical, GSlot{0u, 0, 0.f});
     return;
   }
   int nkb = (K + BK - 1) / BK;
