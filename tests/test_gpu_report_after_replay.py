@@ -6,7 +6,7 @@ import pytest
 
 torch = pytest.importorskip("torch")
 
-from paper_2504_02211_amd import ftdecoupled, ftgemm
+from paper_2504_02211_amd import ftattn, ftdecoupled, ftgemm
 
 pytestmark = pytest.mark.gpu
 
@@ -127,3 +127,36 @@ def test_captured_and_not_run():
         rep = b.report()
         assert rep.n_events == 0 and rep.n_events_dropped == 0 and rep.retried_rows == 0
         a.close(), b.close()
+
+
+@pytest.mark.parametrize("path", ["attention", "linear", "decoupled"])
+def test_replay_on_the_default_stream(path):
+    """A graph captured on one stream and replayed on the default stream, behind enough work there that the
+    replay has not begun when the report is asked for: it waits for the replay and shows it, not the call with
+    a fault that was made before."""
+    print(f"[report after replay] default stream, {path}", flush=True)
+    q, k, v = (torch.randn((1, 2, 200, 64), device="cuda").half() for _ in range(3))
+    o = torch.empty((1, 2, 200, 64), dtype=torch.float32, device="cuda")
+    x, w = (torch.randn((200, 64), device="cuda").half() for _ in range(2))
+    y = torch.empty((200, 200), dtype=torch.float32, device="cuda")
+    if path == "attention":
+        ctx, operands = ftattn.FtAttn(1, 2, 200, 64, 0, False), (q, k, v, o)
+        faults = [(0, 0, ftattn.ST_OACC, 1, 7, 5, 30)]
+    elif path == "linear":
+        ctx, operands, faults = ftgemm.FtGemm(200, 200, 64), (x, w, y), [(7, 5, 30)]
+        ctx.encode_weights(w, torch.cuda.current_stream().cuda_stream)
+    else:
+        ctx, operands, faults = ftdecoupled.FtDecoupled(1, 2, 200, 64, 0, False), (q, k, v, o), [(0, 0, 3, 7, 5, 30)]
+    big = torch.randn((8192, 8192), device="cuda")
+    big @ big
+    graph = _capture(lambda st: ctx.forward(*operands, None, st))
+    side = torch.cuda.Stream()
+    for _ in range(2):
+        torch.cuda.synchronize()
+        ctx.forward(*operands, np.array(faults, np.int32), side.cuda_stream)
+        assert ctx.report().n_events == 1
+        for _ in range(6):
+            big @ big                              # 6.6 TFLOP in fp32: some tens of milliseconds
+        graph.replay()
+        assert ctx.report().n_events == 0
+    ctx.close()
