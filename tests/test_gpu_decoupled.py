@@ -159,3 +159,21 @@ def test_decoupled_random_shapes_and_unprotected_damage():
         assert np.array_equal(bad[0, 0][others], clean[0, 0][others])
         fixed, rep, _, _ = _run(q, k, v, synth.F16, True, np.array([f], np.int32))
         assert rep.n_events == 1 and np.abs(fixed[0, 0] - clean[0, 0]).max() <= 1e-4, f
+
+
+def test_timing_counts_the_transpose_with_the_second_product():
+    """With seq == head_dim the two products and their checksum encodings are launches of the same size, so what
+    V^T takes (64 MB here) decides which of the two stages is longer: it belongs to ABFT-GEMM II."""
+    shape = (64, 64, 64, 64)
+    q, k, v = (torch.randn(shape, device="cuda").half() for _ in range(3))
+    o = torch.empty(shape, dtype=torch.float32, device="cuda")
+    ctx = ftdecoupled.FtDecoupled(*shape, synth.F16, False)
+    ctx.set_timing(True)
+    ms = []
+    for _ in range(12):
+        ctx.forward(q, k, v, o, None, torch.cuda.current_stream().cuda_stream)
+        ms.append(ctx.get_timing())
+    ctx.close()
+    first, _, second = np.median(np.array(ms[2:]), axis=0)
+    print(f"[decoupled timing] GEMM I {1e3 * first:.1f} us, GEMM II {1e3 * second:.1f} us", flush=True)
+    assert second > first > 0
