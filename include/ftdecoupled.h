@@ -72,7 +72,7 @@ typedef struct {
 } ftdec_event;
 
 typedef struct {
-  int32_t n_events, n_events_dropped;
+  int32_t n_events, n_events_dropped;   /* dropped: did not fit max_events (which are kept then is not specified) */
   const ftdec_event* events;   /* sorted by (b, h, stage, row, col); host memory owned by the context */
   int64_t retried_rows;        /* softmax rows that were evaluated more than once */
 } ftdec_report_view;

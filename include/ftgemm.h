@@ -83,7 +83,8 @@ typedef struct {
 /* Views into host memory owned by the context; valid until the next forward / destroy. */
 typedef struct {
   int32_t n_events;           /* events stored */
-  int32_t n_events_dropped;   /* events that did not fit max_events */
+  int32_t n_events_dropped;   /* events that did not fit max_events (which of a call's events are kept then is not
+                                 specified: workgroups log in the order in which they come to it) */
   const ftgemm_event* events; /* sorted by (row, col) */
   float residual_max;         /* largest |check1 - fold| / threshold among classes that passed */
 } ftgemm_report_view;

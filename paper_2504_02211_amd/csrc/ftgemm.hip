@@ -159,9 +159,6 @@ hipError_t gemm_fetch_events(const GSlot* slots, int n_slots, const ftgemm_event
                              std::vector<ftgemm_event>& out) {
   const GStats st = gemm_stats(slots, n_slots);
   if (!st.events) return hipSuccess;
-  std::vector<ftgemm_event> all(ring_n);
-  hipError_t he = hipMemcpy(all.data(), ring, sizeof(ftgemm_event) * ring_n, hipMemcpyDeviceToHost);
-  if (he != hipSuccess) return he;
   // end of this call's entries: the runs of a call are contiguous as a whole, counted without wrapping
   bool any = false;
   uint32_t end = 0;
@@ -171,9 +168,14 @@ hipError_t gemm_fetch_events(const GSlot* slots, int n_slots, const ftgemm_event
       if (!any || (int32_t)(e - end) > 0) end = e;
       any = true;
     }
+  // the last `keep` entries, in one piece or, where the ring wraps, two
   const uint32_t keep = (uint32_t)std::min<long long>(std::min<long long>(st.events, max_events), ring_n);
-  for (uint32_t at = end - keep; at != end; ++at) out.push_back(all[at & (ring_n - 1)]);
-  return hipSuccess;
+  const uint32_t first = (end - keep) & (ring_n - 1), run = std::min(keep, ring_n - first);
+  const size_t at = out.size();
+  out.resize(at + keep);
+  hipError_t he = hipMemcpy(out.data() + at, ring + first, sizeof(ftgemm_event) * run, hipMemcpyDeviceToHost);
+  if (he == hipSuccess && run < keep) he = hipMemcpy(out.data() + at + run, ring, sizeof(ftgemm_event) * (keep - run), hipMemcpyDeviceToHost);
+  return he;
 }
 
 }  // namespace ftgemm

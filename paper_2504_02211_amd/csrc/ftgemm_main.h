@@ -811,7 +811,8 @@ struct GStats { long long events; float stat; };
 GStats gemm_stats(const GSlot* slots, int n_slots);
 // Event ring of at least max_events entries: a power of two.
 inline uint32_t ring_size(int max_events) { uint32_t n = 1; while (n < (uint32_t)max_events) n <<= 1; return n; }
-// The events of one call out of the ring: at most max_events, the latest ones where the ring has wrapped.
+// The events of one call out of the ring: at most max_events.  Where a call logs more than the ring holds, each entry
+// is one of those that were written there, whichever workgroup's store came last.
 hipError_t gemm_fetch_events(const GSlot* slots, int n_slots, const ftgemm_event* ring, uint32_t ring_n, int max_events,
                              std::vector<ftgemm_event>& out);
 

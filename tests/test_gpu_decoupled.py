@@ -177,3 +177,25 @@ def test_timing_counts_the_transpose_with_the_second_product():
     first, _, second = np.median(np.array(ms[2:]), axis=0)
     print(f"[decoupled timing] GEMM I {1e3 * first:.1f} us, GEMM II {1e3 * second:.1f} us", flush=True)
     assert second > first > 0
+
+
+@pytest.mark.parametrize("max_events", [1, 3, 4])
+def test_event_logs_overflow(max_events):
+    """Five faults per log (the products of two heads, the softmax of both) in logs of fewer entries: what is
+    reported belongs to this call, once, and the rest is counted; the call after it starts from nothing."""
+    shape = (1, 2, 130, 64)
+    q, k, v = (torch.randn(shape, device="cuda").half() for _ in range(3))
+    o = torch.empty(shape, dtype=torch.float32, device="cuda")
+    ctx = ftdecoupled.FtDecoupled(*shape, synth.F16, False, max_events=max_events)
+    stream = torch.cuda.current_stream().cuda_stream
+    for call in range(4):
+        faults = [(0, h, st, 11 * i + call, 3 + call, 30) for h in (0, 1) for st in (0, 3) for i in range(5)]
+        faults += [(0, 1, 1, 11 * i + call + 60, 3 + call, 31) for i in range(5)]
+        ctx.forward(q, k, v, o, np.array(faults, np.int32), stream)
+        rep = ctx.report()
+        assert (rep.n_events, rep.n_events_dropped) == (5 * max_events, 5 * (5 - max_events))
+        assert len(rep.event_set()) == rep.n_events and rep.event_set() <= {f[:5] for f in faults} and rep.retried_rows == 5
+        ctx.forward(q, k, v, o, None, stream)
+        rep = ctx.report()
+        assert (rep.n_events, rep.n_events_dropped, rep.retried_rows) == (0, 0, 0)
+    ctx.close()

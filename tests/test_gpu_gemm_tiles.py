@@ -79,3 +79,35 @@ def test_location_and_repair_in_every_tile_shape(m, n, k, dtype, correct):
     ctx.close()
     assert rep.n_events == 0 and float((y.double() - want).abs().max()) <= 1e-4
     assert np.isfinite(rep.residual_max)
+
+
+@pytest.mark.parametrize("max_events", [1, 3, 4, 8, 64])
+@pytest.mark.parametrize("m,n,k", [(5, 300, 64), (70, 1000, 1024), (300, 40, 72)])
+def test_event_log_wraps_and_overflows(m, n, k, max_events):
+    """Calls that each log m or 2 m events, one or two per token: the log wraps from call to call, and holds only a
+    part of a call's events where they are more than max_events.  Every event reported is one of its own call's, none
+    is reported twice, and the rest is counted."""
+    print(f"[gemm event log] m={m} n={n} k={k} max_events={max_events}", flush=True)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(m)
+    x = torch.randn((m, k), generator=g, device="cuda").half()
+    x[:, 3] = 1.0
+    w = (torch.randn((n, k), generator=g, device="cuda") * k ** -0.5).half()
+    y = torch.empty((m, n), dtype=torch.float32, device="cuda")
+    ctx = ftgemm.FtGemm(m, n, k, max_events=max_events)
+    ctx.encode_weights(w)
+    for call in range(7):
+        cols = [(8 * call) % n] + ([(8 * call + 3) % n] if call % 3 == 1 else [])      # (other columns in every call, two classes)
+        was = w[cols, 3].clone()
+        w[cols, 3] = was + 8.0
+        ctx.forward(x, w, y)
+        rep = ctx.report()
+        w[cols, 3] = was
+        total = m * len(cols)
+        assert (rep.n_events, rep.n_events_dropped) == (min(total, max_events), total - min(total, max_events))
+        events = rep.event_list()
+        assert len(set(events)) == len(events) and set(events) <= {(r, c, 1) for r in range(m) for c in cols}
+    ctx.forward(x, w, y)
+    rep = ctx.report()
+    assert (rep.n_events, rep.n_events_dropped) == (0, 0)
+    ctx.close()
