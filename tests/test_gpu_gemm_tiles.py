@@ -81,6 +81,80 @@ def test_location_and_repair_in_every_tile_shape(m, n, k, dtype, correct):
     assert np.isfinite(rep.residual_max)
 
 
+@pytest.mark.parametrize("m,n,k", SHAPES)
+@pytest.mark.parametrize("dtype", [ftgemm.F16, ftgemm.BF16])
+def test_restore_of_16_bit_results_and_of_infinities(m, n, k, dtype):
+    """As above with results in the input type, and with a weight that becomes infinite: then the residuals leave
+    the fp32 range, the fold of overwhelming size is the located one, and the restored value is finite.  Tolerance: the
+    rounding of the result type, and of the checksum words (2^-22 of their value in fp16, 2^-16 in bf16; a value
+    is restored from a sum of at most 32 of order one)."""
+    print(f"[gemm tiles 16-bit] m={m} n={n} k={k} dtype={dtype}", flush=True)
+    tt = torch.float16 if dtype == ftgemm.F16 else torch.bfloat16
+    g = torch.Generator(device="cuda")
+    g.manual_seed(m + 13 * n + 17 * k)
+    x = torch.randn((m, k), generator=g, device="cuda").to(tt)
+    x[:, 3] = 1.0
+    w = (torch.randn((n, k), generator=g, device="cuda") * k ** -0.5).to(tt)
+    want = x.double() @ w.double().t()
+    for out in (dtype, ftgemm.F32):
+        y = torch.full((m, n), float("nan"), dtype=torch.float32 if out == ftgemm.F32 else tt, device="cuda")
+        ctx = ftgemm.FtGemm(m, n, k, in_dtype=dtype, out_dtype=out)
+        ctx.encode_weights(w)
+        for col, value in ((n // 3, 8.0), (n - 1, float("inf")), (0, float("-inf"))):
+            was = w[col, 3].clone()
+            w[col, 3] = was + value
+            ctx.forward(x, w, y)
+            rep = ctx.report()
+            w[col, 3] = was
+            assert rep.n_events_dropped == 0
+            assert rep.event_list() == [(r, col, 1) for r in range(m)]
+            ulp = 0.0 if out == ftgemm.F32 else (2.0 ** -11 if dtype == ftgemm.F16 else 2.0 ** -8)
+            err = (y.double() - want).abs()
+            assert bool((err <= (1e-4 if dtype == ftgemm.F16 else 4e-3) + ulp * want.abs()).all())
+        ctx.close()
+
+
+@pytest.mark.parametrize("m,n,k", SHAPES)
+@pytest.mark.parametrize("fold", [False, True])
+@pytest.mark.parametrize("out", [ftgemm.F32, ftgemm.F16])
+def test_every_class_flagged_is_restored_in_place(m, n, k, fold, out):
+    """With a threshold far below rounding nearly every class is flagged and some element of it, wherever the
+    ratio of two rounding residuals points, is replaced by what the checksum implies for it.  That differs from the
+    element by the residual, which a clean call keeps below 2^-15 of the class's sum of at most 32 magnitudes:
+    the output moves by no more than that, in both orientations, and an element written to another place would be off
+    by its own size.  (With checksums over the token rows they are taken inside the call, so nothing can
+    be changed behind them.)"""
+    print(f"[gemm tiles restore] m={m} n={n} k={k} fold_tokens={fold} out={out}", flush=True)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(m + 19 * n + 23 * k)
+    x = torch.randn((m, k), generator=g, device="cuda").half()
+    w = (torch.randn((n, k), generator=g, device="cuda") * k ** -0.5).half()
+    y = []
+    for tau_rel in (0.0, 1e-12):
+        ctx = ftgemm.FtGemm(m, n, k, out_dtype=out, fold_tokens=fold, tau_rel=tau_rel)
+        ctx.encode_weights(w)
+        y.append(torch.full((m, n), float("nan"), dtype=torch.float32 if out == ftgemm.F32 else torch.float16, device="cuda"))
+        ctx.forward(x, w, y[-1])
+        rep = ctx.report()
+        ctx.close()
+        if tau_rel == 0.0:
+            assert rep.n_events == 0
+    kept, lanes = (n, m) if fold else (m, n)                 # rows of the folded product, and what a row folds
+    classes = kept * sum(min(8, min(256, lanes - at)) for at in range(0, lanes, 256))
+    total = rep.n_events + rep.n_events_dropped
+    if lanes <= 8:                                           # one result per class, accumulated as its checksum is
+        assert total == 0
+        return
+    assert classes // 4 < total <= classes
+    ev = rep.events
+    assert ((ev["row"] >= -1) & (ev["row"] < m) & (ev["col"] >= -1) & (ev["col"] < n)).all()
+    assert (ev["row" if not fold else "col"] >= 0).all() and (ev["action"] == 1).any()
+    top = float(y[0].double().abs().max())
+    ulp = 0.0 if out == ftgemm.F32 else 2.0 ** -10 * top
+    moved = float((y[1].double() - y[0].double()).abs().max())
+    assert moved <= 2.0 ** -15 * 32 * top + ulp
+
+
 @pytest.mark.parametrize("max_events", [1, 3, 4, 8, 64])
 @pytest.mark.parametrize("m,n,k", [(5, 300, 64), (70, 1000, 1024), (300, 40, 72)])
 def test_event_log_wraps_and_overflows(m, n, k, max_events):
