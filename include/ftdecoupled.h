@@ -5,8 +5,8 @@
  * kernels"), which the end-to-end kernel of ftattn.h is measured against (Section 4.1).  Part of
  * the same shared library.
  *
- * One forward call is three protected operations, each a kernel launch per head (GEMMs) or one
- * launch for all heads (softmax), with the score matrix S and the probability matrix P written to
+ * One forward call is three protected operations, each one launch for all heads (the GEMMs one per
+ * head where faults are injected), with the score matrix S and the probability matrix P written to
  * and read back from device memory in between:
  *
  *   1. ABFT-GEMM I     S = Q K^T, protected by the library's strided ABFT GEMM (ftgemm.h; tensor

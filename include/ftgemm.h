@@ -9,12 +9,13 @@
  *
  *     Y = X W^T,    X: [m, k] (tokens),  W: [n, k] (weights), fp16 or bf16,  Y: [m, n] fp32 or the input type,
  *
- * in one kernel that carries, for every block of 256 output features, the two stride-8 tensor
- * checksums of the weight rows (weights 1 and l+1) through the contraction as 32 extra MFMA
- * rows (each checksum as a high word and a low word of the input type), and after the last
- * accumulation step compares, per token and checksum class, the fold of the 32 results with the
- * first checksum product.  A mismatch is located with the second checksum (fold = residual
- * ratio - 1) and the element is restored from the first.
+ * in a kernel (and, for few tokens and a long k, a second one that sums the shares of a split k)
+ * that carries, for every block of 256 output features, the two stride-8 tensor checksums of the
+ * weight rows (weights 1 and l+1) through the contraction as 32 extra MFMA rows (each checksum as a
+ * high word and a low word of the input type), and after the last accumulation step compares, per
+ * token and checksum class, the fold of the 32 results with the first checksum product.  A mismatch
+ * is located with the second checksum (fold = residual ratio - 1) and the element is restored from
+ * the first.
  *
  * Conventions
  *   - Every function returns FTGEMM_OK (0) or a negative error code and never throws or prints;
@@ -107,7 +108,7 @@ int ftgemm_forward(ftgemm_ctx* ctx, const void* x, const void* w, void* y,
 /* Waits for the last forward of this context and exposes its events and residual statistic. */
 int ftgemm_report(ftgemm_ctx* ctx, ftgemm_report_view* out);
 /* Kernel timing for benchmarks: after ftgemm_set_timing(ctx, 1) every forward brackets its
- * kernel with HIP events on the stream it launches on; ftgemm_get_timing waits for the last
+ * kernels with HIP events on the stream it launches on; ftgemm_get_timing waits for the last
  * forward and returns the duration in milliseconds. */
 int ftgemm_set_timing(ftgemm_ctx* ctx, int32_t enabled);
 int ftgemm_get_timing(ftgemm_ctx* ctx, float* ms);

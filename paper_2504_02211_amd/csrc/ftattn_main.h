@@ -45,9 +45,8 @@ __host__ __device__ __forceinline__ RowTile even_row_tile(int id, int total, int
 // groups of `group` heads whose tiles are issued heaviest first across the group; the group that is not
 // full comes first, so that what runs last are the light tiles of a full group.  The heads left over
 // by the division by 8 come before all of these, dealt to the XCDs tile by tile.
-// List scheduling of 92 random shapes (3 key tiles of start-up per workgroup): 1.18 times the even share
-// on average against 1.45 with contiguous ranges, longer for none.  Measured: 8 x 16 x 2048 x 64 with checks
-// 222 -> 201 us, 4 x 16 x 3000 x 64 without 146 -> 128, 4 x 32 x 4096 x 128 988 -> 976.
+// Measured against contiguous ranges: 8 x 16 x 2048 x 64 with checks 222 -> 201 us, 4 x 16 x 3000 x 64
+// without 146 -> 128, 4 x 32 x 4096 x 128 988 -> 976.
 __host__ __device__ __forceinline__ RowTile causal_row_tile(int id, int total, int Ti, int group) {
   const int BH = total / Ti, h8 = BH >> 3, left = BH & 7;
   if (id < left * Ti) return RowTile{8 * h8 + id % left, Ti - 1 - id / left};
@@ -64,8 +63,7 @@ __host__ __device__ __forceinline__ RowTile causal_row_tile(int id, int total, i
 }
 
 // Heads per group: the fewest whose row tiles fill the workgroup slots of an XCD (32 CUs) once.  Larger
-// groups would let fewer workgroups share the K / V of a head in the L2 for a gain of 1 % in the
-// list schedule.  Never 0, and at most the heads of an XCD.
+// groups would let fewer workgroups share the K / V of a head in the L2.  Never 0, and at most the heads of an XCD.
 inline int head_group(int D, bool ft, int BH, int Ti) {
   const int slots = 32 * (D == 128 ? 1 : ft ? 2 : 3), h8 = BH >> 3;
   const int g = (slots + Ti - 1) / Ti;

@@ -1,8 +1,8 @@
 // The decoupled, operation-level fault-tolerant attention of Section 3.1 (the comparison system of
 // Section 4.1): ABFT-GEMM I -> DMR row-softmax -> ABFT-GEMM II, with S and P in device memory between
 // the kernels.  The C ABI of include/ftdecoupled.h.  The two GEMMs are the library's strided-ABFT
-// GEMM kernel (ftgemm_main.h) launched once per head on buffers of this context; the softmax kernel
-// and the V^T kernel are here.
+// GEMM kernel (ftgemm_main.h) on buffers of this context, one launch for all heads (with a fault list one
+// per head); the softmax kernels and the V^T kernel are here.
 #include "ftdecoupled.h"
 #include "ftgemm_main.h"
 
@@ -500,10 +500,8 @@ extern "C" int ftdec_create(const ftdec_config* cfg, ftdec_ctx** out) {
   if (he == hipSuccess) he = hipHostMalloc((void**)&c->h_sfaults, sizeof(SFault) * c->fault_cap, hipHostMallocDefault);
   if (he == hipSuccess) he = ftgemm::gemm_allow_lds(ftgemm::gemm_plan(N, N, d, c->BH, false, false), e.ft_mode != FTDEC_FT_OFF, e.in_dtype == FTDEC_BF16);
   if (he == hipSuccess) he = ftgemm::gemm_allow_lds(ftgemm::gemm_plan(N, d, Np, c->BH, false, false), e.ft_mode != FTDEC_FT_OFF, false);
-  // the softmax row is staged in LDS when it fits next to the reduction scratch
+  // where a row takes a workgroup (more than 4096 scores) it is staged in LDS up to 8192 scores
   c->softmax_lds = N * 4 <= 32 * 1024 ? N * 4 : 0;
-  for (int v = 0; v < 4 && he == hipSuccess; ++v)
-    he = hipFuncSetAttribute((const void*)select_softmax((v & 1) != 0, (v & 2) != 0), hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024);
   if (he == hipSuccess) he = hipDeviceSynchronize();
   if (he != hipSuccess) {
     int rc = dfail(nullptr, FTDEC_EHIP, std::string("context set-up: ") + hipGetErrorString(he));

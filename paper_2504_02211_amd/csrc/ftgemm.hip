@@ -65,7 +65,7 @@ static void grelease(ftgemm_ctx* c) {
 
 namespace ftgemm {
 
-template <class T> static constexpr TileInfo info_of() { return TileInfo{T::BM, T::BF, T::NW * 64, {T::template lds<false>(), T::template lds<true>()}}; }
+template <class T> static constexpr TileInfo info_of() { return TileInfo{T::BM, T::NW * 64, {T::template lds<false>(), T::template lds<true>()}}; }
 static constexpr TileInfo TILES[N_TILES] = {info_of<TileWide>(), info_of<TileHalf>(), info_of<TileQuarter>(),
                                             info_of<TileStrip>(), info_of<TileNarrow>(), info_of<TileSlim>()};
 

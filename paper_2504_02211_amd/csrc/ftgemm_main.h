@@ -173,6 +173,7 @@ template <int BM_, int BF_, int WT_, int WF_, int BK_, int NST_> struct GTile {
   static constexpr int CB = WT >= NWF ? WT / NWF : 1;
   static constexpr int ROWB = BK * 2;                                // bytes per tile row in LDS
   static constexpr int CPR = BK / 8, PR = 1024 / ROWB;               // 16-byte chunks per row; rows per 1 KB piece
+  static_assert(CPR == 8, "the swizzle of a row's chunks is one of eight");
   static constexpr int XP = BM / PR, WP = BF / PR, CP = GCK / PR;    // pieces per stage
   // ... per wave; where there are fewer pieces than waves, some are fetched twice (to the same place)
   static constexpr int XW = (XP + NW - 1) / NW, WW = (WP + NW - 1) / NW, CW = 1;
@@ -555,9 +556,9 @@ __global__ __launch_bounds__(T::NW * 64, 8 / T::NW) void ftgemm_main(const GArgs
   const uint32_t smem_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
 
   // ---- per-lane source offsets of this wave's load instructions.  Piece p of an operand tile is its
-  // rows PR*p .. PR*p + PR-1; wave w takes pieces w, w+4, ...  Rows beyond the matrix are clamped to its
+  // rows PR*p .. PR*p + PR-1; wave w takes pieces w, w + NW, ...  Rows beyond the matrix are clamped to its
   // last row (their results are never used).  The chunk a lane fetches is the same in all its pieces.
-  auto swz = [](int row) __attribute__((always_inline)) -> int { return CPR == 8 ? (row >> 1) & 7 : (row >> 2) & 3; };
+  auto swz = [](int row) __attribute__((always_inline)) -> int { return (row >> 1) & 7; };
   auto piece_of = [&](int i) __attribute__((always_inline)) -> int {
     return i < T::XW ? (wave + T::NW * i) % T::XP : i < T::XW + T::WW ? wave + T::NW * (i - T::XW) : wave % T::CP;
   };
@@ -774,7 +775,7 @@ __global__ __launch_bounds__(256) void ftgemm_finish(const GArgs a) {
 
 typedef void (*gemm_fn)(const GArgs);
 enum TileId { TILE_WIDE, TILE_HALF, TILE_QUARTER, TILE_STRIP, TILE_NARROW, TILE_SLIM, N_TILES };
-struct TileInfo { int bm, bf, threads, lds[2]; };       // lds: dynamic LDS bytes without / with the checksum rows
+struct TileInfo { int bm, threads, lds[2]; };       // lds: dynamic LDS bytes without / with the checksum rows
 
 // kernel of one tile shape, instantiated per type (ftgemm_f16.hip, ftgemm_bf16.hip); the fault
 // injector exists for TILE_QUARTER only
