@@ -21,14 +21,14 @@ struct ftgemm_ctx {
   const void* encoded_w = nullptr;
   GFault* d_faults = nullptr;
   ftgemm_event* d_events = nullptr;   // ring, never cleared: the slots say which entries a call wrote
-  uint32_t* d_cursor = nullptr;
+  uint32_t* d_cursor = nullptr;       // (a cache line to itself)
   int32_t* d_n_slots = nullptr;       // slots the last launch to run has written ...
-  GSlot* d_slots = nullptr;           // ... and these, SLOTS_AT bytes behind, so that a report is one copy
+  GSlot* d_slots = nullptr;           // ... and these, one GSlot behind, so that a report is one copy
   float4v* ws = nullptr;              // shares of a split contraction
   uint32_t ring_n = 0;
   int n_slots = 0;                    // allocated
   int last_slots = 0;                 // what the last call made here writes (a graph's replay may write another number)
-  std::vector<GSlot> slots;           // d_n_slots and d_slots of a report (GSlot holds SLOTS_AT bytes as a whole number)
+  std::vector<GSlot> slots;           // d_n_slots and d_slots of a report
   GFault* h_faults = nullptr; // pinned staging
   int fault_cap = 0;
   std::vector<ftgemm_event> events;
@@ -38,7 +38,7 @@ struct ftgemm_ctx {
   std::string err;
 };
 
-constexpr size_t SLOTS_AT = 2 * sizeof(GSlot);
+constexpr size_t CURSOR_BYTES = 128;
 
 static thread_local std::string g_gemm_create_err;
 
@@ -230,16 +230,15 @@ extern "C" int ftgemm_create(const ftgemm_config* cfg, ftgemm_ctx** out) {
   // cursor and the number of slots have to start from a value: checksum rows are written before they are read.
   struct { void** at; size_t bytes, from; } parts[] = {
       {(void**)&c->wc, (size_t)c->Tn * GCK * e.k * 2, 0}, {(void**)&c->d_faults, sizeof(GFault) * c->fault_cap, 0},
-      {(void**)&c->d_events, sizeof(ftgemm_event) * (size_t)c->ring_n, 0}, {(void**)&c->d_cursor, sizeof(uint32_t), 0},
-      {(void**)&c->d_n_slots, SLOTS_AT + sizeof(GSlot) * (size_t)c->n_slots, 0}, {(void**)&c->ws, gemm_workspace(km, kn, plan), 0}};
+      {(void**)&c->d_events, sizeof(ftgemm_event) * (size_t)c->ring_n, 0}, {(void**)&c->d_cursor, CURSOR_BYTES + sizeof(GSlot) * (size_t)(1 + c->n_slots), 0}, {(void**)&c->ws, gemm_workspace(km, kn, plan), 0}};
   size_t total = 0;
   for (auto& p : parts) { p.from = total; total += (p.bytes + 255) & ~(size_t)255; }
   GCREATE_TRY(hipMalloc(&c->scratch, total));
   for (auto& p : parts) *p.at = static_cast<char*>(c->scratch) + p.from;
-  c->d_slots = reinterpret_cast<GSlot*>(reinterpret_cast<char*>(c->d_n_slots) + SLOTS_AT);
+  c->d_n_slots = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(c->d_cursor) + CURSOR_BYTES);
+  c->d_slots = reinterpret_cast<GSlot*>(c->d_n_slots) + 1;
   GCREATE_TRY(hipHostMalloc((void**)&c->h_faults, sizeof(GFault) * c->fault_cap, hipHostMallocDefault));
-  GCREATE_TRY(hipMemset(c->d_cursor, 0, sizeof(uint32_t)));
-  GCREATE_TRY(hipMemset(c->d_n_slots, 0, sizeof(int32_t)));
+  GCREATE_TRY(hipMemset(c->d_cursor, 0, CURSOR_BYTES + sizeof(int32_t)));
   GCREATE_TRY(gemm_allow_lds(plan, e.ft_mode != FTGEMM_FT_OFF, e.in_dtype == FTGEMM_BF16));
   GCREATE_TRY(hipDeviceSynchronize());
 #undef GCREATE_TRY
@@ -325,15 +324,14 @@ extern "C" int ftgemm_report(ftgemm_ctx* c, ftgemm_report_view* out) {
   const ftgemm_config& e = c->cfg;
   GHIP_TRY(c, hipSetDevice(e.device));
   GHIP_TRY(c, hipStreamSynchronize(c->last_stream));
-  constexpr int head = SLOTS_AT / sizeof(GSlot);
   int32_t n = c->last_slots;
   for (int have = -1; have < n; ) {         // (a second copy only after a replay that wrote more)
     have = n;
-    c->slots.resize(head + n);
+    c->slots.resize(1 + n);
     GHIP_TRY(c, hipMemcpy(c->slots.data(), c->d_n_slots, sizeof(GSlot) * c->slots.size(), hipMemcpyDeviceToHost));
     std::memcpy(&n, c->slots.data(), sizeof n);
   }
-  const GSlot* slots = c->slots.data() + head;
+  const GSlot* slots = c->slots.data() + 1;
   const GStats stats = gemm_stats(slots, n);
   c->events.clear();
   GHIP_TRY(c, gemm_fetch_events(slots, n, c->d_events, c->ring_n, e.max_events, c->events));

@@ -13,8 +13,8 @@
 // of one token range have to exchange after the last K step is one partial fold per class, through LDS.
 //
 // What bounds it: power.  With operands in registers and nothing else running, 32x32x16 products sustain
-// 1643 TFLOP/s on random fp16 data (1.57 GHz) and 16x16x32 products 1935 (1.87 GHz), against 2450 on
-// zeros (2.35 GHz): the smaller block reads and writes half as many accumulators per flop.  A wave owns a
+// 1660 TFLOP/s on random fp16 data (1.7 GHz) and 16x16x32 products 1880 (2.0 GHz), against 2420 and 2320 on
+// zeros (2.4 GHz): the smaller block reads and writes half as many accumulators per flop.  A wave owns a
 // block of blocks because LDS reads and L2-to-LDS traffic are paid from the same budget.
 //
 // The K dimension is walked in steps of BK through a ring of NST LDS stages filled by direct
