@@ -238,7 +238,7 @@ extern "C" int ftgemm_create(const ftgemm_config* cfg, ftgemm_ctx** out) {
   c->d_n_slots = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(c->d_cursor) + CURSOR_BYTES);
   c->d_slots = reinterpret_cast<GSlot*>(c->d_n_slots) + 1;
   GCREATE_TRY(hipHostMalloc((void**)&c->h_faults, sizeof(GFault) * c->fault_cap, hipHostMallocDefault));
-  GCREATE_TRY(hipMemset(c->d_cursor, 0, CURSOR_BYTES + sizeof(int32_t)));
+  GCREATE_TRY(hipMemset(c->d_cursor, 0, CURSOR_BYTES + 16));        // (whole 16-byte words: a remainder is a launch of its own)
   GCREATE_TRY(gemm_allow_lds(plan, e.ft_mode != FTGEMM_FT_OFF, e.in_dtype == FTGEMM_BF16));
   GCREATE_TRY(hipDeviceSynchronize());
 #undef GCREATE_TRY
