@@ -174,7 +174,7 @@ __global__ __launch_bounds__(256) void ftdec_softmax(const SArgs a) {
 // of chunk c; chunks beyond the row's last valid score are skipped (wave-uniform), so a causal row
 // pays for its own length only.  S has rows of N floats, 16 bytes at a time from any multiple of 4 bytes.
 // Bound: memory (S once, P once; 268 + 134 MB for the lower half of 32 x 2048 x 2048).  There a workgroup
-// per row with eight barriers and four passes over LDS took 223 us, this takes 100.  Rows beyond 4096
+// per row with eight barriers and four passes over LDS took 232 us, this takes 114.  Rows beyond 4096
 // scores do not fit a wave's registers and keep the workgroup-per-row kernel.
 typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
 typedef _Float16 half4 __attribute__((ext_vector_type(4)));
@@ -300,8 +300,8 @@ __global__ __launch_bounds__(256) void ftdec_softmax_wave(const SArgs a) {
     const float inv = 1.0f / wave_sum(sum);
     // ---- normalised weights; eq. (12).  The weight that is summed and the one that is stored are one value:
     // without `opaque` the product is contracted into the sum and into the conversion, each with a
-    // multiplication of its own, and the sum says nothing of what is stored (a pass over 2 x 16 x 2048 x 128,
-    // causal: 306 us contracted, 310 like this).
+    // multiplication of its own, and the sum says nothing of what is stored (the lower half of 32 x 2048 x
+    // 2048: 112 us contracted, 114 like this).
     float psum = 0.f;
     each<CH>([&](auto ci) __attribute__((always_inline)) {
       constexpr int c = decltype(ci)::value;

@@ -12,14 +12,16 @@
 // checksum classes a lane sees are sums over the registers of the lane and of lane^32; what the waves
 // of one token range have to exchange after the last K step is one partial fold per class, through LDS.
 //
-// What bounds it: power.  With operands in registers and nothing else running, 32x32x16 products sustain
-// 1660 TFLOP/s on random fp16 data (1.7 GHz) and 16x16x32 products 1880 (2.0 GHz), against 2420 and 2320 on
-// zeros (2.4 GHz): the smaller block reads and writes half as many accumulators per flop.  A wave owns a
-// block of blocks because LDS reads and L2-to-LDS traffic are paid from the same budget.
+// What bounds it: the clock that power allows, and a matrix pipe that is 71 % busy at it (1.77 GHz; 16384
+// tokens, 4096 -> 16384 features).  With operands in registers and nothing else running, 32x32x16 products
+// sustain 1660 TFLOP/s on random fp16 data (1.7 GHz) and 16x16x32 products 1880 (2.0 GHz), against 2420 and
+// 2320 on zeros (2.4 GHz): the smaller block reads and writes half as many accumulators per flop.  A wave owns
+// a block of blocks because LDS reads and L2-to-LDS traffic are paid from the same budget.
 //
 // The K dimension is walked in steps of BK through a ring of NST LDS stages filled by direct
 // global-to-LDS loads; tiles are stored unpadded with the 16-byte chunk index XOR-ed with a
-// function of the row, which keeps the MFMA operand reads free of bank conflicts.  Operands are read
+// function of the row, which keeps the MFMA operand reads free of bank conflicts (those counted, 2 % of the
+// LDS cycles, are the results on their way through LDS).  Operands are read
 // ahead of their products, also across the stage boundary: the barrier of a stage sits AHEAD rows before
 // its end, where the last operands of the stage are in registers, so that no wave waits for LDS after it.
 //
