@@ -25,6 +25,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <type_traits>
 #include "ftattn.h"
 
 namespace ftattn {
@@ -88,6 +89,21 @@ __device__ __forceinline__ float sum32(float x) {
   auto r = __builtin_amdgcn_permlane32_swap(as_u(x), as_u(x), false, false);
   return as_f(r[0]) + as_f(r[1]);
 }
+// largest of the 64 lanes, valid in lane 63: register moves within rows of 16 lanes, then from row to row (through LDS
+// permutes, six dependent ones for each of four values, the end of a workgroup took 1.5 us longer)
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
+  auto step = [&](auto ctrl, auto rows) __attribute__((always_inline)) {
+    const uint32_t t = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, decltype(ctrl)::value, decltype(rows)::value, 0xF, false);
+    v = t > v ? t : v;
+  };
+  step(std::integral_constant<int, 0x111>{}, std::integral_constant<int, 0xF>{});      // row_shr 1, 2, 4, 8
+  step(std::integral_constant<int, 0x112>{}, std::integral_constant<int, 0xF>{});
+  step(std::integral_constant<int, 0x114>{}, std::integral_constant<int, 0xF>{});
+  step(std::integral_constant<int, 0x118>{}, std::integral_constant<int, 0xF>{});
+  step(std::integral_constant<int, 0x142>{}, std::integral_constant<int, 0xA>{});      // row_bcast 15, 31
+  step(std::integral_constant<int, 0x143>{}, std::integral_constant<int, 0xC>{});
+  return v;
+}
 __device__ __forceinline__ bool wave_any(bool p) { return __builtin_amdgcn_ballot_w64(p) != 0ull; }
 
 __device__ __forceinline__ float flip_if(float x, bool c, int bit) {
@@ -142,19 +158,24 @@ __device__ __forceinline__ int key_of(int kb, int v, int hi) { return 32 * kb + 
 // becomes Inf in fp16; a non-zero one below 2^-24 loses every significant bit (zero or the smallest
 // subnormal).  Values between 2^-24 and 2^-14 become fp16 subnormals, an absolute error below 2^-25,
 // and are not flagged; neither are Inf / NaN inputs, which are the caller's.
-__device__ __forceinline__ uint32_t bf16_range_bits(uint4v raw) {
-  uint32_t bits = 0u;
+// Two values at a time on packed 16-bit integers: m - 0x4780 is below 0x3800 exactly for the too large ones, m - 1 below
+// 0x337F for the too small ones (no value is both).
+typedef uint16_t ushort2v __attribute__((ext_vector_type(2)));
+struct RangeCheck {
+  ushort2v over = (ushort2v)(uint16_t)0xFFFF, under = (ushort2v)(uint16_t)0xFFFF;       // smallest m - 0x4780 and m - 1 so far
+  __device__ __forceinline__ void add(uint4v raw) {
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
-#pragma unroll
-    for (int hlf = 0; hlf < 2; ++hlf) {
-      const uint32_t m = (hlf ? raw[k] >> 16 : raw[k]) & 0x7FFFu;
-      if (m >= 0x4780u && m < 0x7F80u) bits |= FTATTN_RANGE_OPERAND_OVERFLOW;
-      if (m != 0u && m < 0x3380u) bits |= FTATTN_RANGE_OPERAND_UNDERFLOW;
+    for (int k = 0; k < 4; ++k) {
+      const ushort2v m = __builtin_bit_cast(ushort2v, raw[k] & 0x7FFF7FFFu);
+      over = __builtin_elementwise_min(over, (ushort2v)(m - (uint16_t)0x4780));
+      under = __builtin_elementwise_min(under, (ushort2v)(m - (uint16_t)1));
     }
   }
-  return bits;
-}
+  __device__ __forceinline__ uint32_t bits() const {
+    return (over[0] < 0x3800 || over[1] < 0x3800 ? FTATTN_RANGE_OPERAND_OVERFLOW : 0u) |
+           (under[0] < 0x337F || under[1] < 0x337F ? FTATTN_RANGE_OPERAND_UNDERFLOW : 0u);
+  }
+};
 
 // 8 consecutive 16-bit inputs (fp16 or bf16 patterns) -> fp16
 __device__ __forceinline__ half8 to_half8(uint4v raw, bool bf16) {
@@ -180,7 +201,7 @@ __device__ __forceinline__ void encode_k_tile(const void* __restrict__ k, int bf
   const uint16_t* src = reinterpret_cast<const uint16_t*>(k) + (size_t)bh * N * D + ch * 8;
   _Float16* out = kc + ((size_t)bh * Tj + j) * ((BN + CKR) * D) + ch * 8;
   float c1[8], c2[8];
-  uint32_t rbits = 0u;
+  RangeCheck operands;
 #pragma unroll
   for (int x = 0; x < 8; ++x) { c1[x] = 0.f; c2[x] = 0.f; }
 #pragma unroll
@@ -188,7 +209,7 @@ __device__ __forceinline__ void encode_k_tile(const void* __restrict__ k, int bf
     const int r = cls + 8 * l, key = j * BN + r;
     uint4v raw = (uint4v)0u;
     if (key < N) raw = *reinterpret_cast<const uint4v*>(src + (size_t)key * D);
-    if (bf16) rbits |= bf16_range_bits(raw);
+    if (bf16) operands.add(raw);
     const half8 h = to_half8(raw, bf16 != 0);
     *reinterpret_cast<half8*>(out + r * D) = h;
 #pragma unroll
@@ -198,6 +219,7 @@ __device__ __forceinline__ void encode_k_tile(const void* __restrict__ k, int bf
       c2[x] += (float)(l + 1) * v;
     }
   }
+  uint32_t rbits = operands.bits();
   if (!with_checksums) {
     if (rbits) atomicOr(range, rbits);
     return;
@@ -234,7 +256,7 @@ __device__ __forceinline__ int vt_key(int p) {
 template <int D>
 __device__ __forceinline__ void encode_v_tile(const void* __restrict__ v, int bf16, _Float16* __restrict__ vt,
                                               int N, int Tj, int with_checksums, int j, int bh, int tid, uint32_t* range) {
-  uint32_t rbits = 0u;
+  RangeCheck operands;
   // with_checksums == 2: class 0 also folds a column of ones at feature index D (fold D/8), which
   // makes the first checksum of class 0 carry the row-sum through GEMM II
   constexpr int KCH = D / 8, PITCH = D + 8;
@@ -246,9 +268,10 @@ __device__ __forceinline__ void encode_v_tile(const void* __restrict__ v, int bf
     const int r = e / KCH, ch = e % KCH, key = j * BN + r;
     uint4v raw = (uint4v)0u;
     if (key < N) raw = *reinterpret_cast<const uint4v*>(src + (size_t)key * D + ch * 8);
-    if (bf16) rbits |= bf16_range_bits(raw);
+    if (bf16) operands.add(raw);
     *reinterpret_cast<half8*>(tile + r * PITCH + ch * 8) = to_half8(raw, bf16 != 0);
   }
+  uint32_t rbits = operands.bits();
   __syncthreads();
   for (int e = tid; e < D * 8; e += 256) {
     const int f = e >> 3, pc = e & 7;

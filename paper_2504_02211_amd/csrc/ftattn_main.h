@@ -224,25 +224,31 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : 2) void ft
   const DevFault* __restrict__ F = a.faults;
   if (INJ && a.fault_off != nullptr) { fcur = a.fault_off[bh * a.Ti + ti]; fend = a.fault_off[bh * a.Ti + ti + 1]; }
 
-  issue_unit(-1, true);
-  issue_unit(0, true);
-  if (ALT) issue_unit(1, nj >= 2);
+  // The first key tile alone, then the queries, and the other units only when both are there: loads are waited for
+  // in their order, and GEMM I of the first tile needs nothing else.  (With the queries behind three units of
+  // tiles a workgroup's start took 5.5-11 us at head_dim 128 and 3-5 us at head_dim 64, now 5-9 and 2.8-4.)
+  prepare_unit(-1, true);
+#pragma unroll
+  for (int n = 0; n < U::KPW; ++n) issue_piece(n);
 
   // ---- Q_i^T as MFMA B operand: lane (query lq, half hi) holds Q[row][16*slab + 8*hi .. +7]
   // (bf16 queries are converted here: exact for magnitudes in the fp16 normal range)
   half8 qf[NSLAB];
   {
     const uint16_t* qp = reinterpret_cast<const uint16_t*>(a.q) + ((size_t)bh * N + (row < N ? row : 0)) * D + 8 * hi;
-    uint32_t qbits = 0u;
+    RangeCheck operands;
 #pragma unroll
     for (int sl = 0; sl < NSLAB; ++sl) {
       uint4v raw = *reinterpret_cast<const uint4v*>(qp + 16 * sl);
       if (row >= N) raw = (uint4v)0u;
-      if (a.q_bf16) qbits |= bf16_range_bits(raw);
+      if (a.q_bf16) operands.add(raw);
       qf[sl] = to_half8(raw, a.q_bf16 != 0);
     }
-    if (qbits) atomicOr(a.range, qbits);
+    if (const uint32_t qbits = operands.bits()) atomicOr(a.range, qbits);
   }
+  wait_vmcnt<0>();
+  issue_unit(0, true);
+  if (ALT) issue_unit(1, nj >= 2);
 
   float16v o[NFB], oc, s[2], sc;
   half8 ph[2][2];             // P^T in fp16, B operand of GEMM II: [key block][8-key half]
@@ -501,8 +507,8 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : 2) void ft
   };
 
   // ---- prologue: the first key tile's scores; group 1 starts one barrier later than group 0
-  wait_vmcnt<(NSTAGE - 1) * U::NLOAD>();          // unit -1 has landed
-  phase_barrier();
+  phase_barrier();                                // everyone's pieces of the first key tile have landed
+
   if (ALT && grp == 1) phase_barrier();
   if (nj_w > 0) matrix_stream(smem_base, smem_base, no{}, yes{}, no{});
   if (ALT) {
@@ -1141,10 +1147,8 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : 2) void ft
     float vals[4] = {dev_max, rmax_o, rmax_u, rmax_l};
 #pragma unroll
     for (int x = 0; x < 4; ++x) {
-      float v = vals[x];
-#pragma unroll
-      for (int off = 32; off >= 1; off >>= 1) v = fmax2(v, __shfl_xor(v, off));
-      if (lane == 0) atomicMax(rm + x, as_u(v));
+      const uint32_t v = wave_max_u32(as_u(vals[x]));
+      if (lane == 63) atomicMax(rm + x, v);
     }
     if (lane == 0 && rechecks) atomicAdd(a.recheck, (unsigned long long)rechecks);
   }
