@@ -16,7 +16,14 @@ using namespace ftattn;
 
 // Shape-derived sizes of one configuration: tiles per head and the element counts of the encoded
 // key / value tiles.
-struct Geometry { int BH = 0, Ti = 0, Tj = 0, BM = 0; size_t n_kc = 0, n_vt = 0; };
+struct Geometry {
+  int BH = 0, Ti = 0, Tj = 0, BM = 0;
+  size_t n_kc = 0, n_vt = 0;
+  // Row tiles split by their keys (see share_of): those launched from number first_split on, in shares of up to `piece`
+  // key tiles, `shares` in all; n_ws floats hold their state.
+  int first_split = 0, piece = 1, shares = 0;
+  size_t n_ws = 0;
+};
 
 // Device buffers one pass works on (owned by a context, or carved out of the static scratch array).
 struct Buffers {
@@ -28,6 +35,7 @@ struct Buffers {
   int32_t* ev_count = nullptr;
   unsigned long long* recheck = nullptr;
   uint32_t* resmax = nullptr;
+  float* ws = nullptr;                // state of split row tiles (null: no row tile is split)
   uint32_t* range = nullptr;          // the word this call sets
   uint32_t* range_next = nullptr;     // the word the next call sets: cleared by this call
 };
@@ -43,6 +51,7 @@ struct ftattn_ctx {
   // device scratch
   _Float16* kc = nullptr;
   _Float16* vt = nullptr;
+  float* ws = nullptr;
   DevFault* d_faults = nullptr;
   int32_t* d_fault_off = nullptr;
   ftattn_event* d_events = nullptr;
@@ -82,7 +91,7 @@ static int fail(ftattn_ctx* c, int code, const std::string& msg) {
 
 static void release(ftattn_ctx* c) {
   if (!c) return;
-  (void)hipFree(c->kc); (void)hipFree(c->vt); (void)hipFree(c->d_faults);
+  (void)hipFree(c->kc); (void)hipFree(c->vt); (void)hipFree(c->ws); (void)hipFree(c->d_faults);
   (void)hipFree(c->d_fault_off); (void)hipFree(c->d_events); (void)hipFree(c->d_stat);
   if (c->h_faults) (void)hipHostFree(c->h_faults);
   if (c->h_stat) (void)hipHostFree(c->h_stat);
@@ -90,7 +99,7 @@ static void release(ftattn_ctx* c) {
   delete c;
 }
 
-typedef void (*main_fn)(const KArgs);
+typedef kernel_fn main_fn;
 
 template <int D, bool INJ>
 static main_fn pick(bool ft, bool causal) {
@@ -106,6 +115,8 @@ namespace ftattn {
 void (*select_perstep(int D, bool causal, bool inject, int mode))(const KArgs);
 void (*select_elementwide(int D, bool causal, bool inject))(const KArgs);
 void (*select_lazy(int D, bool ft, bool causal, bool inject))(const KArgs);
+kernel_fn select_split(int D, bool ft, bool causal);
+kernel_fn select_finish(int D, bool ft, bool causal);
 }
 
 static main_fn select_kernel(int D, bool ft, bool causal, bool inject) {
@@ -117,6 +128,62 @@ static main_fn select_kernel(int D, bool ft, bool causal, bool inject) {
 static size_t lds_bytes(int D, bool ft) {
   if (D == 128) return ft ? Unit<128, true>::LDS_TOTAL : Unit<128, false>::LDS_TOTAL;
   return ft ? Unit<64, true>::LDS_TOTAL : Unit<64, false>::LDS_TOTAL;
+}
+
+// Which row tiles are split by their keys, and into shares of how many: the plan with the least expected time.
+// Microseconds, from timings of both head sizes with 1..512 row tiles of 2..256 key tiles: a workgroup costs `fixed`
+// and `tile` per key tile, one at a time per CU (two that share a CU at head_dim 64 take about twice as long each); a
+// split adds the launch that puts the shares together, and their state passes through memory twice.  Measured, unsplit and
+// as planned here: 1 x 1 x 16384 x 128 causal 497 and 138 us, 2 x 3 x 5001 x 128 187 and 145, 1 x 5 x 3001 x 64 causal
+// 74 and 46, 1 x 20 x 2048 x 128 causal 95 and 79.  Row tiles of equal length that fill the CUs a whole number of
+// times and a little more: only those left over are split (3 x 16 x 1531 x 128, 288 row tiles: 164 and 137 us; all
+// split in two 191).  Beyond twice the CUs (causal: light row tiles fill up the last round; else four times) a split
+// gains nothing, and neither do short rows, where starting and finishing a workgroup is most of it (6 key tiles, 2 x 3 x
+// 333 x 128: 28.8 and 27.9 us; 8, 1 x 2 x 512 x 64: 22.1 and 20.8; 11, 1 x 7 x 700 x 128: 41 and 37; 16, 1 x 1 x 1000 x 128:
+// 48 and 34).  A call with a fault list is never split: faults name values of Algorithm 1's one pass over the keys.
+static void plan_split(const ftattn_config& e, Geometry& g) {
+  constexpr long long CUS = 256;
+  const long long tiles = (long long)g.BH * g.Ti;
+  g.first_split = (int)tiles;
+  if (e.per_step != 0 || e.stride != 8 || e.rescale_margin > 0.f || g.Tj < 12 || tiles >= (e.causal ? 2 : 4) * CUS) return;
+  // (the same plan for every ft_mode, so that the unprotected variant computes the same numbers; its key tiles are about
+  // 0.7 times as long)
+  const bool d128 = e.head_dim == 128;
+  const double fixed = d128 ? 9.0 : 4.5, tile = d128 ? 2.6 : 1.2;
+  constexpr double FINISH = 5.0, PER_PART = 1.0, MEMORY = 4e6;       // bytes per microsecond
+  constexpr size_t WS_BYTES = (size_t)96 << 20;
+  const size_t state = (size_t)nwave_of(e.head_dim) * 64 * sizeof(float) * (d128 ? part_values<128, true>() : part_values<64, true>());
+  const int per_row = g.BM / BN;
+  const double keys = g.BH * (e.causal ? 0.5 * per_row * g.Ti * (g.Ti + 1.0) - (per_row * g.Ti - g.Tj) : (double)g.Ti * g.Tj);
+  auto count = [&](long long whole, int piece) {      // shares of all row tiles but the first `whole`
+    long long n = 0;
+    for (int p = 0; p * piece < g.Tj; ++p) n += row_tiles_with(p, e.causal != 0, (int)(tiles - whole), g.BH, g.Ti, piece, per_row);
+    return n;
+  };
+  auto cost = [&](long long whole, int piece, long long n) {
+    const int parts = (g.Tj + piece - 1) / piece;
+    const double longest = piece * tile + fixed;
+    double us = (double)(whole / CUS) * (g.Tj * tile + fixed);
+    if (n <= CUS || !e.causal) us += std::ceil((double)n / CUS) * longest;
+    else us += std::max(longest, (keys * tile + n * fixed) / CUS + 0.5 * longest);
+    if (parts > 1) us += FINISH + PER_PART * parts + 2.0 * n * (double)state / MEMORY;
+    return us;
+  };
+  double best = cost(0, g.Tj, tiles);
+  for (int some = 0; some < 2; ++some) {
+    const long long whole = some ? tiles / CUS * CUS : 0;
+    if (some ? e.causal || whole == 0 || whole == tiles : tiles >= 2 * CUS) continue;
+    for (int parts = 2; parts <= MAX_PARTS && parts <= g.Tj; ++parts) {
+      const int piece = (g.Tj + parts - 1) / parts;
+      const long long n = count(whole, piece);
+      if (n * state > WS_BYTES) break;
+      const double us = cost(whole, piece, n);
+      if (us < 0.97 * best) {
+        best = us;
+        g.first_split = (int)whole; g.piece = piece; g.shares = (int)n; g.n_ws = n * state / sizeof(float);
+      }
+    }
+  }
 }
 
 // Checks cfg and resolves its defaults into e (tile sizes, thresholds, scale) and g.  Touches no
@@ -168,17 +235,23 @@ static int resolve_config(const ftattn_config* cfg, ftattn_config& e, Geometry& 
   g.Ti = (e.seq + g.BM - 1) / g.BM;
   g.n_kc = (size_t)g.BH * g.Tj * (BN + CKR) * e.head_dim;
   g.n_vt = (size_t)g.BH * g.Tj * (e.head_dim + CKR) * BN;
+  plan_split(e, g);
   return FTATTN_OK;
 }
 
 // Lets the kernels of one head size (and mode) use their dynamic LDS.  Needs the device current.
-static hipError_t allow_lds(int D, int per_step, int stride, const char*& why, bool lazy = false) {
+static hipError_t allow_lds(int D, int per_step, int stride, const char*& why, bool lazy, bool split) {
   why = "no kernel for this tile shape";
   for (int v = 0; v < 8; ++v) {
     const int ft = v & 1, ca = (v >> 1) & 1;
     main_fn f = select_kernel(D, ft != 0, ca != 0, (v >> 2) != 0);
     if (!f) return hipErrorInvalidValue;
     hipError_t he = hipFuncSetAttribute((const void*)f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes(D, ft != 0));
+    if (he != hipSuccess) { why = "hipFuncSetAttribute"; return he; }
+  }
+  for (int v = 0; v < 4 && split; ++v) {
+    const bool ft = (v & 1) != 0;
+    hipError_t he = hipFuncSetAttribute((const void*)select_split(D, ft, (v & 2) != 0), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes(D, ft));
     if (he != hipSuccess) { why = "hipFuncSetAttribute"; return he; }
   }
   for (int v = 0; v < 8 && lazy; ++v) {
@@ -227,6 +300,7 @@ extern "C" int ftattn_create(const ftattn_config* cfg, ftattn_ctx** out) {
   } while (0)
   CREATE_TRY(hipMalloc((void**)&c->kc, g.n_kc * 2));
   CREATE_TRY(hipMalloc((void**)&c->vt, g.n_vt * 2));
+  if (g.n_ws) CREATE_TRY(hipMalloc((void**)&c->ws, g.n_ws * sizeof(float)));
   CREATE_TRY(hipMalloc((void**)&c->d_faults, sizeof(DevFault) * c->fault_cap));
   CREATE_TRY(hipMalloc((void**)&c->d_fault_off, sizeof(int32_t) * (n_rt + 1)));
   CREATE_TRY(hipMalloc((void**)&c->d_events, sizeof(ftattn_event) * (size_t)e.max_events));
@@ -241,7 +315,7 @@ extern "C" int ftattn_create(const ftattn_config* cfg, ftattn_ctx** out) {
   CREATE_TRY(hipMemset(c->kc, 0, g.n_kc * 2));
   CREATE_TRY(hipMemset(c->vt, 0, g.n_vt * 2));
   {
-    hipError_t le = allow_lds(e.head_dim, e.per_step, e.stride, why, e.rescale_margin > 0.f);
+    hipError_t le = allow_lds(e.head_dim, e.per_step, e.stride, why, e.rescale_margin > 0.f, g.n_ws != 0);
     if (le != hipSuccess) {
       int rc = fail(nullptr, le == hipErrorInvalidValue ? FTATTN_EUNSUPPORTED : FTATTN_EHIP, std::string(why) + ": " + hipGetErrorString(le));
       release(c);
@@ -282,6 +356,11 @@ static hipError_t launch_pass(const ftattn_config& e, const Geometry& g, const B
   a.q = q; a.q_bf16 = bf; a.kc = b.kc; a.vt = b.vt; a.o = o; a.out_dtype = e.out_dtype;
   a.N = N; a.H = e.heads; a.Ti = g.Ti; a.Tj = g.Tj;
   a.head_group = head_group(D, ft, g.BH, g.Ti);
+  const bool split = b.ws && !inject;
+  a.n_tiles = g.BH * g.Ti;
+  a.first_split = split ? g.first_split : a.n_tiles;
+  a.piece = g.piece;
+  a.ws = b.ws;
   a.scale = e.softmax_scale;
   a.scale_log2 = e.softmax_scale * 1.4426950408889634f;
   a.eps1 = e.eps1;
@@ -297,10 +376,16 @@ static hipError_t launch_pass(const ftattn_config& e, const Geometry& g, const B
   main_fn f = e.per_step ? select_perstep(D, e.causal != 0, inject, e.per_step)
               : e.stride == 1 ? select_elementwide(D, e.causal != 0, inject)
               : e.rescale_margin > 0.f ? select_lazy(D, ft, e.causal != 0, inject)
+              : split ? select_split(D, ft, e.causal != 0)
                               : select_kernel(D, ft, e.causal != 0, inject);
   if (timing && (he = hipEventRecord(timing[1], st)) != hipSuccess) return he;
-  hipLaunchKernelGGL(f, dim3(g.BH * g.Ti), dim3(nwave_of(D) * 64), lds_bytes(D, ft), st, a);
+  const int n_split = a.n_tiles - a.first_split;
+  hipLaunchKernelGGL(f, dim3(a.first_split + (split ? g.shares : 0)), dim3(nwave_of(D) * 64), lds_bytes(D, ft), st, a);
   if ((he = hipGetLastError()) != hipSuccess) return he;
+  if (split) {
+    hipLaunchKernelGGL(select_finish(D, ft, e.causal != 0), dim3(n_split * nwave_of(D)), dim3(2 * D), 0, st, a);
+    if ((he = hipGetLastError()) != hipSuccess) return he;
+  }
   if (timing && (he = hipEventRecord(timing[2], st)) != hipSuccess) return he;
   return hipSuccess;
 }
@@ -354,7 +439,7 @@ extern "C" int ftattn_forward(ftattn_ctx* c, const void* q, const void* k, const
   }
 
   Buffers bufs;
-  bufs.kc = c->kc; bufs.vt = c->vt; bufs.faults = c->d_faults; bufs.fault_off = n_faults > 0 ? c->d_fault_off : nullptr;
+  bufs.kc = c->kc; bufs.vt = c->vt; bufs.ws = c->ws; bufs.faults = c->d_faults; bufs.fault_off = n_faults > 0 ? c->d_fault_off : nullptr;
   bufs.events = c->d_events;
   bufs.ev_count = (int32_t*)(c->d_stat + STAT_EVENTS);
   bufs.recheck = (unsigned long long*)(c->d_stat + STAT_RECHECK);
@@ -503,7 +588,9 @@ extern "C" int ftattn_forward_static(const ftattn_config* cfg, const void* q, co
   const size_t off_events = off_resmax + up(sizeof(uint32_t) * (size_t)g.BH * g.Ti * 4);
   const size_t off_kc = off_events + up(sizeof(ftattn_event) * (size_t)e.max_events);
   const size_t off_vt = off_kc + up(g.n_kc * 2);
-  const size_t need = off_vt + up(g.n_vt * 2);
+  const size_t off_ws = off_vt + up(g.n_vt * 2), need = off_ws;
+  // (where the state of split row tiles does not fit as well, none is split)
+  const bool split = g.n_ws != 0 && off_ws + g.n_ws * sizeof(float) <= STATIC_SCRATCH_BYTES;
   if (need > STATIC_SCRATCH_BYTES) {
     snprintf(g_static_err, sizeof g_static_err, "this shape needs %zu bytes of scratch, the static array holds %zu", need, STATIC_SCRATCH_BYTES);
     return FTATTN_EUNSUPPORTED;
@@ -523,7 +610,7 @@ extern "C" int ftattn_forward_static(const ftattn_config* cfg, const void* q, co
     }
     const int di = e.head_dim == 128 ? 1 : 0;
     if (!g_static_lds[e.device][di]) {
-      he = allow_lds(e.head_dim, 0, 8, why);
+      he = allow_lds(e.head_dim, 0, 8, why, false, true);
       if (he != hipSuccess) return static_fail(FTATTN_EHIP, why, he);
       g_static_lds[e.device][di] = true;
     }
@@ -540,6 +627,7 @@ extern "C" int ftattn_forward_static(const ftattn_config* cfg, const void* q, co
   bufs.events = (ftattn_event*)(base + off_events);
   bufs.kc = (_Float16*)(base + off_kc);
   bufs.vt = (_Float16*)(base + off_vt);
+  bufs.ws = split ? (float*)(base + off_ws) : nullptr;
   he = launch_pass(e, g, bufs, q, k, v, o, false, (hipStream_t)hip_stream, nullptr);
   if (he != hipSuccess) return static_fail(FTATTN_EHIP, "launch", he);
   return FTATTN_OK;

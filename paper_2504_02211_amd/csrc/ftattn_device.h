@@ -50,6 +50,9 @@ struct KArgs {
   void* o;                 // [BH][N][D], fp32 / fp16 / bf16
   int32_t out_dtype;
   int32_t N, H, Ti, Tj;
+  int32_t n_tiles;         // row tiles of all heads
+  int32_t first_split, piece;      // which of them are split by their keys, and how: see share_of
+  float* ws;               // the state of the shares
   int32_t head_group;      // (causal) heads whose row tiles are issued together, see causal_row_tile
   float scale;             // sigma
   float scale_log2;        // sigma * log2(e)

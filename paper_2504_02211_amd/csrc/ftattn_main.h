@@ -62,6 +62,52 @@ __host__ __device__ __forceinline__ RowTile causal_row_tile(int id, int total, i
   return RowTile{head + slot % n, Ti - 1 - slot / n};
 }
 
+// ---- the share of the keys of a row tile that a workgroup takes.  In a split call the row tiles from launch number
+// `first_split` on are divided among up to `parts` workgroups each, by their key tiles: a row tile of L key tiles has
+// ceil(L / piece) shares, of equal length to within one.  The first shares of all these row tiles are launched first, then
+// the second ones of those that have one, and so on (longest row tiles first, and no workgroup without work: those
+// would still be dealt to the shader engines in turn, and leave some with more than others).  The shares of a row
+// tile leave their state in memory (store_part), ftattn_finish puts it together.
+__host__ __device__ __forceinline__ int row_tiles_with(int part, bool causal, int n_split, int heads, int Ti, int piece, int tiles_per_row) {
+  return causal ? heads * (Ti - part * piece / tiles_per_row) : n_split;      // those of more than `part` shares
+}
+struct Share {
+  RowTile rt;
+  int nj;                  // key tiles of the row tile
+  int part, nparts;
+  int first, count;        // key tiles of this share
+  int rank, slot;          // number of the row tile among the split ones, of this share's state in memory
+};
+template <int D, bool CAUSAL> __device__ __forceinline__ void place_share(const KArgs& a, Share& h, bool split) {
+  const int end = (h.rt.ti + 1) * bm_of(D), last_row = (end < a.N ? end : a.N) - 1;
+  h.nj = CAUSAL ? last_row / BN + 1 : a.Tj;
+  h.nparts = split ? (h.nj + a.piece - 1) / a.piece : 1;
+  h.first = split ? h.nj * h.part / h.nparts : 0;
+  h.count = split ? h.nj * (h.part + 1) / h.nparts - h.first : h.nj;
+}
+template <int D, bool CAUSAL> __device__ __forceinline__ RowTile split_row_tile(const KArgs& a, int rank) {
+  const int heads = a.n_tiles / a.Ti;
+  return CAUSAL ? RowTile{rank % heads, a.Ti - 1 - rank / heads} : even_row_tile(a.first_split + rank, a.n_tiles, a.Ti);
+}
+template <int D, bool CAUSAL, bool SPLIT> __device__ __forceinline__ Share share_of(const KArgs& a, int id) {
+  Share h;
+  h.part = h.slot = h.rank = 0;
+  if (SPLIT && id >= a.first_split) {
+    const int n_split = a.n_tiles - a.first_split, heads = a.n_tiles / a.Ti;
+    h.slot = h.rank = id - a.first_split;
+    for (int n = n_split; h.rank >= n; n = row_tiles_with(h.part, CAUSAL, n_split, heads, a.Ti, a.piece, bm_of(D) / BN)) {
+      h.rank -= n;
+      ++h.part;
+    }
+    h.rt = split_row_tile<D, CAUSAL>(a, h.rank);
+    place_share<D, CAUSAL>(a, h, true);
+    return h;
+  }
+  h.rt = CAUSAL ? causal_row_tile(id, a.n_tiles, a.Ti, a.head_group) : even_row_tile(id, a.n_tiles, a.Ti);
+  place_share<D, CAUSAL>(a, h, false);
+  return h;
+}
+
 // Heads per group: the fewest whose row tiles fill the workgroup slots of an XCD (32 CUs) once.  Larger
 // groups would let fewer workgroups share the K / V of a head in the L2.  Never 0, and at most the heads of an XCD.
 inline int head_group(int D, bool ft, int BH, int Ti) {
@@ -69,6 +115,8 @@ inline int head_group(int D, bool ft, int BH, int Ti) {
   const int g = (slots + Ti - 1) / Ti;
   return g < h8 ? g : h8 > 0 ? h8 : 1;
 }
+
+typedef void (*kernel_fn)(const KArgs);
 
 template <int D, bool FT> struct Unit {
   static constexpr int KROWS = FT ? BN + CKR : BN;
@@ -115,6 +163,386 @@ __device__ __forceinline__ void phase_barrier() {
 __device__ __forceinline__ float opaque(float x) { asm volatile("" : "+v"(x)); return x; }
 __device__ __forceinline__ half2v opaque(half2v x) { asm volatile("" : "+v"(x)); return x; }
 
+// Sum-form check of the output accumulator against its checksums (Algorithm 1, last "if"; text
+// after eq. (16) for location and repair): class r of the lane, folds o[fb][4*gg + r].  `thr` is
+// the threshold in the units the accumulator is in, `tile` the key tile reported with an event
+// (-1 after the loop), `xfold` / `xv` the extra fold of class 0 in the exact row-sum mode.
+template <int D, bool EW>
+__device__ __forceinline__ bool sum_check(const KArgs& a, float16v (&o)[D / 32], const float16v& oc, const int bh, const int row, const int hi,
+                                          const float thr, const int tile, const bool real, const bool xf, const float xv,
+                                          const bool track, float& rmax_o) {
+  constexpr int NFB = D / 32, NFOLD_V = D / 8;
+  if (EW) {
+    // one class over all D features of the row (fold index = feature), from both lanes of the query
+    float sum1 = 0.f, chk1 = 0.f;
+#pragma unroll
+    for (int fb = 0; fb < NFB; ++fb)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) sum1 += o[fb][v];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) chk1 += oc[r] + oc[4 + r];
+    sum1 = sum32(sum1); chk1 = sum32(chk1);
+    const float R1 = chk1 - sum1;
+    const bool d = real && !(__builtin_fabsf(R1) <= thr);
+    if (track && !d && real) rmax_o = fmax2(rmax_o, __builtin_fabsf(R1));
+    if (!wave_any(d)) return false;
+    float chk2 = 0.f, sum2 = 0.f, big = -1.f;
+    int l_big = -1;
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      chk2 += 8.0f * (oc[8 + r] + oc[12 + r]) + (float)(4 * hi + r - 7) * (oc[r] + oc[4 + r]);
+#pragma unroll
+    for (int fb = 0; fb < NFB; ++fb)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int l = 32 * fb + 8 * (v >> 2) + 4 * hi + (v & 3);
+        const float ov = o[fb][v];
+        sum2 += (float)(l + 1) * ov;
+        const float mag = finitef(ov) ? __builtin_fabsf(ov) : __builtin_inff();
+        if (mag > big) { big = mag; l_big = l; } else if (mag == big) { l_big = -1; }
+      }
+    chk2 = sum32(chk2); sum2 = sum32(sum2);
+    {
+      const float bigp = xchg32(big, hi);
+      const int lp = (int)xchg32((float)l_big, hi);
+      if (bigp > big) l_big = lp; else if (bigp == big) l_big = -1;
+    }
+    int lstar = -1;
+    {
+      const float ratio = (chk2 - sum2) / R1;
+      if (finitef(ratio)) {
+        const float c = __builtin_rintf(ratio) - 1.0f;
+        if (c >= 0.f && c < (float)D) lstar = (int)c;
+      } else {
+        lstar = l_big;
+      }
+    }
+    if (!d) lstar = -1;
+    float rest = 0.f;
+#pragma unroll
+    for (int fb = 0; fb < NFB; ++fb)
+#pragma unroll
+      for (int v = 0; v < 16; ++v)
+        if (32 * fb + 8 * (v >> 2) + 4 * hi + (v & 3) != lstar) rest += o[fb][v];
+    rest = sum32(rest);
+    if (d) {
+      const bool fix = a.correct && lstar >= 0;
+      if (hi == 0) log_event(a, bh, FTATTN_CHECK_O, tile, row, lstar, R1, fix ? 1 : 0);
+      if (fix) {
+        const float val = chk1 - rest;
+#pragma unroll
+        for (int fb = 0; fb < NFB; ++fb)
+#pragma unroll
+          for (int v = 0; v < 16; ++v)
+            if (32 * fb + 8 * (v >> 2) + 4 * hi + (v & 3) == lstar) o[fb][v] = val;
+      }
+    }
+    return true;       // events may have been written
+  }
+  bool bad = false;
+  float R[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    float sum1 = 0.f;
+#pragma unroll
+    for (int fb = 0; fb < NFB; ++fb)
+#pragma unroll
+      for (int gg = 0; gg < 4; ++gg) sum1 += o[fb][4 * gg + r];
+    if (r == 0 && xf) sum1 += xv;      // the normalised extra fold of class 0
+    R[r] = (oc[r] + oc[4 + r]) - sum1;
+    bool d = real && !(__builtin_fabsf(R[r]) <= thr);
+    bad |= d;
+    if (track && !d && real) rmax_o = fmax2(rmax_o, __builtin_fabsf(R[r]));
+  }
+  if (wave_any(bad)) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      if (real && !(__builtin_fabsf(R[r]) <= thr)) {
+        float chk1 = oc[r] + oc[4 + r], chk2 = oc[8 + r] + oc[12 + r];
+        float sum2 = 0.f, big = -1.f;
+        int l_big = -1;
+#pragma unroll
+        for (int fb = 0; fb < NFB; ++fb)
+#pragma unroll
+          for (int gg = 0; gg < 4; ++gg) {
+            float ov = o[fb][4 * gg + r];
+            sum2 += (float)(4 * fb + gg + 1) * ov;
+            float mag = finitef(ov) ? __builtin_fabsf(ov) : __builtin_inff();
+            if (mag > big) { big = mag; l_big = 4 * fb + gg; } else if (mag == big) { l_big = -1; }
+          }
+        const bool xfold = r == 0 && xf;      // class 0 has the row-sum as fold NFOLD_V
+        if (xfold) {
+          sum2 += (float)(NFOLD_V + 1) * xv;
+          float mag = finitef(xv) ? __builtin_fabsf(xv) : __builtin_inff();
+          if (mag > big) { big = mag; l_big = NFOLD_V; } else if (mag == big) { l_big = -1; }
+        }
+        float ratio = (chk2 - sum2) / R[r];
+        int lstar = -1;
+        if (finitef(ratio)) {
+          float c = __builtin_rintf(ratio) - 1.0f;
+          if (c >= 0.f && c < (float)(xfold ? NFOLD_V + 1 : NFOLD_V)) lstar = (int)c;
+        } else {
+          lstar = l_big;
+        }
+        if (xfold && lstar == NFOLD_V) continue;             // the row-sum itself: reported by its own check
+        int col = lstar >= 0 ? 8 * lstar + 4 * hi + r : -1;
+        bool fix = a.correct && lstar >= 0;
+        log_event(a, bh, FTATTN_CHECK_O, tile, row, col, R[r], fix ? 1 : 0);
+        if (fix) {
+          float rest = xfold ? xv : 0.f;
+#pragma unroll
+          for (int fb = 0; fb < NFB; ++fb)
+#pragma unroll
+            for (int gg = 0; gg < 4; ++gg)
+              if (4 * fb + gg != lstar) rest += o[fb][4 * gg + r];
+          float val = chk1 - rest;
+#pragma unroll
+          for (int fb = 0; fb < NFB; ++fb)
+#pragma unroll
+            for (int gg = 0; gg < 4; ++gg)
+              if (4 * fb + gg == lstar) o[fb][4 * gg + r] = val;
+        }
+      }
+    }
+    return true;       // events may have been written
+  }
+  return false;
+}
+
+// The largest statistics that passed, per row tile (non-negative floats order like their bits), and the re-evaluations.
+__device__ __forceinline__ void note_statistics(const KArgs& a, const int bh, const int ti, const int lane, const float (&vals)[4], const unsigned rechecks) {
+  uint32_t* rm = a.resmax + ((size_t)bh * a.Ti + ti) * 4;
+#pragma unroll
+  for (int x = 0; x < 4; ++x) {
+    const uint32_t v = wave_max_u32(as_u(vals[x]));
+    if (lane == 63) atomicMax(rm + x, v);
+  }
+  if (lane == 0 && rechecks) atomicAdd(a.recheck, (unsigned long long)rechecks);
+}
+
+// What follows the last key tile of 32 query rows whose state a wave holds: row-sum range check, normalisation,
+// sum-form check, store, statistics.
+template <int D, bool FT, bool CAUSAL, int PS>
+__device__ __forceinline__ void finish_rows(const KArgs& a, float16v (&o)[D / 32], float16v& oc, const int bh, const int ti, const int row,
+                                            const int lane, const float l_part, const float l_low, const float m_run, const float m_true,
+                                            const float dev_max, const unsigned rechecks) {
+  constexpr int NFB = D / 32, NFOLD_V = D / 8;
+  constexpr bool DMR = PS == 2, LAZY = PS == 4;
+  const int N = a.N, hi = lane >> 5;
+  const float sl2 = a.scale_log2;
+  float rmax_o = 0.f, rmax_u = 0.f, rmax_l = 0.f;
+  {
+    const bool real = row < N;
+    float l = sum32(l_part);
+    const bool lfold = FT && a.rowsum_fold != 0;
+    if (FT && lfold) {
+      // The row-sum as fold NFOLD_V of checksum class 0 (held by the lane half hi == 0, register
+      // r == 0): the row-sum the checksum implies against the accumulated one, in units of the
+      // row-sum; on a mismatch the location rule over the NFOLD_V + 1 folds decides whether the
+      // row-sum is the wrong element, and if so it is replaced by the implied one.
+      float sumx = 0.f;
+#pragma unroll
+      for (int fb = 0; fb < NFB; ++fb)
+#pragma unroll
+        for (int gg = 0; gg < 4; ++gg) sumx += o[fb][4 * gg];
+      const float chk1 = oc[0] + oc[4];
+      const float lc = chk1 - sumx;
+      const float rr = (lc - l) / lc;
+      const bool detl = real && hi == 0 && (!(__builtin_fabsf(rr) <= a.tau_o) || !finitef(rr));
+      if (!detl && real && hi == 0) rmax_u = fmax2(rmax_u, __builtin_fabsf(rr));
+      if (wave_any(detl)) {
+        if (detl) {
+          const float chk2 = oc[8] + oc[12];
+          float sum2 = (float)(NFOLD_V + 1) * l;
+          float big = finitef(l) ? __builtin_fabsf(l) : __builtin_inff();
+          int l_big = NFOLD_V;
+#pragma unroll
+          for (int fb = 0; fb < NFB; ++fb)
+#pragma unroll
+            for (int gg = 0; gg < 4; ++gg) {
+              const float ov = o[fb][4 * gg];
+              sum2 += (float)(4 * fb + gg + 1) * ov;
+              const float mag = finitef(ov) ? __builtin_fabsf(ov) : __builtin_inff();
+              if (mag > big) { big = mag; l_big = 4 * fb + gg; } else if (mag == big) { l_big = -1; }
+            }
+          const float ratio = (chk2 - sum2) / (lc - l);
+          int lstar = -1;
+          if (finitef(ratio)) {
+            const float c = __builtin_rintf(ratio) - 1.0f;
+            if (c >= 0.f && c < (float)(NFOLD_V + 1)) lstar = (int)c;
+          } else {
+            lstar = l_big;
+          }
+          if (lstar == NFOLD_V) {
+            log_event(a, bh, FTATTN_CHECK_L, -1, row, 0, rr, a.correct ? 1 : 0);
+            if (a.correct) l = lc;
+          }
+        }
+      }
+      // the other half of the row takes the row-sum of the half that checked it
+      const float lp = xchg32(l, hi);
+      if (hi == 1) l = lp;
+    }
+    if (FT && !lfold && !DMR) {
+      float Ub = CAUSAL ? (float)(row + 1 < N ? row + 1 : N) : (float)N;
+      if (LAZY) Ub *= ex2((m_true - m_run) * sl2);      // exponentials reach exp(running maximum - reference)
+      float lo = l_low;
+      bool detl = real && !(lo * (1.f - a.delta_l) <= l && l <= Ub * (1.f + a.delta_l));
+      if (!detl && real) { rmax_u = fmax2(rmax_u, l / Ub); rmax_l = fmax2(rmax_l, lo / l); }
+      if (detl) {
+        if (hi == 0) log_event(a, bh, FTATTN_CHECK_L, -1, row, 0, l, a.correct ? 1 : 0);
+        if (a.correct) l = lo;     // the approximation of Section 3.4, "optimized EFTA"
+      }
+    }
+    float inv = 1.0f / l;
+#pragma unroll
+    for (int fb = 0; fb < NFB; ++fb) o[fb] *= inv;
+    if (FT) {
+      oc *= inv;
+      (void)sum_check<D, PS == 3>(a, o, oc, bh, row, hi, a.tau_o, -1, real, lfold && hi == 0, l * inv, true, rmax_o);
+    }
+    // ---- store: lane holds features 32*fb + 8*gg + 4*hi + (0..3) of its query
+    if (real) {
+      size_t base = ((size_t)bh * N + row) * D;
+#pragma unroll
+      for (int fb = 0; fb < NFB; ++fb)
+#pragma unroll
+        for (int gg = 0; gg < 4; ++gg) {
+          int f = 32 * fb + 8 * gg + 4 * hi;
+          float x0 = o[fb][4 * gg], x1 = o[fb][4 * gg + 1], x2 = o[fb][4 * gg + 2], x3 = o[fb][4 * gg + 3];
+          if (a.out_dtype == FTATTN_F32) {
+            float4 v = make_float4(x0, x1, x2, x3);
+            *reinterpret_cast<float4*>(reinterpret_cast<float*>(a.o) + base + f) = v;
+          } else if (a.out_dtype == FTATTN_F16) {
+            _Float16 hv[4] = {(_Float16)x0, (_Float16)x1, (_Float16)x2, (_Float16)x3};
+            *reinterpret_cast<uint2*>(reinterpret_cast<_Float16*>(a.o) + base + f) = *reinterpret_cast<uint2*>(hv);
+          } else {
+            uint32_t u[4] = {as_u(x0), as_u(x1), as_u(x2), as_u(x3)};
+            uint16_t bv16[4];
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+              uint32_t rnd = ((u[x] >> 16) & 1u) + 0x7FFFu;
+              bv16[x] = (u[x] & 0x7F800000u) == 0x7F800000u ? (uint16_t)(u[x] >> 16) : (uint16_t)((u[x] + rnd) >> 16);
+            }
+            *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(a.o) + base + f) = *reinterpret_cast<uint2*>(bv16);
+          }
+        }
+    }
+  }
+  if (FT) {
+    const float vals[4] = {dev_max, rmax_o, rmax_u, rmax_l};
+    note_statistics(a, bh, ti, lane, vals, rechecks);
+  }
+}
+
+// The state of 32 query rows after a share of their keys, as 64 lanes hold it: [slot][wave][value][lane].
+template <int D, bool FT> constexpr int part_values() { return D / 2 + (FT ? 16 : 0) + (FT ? 3 : 2); }
+
+template <int D, bool FT>
+__device__ __forceinline__ void store_part(const KArgs& a, const float16v (&o)[D / 32], const float16v& oc, const Share& sh, const int wave,
+                                           const int lane, const float l_part, const float l_low, const float m_run, const float dev_max,
+                                           const unsigned rechecks) {
+  float* at = a.ws + ((size_t)sh.slot * nwave_of(D) + wave) * (part_values<D, FT>() * 64) + lane;
+  at[0] = m_run; at[64] = l_part;
+  if (FT) at[128] = l_low;
+  at += (FT ? 3 : 2) * 64;
+#pragma unroll
+  for (int fb = 0; fb < D / 32; ++fb)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) at[(16 * fb + v) * 64] = o[fb][v];
+  if (FT) {
+    at += D / 2 * 64;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) at[v * 64] = oc[v];
+    const float vals[4] = {dev_max, 0.f, 0.f, 0.f};
+    note_statistics(a, sh.rt.bh, sh.rt.ti, lane, vals, rechecks);
+  }
+}
+
+// Row tiles whose keys were split: the shares brought to one maximum and added up (row-sum, its lower bound, output
+// and output checksums are linear in the same factor e^{m_share - m}), then what the unsplit pass does after its
+// last key tile.  A workgroup per 32 rows; wave w adds up feature block w, the first wave the checksums as well, and
+// finishes.  Bound: the latency of reading one share after the other, so all maxima are requested at once and a share
+// ahead of the one being added (12 row tiles of two shares took 20 us with a wave per 32 rows that read value by value).
+constexpr int MAX_PARTS = 16;
+template <int D, bool FT, bool CAUSAL>
+__global__ __launch_bounds__(D * 2) void ftattn_finish(const KArgs a) {
+  constexpr int NV = part_values<D, FT>(), HEAD = FT ? 3 : 2, NFB = D / 32;
+  __shared__ __attribute__((aligned(16))) float4 block[NFB - 1][4][64];
+  const int rows = blockIdx.x % nwave_of(D), lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  Share sh;
+  sh.part = 0;
+  sh.rank = (int)blockIdx.x / nwave_of(D);
+  sh.rt = split_row_tile<D, CAUSAL>(a, sh.rank);
+  place_share<D, CAUSAL>(a, sh, true);
+  const int row0 = sh.rt.ti * bm_of(D) + 32 * rows, np = sh.nparts;
+  if (np == 1 || row0 >= a.N) return;         // (the whole workgroup)
+  const int n_split = a.n_tiles - a.first_split, heads = a.n_tiles / a.Ti;
+  const float* in = a.ws + ((size_t)sh.rank * nwave_of(D) + rows) * (NV * 64) + lane;
+  float mp[MAX_PARTS], m = -__builtin_inff();
+  uint32_t at_part[MAX_PARTS];          // where the shares stand, in states
+  {
+    uint32_t at = 0;
+#pragma unroll
+    for (int p = 0; p < MAX_PARTS; ++p) {
+      at_part[p] = at * (uint32_t)nwave_of(D);
+      mp[p] = in[(size_t)at_part[p] * (NV * 64)];
+      if (p + 1 < np) at += (uint32_t)row_tiles_with(p, CAUSAL, n_split, heads, a.Ti, a.piece, bm_of(D) / BN);
+    }
+  }
+  // (a share past the last one is the last one again, not added)
+  float16v x = (float16v)0.f, y = (float16v)0.f;
+  float xl = 0.f, xlow = 0.f;
+  auto request = [&](const int p) __attribute__((always_inline)) {
+    const float* at = in + (size_t)at_part[p < MAX_PARTS ? p : MAX_PARTS - 1] * (NV * 64);
+    if (wave == 0) {
+      xl = at[64];
+      if (FT) {
+        xlow = at[128];
+#pragma unroll
+        for (int v = 0; v < 16; ++v) y[v] = at[(HEAD + D / 2 + v) * 64];
+      }
+    }
+#pragma unroll
+    for (int v = 0; v < 16; ++v) x[v] = at[(HEAD + 16 * wave + v) * 64];
+  };
+  request(0);
+#pragma unroll
+  for (int p = 0; p < MAX_PARTS; ++p) m = fmax2(m, mp[p]);
+  float16v ob = (float16v)0.f, oc = (float16v)0.f;
+  float l = 0.f, l_low = 0.f;
+#pragma unroll
+  for (int p = 0; p < MAX_PARTS; ++p) {
+    if (p >= np) break;
+    const float f = ex2((mp[p] - m) * a.scale_log2);
+    const float16v xp = x, yp = y;
+    const float xlp = xl, xlowp = xlow;
+    request(p + 1);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int v = 0; v < 16; ++v) { ob[v] = __builtin_fmaf(xp[v], f, ob[v]); oc[v] = __builtin_fmaf(yp[v], f, oc[v]); }
+    l = __builtin_fmaf(xlp, f, l);
+    l_low = __builtin_fmaf(xlowp, f, l_low);
+  }
+  if (wave > 0) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) block[wave - 1][q][lane] = make_float4(ob[4 * q], ob[4 * q + 1], ob[4 * q + 2], ob[4 * q + 3]);
+  }
+  __syncthreads();
+  if (wave > 0) return;
+  float16v o[NFB];
+  o[0] = ob;
+#pragma unroll
+  for (int fb = 1; fb < NFB; ++fb)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const float4 t = block[fb - 1][q][lane];
+      o[fb][4 * q] = t.x; o[fb][4 * q + 1] = t.y; o[fb][4 * q + 2] = t.z; o[fb][4 * q + 3] = t.w;
+    }
+  finish_rows<D, FT, CAUSAL, 0>(a, o, oc, sh.rt.bh, sh.rt.ti, row0 + (lane & 31), lane, l, l_low, m, m, 0.f, 0u);
+}
+
 // PS >= 1: verification after every step (the paper's EFTA before the unified verification of
 // Section 3.4): GEMM I is verified on its own in every iteration, the row-sum against its range
 // and the unnormalised output accumulator against its checksum after every GEMM II.
@@ -127,8 +555,9 @@ __device__ __forceinline__ half2v opaque(half2v x) { asm volatile("" : "+v"(x));
 // classes of the same encoded tiles (c1 = sum_c c1_c, c2 = sum_c 8 c2_c + (c - 7) c1_c), so the
 // matrix work is the same; what changes is that a row has one residual per key tile, formed by
 // the two lanes of a query together, and can name one element of 64 (of D for the output).
-template <int D, bool FT, bool CAUSAL, bool INJ, int PS = 0>
-__global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : 2) void ftattn_main(const KArgs a) {
+template <int D, bool FT, bool CAUSAL, bool INJ, int PS = 0, bool SPLIT = false>
+__global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : FT ? 2 : 3) void ftattn_main(const KArgs a) {
+  static_assert(!SPLIT || (PS == 0 && !INJ), "split calls run the default verification scheme without a fault list");
   static_assert(FT || PS == 0 || PS == 4, "the verification modes are modes of the protected kernel");
   constexpr bool DMR = PS == 2;
   constexpr bool STEP = PS == 1 || PS == 2;
@@ -148,27 +577,27 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : 2) void ft
   constexpr int KT_ELEMS = (BN + CKR) * D, VT_ELEMS = (D + CKR) * BN;
   extern __shared__ __attribute__((aligned(1024))) char smem[];
 
-  const RowTile rt = CAUSAL ? causal_row_tile((int)blockIdx.x, (int)gridDim.x, a.Ti, a.head_group)
-                            : even_row_tile((int)blockIdx.x, (int)gridDim.x, a.Ti);
-  const int bh = rt.bh, ti = rt.ti;
+  const Share sh = share_of<D, CAUSAL, SPLIT>(a, (int)blockIdx.x);
+  const int bh = sh.rt.bh, ti = sh.rt.ti;
+  const int j0 = sh.first;                  // the loop counts the key tiles of the share, from here
   const int tid = threadIdx.x, lane = tid & 63, lq = lane & 31, hi = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int grp = ALT ? wave >> 2 : 0;
   const int N = a.N;
   const int row0_cta = ti * BM;
   const int row0_w = row0_cta + wave * 32;
-  const int last_row_cta = (row0_cta + BM < N ? row0_cta + BM : N) - 1;
-  const int nj = CAUSAL ? (last_row_cta / BN + 1) : a.Tj;         // key tiles of the workgroup
+  const int nj = sh.count;                                        // key tiles of the workgroup
   int nj_w = 0;                                                   // key tiles this wave takes part in
   if (row0_w < N) {
     int last_row_w = (row0_w + 32 < N ? row0_w + 32 : N) - 1;
-    nj_w = CAUSAL ? (last_row_w / BN + 1) : a.Tj;
+    nj_w = (CAUSAL ? (last_row_w / BN + 1) : a.Tj) - j0;
+    nj_w = nj_w < nj ? nj_w : nj;
   }
   const int row = row0_w + lq;
   const float sl2 = a.scale_log2;
 
-  const _Float16* kc_head = a.kc + (size_t)bh * a.Tj * KT_ELEMS;
-  const _Float16* vt_head = a.vt + (size_t)bh * a.Tj * VT_ELEMS;
+  const _Float16* kc_head = a.kc + ((size_t)bh * a.Tj + j0) * KT_ELEMS;
+  const _Float16* vt_head = a.vt + ((size_t)bh * a.Tj + j0) * VT_ELEMS;
   const uint32_t smem_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
 
   // ---- per-lane source offsets of this wave's load instructions (the same for every tile).
@@ -195,7 +624,7 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : 2) void ft
   auto prepare_unit = [&](int u, bool real) __attribute__((always_inline)) {
     const int st = (u + 1) % NSTAGE;
     ld_lds = smem_base + (uint32_t)st * U::BYTES;
-    const int jk = u + 1 < a.Tj ? u + 1 : a.Tj - 1, jv = u > 0 ? (u < a.Tj ? u : a.Tj - 1) : 0;
+    const int jk = u + 1 < nj ? u + 1 : nj - 1, jv = u > 0 ? (u < nj ? u : nj - 1) : 0;
     ld_kt = kc_head + (size_t)jk * KT_ELEMS;
     ld_vt = vt_head + (size_t)jv * VT_ELEMS;
     ld_real = real;
@@ -363,149 +792,6 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : 2) void ft
     }
     __builtin_amdgcn_sched_group_barrier(0x008, RING - 1, 0);
   };
-  // Sum-form check of the output accumulator against its checksums (Algorithm 1, last "if"; text
-  // after eq. (16) for location and repair): class r of the lane, folds o[fb][4*gg + r].  `thr` is
-  // the threshold in the units the accumulator is in, `tile` the key tile reported with an event
-  // (-1 after the loop), `xfold` / `xv` the extra fold of class 0 in the exact row-sum mode.
-  float rmax_o = 0.f;
-  auto sum_check = [&](const float thr, const int tile, const bool real, const bool xf, const float xv, const bool track) -> bool {
-    if (EW) {
-      // one class over all D features of the row (fold index = feature), from both lanes of the query
-      float sum1 = 0.f, chk1 = 0.f;
-#pragma unroll
-      for (int fb = 0; fb < NFB; ++fb)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) sum1 += o[fb][v];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) chk1 += oc[r] + oc[4 + r];
-      sum1 = sum32(sum1); chk1 = sum32(chk1);
-      const float R1 = chk1 - sum1;
-      const bool d = real && !(__builtin_fabsf(R1) <= thr);
-      if (track && !d && real) rmax_o = fmax2(rmax_o, __builtin_fabsf(R1));
-      if (!wave_any(d)) return false;
-      float chk2 = 0.f, sum2 = 0.f, big = -1.f;
-      int l_big = -1;
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-        chk2 += 8.0f * (oc[8 + r] + oc[12 + r]) + (float)(4 * hi + r - 7) * (oc[r] + oc[4 + r]);
-#pragma unroll
-      for (int fb = 0; fb < NFB; ++fb)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int l = 32 * fb + 8 * (v >> 2) + 4 * hi + (v & 3);
-          const float ov = o[fb][v];
-          sum2 += (float)(l + 1) * ov;
-          const float mag = finitef(ov) ? __builtin_fabsf(ov) : __builtin_inff();
-          if (mag > big) { big = mag; l_big = l; } else if (mag == big) { l_big = -1; }
-        }
-      chk2 = sum32(chk2); sum2 = sum32(sum2);
-      {
-        const float bigp = xchg32(big, hi);
-        const int lp = (int)xchg32((float)l_big, hi);
-        if (bigp > big) l_big = lp; else if (bigp == big) l_big = -1;
-      }
-      int lstar = -1;
-      {
-        const float ratio = (chk2 - sum2) / R1;
-        if (finitef(ratio)) {
-          const float c = __builtin_rintf(ratio) - 1.0f;
-          if (c >= 0.f && c < (float)D) lstar = (int)c;
-        } else {
-          lstar = l_big;
-        }
-      }
-      if (!d) lstar = -1;
-      float rest = 0.f;
-#pragma unroll
-      for (int fb = 0; fb < NFB; ++fb)
-#pragma unroll
-        for (int v = 0; v < 16; ++v)
-          if (32 * fb + 8 * (v >> 2) + 4 * hi + (v & 3) != lstar) rest += o[fb][v];
-      rest = sum32(rest);
-      if (d) {
-        const bool fix = a.correct && lstar >= 0;
-        if (hi == 0) log_event(a, bh, FTATTN_CHECK_O, tile, row, lstar, R1, fix ? 1 : 0);
-        if (fix) {
-          const float val = chk1 - rest;
-#pragma unroll
-          for (int fb = 0; fb < NFB; ++fb)
-#pragma unroll
-            for (int v = 0; v < 16; ++v)
-              if (32 * fb + 8 * (v >> 2) + 4 * hi + (v & 3) == lstar) o[fb][v] = val;
-        }
-      }
-      return true;       // events may have been written
-    }
-    bool bad = false;
-    float R[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      float sum1 = 0.f;
-#pragma unroll
-      for (int fb = 0; fb < NFB; ++fb)
-#pragma unroll
-        for (int gg = 0; gg < 4; ++gg) sum1 += o[fb][4 * gg + r];
-      if (r == 0 && xf) sum1 += xv;      // the normalised extra fold of class 0
-      R[r] = (oc[r] + oc[4 + r]) - sum1;
-      bool d = real && !(__builtin_fabsf(R[r]) <= thr);
-      bad |= d;
-      if (track && !d && real) rmax_o = fmax2(rmax_o, __builtin_fabsf(R[r]));
-    }
-    if (wave_any(bad)) {
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        if (real && !(__builtin_fabsf(R[r]) <= thr)) {
-          float chk1 = oc[r] + oc[4 + r], chk2 = oc[8 + r] + oc[12 + r];
-          float sum2 = 0.f, big = -1.f;
-          int l_big = -1;
-#pragma unroll
-          for (int fb = 0; fb < NFB; ++fb)
-#pragma unroll
-            for (int gg = 0; gg < 4; ++gg) {
-              float ov = o[fb][4 * gg + r];
-              sum2 += (float)(4 * fb + gg + 1) * ov;
-              float mag = finitef(ov) ? __builtin_fabsf(ov) : __builtin_inff();
-              if (mag > big) { big = mag; l_big = 4 * fb + gg; } else if (mag == big) { l_big = -1; }
-            }
-          const bool xfold = r == 0 && xf;      // class 0 has the row-sum as fold NFOLD_V
-          if (xfold) {
-            sum2 += (float)(NFOLD_V + 1) * xv;
-            float mag = finitef(xv) ? __builtin_fabsf(xv) : __builtin_inff();
-            if (mag > big) { big = mag; l_big = NFOLD_V; } else if (mag == big) { l_big = -1; }
-          }
-          float ratio = (chk2 - sum2) / R[r];
-          int lstar = -1;
-          if (finitef(ratio)) {
-            float c = __builtin_rintf(ratio) - 1.0f;
-            if (c >= 0.f && c < (float)(xfold ? NFOLD_V + 1 : NFOLD_V)) lstar = (int)c;
-          } else {
-            lstar = l_big;
-          }
-          if (xfold && lstar == NFOLD_V) continue;             // the row-sum itself: reported by its own check
-          int col = lstar >= 0 ? 8 * lstar + 4 * hi + r : -1;
-          bool fix = a.correct && lstar >= 0;
-          log_event(a, bh, FTATTN_CHECK_O, tile, row, col, R[r], fix ? 1 : 0);
-          if (fix) {
-            float rest = xfold ? xv : 0.f;
-#pragma unroll
-            for (int fb = 0; fb < NFB; ++fb)
-#pragma unroll
-              for (int gg = 0; gg < 4; ++gg)
-                if (4 * fb + gg != lstar) rest += o[fb][4 * gg + r];
-            float val = chk1 - rest;
-#pragma unroll
-            for (int fb = 0; fb < NFB; ++fb)
-#pragma unroll
-              for (int gg = 0; gg < 4; ++gg)
-                if (4 * fb + gg == lstar) o[fb][4 * gg + r] = val;
-          }
-        }
-      }
-      return true;       // events may have been written
-    }
-    return false;
-  };
-
   // ---- prologue: the first key tile's scores; group 1 starts one barrier later than group 0
   phase_barrier();                                // everyone's pieces of the first key tile have landed
 
@@ -517,7 +803,7 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : 2) void ft
   }
 
   for (int i = 0; i < nj; ++i) {
-    const int k0 = i * BN;
+    const int k0 = (j0 + i) * BN;
     const bool on = i < nj_w;
     const uint32_t stage = smem_base + (uint32_t)((i + 1) % NSTAGE) * U::BYTES;
     const bool tile_has_fault = INJ && fcur < fend && F[fcur].kv_tile == i;
@@ -779,7 +1065,7 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : 2) void ft
               logged = true;
               if (linear) {
                 const bool fix = a.correct && lstar >= 0;
-                if (hi == 0) log_event(a, bh, FTATTN_CHECK_S, i, row, lstar >= 0 ? k0 + lstar : -1, lam, fix ? 1 : 0);
+                if (hi == 0) log_event(a, bh, FTATTN_CHECK_S, j0 + i, row, lstar >= 0 ? k0 + lstar : -1, lam, fix ? 1 : 0);
                 if (fix) {
                   const float val = chk1 - rest;
 #pragma unroll
@@ -798,7 +1084,7 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : 2) void ft
                     const bool ok = key < N && (!CAUSAL || key <= row);
                     const float pe = ex2(__builtin_fmaf(s[kb][v], sl2, negm));
                     if (ok && as_u(pe) != as_u(p[kb][v])) {
-                      log_event(a, bh, FTATTN_CHECK_EXP, i, row, key, lam, a.correct ? 1 : 0);
+                      log_event(a, bh, FTATTN_CHECK_EXP, j0 + i, row, key, lam, a.correct ? 1 : 0);
                       if (a.correct) p[kb][v] = pe;
                     }
                   }
@@ -855,7 +1141,7 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : 2) void ft
                 }
                 int col = lstar >= 0 ? k0 + 32 * (lstar >> 2) + 8 * (lstar & 3) + 4 * hi + r : -1;
                 bool fix = a.correct && lstar >= 0;
-                log_event(a, bh, FTATTN_CHECK_S, i, row, col, lam, fix ? 1 : 0);
+                log_event(a, bh, FTATTN_CHECK_S, j0 + i, row, col, lam, fix ? 1 : 0);
                 if (fix) {
                   float rest = 0.f;
 #pragma unroll
@@ -880,7 +1166,7 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : 2) void ft
                     bool ok = key < N && (!CAUSAL || key <= row);
                     float pe = ex2(__builtin_fmaf(s[kb][v], sl2, negm));
                     if (ok && as_u(pe) != as_u(p[kb][v])) {
-                      log_event(a, bh, FTATTN_CHECK_EXP, i, row, key, lam, a.correct ? 1 : 0);
+                      log_event(a, bh, FTATTN_CHECK_EXP, j0 + i, row, key, lam, a.correct ? 1 : 0);
                       if (a.correct) p[kb][v] = pe;
                     }
                   }
@@ -992,7 +1278,7 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : 2) void ft
       // ---- verification of this iteration's reduce-sum (range so far, Section 3.4 case 3) and of
       // GEMM II with the rescale (sum-form check on the unnormalised accumulator)
       const bool real = row < N;
-      float l = sum32(l_part);
+      float l = sum32(l_part), rmax_step = 0.f;
       const int seen = k0 + BN < N ? k0 + BN : N;
       const float Ub = (float)(CAUSAL && row + 1 < seen ? row + 1 : seen);
       if (DMR) {
@@ -1031,7 +1317,7 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : 2) void ft
         }
         wait_vmcnt<0>();      // the event log's stores complete out of order with loads: drain before the counted waits
       }
-      if (sum_check(a.tau_o * l, i, real, false, 0.f, false)) wait_vmcnt<0>();
+      if (sum_check<D, EW>(a, o, oc, bh, row, hi, a.tau_o * l, i, real, false, 0.f, false, rmax_step)) wait_vmcnt<0>();
     }
     if (ALT) {
       if (grp == 1) wait_vmcnt<U::NLOAD>();       // unit i+1 (unit i+2 may still be in flight)
@@ -1040,118 +1326,11 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : 2) void ft
   }
   if (ALT && grp == 0) phase_barrier();
 
-  // ================= after the loop: row-sum range check, normalisation, sum-form check, store
-  float rmax_u = 0.f, rmax_l = 0.f;
-  {
-    const bool real = row < N;
-    float l = sum32(l_part);
-    const bool lfold = FT && a.rowsum_fold != 0;
-    if (FT && lfold) {
-      // The row-sum as fold NFOLD_V of checksum class 0 (held by the lane half hi == 0, register
-      // r == 0): the row-sum the checksum implies against the accumulated one, in units of the
-      // row-sum; on a mismatch the location rule over the NFOLD_V + 1 folds decides whether the
-      // row-sum is the wrong element, and if so it is replaced by the implied one.
-      float sumx = 0.f;
-#pragma unroll
-      for (int fb = 0; fb < NFB; ++fb)
-#pragma unroll
-        for (int gg = 0; gg < 4; ++gg) sumx += o[fb][4 * gg];
-      const float chk1 = oc[0] + oc[4];
-      const float lc = chk1 - sumx;
-      const float rr = (lc - l) / lc;
-      const bool detl = real && hi == 0 && (!(__builtin_fabsf(rr) <= a.tau_o) || !finitef(rr));
-      if (!detl && real && hi == 0) rmax_u = fmax2(rmax_u, __builtin_fabsf(rr));
-      if (wave_any(detl)) {
-        if (detl) {
-          const float chk2 = oc[8] + oc[12];
-          float sum2 = (float)(NFOLD_V + 1) * l;
-          float big = finitef(l) ? __builtin_fabsf(l) : __builtin_inff();
-          int l_big = NFOLD_V;
-#pragma unroll
-          for (int fb = 0; fb < NFB; ++fb)
-#pragma unroll
-            for (int gg = 0; gg < 4; ++gg) {
-              const float ov = o[fb][4 * gg];
-              sum2 += (float)(4 * fb + gg + 1) * ov;
-              const float mag = finitef(ov) ? __builtin_fabsf(ov) : __builtin_inff();
-              if (mag > big) { big = mag; l_big = 4 * fb + gg; } else if (mag == big) { l_big = -1; }
-            }
-          const float ratio = (chk2 - sum2) / (lc - l);
-          int lstar = -1;
-          if (finitef(ratio)) {
-            const float c = __builtin_rintf(ratio) - 1.0f;
-            if (c >= 0.f && c < (float)(NFOLD_V + 1)) lstar = (int)c;
-          } else {
-            lstar = l_big;
-          }
-          if (lstar == NFOLD_V) {
-            log_event(a, bh, FTATTN_CHECK_L, -1, row, 0, rr, a.correct ? 1 : 0);
-            if (a.correct) l = lc;
-          }
-        }
-      }
-      // the other half of the row takes the row-sum of the half that checked it
-      const float lp = xchg32(l, hi);
-      if (hi == 1) l = lp;
-    }
-    if (FT && !lfold && !DMR) {
-      float Ub = CAUSAL ? (float)(row + 1 < N ? row + 1 : N) : (float)N;
-      if (LAZY) Ub *= ex2((m_true - m_run) * sl2);      // exponentials reach exp(running maximum - reference)
-      float lo = l_low;
-      bool detl = real && !(lo * (1.f - a.delta_l) <= l && l <= Ub * (1.f + a.delta_l));
-      if (!detl && real) { rmax_u = fmax2(rmax_u, l / Ub); rmax_l = fmax2(rmax_l, lo / l); }
-      if (detl) {
-        if (hi == 0) log_event(a, bh, FTATTN_CHECK_L, -1, row, 0, l, a.correct ? 1 : 0);
-        if (a.correct) l = lo;     // the approximation of Section 3.4, "optimized EFTA"
-      }
-    }
-    float inv = 1.0f / l;
-#pragma unroll
-    for (int fb = 0; fb < NFB; ++fb) o[fb] *= inv;
-    if (FT) {
-      oc *= inv;
-      (void)sum_check(a.tau_o, -1, real, lfold && hi == 0, l * inv, true);
-    }
-    // ---- store: lane holds features 32*fb + 8*gg + 4*hi + (0..3) of its query
-    if (real) {
-      size_t base = ((size_t)bh * N + row) * D;
-#pragma unroll
-      for (int fb = 0; fb < NFB; ++fb)
-#pragma unroll
-        for (int gg = 0; gg < 4; ++gg) {
-          int f = 32 * fb + 8 * gg + 4 * hi;
-          float x0 = o[fb][4 * gg], x1 = o[fb][4 * gg + 1], x2 = o[fb][4 * gg + 2], x3 = o[fb][4 * gg + 3];
-          if (a.out_dtype == FTATTN_F32) {
-            float4 v = make_float4(x0, x1, x2, x3);
-            *reinterpret_cast<float4*>(reinterpret_cast<float*>(a.o) + base + f) = v;
-          } else if (a.out_dtype == FTATTN_F16) {
-            _Float16 hv[4] = {(_Float16)x0, (_Float16)x1, (_Float16)x2, (_Float16)x3};
-            *reinterpret_cast<uint2*>(reinterpret_cast<_Float16*>(a.o) + base + f) = *reinterpret_cast<uint2*>(hv);
-          } else {
-            uint32_t u[4] = {as_u(x0), as_u(x1), as_u(x2), as_u(x3)};
-            uint16_t bv16[4];
-#pragma unroll
-            for (int x = 0; x < 4; ++x) {
-              uint32_t rnd = ((u[x] >> 16) & 1u) + 0x7FFFu;
-              bv16[x] = (u[x] & 0x7F800000u) == 0x7F800000u ? (uint16_t)(u[x] >> 16) : (uint16_t)((u[x] + rnd) >> 16);
-            }
-            *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(a.o) + base + f) = *reinterpret_cast<uint2*>(bv16);
-          }
-        }
-    }
-  }
-
-  if (FT) {
-    // largest statistics that passed, per row tile (non-negative floats order like their bits)
-    uint32_t* rm = a.resmax + ((size_t)bh * a.Ti + ti) * 4;
-    float vals[4] = {dev_max, rmax_o, rmax_u, rmax_l};
-#pragma unroll
-    for (int x = 0; x < 4; ++x) {
-      const uint32_t v = wave_max_u32(as_u(vals[x]));
-      if (lane == 63) atomicMax(rm + x, v);
-    }
-    if (lane == 0 && rechecks) atomicAdd(a.recheck, (unsigned long long)rechecks);
-  }
+  const int lane_e = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));      // (not kept through the loop)
+  if (!SPLIT || sh.nparts == 1)
+    finish_rows<D, FT, CAUSAL, PS>(a, o, oc, bh, ti, row0_w + (lane_e & 31), lane_e, l_part, l_low, m_run, m_true, dev_max, rechecks);
+  else
+    store_part<D, FT>(a, o, oc, sh, wave, lane_e, l_part, l_low, m_run, dev_max, rechecks);
 }
 
 }  // namespace ftattn
