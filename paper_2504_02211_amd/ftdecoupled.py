@@ -7,7 +7,7 @@ from typing import Optional
 
 import numpy as np
 
-from .ftattn import device_pointer, load_library as _load
+from .ftattn import address, load_library as _load
 
 F16, BF16 = 0, 1
 FT_OFF, FT_CORRECT = 0, 1
@@ -101,6 +101,7 @@ class FtDecoupled:
         eff = Config()
         self.lib.ftdec_get_config(self.handle, C.byref(eff))
         self.config = eff
+        self._tensors = (batch * heads * seq * head_dim, eff.in_dtype, eff.device)       # what they have to be (see ftattn.address)
 
     def _check(self, rc: int) -> None:
         if rc != OK:
@@ -114,16 +115,13 @@ class FtDecoupled:
 
     def forward(self, q, k, v, o, faults: Optional[np.ndarray] = None, stream: int = 0) -> None:
         """q, k, v: device tensors of the input type, o: fp32; faults: int32 [n, 6] of (b, h, stage, row, col, bit)."""
-        c = self.config
-        ne = c.batch * c.heads * c.seq * c.head_dim
         n, fp = 0, None
         if faults is not None and len(faults):
             fa = np.ascontiguousarray(faults, dtype=np.int32).reshape(-1, 6)
             n, fp = fa.shape[0], fa.ctypes.data_as(C.POINTER(Fault))
-        self._check(self.lib.ftdec_forward(self.handle, device_pointer(q, "q", ne, c.in_dtype, c.device),
-                                           device_pointer(k, "k", ne, c.in_dtype, c.device),
-                                           device_pointer(v, "v", ne, c.in_dtype, c.device),
-                                           device_pointer(o, "o", ne, 2, c.device), fp, n, C.c_void_p(stream)))
+        ne, in_dtype, device = self._tensors
+        self._check(self.lib.ftdec_forward(self.handle, address(q, "q", ne, in_dtype, device), address(k, "k", ne, in_dtype, device),
+                                           address(v, "v", ne, in_dtype, device), address(o, "o", ne, 2, device), fp, n, stream))
 
     def report(self) -> Report:
         view = ReportView()
