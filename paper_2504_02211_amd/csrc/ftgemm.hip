@@ -65,9 +65,10 @@ static void grelease(ftgemm_ctx* c) {
 
 namespace ftgemm {
 
-template <class T> static constexpr TileInfo info_of() { return TileInfo{T::BM, T::NW * 64, {T::template lds<false>(), T::template lds<true>()}}; }
+template <class T> static constexpr TileInfo info_of() { return TileInfo{T::BM, T::NW * 64, T::PER_CU, {T::template lds<false>(), T::template lds<true>()}}; }
 static constexpr TileInfo TILES[N_TILES] = {info_of<TileWide>(), info_of<TileHalf>(), info_of<TileQuarter>(),
-                                            info_of<TileStrip>(), info_of<TileNarrow>(), info_of<TileSlim>()};
+                                            info_of<TileStrip>(), info_of<TileNarrow>(), info_of<TileSlim>(),
+                                            info_of<TileNarrow2>(), info_of<TileSlim2>()};
 
 static gemm_fn tile_kernel(int tile, bool ft, bool inject, bool bf16) {
   return bf16 ? tile_kernel_bf16(tile, ft, inject) : tile_kernel_f16(tile, ft, inject);
@@ -107,34 +108,38 @@ size_t gemm_workspace(long long m, long long n, GPlan plan) {
 }
 
 // The tile shape and the split of K with the least expected time.  Microseconds, from timings of every
-// shape at 1..16384 tokens, 64..16384 features, K 64..8192: a round of tiles (one per CU) costs `fixed` and
-// `step` per 64 columns of K, the latter up to (1 + load) times as much when every CU is busy (L2 traffic,
+// shape at 1..16384 tokens, 64..16384 features, K 64..8192: a round of tiles (one per CU, two where two fit) costs
+// `fixed` and `step` per 64 columns of K, the latter up to (1 + load) times as much when every CU has one (L2 traffic,
 // power); a split adds the second launch and a pass of the shares through memory.  Wide tiles move the
 // fewest bytes per product, narrow ones fill the chip: 4096^3 takes 136 / 152 / 188 / 257 us with tiles of
 // 256 / 128 / 64 / 32 tokens, 1024 x 1024 x 1024 takes 31 / 23 / 17 / 13, 128 x 1024 x 8192 takes
 // 161 / 110 / 70 / 56 unsplit and 18.5 with 32-token tiles split eight ways.
+// 128 features or fewer have tiles of that width, which leave the products of the padding out, in two heights: the high
+// ones read the weights half as often, the low ones run two to a CU.  16384 x 128 x 8192 takes 82 us with the
+// high ones, 99 with the low and 126 with 32-token tiles of 256 features, 16384 x 100 x 512 18.0 / 12.9 / 23, 1000 x 100 x
+// 1000 21.4 / 14.4 / 16.0; with K split the 32-token tiles take 18.9 for 37 x 100 x 8192 (69 / 46 unsplit), 20.4 for
+// 2000 x 128 x 4096 (38 / 26) and 20.9 for 2000 x 64 x 4096 (44 / 27).
 GPlan gemm_plan(long long m, long long n, long long k, int batch, bool inject, bool may_split) {
   if (inject) return {TILE_QUARTER, 1};
-  // 128 features or fewer: the tiles of that width, which leave the products of the padding out.  For many tokens, and
-  // in a batch, they are the fastest (16384 x 128 x 8192: 83 us against 87 with tiles of 256 features); for fewer tokens
-  // the 32-token tile with K split would be (37 x 100 x 8192: 65 against 17, 4096 x 128 x 1024: 16 against 13).
-  if (n <= 64) return {TILE_SLIM, 1};
-  if (n <= 128) return {TILE_NARROW, 1};
-  static constexpr struct { int tile; double fixed, step, load; } COST[] = {
-      {TILE_WIDE, 5.5, 1.18, 0.67}, {TILE_HALF, 3.7, 0.8, 0.36}, {TILE_QUARTER, 2.5, 0.5, 0.36}, {TILE_STRIP, 1.5, 0.4, 0.18}};
+  static constexpr struct { int tile, max_n; double fixed, step, load; } COST[] = {
+      {TILE_WIDE, 0, 5.5, 1.18, 0.67}, {TILE_HALF, 0, 3.7, 0.8, 0.36}, {TILE_QUARTER, 0, 2.5, 0.5, 0.36}, {TILE_STRIP, 0, 1.5, 0.4, 0.18},
+      {TILE_NARROW, 128, 5.0, 0.48, 0.4}, {TILE_NARROW2, 128, 2.0, 0.31, 1.5}, {TILE_SLIM, 64, 5.0, 0.55, 0.8}, {TILE_SLIM2, 64, 2.0, 0.32, 2.0}};
   constexpr double CUS = 256.0, LAUNCH = 4.5, MEMORY = 5e6;           // bytes per microsecond
   const long long steps = (k + 63) / 64, tn = (n + GBN - 1) / GBN;
+  const int max_n = n <= 64 ? 64 : n <= 128 ? 128 : 0;
   GPlan best{TILE_WIDE, 1};
   double best_us = 0.0;
-  for (const auto& c : COST)
-    for (int parts = 1; parts <= 16 && (parts == 1 || (may_split && 2 * parts <= steps)); parts *= 2) {
+  for (const auto& c : COST) {
+    if (c.max_n != max_n && !(max_n && c.tile == TILE_STRIP)) continue;
+    for (int parts = 1; parts <= 16 && (parts == 1 || (may_split && c.max_n == 0 && 2 * parts <= steps)); parts *= 2) {
       const GPlan plan{c.tile, parts};
-      const double groups = (double)((m + TILES[c.tile].bm - 1) / TILES[c.tile].bm * tn) * batch * parts;
-      const double rounds = std::ceil(groups / CUS), busy = std::min(1.0, groups / CUS);
+      const double groups = (double)((m + TILES[c.tile].bm - 1) / TILES[c.tile].bm * tn) * batch * parts, per_cu = TILES[c.tile].per_cu;
+      const double rounds = std::ceil(groups / (per_cu * CUS)), busy = std::min(per_cu, groups / CUS);
       double us = LAUNCH + rounds * (c.fixed + (double)((steps + parts - 1) / parts) * c.step * (1.0 + c.load * busy));
       if (parts > 1) us += LAUNCH + 2.0 * (double)gemm_workspace(m, n, plan) / MEMORY;
       if (best_us == 0.0 || us < best_us) { best = plan; best_us = us; }
     }
+  }
   return best;
 }
 

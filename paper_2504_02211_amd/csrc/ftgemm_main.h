@@ -162,8 +162,9 @@ __global__ __launch_bounds__(256) void ftgemm_encode_w(const uint16_t* __restric
   *reinterpret_cast<u16x8*>(wc + ((size_t)tn * GCK + 8 * part + cls) * K + ch * 8) = out;
 }
 
-// Tile shape: BM tokens x BF features, a wave takes WT x WF blocks of 16 x 16, ring of NST stages.
-template <int BM_, int BF_, int WT_, int WF_, int BK_, int NST_> struct GTile {
+// Tile shape: BM tokens x BF features, a wave takes WT x WF blocks of 16 x 16, ring of NST stages, PER_CU workgroups per CU.
+template <int BM_, int BF_, int WT_, int WF_, int BK_, int NST_, int PER_CU_ = 1> struct GTile {
+  static constexpr int PER_CU = PER_CU_;
   static constexpr int BM = BM_, BF = BF_, WT = WT_, WF = WF_, BK = BK_, NST = NST_;
   static constexpr int NWT = BM / (16 * WT), NWF = BF / (16 * WF);   // waves along the tokens / along the features
   static constexpr int NW = NWT * NWF;                               // waves per workgroup
@@ -184,7 +185,7 @@ template <int BM_, int BF_, int WT_, int WF_, int BK_, int NST_> struct GTile {
   template <bool FT> static constexpr int bytes() { return (BM + BF + (FT ? GCK : 0)) * ROWB; }
   template <bool FT> static constexpr int lds() { return NST * bytes<FT>(); }
   static_assert((NST - 1) * (XW + WW + CW) <= 63, "counted waits use a 6-bit immediate");
-  static_assert(NST * (BM + BF + GCK) * ROWB <= 160 * 1024 && NST <= 3, "LDS; the waits of the last stages");
+  static_assert(PER_CU * NST * (BM + BF + GCK) * ROWB <= 160 * 1024 && NST <= 3, "LDS; the waits of the last stages");
 };
 
 // The tile shapes in use (see gemm_plan in ftgemm.hip for when)
@@ -195,6 +196,8 @@ using TileStrip = GTile<32, 256, 2, 4, 64, 3>;
 using TileNarrow = GTile<128, 128, 4, 4, 64, 3>;
 using TileFinish = GTile<16, 256, 1, 4, 64, 1>;      // epilogue only
 using TileSlim = GTile<256, 64, 4, 4, 64, 3>;
+using TileNarrow2 = GTile<64, 128, 2, 4, 64, 2, 2>;
+using TileSlim2 = GTile<128, 64, 2, 4, 64, 2, 2>;
 
 __device__ __forceinline__ void write_slot(const GArgs& a, int logical, const GSlot& s) {
   a.slots[logical] = s;
@@ -502,7 +505,7 @@ __device__ __forceinline__ void finish_tile(const GArgs& a, char* smem, float4v 
 }
 
 template <class T, bool FT, bool INJ, bool BF>
-__global__ __launch_bounds__(T::NW * 64, 8 / T::NW) void ftgemm_main(const GArgs a0) {
+__global__ __launch_bounds__(T::NW * 64, T::PER_CU * T::NW / 4 > 8 / T::NW ? T::PER_CU * T::NW / 4 : 8 / T::NW) void ftgemm_main(const GArgs a0) {
   GArgs a = a0;
   {
     const size_t by = blockIdx.y;          // problem of the batch
@@ -776,8 +779,8 @@ __global__ __launch_bounds__(256) void ftgemm_finish(const GArgs a) {
 }
 
 typedef void (*gemm_fn)(const GArgs);
-enum TileId { TILE_WIDE, TILE_HALF, TILE_QUARTER, TILE_STRIP, TILE_NARROW, TILE_SLIM, N_TILES };
-struct TileInfo { int bm, threads, lds[2]; };       // lds: dynamic LDS bytes without / with the checksum rows
+enum TileId { TILE_WIDE, TILE_HALF, TILE_QUARTER, TILE_STRIP, TILE_NARROW, TILE_SLIM, TILE_NARROW2, TILE_SLIM2, N_TILES };
+struct TileInfo { int bm, threads, per_cu, lds[2]; };       // lds: dynamic LDS bytes without / with the checksum rows
 
 // kernel of one tile shape, instantiated per type (ftgemm_f16.hip, ftgemm_bf16.hip); the fault
 // injector exists for TILE_QUARTER only
@@ -792,6 +795,8 @@ template <bool BF> gemm_fn tile_kernel_of(int tile, bool ft, bool inject) {
     case TILE_HALF: return ft ? ftgemm_main<TileHalf, true, false, BF> : ftgemm_main<TileHalf, false, false, BF>;
     case TILE_QUARTER: return ft ? ftgemm_main<TileQuarter, true, false, BF> : ftgemm_main<TileQuarter, false, false, BF>;
     case TILE_STRIP: return ft ? ftgemm_main<TileStrip, true, false, BF> : ftgemm_main<TileStrip, false, false, BF>;
+    case TILE_NARROW2: return ft ? ftgemm_main<TileNarrow2, true, false, BF> : ftgemm_main<TileNarrow2, false, false, BF>;
+    case TILE_SLIM2: return ft ? ftgemm_main<TileSlim2, true, false, BF> : ftgemm_main<TileSlim2, false, false, BF>;
     case TILE_NARROW: return ft ? ftgemm_main<TileNarrow, true, false, BF> : ftgemm_main<TileNarrow, false, false, BF>;
     default: return ft ? ftgemm_main<TileSlim, true, false, BF> : ftgemm_main<TileSlim, false, false, BF>;
   }
