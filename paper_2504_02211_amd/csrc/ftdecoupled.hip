@@ -328,46 +328,108 @@ __global__ __launch_bounds__(256) void ftdec_softmax_wave(const SArgs a) {
   }
 }
 
-// V [N][d] (fp16 or bf16 patterns) -> V^T [d][Np] in fp16, columns beyond N zero.  One workgroup per 64 keys
-// and 64 features: 16 bytes per lane from memory, transposed through LDS (rows of 33 words: the eight keys
-// a lane gathers, and the 16 lanes of a row, fall on banks of their own), 16 bytes per lane back.  The
-// first workgroup also clears the counters of the softmax log.  Bound: memory, one read and one write of V;
-// 2 x 16 x 2048 x 128 took 24.3 us with 2 bytes per lane, and the reset was a launch of its own.
-__global__ __launch_bounds__(256) void ftdec_transpose_v(const uint16_t* __restrict__ v, _Float16* __restrict__ vt, int N, int Np,
-                                                         int d, int bf16, int32_t* s_count, unsigned long long* retried) {
+// Everything the two products need before they start, in one launch: grid (tiles, heads, roles), the first role `first_role`.
+// Role 0, 64 keys per workgroup: V [N][d] (fp16 or bf16 patterns) -> V^T [d][Np] in fp16, columns beyond N zero, and (FT)
+// the tensor checksums of its rows (eq. (13), (14): 32 rows [32][Np], as encode_weight_rows forms them).  A
+// 64 x 64 block at a time: 16 bytes per lane from memory, transposed through LDS (rows of 33 words: the eight keys
+// a lane gathers, and the 16 lanes of a row, fall on banks of their own), 16 bytes per lane back; four threads per key
+// fold its features from the same block.  The first workgroup also clears the counters of the softmax log.
+// Role 1: the checksum rows of K.
+// Bound: memory, one read of K and V and one write of V^T; for short sequences the launches.  Three launches (V^T with
+// 16 bytes per lane, the checksums of K, those of V^T read back) took 23 us for 2 x 16 x 2048 x 128 and 15 for 2 x 5 x 151 x 128.
+template <bool FT, bool BF>
+__global__ __launch_bounds__(256) void ftdec_prepare(const uint16_t* __restrict__ k, const uint16_t* __restrict__ v, uint16_t* __restrict__ wc1,
+                                                     _Float16* __restrict__ vt, _Float16* __restrict__ wc2, int N, int Np, int d, int Tn1,
+                                                     int first_role, int32_t* s_count, unsigned long long* retried) {
   typedef uint16_t u16x8 __attribute__((ext_vector_type(8)));
   typedef _Float16 half8 __attribute__((ext_vector_type(8)));
   typedef _Float16 half2v __attribute__((ext_vector_type(2)));
+  const int bh = blockIdx.y, tid = threadIdx.x;
+  if (blockIdx.z + first_role == 1) {
+    const int chunks = (d / 8 + 7) / 8, tn = blockIdx.x / chunks;
+    if (tn < Tn1)
+      ftgemm::encode_weight_rows<BF>(k + (size_t)bh * N * d, wc1 + (size_t)bh * Tn1 * ftgemm::GCK * d, N, d, tn, blockIdx.x % chunks);
+    return;
+  }
   __shared__ __attribute__((aligned(16))) _Float16 tile[64][66];
-  const int bh = blockIdx.y, k0 = blockIdx.x * 64, f0 = blockIdx.z * 64, tid = threadIdx.x;
-  if (tid == 0 && blockIdx.x == 0 && bh == 0 && f0 == 0) { *s_count = 0; *retried = 0ull; }
+  __shared__ __attribute__((aligned(16))) _Float16 cks[ftgemm::GCK][64];
+  const int k0 = blockIdx.x * 64;
+  if (k0 >= Np) return;                     // (the whole workgroup, before any barrier)
+  if (tid == 0 && blockIdx.x == 0 && bh == 0) { *s_count = 0; *retried = 0ull; }
   const uint16_t* src = v + (size_t)bh * N * d;
   _Float16* dst = vt + (size_t)bh * d * Np;
+  // thread: key tid / 4 of the 64, classes 2 (tid % 4) and the next
+  float c1[2] = {0.f, 0.f}, c2[2] = {0.f, 0.f};
+  u16x8 u[2];                               // the thread's part of the block to come, requested while one is worked on
+  auto request = [&](const int f0) __attribute__((always_inline)) {
 #pragma unroll
-  for (int e = tid; e < 64 * 8; e += 256) {
-    const int r = e >> 3, c = (e & 7) * 8, key = k0 + r;
-    u16x8 u = (u16x8)(uint16_t)0;
-    if (key < N && f0 + c < d) u = *reinterpret_cast<const u16x8*>(src + (size_t)key * d + f0 + c);      // (d is a multiple of 8)
-#pragma unroll
-    for (int x = 0; x < 8; x += 2) {
-      half2v h;
-#pragma unroll
-      for (int y = 0; y < 2; ++y) {
-        const uint16_t w = u[x + y];
-        h[y] = bf16 ? (_Float16)__builtin_bit_cast(float, (uint32_t)w << 16) : __builtin_bit_cast(_Float16, w);
-      }
-      *reinterpret_cast<half2v*>(&tile[r][c + x]) = h;
+    for (int i = 0; i < 2; ++i) {
+      const int key = k0 + (tid >> 3) + 32 * i, c = (tid & 7) * 8;
+      u[i] = (u16x8)(uint16_t)0;
+      if (key < N && f0 + c < d) u[i] = *reinterpret_cast<const u16x8*>(src + (size_t)key * d + f0 + c);      // (d is a multiple of 8)
     }
+  };
+  request(0);
+  for (int f0 = 0; f0 < d; f0 += 64) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int r = (tid >> 3) + 32 * i, c = (tid & 7) * 8;
+#pragma unroll
+      for (int x = 0; x < 8; x += 2) {
+        half2v h;
+#pragma unroll
+        for (int y = 0; y < 2; ++y) {
+          const uint16_t w = u[i][x + y];
+          h[y] = BF ? (_Float16)__builtin_bit_cast(float, (uint32_t)w << 16) : __builtin_bit_cast(_Float16, w);
+        }
+        *reinterpret_cast<half2v*>(&tile[r][c + x]) = h;
+      }
+    }
+    __syncthreads();
+    request(f0 + 64);
+#pragma unroll
+    for (int e = tid; e < 64 * 8; e += 256) {
+      const int f = e >> 3, r = (e & 7) * 8, key = k0 + r;
+      half8 h;
+#pragma unroll
+      for (int x = 0; x < 8; ++x) h[x] = tile[r + x][f];
+      if (f0 + f < d && key < Np) *reinterpret_cast<half8*>(dst + (size_t)(f0 + f) * Np + key) = h;      // (Np is a multiple of 8)
+    }
+    if (FT) {
+      // (features beyond d are zeros in the tile)
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const half2v h = *reinterpret_cast<const half2v*>(&tile[tid >> 2][8 * i + 2 * (tid & 3)]);
+        const float weight = (float)(f0 / 8 + i + 1);
+#pragma unroll
+        for (int y = 0; y < 2; ++y) {
+          c1[y] += (float)h[y];
+          c2[y] += weight * (float)h[y];
+        }
+      }
+    }
+    __syncthreads();
+  }
+  if (!FT) return;
+#pragma unroll
+  for (int y = 0; y < 2; ++y) {
+    const int cls = 2 * (tid & 3) + y, key = tid >> 2;
+    const _Float16 h1 = (_Float16)c1[y], h2 = (_Float16)c2[y];
+    cks[cls][key] = h1;
+    cks[8 + cls][key] = (_Float16)(c1[y] - (float)h1);
+    cks[16 + cls][key] = h2;
+    cks[24 + cls][key] = (_Float16)(c2[y] - (float)h2);
   }
   __syncthreads();
-#pragma unroll
-  for (int e = tid; e < 64 * 8; e += 256) {
-    const int f = e >> 3, r = (e & 7) * 8, key = k0 + r;
-    half8 h;
-#pragma unroll
-    for (int x = 0; x < 8; ++x) h[x] = tile[r + x][f];
-    if (f0 + f < d && key < Np) *reinterpret_cast<half8*>(dst + (size_t)(f0 + f) * Np + key) = h;      // (Np is a multiple of 8)
-  }
+  const int row = tid >> 3, at = (tid & 7) * 8;
+  if (k0 + at < Np)
+    *reinterpret_cast<half8*>(wc2 + ((size_t)bh * ftgemm::GCK + row) * Np + k0 + at) = *reinterpret_cast<const half8*>(&cks[row][at]);
+}
+
+typedef void (*prepare_fn)(const uint16_t*, const uint16_t*, uint16_t*, _Float16*, _Float16*, int, int, int, int, int, int32_t*, unsigned long long*);
+static prepare_fn select_prepare(bool ft, bool bf) {
+  if (ft) return bf ? ftdec_prepare<true, true> : ftdec_prepare<true, false>;
+  return bf ? ftdec_prepare<false, true> : ftdec_prepare<false, false>;
 }
 
 }  // namespace ftdec
@@ -574,11 +636,21 @@ extern "C" int ftdec_forward(ftdec_ctx* c, const void* q, const void* k, const v
     DHIP_TRY(c, hipStreamSynchronize(st));     // the staging buffers may be rewritten by the next call
   }
 
+  // ---- V^T and the checksum rows of both products, one launch; while the stages are timed one for each, so that every
+  // encode counts with its product
+  const uint16_t* q16 = reinterpret_cast<const uint16_t*>(q);
+  const uint16_t* k16 = reinterpret_cast<const uint16_t*>(k);
+  const long long wc1_stride = (long long)c->Tn1 * ftgemm::GCK * d, wc2_stride = (long long)ftgemm::GCK * Np;
+  auto prepare = [&](int first_role, int roles) {
+    const int tiles = std::max((Np + 63) / 64, c->Tn1 * ((d / 8 + 7) / 8));
+    hipLaunchKernelGGL(select_prepare(ft, bf), dim3(tiles, BH, roles), dim3(256), 0, st, k16, reinterpret_cast<const uint16_t*>(v), c->wc1, c->vt,
+                       reinterpret_cast<_Float16*>(c->wc2), N, Np, d, c->Tn1, first_role, &c->stat->s_count, &c->stat->retried);
+    return hipGetLastError();
+  };
   if (c->timing) DHIP_TRY(c, hipEventRecord(c->ev[4], st));
-  ftdec_transpose_v<<<dim3((Np + 63) / 64, BH, (d + 63) / 64), 256, 0, st>>>(reinterpret_cast<const uint16_t*>(v), c->vt, N, Np, d, bf ? 1 : 0,
-                                                                            &c->stat->s_count, &c->stat->retried);
-  DHIP_TRY(c, hipGetLastError());
+  DHIP_TRY(c, prepare(0, ft && !c->timing ? 2 : 1));
   if (c->timing) DHIP_TRY(c, hipEventRecord(c->ev[0], st));
+  if (ft && c->timing) DHIP_TRY(c, prepare(1, 1));
   // (with a fault list every head runs the injecting tile shape, so that all slots have one stride)
   const ftgemm::GPlan plan1 = ftgemm::gemm_plan(N, N, d, BH, n_g > 0, false), plan2 = ftgemm::gemm_plan(N, d, Np, BH, n_g > 0, false);
   auto gemm_args = [&](int which, int bh) {
@@ -601,10 +673,6 @@ extern "C" int ftdec_forward(ftdec_ctx* c, const void* q, const void* k, const v
 
   // ---- 1. ABFT-GEMM I: S = Q K^T (tokens = queries, weight rows = keys).  Without a fault list all
   // heads go out as one batched launch; a fault list is applied head by head.
-  const uint16_t* q16 = reinterpret_cast<const uint16_t*>(q);
-  const uint16_t* k16 = reinterpret_cast<const uint16_t*>(k);
-  const long long wc1_stride = (long long)c->Tn1 * ftgemm::GCK * d;
-  if (ft) DHIP_TRY(c, ftgemm::gemm_launch_encode_w(k16, c->wc1, N, d, bf, st, BH, (long long)N * d, wc1_stride));
   for (int bh = 0; bh < (n_g ? BH : 1); ++bh) {
     ftgemm::GArgs a = gemm_args(0, bh);
     a.x = q16 + (size_t)bh * N * d; a.w = k16 + (size_t)bh * N * d; a.wc = c->wc1 + (size_t)bh * wc1_stride;
@@ -640,8 +708,6 @@ extern "C" int ftdec_forward(ftdec_ctx* c, const void* q, const void* k, const v
   // ---- 3. ABFT-GEMM II: O = P V per head (tokens = queries, weight rows = the features of V^T)
   const uint16_t* vt16 = reinterpret_cast<const uint16_t*>(c->vt);
   const uint16_t* p16 = reinterpret_cast<const uint16_t*>(c->P);
-  const long long wc2_stride = (long long)ftgemm::GCK * Np;
-  if (ft) DHIP_TRY(c, ftgemm::gemm_launch_encode_w(vt16, c->wc2, d, Np, false, st, BH, (long long)d * Np, wc2_stride));
   for (int bh = 0; bh < (n_g ? BH : 1); ++bh) {
     ftgemm::GArgs a = gemm_args(1, bh);
     a.x = p16 + (size_t)bh * N * Np; a.w = vt16 + (size_t)bh * d * Np; a.wc = c->wc2 + (size_t)bh * wc2_stride;

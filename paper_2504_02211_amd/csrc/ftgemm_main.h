@@ -122,13 +122,10 @@ struct GArgs {
 // rounded, low = the remainder rounded).  Rows beyond N count as zero.  Bound: reading W once; with one
 // thread per whole (class, chunk) a 2048 x 1024 matrix had 32 workgroups on 256 CUs and took 14 us.
 template <bool BF>
-__global__ __launch_bounds__(256) void ftgemm_encode_w(const uint16_t* __restrict__ w, uint16_t* __restrict__ wc,
-                                                       int N, int K, long long bs_w = 0, long long bs_wc = 0) {
+__device__ __forceinline__ void encode_weight_rows(const uint16_t* __restrict__ w, uint16_t* __restrict__ wc, int N, int K, int tn, int chunks8) {
   typedef uint16_t u16x8 __attribute__((ext_vector_type(8)));
-  w += (size_t)blockIdx.z * bs_w;        // batch of weight matrices
-  wc += (size_t)blockIdx.z * bs_wc;
-  const int tn = blockIdx.x, tid = threadIdx.x;
-  const int cls = tid >> 5, part = (tid >> 3) & 3, ch = blockIdx.y * 8 + (tid & 7);
+  const int tid = threadIdx.x;
+  const int cls = tid >> 5, part = (tid >> 3) & 3, ch = chunks8 * 8 + (tid & 7);
   const bool on = ch * 8 < K;
   float c1[8], c2[8];
 #pragma unroll
@@ -160,6 +157,11 @@ __global__ __launch_bounds__(256) void ftgemm_encode_w(const uint16_t* __restric
     out[e] = part & 1 ? from_f32<BF>(c - to_f32<BF>(high)) : high;
   }
   *reinterpret_cast<u16x8*>(wc + ((size_t)tn * GCK + 8 * part + cls) * K + ch * 8) = out;
+}
+
+template <bool BF>
+__global__ __launch_bounds__(256) void ftgemm_encode_w(const uint16_t* __restrict__ w, uint16_t* __restrict__ wc, int N, int K) {
+  encode_weight_rows<BF>(w, wc, N, K, blockIdx.x, blockIdx.y);
 }
 
 // Tile shape: BM tokens x BF features, a wave takes WT x WF blocks of 16 x 16, ring of NST stages, PER_CU workgroups per CU.
@@ -805,8 +807,7 @@ template <bool BF> gemm_fn tile_kernel_of(int tile, bool ft, bool inject) {
 // Launch helpers (ftgemm.hip), for other host code of the library that runs the same protected
 // product on buffers of its own (the decoupled attention baseline).  None of them allocates or
 // synchronises.
-hipError_t gemm_launch_encode_w(const uint16_t* w, uint16_t* wc, int n, int k, bool bf16, hipStream_t st,
-                                int batch = 1, long long bs_w = 0, long long bs_wc = 0);
+hipError_t gemm_launch_encode_w(const uint16_t* w, uint16_t* wc, int n, int k, bool bf16, hipStream_t st);
 // How a product is run: its tile shape, and over how many workgroups a tile's K dimension is split.
 struct GPlan { int tile, parts; };
 GPlan gemm_plan(long long m, long long n, long long k, int batch, bool inject, bool may_split);
