@@ -91,7 +91,7 @@ static int fail(ftattn_ctx* c, int code, const std::string& msg) {
 
 static void release(ftattn_ctx* c) {
   if (!c) return;
-  (void)hipFree(c->kc); (void)hipFree(c->vt); (void)hipFree(c->ws); (void)hipFree(c->d_faults);
+  (void)hipFree(c->kc); (void)hipFree(c->d_faults);
   (void)hipFree(c->d_fault_off); (void)hipFree(c->d_events); (void)hipFree(c->d_stat);
   if (c->h_faults) (void)hipHostFree(c->h_faults);
   if (c->h_stat) (void)hipHostFree(c->h_stat);
@@ -298,9 +298,12 @@ extern "C" int ftattn_create(const ftattn_config* cfg, ftattn_ctx** out) {
       return rc_;                                                                                         \
     }                                                                                                     \
   } while (0)
-  CREATE_TRY(hipMalloc((void**)&c->kc, g.n_kc * 2));
-  CREATE_TRY(hipMalloc((void**)&c->vt, g.n_vt * 2));
-  if (g.n_ws) CREATE_TRY(hipMalloc((void**)&c->ws, g.n_ws * sizeof(float)));
+  // (one allocation for the encoded tiles and the state of split row tiles: each one costs tens of microseconds)
+  auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
+  const size_t tiles_bytes = up(g.n_kc * 2) + up(g.n_vt * 2);
+  CREATE_TRY(hipMalloc((void**)&c->kc, tiles_bytes + g.n_ws * sizeof(float)));
+  c->vt = c->kc + up(g.n_kc * 2) / 2;
+  if (g.n_ws) c->ws = reinterpret_cast<float*>(reinterpret_cast<char*>(c->kc) + tiles_bytes);
   CREATE_TRY(hipMalloc((void**)&c->d_faults, sizeof(DevFault) * c->fault_cap));
   CREATE_TRY(hipMalloc((void**)&c->d_fault_off, sizeof(int32_t) * (n_rt + 1)));
   CREATE_TRY(hipMalloc((void**)&c->d_events, sizeof(ftattn_event) * (size_t)e.max_events));
@@ -312,8 +315,7 @@ extern "C" int ftattn_create(const ftattn_config* cfg, ftattn_ctx** out) {
   c->h_fault_off = reinterpret_cast<int32_t*>(c->h_stat + c->stat_bytes);
   CREATE_TRY(hipHostMalloc((void**)&c->h_faults, sizeof(DevFault) * c->fault_cap, hipHostMallocDefault));
   // the checksum rows of the encoded tiles are never written when ft_mode is OFF; keep them defined
-  CREATE_TRY(hipMemset(c->kc, 0, g.n_kc * 2));
-  CREATE_TRY(hipMemset(c->vt, 0, g.n_vt * 2));
+  CREATE_TRY(hipMemset(c->kc, 0, tiles_bytes));
   {
     hipError_t le = allow_lds(e.head_dim, e.per_step, e.stride, why, e.rescale_margin > 0.f, g.n_ws != 0);
     if (le != hipSuccess) {
