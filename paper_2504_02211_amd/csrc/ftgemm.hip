@@ -110,8 +110,8 @@ size_t gemm_workspace(long long m, long long n, GPlan plan) {
 // shape at 1..16384 tokens, 64..16384 features, K 64..8192: a round of tiles (one per CU, two where two fit) costs
 // `fixed` and `step` per 64 columns of K, the latter up to (1 + load) times as much when every CU has one (L2 traffic,
 // power); a split adds the second launch and a pass of the shares through memory.  Wide tiles move the
-// fewest bytes per product, narrow ones fill the chip: 4096^3 takes 136 / 152 / 188 / 257 us with tiles of
-// 256 / 128 / 64 / 32 tokens, 1024 x 1024 x 1024 takes 31 / 23 / 17 / 13, 128 x 1024 x 8192 takes
+// fewest bytes per product, narrow ones fill the chip: 4096^3 takes 119 / 141 / 177 / 255 us with tiles of
+// 256 / 128 / 64 / 32 tokens, 5000 x 1300 x 8000 197 / 134 / 159 / 235, 2048 x 2048 x 1024 33 / 22 / 17 / 26, 128 x 1024 x 8192
 // 161 / 110 / 70 / 56 unsplit and 18.5 with 32-token tiles split eight ways.
 // 128 features or fewer have tiles of that width, which leave the products of the padding out, in two heights: the high
 // ones read the weights half as often, the low ones run two to a CU.  16384 x 128 x 8192 takes 82 us with the
@@ -121,7 +121,7 @@ size_t gemm_workspace(long long m, long long n, GPlan plan) {
 GPlan gemm_plan(long long m, long long n, long long k, int batch, bool inject, bool may_split) {
   if (inject) return {TILE_QUARTER, 1};
   static constexpr struct { int tile, max_n; double fixed, step, load; } COST[] = {
-      {TILE_WIDE, 0, 5.5, 1.18, 0.67}, {TILE_HALF, 0, 3.7, 0.8, 0.36}, {TILE_QUARTER, 0, 2.5, 0.5, 0.36}, {TILE_STRIP, 0, 1.5, 0.4, 0.18},
+      {TILE_WIDE, 0, 9.0, 1.18, 0.42}, {TILE_HALF, 0, 5.5, 0.66, 0.45}, {TILE_QUARTER, 0, 3.0, 0.42, 0.7}, {TILE_STRIP, 0, 1.5, 0.37, 0.4},
       {TILE_NARROW, 128, 5.0, 0.48, 0.4}, {TILE_NARROW2, 128, 2.0, 0.31, 1.5}, {TILE_SLIM, 64, 5.0, 0.55, 0.8}, {TILE_SLIM2, 64, 2.0, 0.32, 2.0}};
   constexpr double CUS = 256.0, LAUNCH = 4.5, MEMORY = 5e6;           // bytes per microsecond
   const long long steps = (k + 63) / 64, tn = (n + GBN - 1) / GBN;

@@ -180,7 +180,10 @@ template <int BM_, int BF_, int WT_, int WF_, int BK_, int NST_, int PER_CU_ = 1
   static constexpr int CPR = BK / 8, PR = 1024 / ROWB;               // 16-byte chunks per row; rows per 1 KB piece
   static_assert(CPR == 8, "the swizzle of a row's chunks is one of eight");
   static constexpr int XP = BM / PR, WP = BF / PR, CP = GCK / PR;    // pieces per stage
-  // ... per wave; where there are fewer pieces than waves, some are fetched twice (to the same place)
+  // ... per wave.  Where there are fewer pieces of checksum rows than waves the last waves have none (C_SPARE); in the largest
+  // tile, which has no registers left for a second form of its loop, and with fewer pieces of token rows than waves, some
+  // are fetched twice (to the same place)
+  static constexpr bool C_SPARE = CP < NW && BM < 256;
   static constexpr int XW = (XP + NW - 1) / NW, WW = (WP + NW - 1) / NW, CW = 1;
   static_assert((XP % NW == 0 || XP < NW) && (WP % NW == 0) && CP <= NW, "pieces split evenly");
   template <bool FT> static constexpr int nload() { return XW + WW + (FT ? CW : 0); }
@@ -190,10 +193,12 @@ template <int BM_, int BF_, int WT_, int WF_, int BK_, int NST_, int PER_CU_ = 1
   static_assert(PER_CU * NST * (BM + BF + GCK) * ROWB <= 160 * 1024 && NST <= 3, "LDS; the waits of the last stages");
 };
 
-// The tile shapes in use (see gemm_plan in ftgemm.hip for when)
+// The tile shapes in use (see gemm_plan in ftgemm.hip for when).  The tiles of 128 and 64 tokens are spread over eight waves,
+// two per SIMD, although four with blocks twice as high would read a third less LDS: a wave alone on its SIMD waits
+// for LDS and for its own barrier (2048 x 2048 x 1024 19.2 -> 16.9 us with 64 tokens, 5000 x 1300 x 8000 152 -> 134 with 128).
 using TileWide = GTile<256, 256, 4, 8, 64, 2>;
-using TileHalf = GTile<128, 256, 4, 8, 64, 3>;
-using TileQuarter = GTile<64, 256, 4, 4, 64, 3>;
+using TileHalf = GTile<128, 256, 4, 4, 64, 3>;
+using TileQuarter = GTile<64, 256, 2, 4, 64, 3>;
 using TileStrip = GTile<32, 256, 2, 4, 64, 3>;
 using TileNarrow = GTile<128, 128, 4, 4, 64, 3>;
 using TileFinish = GTile<16, 256, 1, 4, 64, 1>;      // epilogue only
@@ -590,9 +595,14 @@ __global__ __launch_bounds__(T::NW * 64, T::PER_CU * T::NW / 4 > 8 / T::NW ? T::
     gload_lds16_off(src + (size_t)kb * BK, off[i], piece_lds(i, st));
   };
   // the last K step of a ragged K: the chunks beyond column K are filled with zeros instead
+  // (a wave without a piece of the checksum rows has one load less; fetching another wave's piece once more to keep the
+  // counts alike made the steps of the 64-token tile, whose 48 pieces include 4 such, 10 % longer where rows are not
+  // multiples of a cache line: 1733 x 539 x 6344)
+  const bool has_c = FT && (!T::C_SPARE || wave < T::CP);
   auto issue_ragged = [&](int kb, int st) {
 #pragma unroll
     for (int i = 0; i < NLOAD; ++i) {
+      if (i == T::XW + T::WW && !has_c) continue;
       if (chunk * 8 < krem) issue_piece(i, kb, st);
       else *reinterpret_cast<__attribute__((address_space(3))) half8*>((uintptr_t)(piece_lds(i, st) + 16u * lane)) = (half8)(_Float16)0.f;
     }
@@ -659,16 +669,19 @@ __global__ __launch_bounds__(T::NW * 64, T::PER_CU * T::NW / 4 > 8 / T::NW ? T::
       if (st == kb_ragged) issue_ragged(st, st);
       else {
 #pragma unroll
-        for (int i = 0; i < NLOAD; ++i) issue_piece(i, st, st);
+        for (int i = 0; i < NLOAD; ++i)
+          if (i < T::XW + T::WW || has_c) issue_piece(i, st, st);
       }
     }
-  if (nkb >= NST) wait_vmcnt<(NST - 1) * NLOAD>();
-  else wait_vmcnt<0>();
+  if (nkb < NST) wait_vmcnt<0>();
+  else if (has_c) wait_vmcnt<(NST - 1) * NLOAD>();
+  else wait_vmcnt<(NST - 1) * (T::XW + T::WW)>();
   wait_lds();
   phase_barrier();
   const int nfull = kb_ragged >= 0 && kb_ragged < nkb ? nkb - 1 : nkb;      // steps that are requested in the stream
-  auto contract = [&](auto chk_tag) __attribute__((always_inline)) {
+  auto contract = [&](auto chk_tag, auto c_tag) __attribute__((always_inline)) {
     constexpr bool CHK = decltype(chk_tag)::value;
+    constexpr int NL = T::XW + T::WW + (decltype(c_tag)::value ? 1 : 0);      // loads per step of this wave
     constexpr int NCHK = CHK ? 2 * CB : 0;
     int st = 0;
     // Row y of k-step ks: its products, and the LDS reads behind them.  `tail`: the last AHEAD rows of a
@@ -701,7 +714,7 @@ __global__ __launch_bounds__(T::NW * 64, T::PER_CU * T::NW / 4 > 8 / T::NW ? T::
         if (LD && tail) {
           const int q = (y - (WF - AHEAD)) * WT + m;
 #pragma unroll
-          for (int i = NLOAD * q / TAILP; i < NLOAD * (q + 1) / TAILP; ++i) issue_piece(i, kb_ld, st);
+          for (int i = NL * q / TAILP; i < NL * (q + 1) / TAILP; ++i) issue_piece(i, kb_ld, st);
         }
       }
 #pragma unroll
@@ -715,7 +728,7 @@ __global__ __launch_bounds__(T::NW * 64, T::PER_CU * T::NW / 4 > 8 / T::NW ? T::
       for_each_index<NKS * WF - AHEAD>([&](auto row) __attribute__((always_inline)) { row_step(row, stage, next, kb + NST, ld_tag); });
       wait_lds();                            // the operands of the last rows are in registers: this wave is done with the stage
       // the next stage has landed; up to NST-2 younger ones may be in flight
-      if (LD || kb + NST - 1 < nkb) wait_vmcnt<(NST - 2) * NLOAD>();
+      if (LD || kb + NST - 1 < nkb) wait_vmcnt<(NST - 2) * NL>();
       else wait_vmcnt<0>();
       phase_barrier();                       // everyone's pieces of the next stage have landed, and everyone is done with this one
       if (!LD && kb + NST < nkb) issue_ragged(kb + NST, st);
@@ -732,12 +745,18 @@ __global__ __launch_bounds__(T::NW * 64, T::PER_CU * T::NW / 4 > 8 / T::NW ? T::
     for (; kb + NST < nfull; ++kb) stage_step(kb, ftattn::yes{});
     for (; kb < nkb; ++kb) stage_step(kb, ftattn::no{});
   };
+  auto contract_as = [&](auto chk_tag) __attribute__((always_inline)) {
+    if constexpr (!FT) contract(chk_tag, ftattn::no{});
+    else if constexpr (!T::C_SPARE) contract(chk_tag, ftattn::yes{});
+    else if (has_c) contract(chk_tag, ftattn::yes{});
+    else contract(chk_tag, ftattn::no{});
+  };
   if (FT && WT < NWF) {
-    if (check_wave) contract(ftattn::yes{}); else contract(ftattn::no{});
+    if (check_wave) contract_as(ftattn::yes{}); else contract_as(ftattn::no{});
   } else if (FT) {
-    contract(ftattn::yes{});
+    contract_as(ftattn::yes{});
   } else {
-    contract(ftattn::no{});
+    contract_as(ftattn::no{});
   }
 
   wait_lds();
