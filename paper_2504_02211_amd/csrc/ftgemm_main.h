@@ -790,12 +790,29 @@ __global__ __launch_bounds__(256) void ftgemm_finish(const GArgs a) {
   sc[0][0] = sc[0][1] = (float4v)0.f;
   const float4v* in = a.ws + ((size_t)tm * a.Tn + tn) * WS_BLOCKS * 64 + lane;
   const size_t step = (size_t)a.ws_tokens * a.Tn * WS_BLOCKS * 64;
-#pragma unroll 4
-  for (int p = 0; p < a.parts; ++p) {
+  // up to eight shares are requested before the first is added: what this kernel takes is the latency of its loads
+  auto add = [&](const int first, auto n_tag) __attribute__((always_inline)) {
+    constexpr int NP = decltype(n_tag)::value;
+    float4v x[NP][T::WF], c[NP][2];
 #pragma unroll
-    for (int y = 0; y < T::WF; ++y) acc[y][0] += in[p * step + (T::WF * wave + y) * 64];
-    if (FT && wave == 0) { sc[0][0] += in[p * step + 16 * 64]; sc[0][1] += in[p * step + 17 * 64]; }
-  }
+    for (int i = 0; i < NP; ++i) {
+      const float4v* at = in + (first + i) * step;
+#pragma unroll
+      for (int y = 0; y < T::WF; ++y) x[i][y] = at[(T::WF * wave + y) * 64];
+      if (FT && wave == 0) { c[i][0] = at[16 * 64]; c[i][1] = at[17 * 64]; }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+#pragma unroll
+      for (int y = 0; y < T::WF; ++y) acc[y][0] += x[i][y];
+      if (FT && wave == 0) { sc[0][0] += c[i][0]; sc[0][1] += c[i][1]; }
+    }
+  };
+  int p = 0;
+  for (; p + 8 <= a.parts; p += 8) add(p, std::integral_constant<int, 8>{});
+  if (p + 4 <= a.parts) { add(p, std::integral_constant<int, 4>{}); p += 4; }
+  for (; p < a.parts; ++p) add(p, std::integral_constant<int, 1>{});
   finish_tile<T, FT, false, BF>(a, smem, acc, sc, tm * T::BM, tn * GBN, blockIdx.x);
 }
 
