@@ -11,7 +11,8 @@
 //   main kernel      one workgroup per (batch, head, row tile); loop over key tiles:
 //                    GEMM I (+checksum block) -> max -> exp -> product-form check -> row-sum ->
 //                    GEMM II with rescale (+checksum block); after the loop: row-sum range check,
-//                    normalisation, sum-form check, store.
+//                    normalisation, sum-form check, store.  In calls with few row tiles the keys of a row tile are
+//                    divided among several workgroups, and ftattn_finish does what follows the loop.
 //
 // Register layout.  Scores are computed transposed, S^T = K_j Q_i^T, with the 32x32x16 fp16 MFMA.
 // A lane then owns ONE query (column lane%32) and, per 32-key block, the 16 keys

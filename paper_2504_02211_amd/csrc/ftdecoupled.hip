@@ -2,7 +2,7 @@
 // Section 4.1): ABFT-GEMM I -> DMR row-softmax -> ABFT-GEMM II, with S and P in device memory between
 // the kernels.  The C ABI of include/ftdecoupled.h.  The two GEMMs are the library's strided-ABFT
 // GEMM kernel (ftgemm_main.h) on buffers of this context, one launch for all heads (with a fault list one
-// per head); the softmax kernels and the V^T kernel are here.
+// per head); the softmax kernels and the kernel that prepares both products are here.
 #include "ftdecoupled.h"
 #include "ftgemm_main.h"
 
