@@ -184,9 +184,12 @@ def forward_static(q, k, v, o, batch: int, heads: int, seq: int, head_dim: int, 
     library's static scratch array.  n_events: a device int32 tensor (or address) that receives the
     number of events, or None."""
     lib = load_library()
-    cfg = Config.from_buffer_copy(_CONFIG.pack(_CONFIG.size, batch, heads, seq, head_dim, in_dtype, out_dtype, int(bool(causal)),
-                                               softmax_scale, ft_mode, 8, 0, 0, 0.0, 0.0, 0.0, int(bool(rowsum_fold)), 0, 0.0,
-                                               0, device))
+    fields = (C.sizeof(Config), batch, heads, seq, head_dim, in_dtype, out_dtype, int(bool(causal)), softmax_scale, ft_mode, 8, 0, 0,
+              0.0, 0.0, 0.0, int(bool(rowsum_fold)), 0, 0.0, 0, device)
+    try:
+        cfg = Config.from_buffer_copy(_CONFIG.pack(*fields))
+    except (struct.error, OverflowError):       # values that the fields of a structure wrap, turn into infinity or refuse
+        cfg = Config(*fields)
     n = batch * heads * seq * head_dim
     ptr = lambda t, name, dt: None if t is None else address(t, name, n, dt, device)
     nev = None if n_events is None else n_events if isinstance(n_events, int) else n_events.data_ptr()

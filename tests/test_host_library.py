@@ -178,6 +178,16 @@ def test_binding_checks_tensors_before_passing_raw_pointers():
         ftattn.device_pointer(object(), "q", 64, ftattn.F16, 0)
 
 
+@pytest.mark.parametrize("change", [dict(softmax_scale=1e39), dict(batch=2 ** 32 + 1), dict(heads=-2 ** 31 - 1), dict(in_dtype=2 ** 33)])
+def test_static_call_takes_values_as_the_fields_of_its_structure_do(change):
+    """Numbers beyond the range of a field wrap or become infinite and are the library's to refuse, as in ftattn_create."""
+    shape = dict(batch=1, heads=1, seq=64, head_dim=64, in_dtype=ftattn.F16, causal=False)
+    with pytest.raises(ftattn.FtAttnError):
+        ftattn.forward_static(None, None, None, None, **{**shape, **change})
+    with pytest.raises(TypeError):
+        ftattn.forward_static(None, None, None, None, **{**shape, "batch": 1.0})
+
+
 def test_decoupled_create_rejects_bad_configs_without_a_device():
     lib = ftdecoupled.load_library()
     assert C.sizeof(ftdecoupled.Config) == 13 * 4 and C.sizeof(ftdecoupled.Fault) == 24 == C.sizeof(ftdecoupled.Event)
