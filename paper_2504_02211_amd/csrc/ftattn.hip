@@ -239,32 +239,23 @@ static int resolve_config(const ftattn_config* cfg, ftattn_config& e, Geometry& 
   return FTATTN_OK;
 }
 
-// Lets the kernels of one head size (and mode) use their dynamic LDS.  Needs the device current.
-static hipError_t allow_lds(int D, int per_step, int stride, const char*& why, bool lazy, bool split) {
+// Lets the kernels that a configuration runs, with a fault list or without one, use their dynamic LDS.  Needs the
+// device current.  (Only those: a call to the runtime for each takes about 10 us of the 110 to 300 that creating a
+// context takes.)
+static hipError_t allow_lds(const ftattn_config& e, bool split, const char*& why) {
+  const int D = e.head_dim;
+  const bool ft = e.ft_mode != FTATTN_FT_OFF, causal = e.causal != 0, lazy = e.rescale_margin > 0.f;
+  const int bytes = (int)lds_bytes(D, ft);
   why = "no kernel for this tile shape";
-  for (int v = 0; v < 8; ++v) {
-    const int ft = v & 1, ca = (v >> 1) & 1;
-    main_fn f = select_kernel(D, ft != 0, ca != 0, (v >> 2) != 0);
+  for (int v = 0; v < (split ? 3 : 2); ++v) {
+    const bool inject = v == 1;
+    main_fn f = v == 2 ? select_split(D, ft, causal)
+                : e.per_step ? select_perstep(D, causal, inject, e.per_step)
+                : e.stride == 1 ? select_elementwide(D, causal, inject)
+                : lazy ? select_lazy(D, ft, causal, inject)
+                       : select_kernel(D, ft, causal, inject);
     if (!f) return hipErrorInvalidValue;
-    hipError_t he = hipFuncSetAttribute((const void*)f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes(D, ft != 0));
-    if (he != hipSuccess) { why = "hipFuncSetAttribute"; return he; }
-  }
-  for (int v = 0; v < 4 && split; ++v) {
-    const bool ft = (v & 1) != 0;
-    hipError_t he = hipFuncSetAttribute((const void*)select_split(D, ft, (v & 2) != 0), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes(D, ft));
-    if (he != hipSuccess) { why = "hipFuncSetAttribute"; return he; }
-  }
-  for (int v = 0; v < 8 && lazy; ++v) {
-    const bool ft = (v & 1) != 0;
-    main_fn f = select_lazy(D, ft, (v & 2) != 0, (v & 4) != 0);
-    if (!f) return hipErrorInvalidValue;
-    hipError_t he = hipFuncSetAttribute((const void*)f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes(D, ft));
-    if (he != hipSuccess) { why = "hipFuncSetAttribute"; return he; }
-  }
-  for (int v = 0; v < 4 && (per_step || stride == 1); ++v) {
-    main_fn f = per_step ? select_perstep(D, (v & 1) != 0, (v >> 1) != 0, per_step) : select_elementwide(D, (v & 1) != 0, (v >> 1) != 0);
-    if (!f) return hipErrorInvalidValue;
-    hipError_t he = hipFuncSetAttribute((const void*)f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes(D, true));
+    hipError_t he = hipFuncSetAttribute((const void*)f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
     if (he != hipSuccess) { why = "hipFuncSetAttribute"; return he; }
   }
   return hipSuccess;
@@ -317,7 +308,7 @@ extern "C" int ftattn_create(const ftattn_config* cfg, ftattn_ctx** out) {
   // the checksum rows of the encoded tiles are never written when ft_mode is OFF; keep them defined
   CREATE_TRY(hipMemset(c->kc, 0, tiles_bytes));
   {
-    hipError_t le = allow_lds(e.head_dim, e.per_step, e.stride, why, e.rescale_margin > 0.f, g.n_ws != 0);
+    hipError_t le = allow_lds(e, g.n_ws != 0, why);
     if (le != hipSuccess) {
       int rc = fail(nullptr, le == hipErrorInvalidValue ? FTATTN_EUNSUPPORTED : FTATTN_EHIP, std::string(why) + ": " + hipGetErrorString(le));
       release(c);
@@ -556,7 +547,7 @@ static __device__ __align__(256) unsigned char scratch[STATIC_SCRATCH_BYTES];
 
 static std::mutex g_static_mu;
 static unsigned char* g_static_ptr[STATIC_MAX_DEVICES];      // per device, null until set up
-static bool g_static_lds[STATIC_MAX_DEVICES][2];             // kernels of head_dim 64 / 128 prepared
+static bool g_static_lds[STATIC_MAX_DEVICES][8];             // kernels of a head size, protected or not, causal or not, prepared
 static unsigned g_static_calls[STATIC_MAX_DEVICES];          // parity picks the range word of a call
 static thread_local char g_static_err[256];
 
@@ -610,9 +601,9 @@ extern "C" int ftattn_forward_static(const ftattn_config* cfg, const void* q, co
       if (he != hipSuccess || !ptr) return static_fail(FTATTN_EHIP, "hipGetSymbolAddress(scratch)", he);
       g_static_ptr[e.device] = (unsigned char*)ptr;
     }
-    const int di = e.head_dim == 128 ? 1 : 0;
+    const int di = (e.head_dim == 128 ? 4 : 0) + (e.ft_mode != FTATTN_FT_OFF ? 2 : 0) + (e.causal != 0 ? 1 : 0);
     if (!g_static_lds[e.device][di]) {
-      he = allow_lds(e.head_dim, 0, 8, why, false, true);
+      he = allow_lds(e, true, why);
       if (he != hipSuccess) return static_fail(FTATTN_EHIP, why, he);
       g_static_lds[e.device][di] = true;
     }

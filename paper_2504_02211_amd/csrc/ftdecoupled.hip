@@ -448,6 +448,7 @@ struct ftdec_ctx {
   // device
   float* S = nullptr;
   _Float16* P = nullptr;
+  void* scratch = nullptr;       // the allocation that holds all of the following
   _Float16* vt = nullptr;
   uint16_t* wc1 = nullptr;       // [BH][Tn1][32][d]
   uint16_t* wc2 = nullptr;       // [BH][1][32][Np]
@@ -487,9 +488,7 @@ static int dfail(ftdec_ctx* c, int code, const std::string& msg) {
 
 static void drelease(ftdec_ctx* c) {
   if (!c) return;
-  (void)hipFree(c->S); (void)hipFree(c->P); (void)hipFree(c->vt); (void)hipFree(c->wc1); (void)hipFree(c->wc2);
-  (void)hipFree(c->g_events); (void)hipFree(c->cursors); (void)hipFree(c->g_slots); (void)hipFree(c->stat); (void)hipFree(c->s_events);
-  (void)hipFree(c->d_gfaults); (void)hipFree(c->d_sfaults);
+  (void)hipFree(c->S); (void)hipFree(c->P); (void)hipFree(c->scratch);
   if (c->h_gfaults) (void)hipHostFree(c->h_gfaults);
   if (c->h_sfaults) (void)hipHostFree(c->h_sfaults);
   for (hipEvent_t e : c->ev) if (e) (void)hipEventDestroy(e);
@@ -547,16 +546,29 @@ extern "C" int ftdec_create(const ftdec_config* cfg, ftdec_ctx** out) {
       {(void**)&c->g_slots, BH * (c->slots1 + c->slots2) * sizeof(ftgemm::GSlot), false}, {(void**)&c->stat, sizeof(DStat), false}, {(void**)&c->s_events, cap * sizeof(ftdec_event), false},
       {(void**)&c->d_gfaults, sizeof(ftgemm::GFault) * c->fault_cap, false},
       {(void**)&c->d_sfaults, sizeof(SFault) * c->fault_cap, false}};
+  // S and P by themselves, everything else in one allocation: each one and its memset cost tens of microseconds
+  auto room = [](size_t x) { return (x + 255) & ~(size_t)255; };
+  size_t rest = 0;
+  for (auto& al : allocs) rest += al.sp ? 0 : room(al.bytes);
+  auto allocate = [&](void** p, size_t bytes) {
+    he = hipMalloc(p, bytes);
+    if (he == hipSuccess) he = hipMemset(*p, 0, bytes);
+    if (he == hipSuccess) return (int)FTDEC_OK;
+    int rc = dfail(nullptr, he == hipErrorOutOfMemory ? FTDEC_ENOMEM : FTDEC_EHIP, std::string("allocating device scratch: ") + hipGetErrorString(he));
+    drelease(c);
+    return rc;
+  };
+  if (const int rc = allocate(&c->scratch, rest)) return rc;
+  size_t at = 0;
   for (auto& al : allocs) {
-    he = hipMalloc(al.p, al.bytes);
-    if (he == hipSuccess) he = hipMemset(*al.p, 0, al.bytes);
-    if (he != hipSuccess) {
-      int rc = dfail(nullptr, he == hipErrorOutOfMemory ? FTDEC_ENOMEM : FTDEC_EHIP, std::string("allocating device scratch: ") + hipGetErrorString(he));
-      drelease(c);
-      return rc;
+    if (al.sp) {
+      if (const int rc = allocate(al.p, al.bytes)) return rc;
+      c->bytes_sp += (int64_t)al.bytes;
+    } else {
+      *al.p = static_cast<char*>(c->scratch) + at;
+      at += room(al.bytes);
     }
     c->bytes_total += (int64_t)al.bytes;
-    if (al.sp) c->bytes_sp += (int64_t)al.bytes;
   }
   he = hipHostMalloc((void**)&c->h_gfaults, sizeof(ftgemm::GFault) * c->fault_cap, hipHostMallocDefault);
   if (he == hipSuccess) he = hipHostMalloc((void**)&c->h_sfaults, sizeof(SFault) * c->fault_cap, hipHostMallocDefault);
