@@ -328,7 +328,7 @@ __global__ __launch_bounds__(256) void ftdec_softmax_wave(const SArgs a) {
   }
 }
 
-// Everything the two products need before they start, in one launch: grid (tiles, heads, roles), the first role `first_role`.
+// Everything the two products need before they start, in one launch: grid (tiles, heads, roles).
 // Role 0, 64 keys per workgroup: V [N][d] (fp16 or bf16 patterns) -> V^T [d][Np] in fp16, columns beyond N zero, and (FT)
 // the tensor checksums of its rows (eq. (13), (14): 32 rows [32][Np], as encode_weight_rows forms them).  A
 // 64 x 64 block at a time: 16 bytes per lane from memory, transposed through LDS (rows of 33 words: the eight keys
@@ -336,16 +336,16 @@ __global__ __launch_bounds__(256) void ftdec_softmax_wave(const SArgs a) {
 // fold its features from the same block.  The first workgroup also clears the counters of the softmax log.
 // Role 1: the checksum rows of K.
 // Bound: memory, one read of K and V and one write of V^T; for short sequences the launches.  Three launches (V^T with
-// 16 bytes per lane, the checksums of K, those of V^T read back) took 23 us for 2 x 16 x 2048 x 128 and 15 for 2 x 5 x 151 x 128.
+// 16 bytes per lane, the checksums of K, those of V^T read back) took 23 us for 2 x 16 x 2048 x 128, this takes 14; for 2 x 5 x 151 x 128 they took 15.
 template <bool FT, bool BF>
 __global__ __launch_bounds__(256) void ftdec_prepare(const uint16_t* __restrict__ k, const uint16_t* __restrict__ v, uint16_t* __restrict__ wc1,
                                                      _Float16* __restrict__ vt, _Float16* __restrict__ wc2, int N, int Np, int d, int Tn1,
-                                                     int first_role, int32_t* s_count, unsigned long long* retried) {
+                                                     int32_t* s_count, unsigned long long* retried) {
   typedef uint16_t u16x8 __attribute__((ext_vector_type(8)));
   typedef _Float16 half8 __attribute__((ext_vector_type(8)));
   typedef _Float16 half2v __attribute__((ext_vector_type(2)));
   const int bh = blockIdx.y, tid = threadIdx.x;
-  if (blockIdx.z + first_role == 1) {
+  if (blockIdx.z == 1) {
     const int chunks = (d / 8 + 7) / 8, tn = blockIdx.x / chunks;
     if (tn < Tn1)
       ftgemm::encode_weight_rows<BF>(k + (size_t)bh * N * d, wc1 + (size_t)bh * Tn1 * ftgemm::GCK * d, N, d, tn, blockIdx.x % chunks);
@@ -426,7 +426,7 @@ __global__ __launch_bounds__(256) void ftdec_prepare(const uint16_t* __restrict_
     *reinterpret_cast<half8*>(wc2 + ((size_t)bh * ftgemm::GCK + row) * Np + k0 + at) = *reinterpret_cast<const half8*>(&cks[row][at]);
 }
 
-typedef void (*prepare_fn)(const uint16_t*, const uint16_t*, uint16_t*, _Float16*, _Float16*, int, int, int, int, int, int32_t*, unsigned long long*);
+typedef void (*prepare_fn)(const uint16_t*, const uint16_t*, uint16_t*, _Float16*, _Float16*, int, int, int, int, int32_t*, unsigned long long*);
 static prepare_fn select_prepare(bool ft, bool bf) {
   if (ft) return bf ? ftdec_prepare<true, true> : ftdec_prepare<true, false>;
   return bf ? ftdec_prepare<false, true> : ftdec_prepare<false, false>;
@@ -648,21 +648,19 @@ extern "C" int ftdec_forward(ftdec_ctx* c, const void* q, const void* k, const v
     DHIP_TRY(c, hipStreamSynchronize(st));     // the staging buffers may be rewritten by the next call
   }
 
-  // ---- V^T and the checksum rows of both products, one launch; while the stages are timed one for each, so that every
-  // encode counts with its product
+  // ---- V^T and the checksum rows of both products, one launch; while the stages are timed V^T alone, and the checksum
+  // rows in launches of their own beside their products, so that every encode counts with its product
   const uint16_t* q16 = reinterpret_cast<const uint16_t*>(q);
   const uint16_t* k16 = reinterpret_cast<const uint16_t*>(k);
   const long long wc1_stride = (long long)c->Tn1 * ftgemm::GCK * d, wc2_stride = (long long)ftgemm::GCK * Np;
-  auto prepare = [&](int first_role, int roles) {
-    const int tiles = std::max((Np + 63) / 64, c->Tn1 * ((d / 8 + 7) / 8));
-    hipLaunchKernelGGL(select_prepare(ft, bf), dim3(tiles, BH, roles), dim3(256), 0, st, k16, reinterpret_cast<const uint16_t*>(v), c->wc1, c->vt,
-                       reinterpret_cast<_Float16*>(c->wc2), N, Np, d, c->Tn1, first_role, &c->stat->s_count, &c->stat->retried);
-    return hipGetLastError();
-  };
+  const bool fused = ft && !c->timing;
   if (c->timing) DHIP_TRY(c, hipEventRecord(c->ev[4], st));
-  DHIP_TRY(c, prepare(0, ft && !c->timing ? 2 : 1));
+  hipLaunchKernelGGL(select_prepare(fused, bf), dim3(std::max((Np + 63) / 64, c->Tn1 * ((d / 8 + 7) / 8)), BH, fused ? 2 : 1), dim3(256), 0, st,
+                     k16, reinterpret_cast<const uint16_t*>(v), c->wc1, c->vt, reinterpret_cast<_Float16*>(c->wc2), N, Np, d, c->Tn1,
+                     &c->stat->s_count, &c->stat->retried);
+  DHIP_TRY(c, hipGetLastError());
   if (c->timing) DHIP_TRY(c, hipEventRecord(c->ev[0], st));
-  if (ft && c->timing) DHIP_TRY(c, prepare(1, 1));
+  if (ft && !fused) DHIP_TRY(c, ftgemm::gemm_launch_encode_w(k16, c->wc1, N, d, bf, st, BH, (long long)N * d, wc1_stride));
   // (with a fault list every head runs the injecting tile shape, so that all slots have one stride)
   const ftgemm::GPlan plan1 = ftgemm::gemm_plan(N, N, d, BH, n_g > 0, false), plan2 = ftgemm::gemm_plan(N, d, Np, BH, n_g > 0, false);
   auto gemm_args = [&](int which, int bh) {
@@ -720,6 +718,7 @@ extern "C" int ftdec_forward(ftdec_ctx* c, const void* q, const void* k, const v
   // ---- 3. ABFT-GEMM II: O = P V per head (tokens = queries, weight rows = the features of V^T)
   const uint16_t* vt16 = reinterpret_cast<const uint16_t*>(c->vt);
   const uint16_t* p16 = reinterpret_cast<const uint16_t*>(c->P);
+  if (ft && !fused) DHIP_TRY(c, ftgemm::gemm_launch_encode_w(vt16, c->wc2, d, Np, false, st, BH, (long long)d * Np, wc2_stride));
   for (int bh = 0; bh < (n_g ? BH : 1); ++bh) {
     ftgemm::GArgs a = gemm_args(1, bh);
     a.x = p16 + (size_t)bh * N * Np; a.w = vt16 + (size_t)bh * d * Np; a.wc = c->wc2 + (size_t)bh * wc2_stride;

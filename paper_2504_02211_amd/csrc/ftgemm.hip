@@ -84,10 +84,11 @@ hipError_t gemm_allow_lds(GPlan plan, bool ft, bool bf16) {
   return hipSuccess;
 }
 
-hipError_t gemm_launch_encode_w(const uint16_t* w, uint16_t* wc, int n, int k, bool bf16, hipStream_t st) {
-  dim3 grid((n + GBN - 1) / GBN, (k / 8 + 7) / 8);
-  if (bf16) ftgemm_encode_w<true><<<grid, 256, 0, st>>>(w, wc, n, k);
-  else ftgemm_encode_w<false><<<grid, 256, 0, st>>>(w, wc, n, k);
+hipError_t gemm_launch_encode_w(const uint16_t* w, uint16_t* wc, int n, int k, bool bf16, hipStream_t st, int batch,
+                                long long bs_w, long long bs_wc) {
+  dim3 grid((n + GBN - 1) / GBN, (k / 8 + 7) / 8, batch);
+  if (bf16) ftgemm_encode_w<true><<<grid, 256, 0, st>>>(w, wc, n, k, bs_w, bs_wc);
+  else ftgemm_encode_w<false><<<grid, 256, 0, st>>>(w, wc, n, k, bs_w, bs_wc);
   return hipGetLastError();
 }
 

@@ -160,8 +160,9 @@ __device__ __forceinline__ void encode_weight_rows(const uint16_t* __restrict__ 
 }
 
 template <bool BF>
-__global__ __launch_bounds__(256) void ftgemm_encode_w(const uint16_t* __restrict__ w, uint16_t* __restrict__ wc, int N, int K) {
-  encode_weight_rows<BF>(w, wc, N, K, blockIdx.x, blockIdx.y);
+__global__ __launch_bounds__(256) void ftgemm_encode_w(const uint16_t* __restrict__ w, uint16_t* __restrict__ wc, int N, int K,
+                                                       long long bs_w, long long bs_wc) {
+  encode_weight_rows<BF>(w + (size_t)blockIdx.z * bs_w, wc + (size_t)blockIdx.z * bs_wc, N, K, blockIdx.x, blockIdx.y);      // z: matrix of a batch
 }
 
 // Tile shape: BM tokens x BF features, a wave takes WT x WF blocks of 16 x 16, ring of NST stages, PER_CU workgroups per CU.
@@ -843,7 +844,8 @@ template <bool BF> gemm_fn tile_kernel_of(int tile, bool ft, bool inject) {
 // Launch helpers (ftgemm.hip), for other host code of the library that runs the same protected
 // product on buffers of its own (the decoupled attention baseline).  None of them allocates or
 // synchronises.
-hipError_t gemm_launch_encode_w(const uint16_t* w, uint16_t* wc, int n, int k, bool bf16, hipStream_t st);
+hipError_t gemm_launch_encode_w(const uint16_t* w, uint16_t* wc, int n, int k, bool bf16, hipStream_t st,
+                                int batch = 1, long long bs_w = 0, long long bs_wc = 0);
 // How a product is run: its tile shape, and over how many workgroups a tile's K dimension is split.
 struct GPlan { int tile, parts; };
 GPlan gemm_plan(long long m, long long n, long long k, int batch, bool inject, bool may_split);
