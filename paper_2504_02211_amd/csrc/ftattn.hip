@@ -52,6 +52,8 @@ struct ftattn_ctx {
   _Float16* kc = nullptr;
   _Float16* vt = nullptr;
   float* ws = nullptr;
+  void* vt_alloc = nullptr;      // the allocations of vt and ws where they have one of their own
+  void* ws_alloc = nullptr;
   DevFault* d_faults = nullptr;
   int32_t* d_fault_off = nullptr;
   ftattn_event* d_events = nullptr;
@@ -91,7 +93,7 @@ static int fail(ftattn_ctx* c, int code, const std::string& msg) {
 
 static void release(ftattn_ctx* c) {
   if (!c) return;
-  (void)hipFree(c->kc); (void)hipFree(c->d_faults);
+  (void)hipFree(c->kc); (void)hipFree(c->vt_alloc); (void)hipFree(c->ws_alloc); (void)hipFree(c->d_faults);
   (void)hipFree(c->d_fault_off); (void)hipFree(c->d_events); (void)hipFree(c->d_stat);
   if (c->h_faults) (void)hipHostFree(c->h_faults);
   if (c->h_stat) (void)hipHostFree(c->h_stat);
@@ -134,13 +136,13 @@ static size_t lds_bytes(int D, bool ft) {
 // Microseconds, from timings of both head sizes with 1..512 row tiles of 2..256 key tiles: a workgroup costs `fixed`
 // and `tile` per key tile, one at a time per CU (two that share a CU at head_dim 64 take about twice as long each); a
 // split adds the launch that puts the shares together, and their state passes through memory twice.  Measured, unsplit and
-// as planned here: 1 x 1 x 16384 x 128 causal 497 and 138 us, 2 x 3 x 5001 x 128 187 and 145, 1 x 5 x 3001 x 64 causal
-// 74 and 46, 1 x 20 x 2048 x 128 causal 95 and 79.  Row tiles of equal length that fill the CUs a whole number of
-// times and a little more: only those left over are split (3 x 16 x 1531 x 128, 288 row tiles: 164 and 137 us; all
+// as planned here: 1 x 1 x 16384 x 128 causal 496 and 128 us, 2 x 3 x 5001 x 128 178 and 134, 1 x 5 x 3001 x 64 causal
+// 74 and 45, 1 x 20 x 2048 x 128 causal 92 and 74.  Row tiles of equal length that fill the CUs a whole number of
+// times and a little more: only those left over are split (3 x 16 x 1531 x 128, 288 row tiles: 154 and 131 us; all
 // split in two 191).  Beyond twice the CUs (causal: light row tiles fill up the last round; else four times) a split
 // gains nothing, and neither do short rows, where starting and finishing a workgroup is most of it (6 key tiles, 2 x 3 x
 // 333 x 128: 28.8 and 27.9 us; 8, 1 x 2 x 512 x 64: 22.1 and 20.8; 11, 1 x 7 x 700 x 128: 41 and 37; 16, 1 x 1 x 1000 x 128:
-// 48 and 34).  A call with a fault list is never split: faults name values of Algorithm 1's one pass over the keys.
+// 48 and 32).  A call with a fault list is never split: faults name values of Algorithm 1's one pass over the keys.
 static void plan_split(const ftattn_config& e, Geometry& g) {
   constexpr long long CUS = 256;
   const long long tiles = (long long)g.BH * g.Ti;
@@ -289,12 +291,28 @@ extern "C" int ftattn_create(const ftattn_config* cfg, ftattn_ctx** out) {
       return rc_;                                                                                         \
     }                                                                                                     \
   } while (0)
-  // (one allocation for the encoded tiles and the state of split row tiles: each one costs tens of microseconds)
+  // The encoded tiles and the state of split row tiles share an allocation (each one, with its memset, costs about 30 us to
+  // make and 15 to 20 to free) unless only that takes it beyond 64 MiB, where the runtime needs 35 us to make one and 270 to free it.
+  constexpr size_t CHEAP = (size_t)64 << 20;
   auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
-  const size_t tiles_bytes = up(g.n_kc * 2) + up(g.n_vt * 2);
-  CREATE_TRY(hipMalloc((void**)&c->kc, tiles_bytes + g.n_ws * sizeof(float)));
-  c->vt = c->kc + up(g.n_kc * 2) / 2;
-  if (g.n_ws) c->ws = reinterpret_cast<float*>(reinterpret_cast<char*>(c->kc) + tiles_bytes);
+  auto together = [](size_t x, size_t y) { return x + y <= CHEAP || x > CHEAP || y > CHEAP; };
+  const size_t kc_bytes = up(g.n_kc * 2), vt_bytes = up(g.n_vt * 2), ws_bytes = g.n_ws * sizeof(float);
+  const bool vt_joined = together(kc_bytes, vt_bytes);
+  const size_t tiles_bytes = kc_bytes + (vt_joined ? vt_bytes : 0);
+  const bool ws_joined = ws_bytes && together(tiles_bytes, ws_bytes);
+  CREATE_TRY(hipMalloc((void**)&c->kc, tiles_bytes + (ws_joined ? ws_bytes : 0)));
+  if (vt_joined) {
+    c->vt = c->kc + kc_bytes / 2;
+  } else {
+    CREATE_TRY(hipMalloc(&c->vt_alloc, vt_bytes));
+    c->vt = static_cast<_Float16*>(c->vt_alloc);
+  }
+  if (ws_joined) {
+    c->ws = reinterpret_cast<float*>(reinterpret_cast<char*>(c->kc) + tiles_bytes);
+  } else if (ws_bytes) {
+    CREATE_TRY(hipMalloc(&c->ws_alloc, ws_bytes));
+    c->ws = static_cast<float*>(c->ws_alloc);
+  }
   CREATE_TRY(hipMalloc((void**)&c->d_faults, sizeof(DevFault) * c->fault_cap));
   CREATE_TRY(hipMalloc((void**)&c->d_fault_off, sizeof(int32_t) * (n_rt + 1)));
   CREATE_TRY(hipMalloc((void**)&c->d_events, sizeof(ftattn_event) * (size_t)e.max_events));
@@ -307,6 +325,7 @@ extern "C" int ftattn_create(const ftattn_config* cfg, ftattn_ctx** out) {
   CREATE_TRY(hipHostMalloc((void**)&c->h_faults, sizeof(DevFault) * c->fault_cap, hipHostMallocDefault));
   // the checksum rows of the encoded tiles are never written when ft_mode is OFF; keep them defined
   CREATE_TRY(hipMemset(c->kc, 0, tiles_bytes));
+  if (!vt_joined) CREATE_TRY(hipMemset(c->vt, 0, vt_bytes));
   {
     hipError_t le = allow_lds(e, g.n_ws != 0, why);
     if (le != hipSuccess) {
