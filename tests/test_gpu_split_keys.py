@@ -106,3 +106,47 @@ def test_faults_in_a_call_that_would_be_split():
     ctx.forward(q, k, v, b, None, st)
     assert ctx.report().n_events == 0 and torch.equal(a, b)
     ctx.close()
+
+
+MASKED = {"end": (0.5, 1.0), "middle": (0.25, 0.75), "first": (0.0, 0.5)}      # whole shares at -inf (four shares or more a row)
+
+
+@pytest.mark.parametrize("batch,heads,seq,head_dim,causal", [(1, 1, 8192, 128, False), (1, 1, 8200, 128, True), (1, 2, 6000, 64, True), (1, 1, 6001, 64, False)])
+@pytest.mark.parametrize("mode", [ftattn.FT_OFF, ftattn.FT_DETECT])
+@pytest.mark.parametrize("masked", MASKED)
+def test_shares_without_a_finite_score(batch, heads, seq, head_dim, causal, mode, masked):
+    """Keys masked by an infinite component (query 1 there): their scores are -inf and weigh nothing, also where a whole share
+    of the keys has no other score.  Rows that have none at all are not looked at."""
+    print(f"[split keys, -inf] {batch} x {heads} x {seq} x {head_dim} causal {causal} mode {mode} masked {masked}", flush=True)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seq + head_dim)
+    shape = (batch, heads, seq, head_dim)
+    q, k, v = (torch.randn(shape, generator=g, device="cuda").half() for _ in range(3))
+    q[..., 0] = 1.0
+    lo, hi = (int(seq * x) for x in MASKED[masked])
+    k[:, :, lo:hi, 0] = float("-inf")
+    o = torch.full(shape, float("nan"), dtype=torch.float32, device="cuda")
+    ctx = ftattn.FtAttn(*shape, 0, causal, ft_mode=mode)
+    ctx.forward(q, k, v, o, None, torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    ctx.close()
+    num = den = 0.0
+    for b, h, r0, want in reference(q, k, v, causal):
+        keep = torch.isfinite(want).all(-1)
+        assert int((~keep).sum()) == (min(max(hi - r0, 0), want.shape[0]) if causal and masked == "first" else 0)
+        diff = (o[b, h, r0:r0 + want.shape[0]].double() - want)[keep]
+        assert bool((diff.abs() <= 2e-3).all())
+        num += float((diff ** 2).sum())
+        den += float((want[keep] ** 2).sum())
+    assert (num / den) ** 0.5 <= 1e-3
+
+
+def test_a_share_of_nan_scores_is_not_lost():
+    shape = (1, 1, 8192, 128)
+    q, k, v = (torch.randn(shape, device="cuda").half() for _ in range(3))
+    k[:, :, 4096:] = float("nan")
+    o = torch.zeros(shape, dtype=torch.float32, device="cuda")
+    ctx = ftattn.FtAttn(*shape, 0, False, ft_mode=ftattn.FT_OFF)
+    ctx.forward(q, k, v, o, None, torch.cuda.current_stream().cuda_stream)
+    assert bool(torch.isnan(o).all())
+    ctx.close()
