@@ -66,6 +66,10 @@ EVENT_DTYPE = np.dtype([("b", "<i4"), ("h", "<i4"), ("check", "<i4"), ("kv_tile"
 
 _U8, _F32 = np.dtype(np.uint8), np.dtype(np.float32)
 
+# host memory of the library as a buffer, for numpy to copy out of
+_memory = C.PYFUNCTYPE(C.py_object, C.c_void_p, C.c_ssize_t, C.c_int)(("PyMemoryView_FromMemory", C.pythonapi))
+_READ = 0x100
+
 _lib = None
 
 
@@ -120,13 +124,9 @@ class Report:
         self.n_events = n
         self.n_events_dropped = view.n_events_dropped
         self.tiles_m, self.tiles_n = view.tiles_m, view.tiles_n
-        if n:
-            buf = C.string_at(view.events, n * C.sizeof(Event))
-            self.events = np.frombuffer(buf, dtype=EVENT_DTYPE).copy()
-        else:
-            self.events = np.zeros(0, dtype=EVENT_DTYPE)
-        def array(at, dtype, *shape):       # (np.ctypeslib.as_array takes ten times as long)
-            return np.frombuffer(C.string_at(at, math.prod(shape) * dtype.itemsize), dtype=dtype).reshape(shape).copy()
+        def array(at, dtype, *shape):       # (np.ctypeslib.as_array takes ten times as long, string_at a size of at most 2^31 - 1)
+            return np.frombuffer(_memory(at, math.prod(shape) * dtype.itemsize, _READ), dtype=dtype).reshape(shape).copy()
+        self.events = array(view.events, EVENT_DTYPE, n) if n else np.zeros(0, dtype=EVENT_DTYPE)
         self.tile_flags = array(view.tile_flags, _U8, batch, heads, view.tiles_m, view.tiles_n)
         self.rowtile_flags = array(view.rowtile_flags, _U8, batch, heads, view.tiles_m)
         self.residual_max = array(view.residual_max, _F32, batch, heads, view.tiles_m, 4)

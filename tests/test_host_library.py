@@ -188,6 +188,23 @@ def test_static_call_takes_values_as_the_fields_of_its_structure_do(change):
         ftattn.forward_static(None, None, None, None, **{**shape, "batch": 1.0})
 
 
+def test_report_of_two_to_the_31_tile_flags():
+    """1 x 16 x 1048576 x 64: 8192 row tiles and 16384 key tiles a head, 2 GiB of flags."""
+    tiles_m, tiles_n, heads = 8192, 16384, 16
+    flags, rows, stats = np.zeros(heads * tiles_m * tiles_n, np.uint8), np.zeros(heads * tiles_m, np.uint8), np.zeros(heads * tiles_m * 4, np.float32)
+    events = np.zeros(2, ftattn.EVENT_DTYPE)
+    flags[-1], rows[-1], stats[-1], events[1]["row"] = 5, 7, 0.5, 9
+    at = lambda x, t: x.ctypes.data_as(C.POINTER(t))
+    view = ftattn.ReportView(n_events=2, events=at(events, ftattn.Event), tiles_m=tiles_m, tiles_n=tiles_n, tile_flags=at(flags, C.c_uint8),
+                             rowtile_flags=at(rows, C.c_uint8), residual_max=at(stats, C.c_float))
+    rep = ftattn.Report(view, 1, heads)
+    assert rep.tile_flags.shape == (1, heads, tiles_m, tiles_n) and rep.tile_flags[0, -1, -1, -1] == 5 and rep.tile_flags[0, 0, 0, 0] == 0
+    assert rep.rowtile_flags[0, -1, -1] == 7 and rep.residual_max[0, -1, -1, 3] == 0.5 and rep.events["row"].tolist() == [0, 9]
+    flags[0] = 1                          # the report is a copy, and the caller's to change
+    rep.tile_flags[0, 0, 0, 1] = 2
+    assert rep.tile_flags[0, 0, 0, 0] == 0 and flags[1] == 0
+
+
 def test_decoupled_create_rejects_bad_configs_without_a_device():
     lib = ftdecoupled.load_library()
     assert C.sizeof(ftdecoupled.Config) == 13 * 4 and C.sizeof(ftdecoupled.Fault) == 24 == C.sizeof(ftdecoupled.Event)
