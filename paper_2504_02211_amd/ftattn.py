@@ -125,7 +125,7 @@ class Report:
         self.n_events_dropped = view.n_events_dropped
         self.tiles_m, self.tiles_n = view.tiles_m, view.tiles_n
         def array(at, dtype, *shape):       # (np.ctypeslib.as_array takes ten times as long, string_at a size of at most 2^31 - 1)
-            return np.frombuffer(_memory(at, math.prod(shape) * dtype.itemsize, _READ), dtype=dtype).reshape(shape).copy()
+            return np.ndarray(shape, dtype, _memory(at, math.prod(shape) * dtype.itemsize, _READ)).copy()
         self.events = array(view.events, EVENT_DTYPE, n) if n else np.zeros(0, dtype=EVENT_DTYPE)
         self.tile_flags = array(view.tile_flags, _U8, batch, heads, view.tiles_m, view.tiles_n)
         self.rowtile_flags = array(view.rowtile_flags, _U8, batch, heads, view.tiles_m)
