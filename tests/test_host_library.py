@@ -178,6 +178,17 @@ def test_binding_checks_tensors_before_passing_raw_pointers():
         ftattn.device_pointer(object(), "q", 64, ftattn.F16, 0)
 
 
+def test_quick_check_of_a_tensor_refuses_as_the_general_one():
+    torch = pytest.importorskip("torch")
+    ftattn.load_library()
+    for bad, error in ((torch.zeros(64, dtype=torch.float16), ValueError), ([1], TypeError)):      # (not on a GPU; not a tensor)
+        for dtype in (ftattn.F16, 7):
+            for check in (ftattn.device_pointer, ftattn.address):
+                with pytest.raises(error):
+                    check(bad, "q", 64, dtype, 0)
+    assert ftattn.address(4096, "q", 64, 7, 0) == ftattn.device_pointer(4096, "q", 64, 7, 0).value == 4096
+
+
 @pytest.mark.parametrize("change", [dict(softmax_scale=1e39), dict(batch=2 ** 32 + 1), dict(heads=-2 ** 31 - 1), dict(in_dtype=2 ** 33)])
 def test_static_call_takes_values_as_the_fields_of_its_structure_do(change):
     """Numbers beyond the range of a field wrap or become infinite and are the library's to refuse, as in ftattn_create."""
