@@ -241,6 +241,17 @@ static int resolve_config(const ftattn_config* cfg, ftattn_config& e, Geometry& 
   return FTATTN_OK;
 }
 
+// For the tests, and no part of the interface: how a call without a fault list is split.  out: number of the first row
+// tile that is split (all row tiles: none is), key tiles of a share at most, shares, bytes of their state.
+extern "C" int ftattn_split_of(const ftattn_config* cfg, int64_t out[4]) {
+  ftattn_config e;
+  Geometry g;
+  const char* why;
+  if (int rc = resolve_config(cfg, e, g, why)) return rc;
+  out[0] = g.first_split; out[1] = g.piece; out[2] = g.shares; out[3] = (int64_t)(g.n_ws * sizeof(float));
+  return FTATTN_OK;
+}
+
 // Lets the kernels that a configuration runs, with a fault list or without one, use their dynamic LDS.  Needs the
 // device current.  (Only those: a call to the runtime for each takes about 10 us of the 110 to 300 that creating a
 // context takes.)

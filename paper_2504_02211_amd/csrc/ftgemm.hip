@@ -188,6 +188,13 @@ hipError_t gemm_fetch_events(const GSlot* slots, int n_slots, const ftgemm_event
 
 }  // namespace ftgemm
 
+// For the tests, and no part of the interface: the tile shape (TileId) and the number of shares of K that a call without a
+// fault list runs with.  m, n: tokens and features, exchanged by the caller where the checksums fold tokens.
+extern "C" void ftgemm_plan_of(int64_t m, int64_t n, int64_t k, int32_t batch, int32_t out[2]) {
+  const GPlan plan = gemm_plan(m, n, k, batch, false, batch == 1);
+  out[0] = plan.tile; out[1] = plan.parts;
+}
+
 extern "C" int ftgemm_create(const ftgemm_config* cfg, ftgemm_ctx** out) {
   if (!cfg || !out) return gfail(nullptr, FTGEMM_EINVAL, "null argument");
   *out = nullptr;

@@ -3,7 +3,7 @@ remainders in tokens, features and K.  Verification is exercised without the inj
 one weight row is changed after its checksums were taken, which shifts one output of every token by a
 known amount; every token must be reported at that column and restored from the checksum of the
 unchanged weights.  Reference: the product in fp64 on the device.  Tolerance as in test_gpu_gemm.py:
-fp32 accumulation over k <= 4096 terms of outputs of order one, 1e-4; a value restored from bf16 words
+fp32 accumulation over k <= 6136 terms of outputs of order one, 1e-4; a value restored from bf16 words
 (16 bits) 4e-3."""
 import numpy as np
 import pytest
@@ -14,12 +14,17 @@ from paper_2504_02211_amd import ftgemm
 
 pytestmark = pytest.mark.gpu
 
-SHAPES = [(1, 70, 72), (130, 33, 200),              # all features in one narrow tile
-          (37, 1000, 1024), (40, 601, 2056),        # 32-token tiles, K split over workgroups
-          (700, 1000, 1024), (31, 300, 64),         # 32-token tiles
-          (2049, 1030, 72), (2000, 1999, 512),      # 64-token tiles
-          (1000, 8000, 136),                        # 128-token tiles
-          (4097, 2050, 264), (3000, 3000, 72)]      # 256-token tiles
+# (m, n, k): tile shape and shares of K with the checksums over the features, and over the tokens (the same kernel with m
+# and n exchanged); test_launch_plans.py holds the plan to it.  Matrices of 128 features or fewer are in
+# test_gpu_gemm_narrow.py, those here are too small for their tiles.
+PLANS = {(1, 70, 72): (("strip", 1), ("strip", 1)), (130, 33, 200): (("strip", 1), ("strip", 1)),
+         (37, 1000, 1024): (("strip", 1), ("slim2", 1)), (40, 601, 2056): (("strip", 16), ("strip", 8)),
+         (700, 1000, 1024): (("strip", 1), ("strip", 1)), (31, 300, 64): (("strip", 1), ("strip", 1)),
+         (2049, 1030, 72): (("quarter", 1), ("quarter", 1)), (2000, 1999, 512): (("quarter", 1), ("quarter", 1)),
+         (1000, 8000, 136): (("half", 1), ("half", 1)),
+         (4097, 2050, 264): (("wide", 1), ("wide", 1)), (3000, 3000, 72): (("wide", 1), ("wide", 1)),
+         (701, 1499, 4040): (("quarter", 2), ("strip", 1)), (5001, 299, 6136): (("half", 2), ("quarter", 2))}
+SHAPES = list(PLANS)
 
 
 @pytest.mark.parametrize("m,n,k", SHAPES)

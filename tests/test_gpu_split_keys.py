@@ -10,10 +10,13 @@ from paper_2504_02211_amd import ftattn
 
 pytestmark = pytest.mark.gpu
 
-# one row tile, row tiles of one share beside others of many (causal), a ragged last row tile and key tile, sixteen
-# shares, the row tiles left over by whole rounds of 256, heads that the 8 XCDs do not divide
-SHAPES = [(1, 1, 1024, 128, False), (1, 1, 8200, 128, True), (2, 3, 733, 128, True), (1, 5, 3001, 64, True), (1, 1, 2047, 64, False),
-          (1, 2, 6000, 64, True), (3, 16, 1531, 128, False), (1, 20, 2048, 128, True), (1, 129, 600, 128, False), (2, 7, 1100, 64, False)]
+# shape: (row tiles that are not split, shares of the longest row tile that is); test_launch_plans.py holds the plan to it.
+# Row tiles of one share beside others of many (causal), a ragged last row tile and key tile, sixteen shares, the row tiles
+# left over by one and by three whole rounds of 256 at both head sizes, heads that the 8 XCDs do not divide
+PLANS = {(1, 1, 1024, 128, False): (0, 4), (1, 1, 8200, 128, True): (0, 10), (2, 3, 733, 128, True): (0, 3), (1, 5, 3001, 64, True): (0, 3),
+         (1, 1, 2047, 64, False): (0, 4), (1, 2, 6000, 64, True): (0, 4), (3, 16, 1531, 128, False): (256, 3), (1, 20, 2048, 128, True): (0, 2),
+         (1, 22, 8900, 128, False): (768, 16), (3, 5, 2244, 64, False): (256, 6)}
+SHAPES = list(PLANS)
 
 
 def reference(q, k, v, causal):
@@ -108,10 +111,12 @@ def test_faults_in_a_call_that_would_be_split():
     ctx.close()
 
 
-MASKED = {"end": (0.5, 1.0), "middle": (0.25, 0.75), "first": (0.0, 0.5)}      # whole shares at -inf (four shares or more a row)
+# whole shares at -inf: the longest row tiles have four or more
+MASKED = {"end": (0.5, 1.0), "middle": (0.25, 0.75), "first": (0.0, 0.5)}
+MASKED_PLANS = {(1, 1, 8192, 128, False): (0, 8), (1, 1, 8200, 128, True): (0, 10), (1, 2, 6000, 64, True): (0, 4), (1, 1, 6001, 64, False): (0, 5)}
 
 
-@pytest.mark.parametrize("batch,heads,seq,head_dim,causal", [(1, 1, 8192, 128, False), (1, 1, 8200, 128, True), (1, 2, 6000, 64, True), (1, 1, 6001, 64, False)])
+@pytest.mark.parametrize("batch,heads,seq,head_dim,causal", MASKED_PLANS)
 @pytest.mark.parametrize("mode", [ftattn.FT_OFF, ftattn.FT_DETECT])
 @pytest.mark.parametrize("masked", MASKED)
 def test_shares_without_a_finite_score(batch, heads, seq, head_dim, causal, mode, masked):
