@@ -2,6 +2,7 @@
 against attention in fp64 on the device from the inputs as the kernel takes them.  Tolerance as in
 test_gpu_parity.py (fp16 weights): 2e-3 absolute, 1e-3 relative Frobenius; a 16-bit result adds half a unit of its last
 place (2^-11 / 2^-8 relative)."""
+import numpy as np
 import pytest
 
 torch = pytest.importorskip("torch")
@@ -94,7 +95,7 @@ def test_split_call_in_a_graph_and_from_static_scratch():
 
 def test_faults_in_a_call_that_would_be_split():
     """A call with a fault list runs unsplit on the same context: the fault is found and repaired, and the result is that of
-    the split call to within the two tolerances."""
+    the split call to within the two tolerances, the row with the fault by itself as well."""
     shape = (1, 1, 4096, 128)
     g = torch.Generator(device="cuda")
     g.manual_seed(9)
@@ -106,9 +107,81 @@ def test_faults_in_a_call_that_would_be_split():
     ctx.forward(q, k, v, b, [[0, 0, 0, 7, 3000, 450, 27]], st)
     rep = ctx.report()
     assert [(e[2], e[3], e[4], e[5]) for e in sorted(rep.event_set())] == [(0, 7, 3000, 450)]
+    for rows in (slice(None), slice(3000, 3001)):
+        diff = (b - a)[0, 0, rows].double()
+        assert float(diff.abs().max()) <= 4e-3 and float(diff.norm() / a[0, 0, rows].double().norm()) <= 2e-3
     ctx.forward(q, k, v, b, None, st)
     assert ctx.report().n_events == 0 and torch.equal(a, b)
     ctx.close()
+
+
+FIRING = [(1, 1, 1024, 128, False), (2, 3, 733, 128, True), (1, 5, 3001, 64, True), (1, 1, 2047, 64, False)]
+
+
+@pytest.mark.parametrize("batch,heads,seq,head_dim,causal", FIRING)
+@pytest.mark.parametrize("fold", [False, True])
+def test_checks_of_shares_and_of_their_sums_fire(batch, heads, seq, head_dim, causal, fold):
+    """With thresholds far below rounding nearly every check fires, in every share and on the sums.  Detected only, values
+    stay as they are, bit for bit, and the events name rows, key tiles and columns of the whole row; corrected, an element
+    moves by its rounding residual, which is far below the tolerance, where one written to another place would not be."""
+    print(f"[split keys, events] {batch} x {heads} x {seq} x {head_dim} causal {causal} fold {fold}", flush=True)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seq + head_dim)
+    shape = (batch, heads, seq, head_dim)
+    q, k, v = (torch.randn(shape, generator=g, device="cuda").half() for _ in range(3))
+    st = torch.cuda.current_stream().cuda_stream
+
+    def run(mode, **thresholds):
+        o = torch.full(shape, float("nan"), dtype=torch.float32, device="cuda")
+        ctx = ftattn.FtAttn(*shape, 0, causal, ft_mode=mode, rowsum_fold=fold, max_events=1 << 23, **thresholds)
+        ctx.forward(q, k, v, o, None, st)
+        rep = ctx.report()
+        ctx.close()
+        assert rep.n_events_dropped == 0
+        return o, rep
+
+    clean, rep = run(ftattn.FT_DETECT)
+    assert rep.n_events == 0
+    detected, rep = run(ftattn.FT_DETECT, eps1=1e-30, tau_o=1e-30)
+    assert torch.equal(detected, clean)
+    ev = rep.events
+    assert (ev["action"] == 0).all() and ((ev["row"] >= 0) & (ev["row"] < seq)).all()
+    head = ev["b"].astype(np.int64) * heads + ev["h"]
+    assert ((head >= 0) & (head < batch * heads)).all()
+    n_tiles, n_blocks = -(-seq // 64), -(-seq // 32)                     # a wave has 32 rows
+    # scores: one event per row, key tile and class at most, some in every key tile of every wave, columns of that key tile
+    s = ev["check"] == 0
+    tile, row, col = ev["kv_tile"][s].astype(np.int64), ev["row"][s].astype(np.int64), ev["col"][s].astype(np.int64)
+    assert ((tile >= 0) & (tile < n_tiles) & ((col == -1) | (col // 64 == tile))).all()
+    key = ((head[s] * seq + row) * n_tiles + tile) * 8 + col % 8
+    assert len(np.unique(key[col >= 0])) == int((col >= 0).sum())
+    seen = np.zeros((batch * heads, n_blocks, n_tiles), bool)
+    seen[head[s], row // 32, tile] = True
+    last = np.minimum(np.arange(n_blocks) * 32 + 31, seq - 1) // 64 if causal else np.full(n_blocks, n_tiles - 1)
+    assert (seen == (np.arange(n_tiles)[None, :] <= last[:, None])[None]).all()
+    # outputs, and with the fold row-sums (where the location rule names them: with rounding residuals in few rows or none),
+    # after the last share: no key tile, one event per row and class at most
+    o = ev["check"] == 3
+    assert (ev["kv_tile"][o] == -1).all() and ((ev["col"][o] >= -1) & (ev["col"][o] < head_dim)).all()
+    found = o & (ev["col"] >= 0)
+    key = (head[found] * seq + ev["row"][found]) * 8 + ev["col"][found] % 8
+    assert len(np.unique(key)) == len(key)
+    assert len(np.unique(head[o] * n_blocks + ev["row"][o] // 32)) == batch * heads * n_blocks
+    l = ev["check"] == 2
+    assert (ev["kv_tile"][l] == -1).all() and (ev["col"][l] == 0).all() and (fold or not l.any())
+    assert len(np.unique(head[l] * seq + ev["row"][l])) == int(l.sum()) and not (ev["check"] == 1).any()
+
+    corrected, rep = run(ftattn.FT_CORRECT, eps1=1e-30, tau_o=1e-30)
+    ev = rep.events
+    assert (ev["action"] == (ev["col"] >= 0)).all() and (ev["action"] == 1).any()
+    num = den = 0.0
+    for b, h, r0, want in reference(q, k, v, causal):
+        diff = corrected[b, h, r0:r0 + want.shape[0]].double() - want
+        assert bool((diff.abs() <= 2e-3).all())
+        num += float((diff ** 2).sum())
+        den += float((want ** 2).sum())
+    assert (num / den) ** 0.5 <= 1e-3
+    print(f"  events {rep.n_events}, corrected against clean {float((corrected - clean).abs().max()):.1e}", flush=True)
 
 
 # whole shares at -inf: the longest row tiles have four or more
