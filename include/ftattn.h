@@ -202,7 +202,8 @@ const char* ftattn_last_error(const ftattn_ctx* ctx);
  * one array of FTATTN_STATIC_SCRATCH_MIB MiB that is part of the library's device code and that
  * every GPU the library runs on holds until the process ends.  The call allocates and frees
  * nothing, on the host or on the device, and is two kernel launches on `hip_stream` (three where a call has
- * so few row tiles that their keys are split over several workgroups and the array has room for their state).
+ * so few row tiles that their keys are split over several workgroups and the array has room for their state;
+ * where it has none the call runs unsplit, and its result is that of ftattn_forward to within rounding instead of bit for bit).
  *   cfg           host pointer, as for ftattn_create (defaults resolved the same way; max_events is
  *                 capped at 4096).  A shape whose encoded tiles do not fit the array fails with
  *                 FTATTN_EUNSUPPORTED and a message that names both sizes; nothing is launched.

@@ -93,6 +93,28 @@ def test_split_call_in_a_graph_and_from_static_scratch():
     assert torch.equal(o, want)
 
 
+TOO_LARGE_FOR_STATIC_STATE = (1, 4, 16384, 128, True)       # 46 MB of encoded tiles and 87 MB of state; the array holds 67 MB
+
+
+def test_static_call_whose_state_does_not_fit_runs_unsplit():
+    """The tiles fit the library's array, the state of the shares does not: same result to within rounding, not bit for bit."""
+    *shape, causal = TOO_LARGE_FOR_STATIC_STATE
+    g = torch.Generator(device="cuda")
+    g.manual_seed(7)
+    q, k, v = (torch.randn(shape, generator=g, device="cuda").half() for _ in range(3))
+    o = torch.full(shape, float("nan"), dtype=torch.float32, device="cuda")
+    nev = torch.full((1,), -7, dtype=torch.int32, device="cuda")
+    ftattn.forward_static(q, k, v, o, *shape, 0, causal, n_events=nev, stream=torch.cuda.current_stream().cuda_stream)
+    assert int(nev.item()) == 0
+    num = den = 0.0
+    for b, h, r0, want in reference(q, k, v, causal):
+        diff = o[b, h, r0:r0 + want.shape[0]].double() - want
+        assert bool((diff.abs() <= 2e-3).all())
+        num += float((diff ** 2).sum())
+        den += float((want ** 2).sum())
+    assert (num / den) ** 0.5 <= 1e-3
+
+
 def test_faults_in_a_call_that_would_be_split():
     """A call with a fault list runs unsplit on the same context: the fault is found and repaired, and the result is that of
     the split call to within the two tolerances, the row with the fault by itself as well."""

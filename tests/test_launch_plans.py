@@ -15,14 +15,14 @@ TILES = ["wide", "half", "quarter", "strip", "narrow", "slim", "narrow2", "slim2
 
 
 def split_of(batch, heads, seq, head_dim, causal, **options):
-    """(row tiles that are not split, shares of the longest row tile that is, or 1, key tiles of a share at most)"""
+    """(row tiles that are not split, shares of the longest row tile that is, or 1, key tiles of a share at most, bytes of state)"""
     lib = ftattn.load_library()
     cfg = ftattn.Config(struct_size=C.sizeof(ftattn.Config), batch=batch, heads=heads, seq=seq, head_dim=head_dim, in_dtype=0, out_dtype=2,
                         causal=int(causal), ft_mode=ftattn.FT_CORRECT, **options)
     out = (C.c_int64 * 4)()
     assert lib.ftattn_split_of(C.byref(cfg), out) == 0
     first, piece, shares, state = out
-    return first, (-(-(-(-seq // 64)) // piece) if shares else 1), piece
+    return first, (-(-(-(-seq // 64)) // piece) if shares else 1), piece, state
 
 
 def gemm_plan_of(m, n, k, batch=1):
@@ -40,6 +40,13 @@ def test_keys_are_divided_as_the_tests_of_it_say():
             n, piece = -(-shape[2] // 64), split_of(*shape)[2]
             firsts = [n * p // parts for p in range(parts + 1)]
             assert any(lo * n <= a and b <= hi * n for a, b in zip(firsts, firsts[1:])) and max(b - a for a, b in zip(firsts, firsts[1:])) <= piece
+
+
+def test_static_call_whose_state_does_not_fit():
+    batch, heads, seq, head_dim, causal = shape = split_keys.TOO_LARGE_FOR_STATIC_STATE
+    *_, parts, _, state = split_of(*shape)
+    tiles_bytes = batch * heads * (seq // 64) * ((64 + 32) * head_dim + (head_dim + 32) * 64) * 2
+    assert parts > 1 and tiles_bytes < 60 << 20 and state > 64 << 20
 
 
 @pytest.mark.parametrize("options", [dict(per_step=1), dict(stride=1), dict(rescale_margin=4.0)])

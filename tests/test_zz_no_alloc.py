@@ -1,6 +1,6 @@
 """The entry point that allocates nothing (ftattn_forward_static) against ftattn_forward: same
 kernels on the library's static scratch array instead of a context's buffers, so the outputs must
-be identical bit for bit.  Two calls in a row on one stream, the second with a smaller input (the
+be identical bit for bit (unless the state of divided keys does not fit the array: test_gpu_split_keys.py).  Two calls in a row on one stream, the second with a smaller input (the
 array keeps the first call's contents), then a shape that does not fit the array."""
 import numpy as np
 import pytest
