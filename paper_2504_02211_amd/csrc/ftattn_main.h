@@ -689,19 +689,16 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : FT ? 2 : 3
 #pragma unroll
   for (int fb = 0; fb < NFB; ++fb) o[fb] = (float16v)0.f;
   oc = (float16v)0.f;
-  float m_run = -__builtin_inff(), l_part = 0.f, l_low = 0.f, dev_max = 0.f;
+  // A share may begin with key tiles that hold only -inf for a row whose other shares hold finite scores (a pass over all keys
+  // has met those by then): it starts from a maximum below every finite score (at most 128 * 65504^2 in magnitude), so
+  // that these keys weigh 0, where -inf - -inf would make the row NaN.
+  float m_run = SPLIT ? -1e20f : -__builtin_inff(), l_part = 0.f, l_low = 0.f, dev_max = 0.f;
   float m_true = -__builtin_inff();       // (LAZY) the running maximum; m_run is then the reference
   // the maximum to subtract after a key tile whose maximum is mxv (Algorithm 1: m_ij = max(m_i,j-1, rowmax))
   auto renewed = [&](const float mxv) __attribute__((always_inline)) -> float {
     if (!LAZY) return fmax2(m_run, mxv);
     const float mt = fmax2(m_true, mxv);
     return (mt - m_run) * a.scale > a.rescale_margin ? mt : m_run;      // (a reference of -inf is always renewed)
-  };
-  // What is subtracted from the scores and from the old maximum.  A share may begin with key tiles that hold only -inf
-  // for a row whose other shares hold finite scores (a pass over all keys has met those by then): until a finite one
-  // comes, 0 takes the place of the maximum, so that these keys weigh 0 (-inf - -inf would make the row NaN).
-  auto subtracted = [&](const float m) __attribute__((always_inline)) -> float {
-    return SPLIT && m == -__builtin_inff() ? 0.f : m;
   };
   unsigned rechecks = 0;
 
@@ -845,7 +842,7 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : FT ? 2 : 3
         }
         mx = max32(fmax2(m0, m1));
         m_new = renewed(mx);
-        negm = -subtracted(m_new) * sl2;
+        negm = -m_new * sl2;
         // all 32 arguments first, then all 32 exponentials, in place: neighbouring instructions are
         // independent, where (argument, exponential) pairs through one temporary would each wait
         // for the other
@@ -871,7 +868,7 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : FT ? 2 : 3
           }
         mx = max32(mx);
         m_new = renewed(mx);
-        negm = -subtracted(m_new) * sl2;
+        negm = -m_new * sl2;
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
@@ -926,7 +923,7 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : FT ? 2 : 3
               mc = max32(mc);
               if (as_u(mc) == as_u(mxb)) mx = mxb;          // two of three agree on the duplicate
               m_new = renewed(mx);
-              negm = -subtracted(m_new) * sl2;
+              negm = -m_new * sl2;
               bad = true;                                    // every exponential is looked at again below
             }
             uint32_t diff = 0u;
@@ -1199,7 +1196,7 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : FT ? 2 : 3
             if (redo) {
               mx = mx2;
               m_new = renewed(mx);
-              negm = -subtracted(m_new) * sl2;
+              negm = -m_new * sl2;
             }
 #pragma unroll
             for (int kb = 0; kb < 2; ++kb)
@@ -1220,7 +1217,7 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : FT ? 2 : 3
       // e^{m_old - m_new}, formed from the difference so that an unchanged maximum gives exactly one (the
       // product m_old * sl2 against the rounded m_new * sl2 would leave a rounding residue, and with it a
       // rescale of the whole output by 1 + 2^-23)
-      al = ex2((m_run - subtracted(m_new)) * sl2);
+      al = ex2((m_run - m_new) * sl2);
       if (FT) l_low = l_low * al + ex2(__builtin_fmaf(mx, sl2, negm));
       m_run = m_new;
       convert_quarter(0);
