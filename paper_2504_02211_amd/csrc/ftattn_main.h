@@ -464,6 +464,10 @@ __device__ __forceinline__ void store_part(const KArgs& a, const float16v (&o)[D
 // last key tile.  A workgroup per 32 rows; wave w adds up feature block w, the first wave the checksums as well, and
 // finishes.  Bound: the latency of reading one share after the other, so all maxima are requested at once and a share
 // ahead of the one being added (12 row tiles of two shares took 20 us with a wave per 32 rows that read value by value).
+// The maximum of a share is not checked: it scales row-sum, bound, output and checksums of its share alike, as a wrong
+// running maximum does in the register of an unsplit pass.  Between the two launches it stands in memory, which the fault
+// model leaves to ECC; every wave reads it and forms the factor by itself, so that an error in either by one wave shows
+// in the sum-form check.
 constexpr int MAX_PARTS = 16;
 template <int D, bool FT, bool CAUSAL>
 __global__ __launch_bounds__(D * 2) void ftattn_finish(const KArgs a) {
