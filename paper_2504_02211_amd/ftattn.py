@@ -194,7 +194,7 @@ def forward_static(q, k, v, o, batch: int, heads: int, seq: int, head_dim: int, 
     ptr = lambda t, name, dt: None if t is None else address(t, name, n, dt, device)
     nev = None if n_events is None else n_events if isinstance(n_events, int) else n_events.data_ptr()
     rc = lib.ftattn_forward_static(C.byref(cfg), ptr(q, "q", in_dtype), ptr(k, "k", in_dtype), ptr(v, "v", in_dtype),
-                                   ptr(o, "o", out_dtype), nev, stream)
+                                   ptr(o, "o", out_dtype), nev, C.c_void_p(stream))
     if rc != OK:
         raise FtAttnError(rc, lib.ftattn_static_last_error().decode())
 
@@ -231,7 +231,7 @@ class FtAttn:
             n = fa.shape[0]
             fp = fa.ctypes.data_as(C.POINTER(Fault))
         rc = self.lib.ftattn_forward(self.handle, address(q, "q", ne, in_dtype, device), address(k, "k", ne, in_dtype, device),
-                                     address(v, "v", ne, in_dtype, device), address(o, "o", ne, out_dtype, device), fp, n, stream)
+                                     address(v, "v", ne, in_dtype, device), address(o, "o", ne, out_dtype, device), fp, n, C.c_void_p(stream))
         if rc != OK:
             raise FtAttnError(rc, self.lib.ftattn_last_error(self.handle).decode())
 

@@ -121,7 +121,7 @@ class FtDecoupled:
             n, fp = fa.shape[0], fa.ctypes.data_as(C.POINTER(Fault))
         ne, in_dtype, device = self._tensors
         self._check(self.lib.ftdec_forward(self.handle, address(q, "q", ne, in_dtype, device), address(k, "k", ne, in_dtype, device),
-                                           address(v, "v", ne, in_dtype, device), address(o, "o", ne, 2, device), fp, n, stream))
+                                           address(v, "v", ne, in_dtype, device), address(o, "o", ne, 2, device), fp, n, C.c_void_p(stream)))
 
     def report(self) -> Report:
         view = ReportView()

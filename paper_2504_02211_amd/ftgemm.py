@@ -120,7 +120,7 @@ class FtGemm:
             raise FtGemmError(rc, self.lib.ftgemm_last_error(self.handle).decode())
 
     def encode_weights(self, w, stream: int = 0) -> None:
-        self._check(self.lib.ftgemm_encode_weights(self.handle, _base.address(w, "w", *self._w), stream))
+        self._check(self.lib.ftgemm_encode_weights(self.handle, _base.address(w, "w", *self._w), C.c_void_p(stream)))
 
     def forward(self, x, w, y, faults: Optional[np.ndarray] = None, stream: int = 0) -> None:
         """x, w, y: objects with data_ptr() (torch device tensors) or integer device addresses.
@@ -132,7 +132,7 @@ class FtGemm:
             n = fa.shape[0]
             fp = fa.ctypes.data_as(C.POINTER(Fault))
         self._check(self.lib.ftgemm_forward(self.handle, _base.address(x, "x", *self._x), _base.address(w, "w", *self._w),
-                                            _base.address(y, "y", *self._y), fp, n, stream))
+                                            _base.address(y, "y", *self._y), fp, n, C.c_void_p(stream)))
 
     def report(self) -> Report:
         view = ReportView()

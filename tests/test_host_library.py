@@ -189,6 +189,16 @@ def test_quick_check_of_a_tensor_refuses_as_the_general_one():
     assert ftattn.address(4096, "q", 64, 7, 0) == ftattn.device_pointer(4096, "q", 64, 7, 0).value == 4096
 
 
+def test_stream_is_an_integer_address():
+    """Text and bytes are refused: ctypes would pass the address of their characters as the stream."""
+    for stream in (b"stream", "stream", 1.5):
+        with pytest.raises(TypeError):
+            ftattn.forward_static(0, 0, 0, 0, 1, 1, 64, 64, ftattn.F16, False, stream=stream)
+    for stream in (0, None):
+        with pytest.raises(ftattn.FtAttnError, match="null tensor pointer"):
+            ftattn.forward_static(0, 0, 0, 0, 1, 1, 64, 64, ftattn.F16, False, stream=stream)
+
+
 @pytest.mark.parametrize("change", [dict(softmax_scale=1e39), dict(batch=2 ** 32 + 1), dict(heads=-2 ** 31 - 1), dict(in_dtype=2 ** 33)])
 def test_static_call_takes_values_as_the_fields_of_its_structure_do(change):
     """Numbers beyond the range of a field wrap or become infinite and are the library's to refuse, as in ftattn_create."""
