@@ -24,9 +24,13 @@ def _capture(forward):
     return g
 
 
-@pytest.mark.parametrize("m,n,k", [(37, 1000, 1024),       # split K: 12 report slots, 4 with a fault list
-                                   (700, 1000, 1024),      # 32-token tiles against 64-token ones
-                                   (4097, 2050, 264)])     # 256-token tiles: 153 against 585
+# (m, n, k): tile shape and shares of K without a fault list, report slots without one and with one; test_launch_plans.py
+# holds the plan to it
+PLANS = {(37, 1000, 1024): ("strip", 1, 8, 4), (700, 1000, 1024): ("strip", 1, 88, 44),      # 32-token tiles against 64-token ones
+         (40, 601, 2056): ("strip", 16, 9, 3), (4097, 2050, 264): ("wide", 1, 153, 585)}     # K split; 256-token tiles
+
+
+@pytest.mark.parametrize("m,n,k", PLANS)
 def test_linear(m, n, k):
     print(f"[report after replay] linear {m} x {n} x {k}", flush=True)
     g = torch.Generator(device="cuda")

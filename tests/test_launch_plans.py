@@ -9,6 +9,7 @@ pytest.importorskip("torch")
 from paper_2504_02211_amd import ftattn
 import test_gpu_gemm_narrow as narrow
 import test_gpu_gemm_tiles as tiles
+import test_gpu_report_after_replay as replay
 import test_gpu_split_keys as split_keys
 
 TILES = ["wide", "half", "quarter", "strip", "narrow", "slim", "narrow2", "slim2"]
@@ -59,3 +60,11 @@ def test_tile_shapes_of_the_linear_layer_are_what_the_tests_of_them_say():
     assert {s: gemm_plan_of(*s) for s in narrow.PLANS} == narrow.PLANS
     seen = [plan for pair in tiles.PLANS.values() for plan in pair] + list(narrow.PLANS.values())
     assert {tile for tile, _ in seen} == set(TILES) and {parts for _, parts in seen} == {1, 2, 4, 8, 16}
+
+
+def test_calls_before_a_replay_have_another_number_of_slots():
+    rows = {"wide": 256, "half": 128, "quarter": 64, "strip": 32}
+    for (m, n, k), (tile, parts, slots, slots_with_faults) in replay.PLANS.items():
+        assert gemm_plan_of(m, n, k) == (tile, parts)
+        features = -(-n // 256)
+        assert slots == -(-m // (16 if parts > 1 else rows[tile])) * features != slots_with_faults == -(-m // rows["quarter"]) * features
