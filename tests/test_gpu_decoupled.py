@@ -179,6 +179,33 @@ def test_timing_counts_the_transpose_with_the_second_product():
     assert second > first > 0
 
 
+@pytest.mark.parametrize("shape,dtype,causal", [((2, 3, 333, 128), synth.BF16, True), ((1, 2, 700, 72), synth.F16, False)])
+def test_a_timed_pass_gives_what_others_give(shape, dtype, causal):
+    """Timing takes other launches for V^T and the checksum rows: same output without faults, bit for bit, and the same
+    faults found; what is restored differs by the rounding of the checksum words (2^-22 of a sum of 32 in fp16, 2^-16 in bf16)."""
+    print(f"[decoupled timed] {shape} dtype {dtype} causal {causal}", flush=True)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(shape[2])
+    tt = torch.float16 if dtype == synth.F16 else torch.bfloat16
+    q, k, v = (torch.randn(shape, generator=g, device="cuda").to(tt) for _ in range(3))
+    n, d = shape[2], shape[3]
+    faults = np.array([(0, 0, dorc.ST_GEMM1, n - 1, 5, 30), (0, 1, dorc.ST_EXP, n // 2, 9, 31), (0, 1, dorc.ST_GEMM2, n - 2, d - 1, 30)], np.int32)
+    ctx = ftdecoupled.FtDecoupled(*shape, dtype, causal)
+    stream = torch.cuda.current_stream().cuda_stream
+    for some in (None, faults):
+        outs, events = [], []
+        for timed in (False, True):
+            ctx.set_timing(timed)
+            outs.append(torch.full(shape, float("nan"), dtype=torch.float32, device="cuda"))
+            ctx.forward(q, k, v, outs[-1], some, stream)
+            events.append(ctx.report().event_set())
+        assert events[0] == events[1] and len(events[0]) == (0 if some is None else 3)
+        if some is None:
+            assert torch.equal(*outs)
+        assert float((outs[0] - outs[1]).abs().max()) <= (1e-4 if dtype == synth.F16 else 4e-3)
+    ctx.close()
+
+
 @pytest.mark.parametrize("max_events", [1, 3, 4])
 def test_event_logs_overflow(max_events):
     """Five faults per log (the products of two heads, the softmax of both) in logs of fewer entries: what is
