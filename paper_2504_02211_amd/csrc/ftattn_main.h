@@ -161,6 +161,7 @@ __device__ __forceinline__ void phase_barrier() {
 
 // Value that the compiler must take as new: a second evaluation built on it is not merged with the first.
 __device__ __forceinline__ float opaque(float x) { asm volatile("" : "+v"(x)); return x; }
+__device__ __forceinline__ int opaque(int x) { asm volatile("" : "+v"(x)); return x; }
 __device__ __forceinline__ half2v opaque(half2v x) { asm volatile("" : "+v"(x)); return x; }
 
 // Sum-form check of the output accumulator against its checksums (Algorithm 1, last "if"; text
@@ -598,6 +599,7 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : FT ? 2 : 3
     nj_w = nj_w < nj ? nj_w : nj;
   }
   const int row = row0_w + lq;
+  const int row_end = (CAUSAL && row + 1 < N ? row + 1 : N) - 4 * hi;      // (see `valid`)
   const float sl2 = a.scale_log2;
 
   const _Float16* kc_head = a.kc + ((size_t)bh * a.Tj + j0) * KT_ELEMS;
@@ -818,6 +820,12 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : FT ? 2 : 3
     // =========================================================== softmax phase
     if (on) {
       const bool g_mask = (CAUSAL && k0 + BN - 1 > row0_w) || (k0 + BN > N);
+      // keys of this tile that the row attends to, less what the lane half shifts its keys by: one comparison with a
+      // constant tells whether a score is masked.  (With the key of every score compared with the row and the end of the
+      // sequence, for the maximum, the exponentials and the filter each, 8 x 32 x 512 x 128 causal took 102.6 us and takes
+      // 99.4, 2 x 3 x 333 x 128 28.9 and 26.7, 16 x 12 x 512 x 64 42.1 and 40.1.)
+      int n_ok = row_end - k0;
+      auto valid = [&](const int kb, const int v) __attribute__((always_inline)) -> bool { return 32 * kb + 8 * (v >> 2) + (v & 3) < n_ok; };
 
       // ---- injection point: raw scores
       if (tile_has_fault) {
@@ -860,27 +868,24 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : FT ? 2 : 3
 #pragma unroll
           for (int v = 0; v < 16; ++v) p[kb][v] = ex2(p[kb][v]);
       } else {
-        // ============ same with the causal / sequence-end mask applied per element
-        mx = -__builtin_inff();
+        // ============ same with the causal / sequence-end mask: a masked score counts as -inf, whose exponential is 0
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-          for (int v = 0; v < 16; ++v) {
-            int key = k0 + key_of(kb, v, hi);
-            bool ok = key < N && (!CAUSAL || key <= row);
-            mx = fmax2(mx, ok ? s[kb][v] : -__builtin_inff());
-          }
-        mx = max32(mx);
+          for (int v = 0; v < 16; ++v) p[kb][v] = valid(kb, v) ? s[kb][v] : -__builtin_inff();
+        float m0 = fmax2(p[0][0], p[0][1]), m1 = fmax2(p[1][0], p[1][1]);
+#pragma unroll
+        for (int v = 2; v < 16; v += 2) {
+          m0 = fmax2(fmax2(m0, p[0][v]), p[0][v + 1]);
+          m1 = fmax2(fmax2(m1, p[1][v]), p[1][v + 1]);
+        }
+        mx = max32(fmax2(m0, m1));
         m_new = renewed(mx);
         negm = -m_new * sl2;
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-          for (int v = 0; v < 16; ++v) {
-            int key = k0 + key_of(kb, v, hi);
-            bool ok = key < N && (!CAUSAL || key <= row);
-            p[kb][v] = ok ? ex2(__builtin_fmaf(s[kb][v], sl2, negm)) : 0.f;
-          }
+          for (int v = 0; v < 16; ++v) p[kb][v] = ex2(__builtin_fmaf(p[kb][v], sl2, negm));
       }
 
       // ---- injection point: exponentials
@@ -988,6 +993,7 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : FT ? 2 : 3
           // with it, 2047 keys 292 and 295, 16 x 12 x 512 x 64 54.2 and 55.4, 333 keys 41.1 and 40.7.)
           bool bad = false;
           uint32_t diff = 0u;
+          n_ok = opaque(n_ok);      // (the 32 comparisons are made again: kept, they would take 64 scalar registers)
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
             float sum1 = 0.f;
@@ -995,8 +1001,8 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : FT ? 2 : 3
             for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
               for (int gg = 0; gg < 4; ++gg) {
-                const int v = 4 * gg + r, key = k0 + key_of(kb, v, hi);
-                const bool ok = key < N && (!CAUSAL || key <= row);
+                const int v = 4 * gg + r;
+                const bool ok = valid(kb, v);
                 sum1 += s[kb][v];
                 const uint32_t pe = as_u(ex2(__builtin_fmaf(opaque(s[kb][v]), sl2, negm)));
                 diff |= ok ? pe ^ as_u(p[kb][v]) : 0u;
@@ -1009,6 +1015,7 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : FT ? 2 : 3
           // ============ exact re-evaluation (rare: a fast check tripped, or the filter of a masked tile did).
           // lambda = ln prod P - (sigma*check1_eff - n_valid*m) = sum_l (ln P_l - x_l) - sigma*R1.
           bool lin_fixed = false, logged = false;
+          n_ok = opaque(n_ok);
           if (EW) {
             // the whole tile row as one class (fold index = position of the key in the tile): every
             // sum is the lane's half plus its partner's, formed by all lanes alike (the exchanges
@@ -1025,8 +1032,8 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : FT ? 2 : 3
             for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
               for (int v = 0; v < 16; ++v) {
-                const int l = key_of(kb, v, hi), key = k0 + l;
-                const bool ok = key < N && (!CAUSAL || key <= row);
+                const int l = key_of(kb, v, hi);
+                const bool ok = valid(kb, v);
                 const float sv = s[kb][v];
                 sum1 += sv;
                 sum2 += (float)(l + 1) * sv;
@@ -1088,7 +1095,7 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : FT ? 2 : 3
 #pragma unroll
                   for (int v = 0; v < 16; ++v) {
                     const int key = k0 + key_of(kb, v, hi);
-                    const bool ok = key < N && (!CAUSAL || key <= row);
+                    const bool ok = valid(kb, v);
                     const float pe = ex2(__builtin_fmaf(s[kb][v], sl2, negm));
                     if (ok && as_u(pe) != as_u(p[kb][v])) {
                       log_event(a, bh, FTATTN_CHECK_EXP, j0 + i, row, key, lam, a.correct ? 1 : 0);
@@ -1108,8 +1115,8 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : FT ? 2 : 3
             for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
               for (int gg = 0; gg < 4; ++gg) {
-                int v = 4 * gg + r, key = k0 + key_of(kb, v, hi);
-                bool ok = key < N && (!CAUSAL || key <= row);
+                int v = 4 * gg + r;
+                bool ok = valid(kb, v);
                 float sv = s[kb][v];
                 sum1 += sv;
                 float t = __builtin_fmaf(sv, sl2, negm);
@@ -1170,7 +1177,7 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : FT ? 2 : 3
 #pragma unroll
                   for (int gg = 0; gg < 4; ++gg) {
                     int v = 4 * gg + r, key = k0 + key_of(kb, v, hi);
-                    bool ok = key < N && (!CAUSAL || key <= row);
+                    bool ok = valid(kb, v);
                     float pe = ex2(__builtin_fmaf(s[kb][v], sl2, negm));
                     if (ok && as_u(pe) != as_u(p[kb][v])) {
                       log_event(a, bh, FTATTN_CHECK_EXP, j0 + i, row, key, lam, a.correct ? 1 : 0);
@@ -1192,8 +1199,7 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : FT ? 2 : 3
             for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
               for (int v = 0; v < 16; ++v) {
-                int key = k0 + key_of(kb, v, hi);
-                bool ok = key < N && (!CAUSAL || key <= row);
+                bool ok = valid(kb, v);
                 mx2 = fmax2(mx2, ok ? s[kb][v] : -__builtin_inff());
               }
             mx2 = max32(mx2);
@@ -1206,8 +1212,7 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : FT ? 2 : 3
             for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
               for (int v = 0; v < 16; ++v) {
-                int key = k0 + key_of(kb, v, hi);
-                bool ok = key < N && (!CAUSAL || key <= row);
+                bool ok = valid(kb, v);
                 float pe = ok ? ex2(__builtin_fmaf(s[kb][v], sl2, negm)) : 0.f;
                 if (redo) p[kb][v] = pe;
               }
