@@ -19,6 +19,7 @@ using namespace ftattn;
 struct Geometry {
   int BH = 0, Ti = 0, Tj = 0, BM = 0;
   size_t n_kc = 0, n_vt = 0;
+  size_t beyond = 0;      // bytes behind the encoded tiles that may be read (TILES_BEYOND)
   // Row tiles split by their keys (see share_of): those launched from number first_split on, in shares of up to `piece`
   // key tiles, `shares` in all; n_ws floats hold their state.
   int first_split = 0, piece = 1, shares = 0;
@@ -188,6 +189,8 @@ static void plan_split(const ftattn_config& e, Geometry& g) {
   }
 }
 
+constexpr size_t tiles_beyond(int D) { return (size_t)TILES_BEYOND * (BN + CKR) * D * 2; }      // (value tiles are no larger)
+
 // Checks cfg and resolves its defaults into e (tile sizes, thresholds, scale) and g.  Touches no
 // device.  On failure returns the error code and points `why` at a constant message.
 static int resolve_config(const ftattn_config* cfg, ftattn_config& e, Geometry& g, const char*& why) {
@@ -237,6 +240,7 @@ static int resolve_config(const ftattn_config* cfg, ftattn_config& e, Geometry& 
   g.Ti = (e.seq + g.BM - 1) / g.BM;
   g.n_kc = (size_t)g.BH * g.Tj * (BN + CKR) * e.head_dim;
   g.n_vt = (size_t)g.BH * g.Tj * (e.head_dim + CKR) * BN;
+  g.beyond = tiles_beyond(e.head_dim);
   plan_split(e, g);
   return FTATTN_OK;
 }
@@ -308,18 +312,18 @@ extern "C" int ftattn_create(const ftattn_config* cfg, ftattn_ctx** out) {
   auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
   auto together = [](size_t x, size_t y) { return x + y <= CHEAP || x > CHEAP || y > CHEAP; };
   const size_t kc_bytes = up(g.n_kc * 2), vt_bytes = up(g.n_vt * 2), ws_bytes = g.n_ws * sizeof(float);
-  const bool vt_joined = together(kc_bytes, vt_bytes);
+  const bool vt_joined = together(kc_bytes, vt_bytes + g.beyond);
   const size_t tiles_bytes = kc_bytes + (vt_joined ? vt_bytes : 0);
-  const bool ws_joined = ws_bytes && together(tiles_bytes, ws_bytes);
-  CREATE_TRY(hipMalloc((void**)&c->kc, tiles_bytes + (ws_joined ? ws_bytes : 0)));
+  const bool ws_joined = ws_bytes && together(tiles_bytes + g.beyond, ws_bytes);
+  CREATE_TRY(hipMalloc((void**)&c->kc, tiles_bytes + g.beyond + (ws_joined ? ws_bytes : 0)));
   if (vt_joined) {
     c->vt = c->kc + kc_bytes / 2;
   } else {
-    CREATE_TRY(hipMalloc(&c->vt_alloc, vt_bytes));
+    CREATE_TRY(hipMalloc(&c->vt_alloc, vt_bytes + g.beyond));
     c->vt = static_cast<_Float16*>(c->vt_alloc);
   }
   if (ws_joined) {
-    c->ws = reinterpret_cast<float*>(reinterpret_cast<char*>(c->kc) + tiles_bytes);
+    c->ws = reinterpret_cast<float*>(reinterpret_cast<char*>(c->kc) + tiles_bytes + g.beyond);
   } else if (ws_bytes) {
     CREATE_TRY(hipMalloc(&c->ws_alloc, ws_bytes));
     c->ws = static_cast<float*>(c->ws_alloc);
@@ -573,7 +577,8 @@ extern "C" const char* ftattn_last_error(const ftattn_ctx* c) {
 constexpr size_t STATIC_SCRATCH_BYTES = (size_t)FTATTN_STATIC_SCRATCH_MIB << 20;
 constexpr int STATIC_MAX_EVENTS = 4096;
 constexpr int STATIC_MAX_DEVICES = 64;
-static __device__ __align__(256) unsigned char scratch[STATIC_SCRATCH_BYTES];
+// (behind it what a workgroup may read past the last encoded tile)
+static __device__ __align__(256) unsigned char scratch[STATIC_SCRATCH_BYTES + tiles_beyond(128)];
 
 static std::mutex g_static_mu;
 static unsigned char* g_static_ptr[STATIC_MAX_DEVICES];      // per device, null until set up

@@ -33,12 +33,15 @@ namespace ftattn {
 
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef _Float16 half2v __attribute__((ext_vector_type(2)));
+typedef _Float16 half4v __attribute__((ext_vector_type(4)));
+typedef float float4a __attribute__((ext_vector_type(4)));
 typedef float float16v __attribute__((ext_vector_type(16)));
 typedef uint32_t uint4v __attribute__((ext_vector_type(4)));
 
 constexpr int BN = 64;        // keys per tile (B_c)
 constexpr int CKR = 32;       // checksum rows per tile: {c1 hi, c1 lo, c2 hi, c2 lo} x 8 classes
 constexpr int NFOLD_K = BN / 8;
+constexpr int TILES_BEYOND = 3;      // encoded tiles a workgroup may read past its last one, of either kind (never used)
 constexpr float LN2 = 0.6931471805599453f;
 
 struct DevFault { int32_t stage, kv_tile, row, col, bit; };
@@ -85,9 +88,12 @@ __device__ __forceinline__ float xchg32(float x, int hi) {
   auto r = __builtin_amdgcn_permlane32_swap(as_u(x), as_u(x), false, false);
   return as_f(hi ? r[0] : r[1]);
 }
+// (as an instruction: the compiler would first quieten both values, which come out of a maximum already)
 __device__ __forceinline__ float max32(float x) {
   auto r = __builtin_amdgcn_permlane32_swap(as_u(x), as_u(x), false, false);
-  return fmax2(as_f(r[0]), as_f(r[1]));
+  float m;
+  asm("v_max_f32 %0, %1, %2" : "=v"(m) : "v"(r[0]), "v"(r[1]));
+  return m;
 }
 __device__ __forceinline__ float sum32(float x) {
   auto r = __builtin_amdgcn_permlane32_swap(as_u(x), as_u(x), false, false);

@@ -123,19 +123,18 @@ template <int D, bool FT> struct Unit {
   static constexpr int VROWS = FT ? D + CKR : D;
   static constexpr int KBYTES = KROWS * D * 2;
   static constexpr int VBYTES = VROWS * BN * 2;
-  static constexpr int BYTES = KBYTES + VBYTES;
   static constexpr int K_INSTR = KBYTES / 1024;     // one instruction moves 64 lanes x 16 bytes
   static constexpr int V_INSTR = VBYTES / 1024;
   static constexpr int NWAVE = nwave_of(D), NSTAGE = nstage_of(D);
-  static constexpr int KPW = (K_INSTR + NWAVE - 1) / NWAVE;
+  static constexpr int KPW = K_INSTR / NWAVE;
   static constexpr int VPW = (V_INSTR + NWAVE - 1) / NWAVE;
-  // Every wave issues NLOAD instructions per unit; a wave that has no real piece left (uneven
-  // split, or no further unit to fetch) aims the instruction at a 1 KB dump area behind the ring,
-  // so that the counted waits below hold for every wave in every iteration.
+  // Every wave issues NLOAD instructions per unit.  A wave that has no piece left (uneven split) fetches its
+  // first one again, into a 1 KB dump area at the end of the stage, so that the counted waits below hold for every wave.
   static constexpr int NLOAD = KPW + VPW;
-  static constexpr int DUMP = 1024;
-  static constexpr int LDS_TOTAL = NSTAGE * BYTES + DUMP;
-  static_assert(K_INSTR >= NWAVE && V_INSTR >= NWAVE, "every wave owns at least one piece of each tile");
+  static constexpr int DUMP = V_INSTR % NWAVE ? 1024 : 0;
+  static constexpr int BYTES = KBYTES + VBYTES + DUMP;
+  static constexpr int LDS_TOTAL = NSTAGE * BYTES;
+  static_assert(K_INSTR % NWAVE == 0 && V_INSTR >= NWAVE, "every wave owns as many pieces of a key tile, and at least one of a value tile");
   static_assert((NSTAGE - 1) * NLOAD <= 15, "counted waits use a 4-bit immediate");
   static_assert(NWAVE == 8 || 2 * LDS_TOTAL <= 160 * 1024, "two workgroups per CU");
 };
@@ -163,6 +162,18 @@ __device__ __forceinline__ void phase_barrier() {
 __device__ __forceinline__ float opaque(float x) { asm volatile("" : "+v"(x)); return x; }
 __device__ __forceinline__ int opaque(int x) { asm volatile("" : "+v"(x)); return x; }
 __device__ __forceinline__ half2v opaque(half2v x) { asm volatile("" : "+v"(x)); return x; }
+
+// largest of 32 values, in two chains of three-input maxima
+template <class T> __device__ __forceinline__ float max_of(const T& x, const T& y) {
+  float a = fmax2(fmax2(x[0], x[1]), x[2]), b = fmax2(fmax2(y[0], y[1]), y[2]);
+#pragma unroll
+  for (int v = 3; v < 15; v += 2) {
+    a = fmax2(fmax2(a, x[v]), x[v + 1]);
+    b = fmax2(fmax2(b, y[v]), y[v + 1]);
+  }
+  a = fmax2(fmax2(a, x[15]), y[15]);
+  return fmax2(a, b);
+}
 
 // Sum-form check of the output accumulator against its checksums (Algorithm 1, last "if"; text
 // after eq. (16) for location and repair): class r of the lane, folds o[fb][4*gg + r].  `thr` is
@@ -620,38 +631,36 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : FT ? 2 : 3
   }
   constexpr int PIECE_STEP = NWAVE * 64 * 8;      // halfs between the sources of consecutive pieces of a wave
   static_assert((NWAVE * 64 / KCH) * D == PIECE_STEP && (NWAVE * 64 / 8) * BN == PIECE_STEP, "piece stride");
-  // unit u = { V_u^T, K_{u+1} } goes to stage (u+1) mod 3.  A unit is fetched in NLOAD pieces per
-  // wave; the pieces of one unit are spread over a matrix phase (see matrix_stream).
-  uint32_t ld_lds = 0;
+  // unit u = { V_u^T, K_{u+1} } goes to stage (u+1) mod NSTAGE.  A unit is fetched in NLOAD pieces per wave; the pieces
+  // of one unit are spread over a matrix phase (see matrix_stream).  Units are requested in their order, also
+  // the one or two after the last key tile: those land in a stage that nobody reads any more, and what they fetch from
+  // is the next tile in memory (the buffers end in TILES_BEYOND tiles nobody writes), so that neither addresses nor
+  // destinations have to be selected in the stream.
+  uint32_t ld_lds = smem_base + (uint32_t)wave * 1024u;
   const _Float16* ld_kt = kc_head;
   const _Float16* ld_vt = vt_head;
-  bool ld_real = false;
-  const uint32_t dump = smem_base + (uint32_t)NSTAGE * U::BYTES;
-  auto prepare_unit = [&](int u, bool real) __attribute__((always_inline)) {
-    const int st = (u + 1) % NSTAGE;
-    ld_lds = smem_base + (uint32_t)st * U::BYTES;
-    const int jk = u + 1 < nj ? u + 1 : nj - 1, jv = u > 0 ? (u < nj ? u : nj - 1) : 0;
-    ld_kt = kc_head + (size_t)jk * KT_ELEMS;
-    ld_vt = vt_head + (size_t)jv * VT_ELEMS;
-    ld_real = real;
-  };
+  constexpr bool UNEVEN = U::DUMP != 0;
+  const bool last_v = !UNEVEN || U::VPW * NWAVE <= U::V_INSTR + NWAVE - 1 - wave;      // this wave has a VPW-th piece of a value tile
+  const uint32_t last_v_lds = last_v ? (uint32_t)(U::KBYTES + (U::VPW - 1) * NWAVE * 1024) : (uint32_t)(U::KBYTES + U::VBYTES) - (uint32_t)wave * 1024u;
+  const int last_v_src = last_v ? (U::VPW - 1) * PIECE_STEP : 0;
   auto issue_piece = [&](int n) __attribute__((always_inline)) {
     if (n < U::KPW) {
-      const int ins = wave + NWAVE * n;
-      const bool have = (n + 1) * NWAVE <= U::K_INSTR || ins < U::K_INSTR;     // (a piece this wave does not have reads piece 0 again)
-      const bool ok = ld_real && have;
-      gload_lds16_off(ld_kt + (have ? n * PIECE_STEP : 0), koff0, ok ? ld_lds + (uint32_t)ins * 1024u : dump);
+      gload_lds16_off(ld_kt + n * PIECE_STEP, koff0, ld_lds + (uint32_t)(n * NWAVE * 1024));
     } else {
-      const int m = n - U::KPW, ins = wave + NWAVE * m;
-      const bool have = (m + 1) * NWAVE <= U::V_INSTR || ins < U::V_INSTR;
-      const bool ok = ld_real && have;
-      gload_lds16_off(ld_vt + (have ? m * PIECE_STEP : 0), voff0, ok ? ld_lds + (uint32_t)U::KBYTES + (uint32_t)ins * 1024u : dump);
+      const int m = n - U::KPW;
+      if (UNEVEN && m == U::VPW - 1) gload_lds16_off(ld_vt + last_v_src, voff0, ld_lds + last_v_lds);
+      else gload_lds16_off(ld_vt + m * PIECE_STEP, voff0, ld_lds + (uint32_t)(U::KBYTES + m * NWAVE * 1024));
     }
   };
-  auto issue_unit = [&](int u, bool real) __attribute__((always_inline)) {
-    prepare_unit(u, real);
+  auto next_unit = [&]() __attribute__((always_inline)) {
+    ld_kt += KT_ELEMS;
+    ld_vt += VT_ELEMS;
+    ld_lds = ld_lds == smem_base + (uint32_t)((NSTAGE - 1) * U::BYTES) + (uint32_t)wave * 1024u ? smem_base + (uint32_t)wave * 1024u : ld_lds + (uint32_t)U::BYTES;
+  };
+  auto issue_unit = [&]() __attribute__((always_inline)) {
 #pragma unroll
     for (int n = 0; n < U::NLOAD; ++n) issue_piece(n);
+    next_unit();
   };
 
   // faults of this workgroup
@@ -662,9 +671,10 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : FT ? 2 : 3
   // The first key tile alone, then the queries, and the other units only when both are there: loads are waited for
   // in their order, and GEMM I of the first tile needs nothing else.  (With the queries behind three units of
   // tiles a workgroup's start took 5.5-11 us at head_dim 128 and 3-5 us at head_dim 64, now 5-9 and 2.8-4.)
-  prepare_unit(-1, true);
 #pragma unroll
   for (int n = 0; n < U::KPW; ++n) issue_piece(n);
+  next_unit();
+  ld_vt = vt_head;          // (unit -1 has no value tile)
 
   // ---- Q_i^T as MFMA B operand: lane (query lq, half hi) holds Q[row][16*slab + 8*hi .. +7]
   // (bf16 queries are converted here: exact for magnitudes in the fp16 normal range)
@@ -682,13 +692,14 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : FT ? 2 : 3
     if (const uint32_t qbits = operands.bits()) atomicOr(a.range, qbits);
   }
   wait_vmcnt<0>();
-  issue_unit(0, true);
-  if (ALT) issue_unit(1, nj >= 2);
+  issue_unit();
+  if (ALT) issue_unit();
 
   float16v o[NFB], oc, s[2], sc;
   half8 ph[2][2];             // P^T in fp16, B operand of GEMM II: [key block][8-key half]
   float p[2][16];             // exp(S - m) of the key tile in flight, fp32
-  float ps[2][2];             // its row-sum, one partial per quarter
+  float ps[2][2];             // (duplication mode) its row-sum, one partial per quarter
+  float4a rs = (float4a)0.f;  // its row-sum (four times the same value)
   float ps2[2][2];            // (duplication mode) the second evaluation of the same
   float l2_part = 0.f, l_prev = 0.f;
   float al = 1.f;             // e^{m_old - m_new} of the key tile in flight
@@ -725,16 +736,27 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : FT ? 2 : 3
   // k-step, where the vector instructions run in the shadow of the wave's own MFMAs.
   auto convert_quarter = [&](const int t) __attribute__((always_inline)) {
     const int kb = t >> 1, n = t & 1;
-    ps[kb][n] = 0.f;
+    if (DMR) ps[kb][n] = 0.f;
 #pragma unroll
     for (int x = 0; x < 8; x += 2) {
       half2v pr2;
       pr2[0] = (_Float16)p[kb][8 * n + x]; pr2[1] = (_Float16)p[kb][8 * n + x + 1];
       ph[kb][n][x] = pr2[0]; ph[kb][n][x + 1] = pr2[1];
       const half2v ones = {(_Float16)1.f, (_Float16)1.f};
-      ps[kb][n] = __builtin_amdgcn_fdot2(pr2, ones, ps[kb][n], false);
+      if (DMR) ps[kb][n] = __builtin_amdgcn_fdot2(pr2, ones, ps[kb][n], false);
       if (DMR) ps2[kb][n] = __builtin_amdgcn_fdot2(opaque(pr2), ones, x == 0 ? 0.f : ps2[kb][n], false);
     }
+  };
+  // The row-sum of a quarter, on the matrix pipe: with ones as the A operand of the 4x4x4 product a lane's column is the sum of the
+  // lane's own four values.  (As 16 dot products of fp16 pairs, which wait for the other wave's matrix instructions: one takes 40 cycles
+  // while that wave keeps the pipe busy, a multiplication 9.  With that and the shorter requests of units
+  // 8 x 16 x 2048 x 64 takes 280 us instead of 290, 1 x 32 x 16384 x 128 causal 2907 instead of 2967, 4 x 16 x 3000 x 64
+  // without checks 124 instead of 128.)
+  auto rowsum_quarter = [&](const int t) __attribute__((always_inline)) {
+    const half8 h = ph[t >> 1][t & 1];
+    const half4v one = {(_Float16)1.f, (_Float16)1.f, (_Float16)1.f, (_Float16)1.f};
+    rs = __builtin_amdgcn_mfma_f32_4x4x4f16(one, __builtin_shufflevector(h, h, 0, 1, 2, 3), t == 0 ? (float4a)0.f : rs, 0, 0, 0);
+    rs = __builtin_amdgcn_mfma_f32_4x4x4f16(one, __builtin_shufflevector(h, h, 4, 5, 6, 7), rs, 0, 0, 0);
   };
   // reduce sum (Algorithm 1): one expression for every evaluation, so that they round alike
   auto rowsum_update = [&](float l_old, const float (&q4)[2][2]) __attribute__((always_inline)) -> float {
@@ -778,25 +800,28 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : FT ? 2 : 3
       if (LD && k % (NOPS / U::NLOAD) == 1 && k / (NOPS / U::NLOAD) < U::NLOAD) issue_piece(k / (NOPS / U::NLOAD));
       const half8 av = buf[k % RING];
       if (DO2 && k < 3 * NA2 && k % NA2 == 0) convert_quarter(k / NA2 + 1);     // one k-step ahead of its use
-      if (DO2 && k == 3 * NA2) {
+      if (DMR && DO2 && k == 3 * NA2) {
         l_part = rowsum_update(l_part, ps);
-        if (DMR) l2_part = rowsum_update(opaque(l2_part), ps2);
+        l2_part = rowsum_update(opaque(l2_part), ps2);
       }
       if (k < N2) {
         const int t = k / NA2, x = k % NA2;
         if (x < NFB) o[x] = __builtin_amdgcn_mfma_f32_32x32x16_f16(av, ph[t >> 1][t & 1], o[x], 0, 0, 0);
         else oc = __builtin_amdgcn_mfma_f32_32x32x16_f16(av, ph[t >> 1][t & 1], oc, 0, 0, 0);
+        if (!DMR && x == 0) rowsum_quarter(t);
       } else {
         const int kk = k - N2, sl = kk / NA1, y = kk % NA1;
         if (y < 2) s[y] = __builtin_amdgcn_mfma_f32_32x32x16_f16(av, qf[sl], s[y], 0, 0, 0);
         else sc = __builtin_amdgcn_mfma_f32_32x32x16_f16(av, qf[sl], sc, 0, 0, 0);
+        if (!DMR && DO2 && kk == 2) l_part = l_part * al + rs[0];      // reduce sum (Algorithm 1)
       }
     }
     // pin the order: RING-1 reads, then (MFMA, read) pairs, then the remaining MFMAs
     __builtin_amdgcn_sched_group_barrier(0x100, RING - 1, 0);
 #pragma unroll
     for (int k = 0; k + RING - 1 < NOPS; ++k) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      if (!DMR && k < N2 && k % NA2 == 0) __builtin_amdgcn_sched_group_barrier(0x008, 3, 0);
+      else __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
       __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
     }
     __builtin_amdgcn_sched_group_barrier(0x008, RING - 1, 0);
@@ -846,13 +871,7 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : FT ? 2 : 3
 
       if (!g_mask) {
         // ============ reduce max, exp (fast path: no masked entry in this tile)
-        float m0 = fmax2(s[0][0], s[0][1]), m1 = fmax2(s[1][0], s[1][1]);
-#pragma unroll
-        for (int v = 2; v < 16; v += 2) {
-          m0 = fmax2(fmax2(m0, s[0][v]), s[0][v + 1]);
-          m1 = fmax2(fmax2(m1, s[1][v]), s[1][v + 1]);
-        }
-        mx = max32(fmax2(m0, m1));
+        mx = max32(max_of(s[0], s[1]));
         m_new = renewed(mx);
         negm = -m_new * sl2;
         // all 32 arguments first, then all 32 exponentials, in place: neighbouring instructions are
@@ -873,13 +892,7 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : FT ? 2 : 3
         for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
           for (int v = 0; v < 16; ++v) p[kb][v] = valid(kb, v) ? s[kb][v] : -__builtin_inff();
-        float m0 = fmax2(p[0][0], p[0][1]), m1 = fmax2(p[1][0], p[1][1]);
-#pragma unroll
-        for (int v = 2; v < 16; v += 2) {
-          m0 = fmax2(fmax2(m0, p[0][v]), p[0][v + 1]);
-          m1 = fmax2(fmax2(m1, p[1][v]), p[1][v + 1]);
-        }
-        mx = max32(fmax2(m0, m1));
+        mx = max32(max_of(p[0], p[1]));
         m_new = renewed(mx);
         negm = -m_new * sl2;
 #pragma unroll
@@ -949,11 +962,7 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : FT ? 2 : 3
               float s2 = ex2(__builtin_fmaf(chk, c_chk, c_m));
               float pr = ((p[0][r] * p[0][4 + r]) * s2) * ((p[0][8 + r] * p[0][12 + r]) * s2);
               pr *= ((p[1][r] * p[1][4 + r]) * s2) * ((p[1][8 + r] * p[1][12 + r]) * s2);
-              if (EW) dv[r] = pr;
-              else {
-                dv[r] = pr - 1.0f;
-                bad |= !(__builtin_fabsf(dv[r]) <= a.tau_fast);
-              }
+              dv[r] = EW ? pr : pr - 1.0f;
             }
             if (STEP) {
               // strided ABFT of GEMM I alone (eq. (15)): same sum order as the exact evaluation below
@@ -971,15 +980,16 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : FT ? 2 : 3
             dv[0] = pl * xchg32(pl, hi) - 1.0f;
             bad = !(__builtin_fabsf(dv[0]) <= a.tau_fast);
           }
+          float dev = dev_max;           // the largest deviation that passed so far, and these (a NaN stays one)
+          if (!EW && !DMR) {
+            asm("v_maximum3_f32 %0, %0, |%1|, |%2|" : "+v"(dev) : "v"(dv[0]), "v"(dv[1]));
+            asm("v_maximum3_f32 %0, %0, |%1|, |%2|" : "+v"(dev) : "v"(dv[2]), "v"(dv[3]));
+            bad |= !(dev <= a.tau_fast);
+          }
           recheck = wave_any(bad);
           if (recheck) ++rechecks;
-          else if (EW) {
-            dev_max = fmax2(dev_max, __builtin_fabsf(dv[0]));
-          } else {
-            // largest deviation that passed (two three-input maxima; the values are finite here)
-            asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(dev_max) : "v"(dv[0]), "v"(dv[1]));
-            asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(dev_max) : "v"(dv[2]), "v"(dv[3]));
-          }
+          else if (EW) dev_max = fmax2(dev_max, __builtin_fabsf(dv[0]));
+          else if (!DMR) dev_max = dev;
         }
         else if (!INJ && (PS == 0 || LAZY) && (CAUSAL || D == 128)) {
           // ============ masked tile: is there anything for the exact re-evaluation below to report?  With
@@ -1246,7 +1256,6 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : FT ? 2 : 3
     phase_barrier();                              // ... everyone's pieces; and everyone is past the reads of the stage refilled next
 
     // =========================================================== matrix phase
-    prepare_unit(ALT ? i + 2 : i + 1, (ALT ? i + 2 : i + 1) < nj);
     __builtin_amdgcn_s_setprio(1);
     // (after a wave's last key tile GEMM I runs on a tile it does not need: same code, result unused)
     if (DMR) l_prev = l_part;
@@ -1255,6 +1264,7 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : FT ? 2 : 3
 #pragma unroll
       for (int n = 0; n < U::NLOAD; ++n) issue_piece(n);
     }
+    next_unit();
     __builtin_amdgcn_s_setprio(0);
 
     // ---- injection point: row-sum (right after the update of this iteration)
@@ -1337,6 +1347,7 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : FT ? 2 : 3
     }
   }
   if (ALT && grp == 0) phase_barrier();
+  wait_vmcnt<0>();          // (the units after the last key tile: LDS is given back at the end)
 
   const int lane_e = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));      // (not kept through the loop)
   if (!SPLIT || sh.nparts == 1)
