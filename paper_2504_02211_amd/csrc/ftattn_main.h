@@ -110,11 +110,11 @@ template <int D, bool CAUSAL, bool SPLIT> __device__ __forceinline__ Share share
 
 // Heads per group: the fewest whose row tiles fill the workgroup slots of an XCD (32 CUs) once.  Larger
 // groups would let fewer workgroups share the K / V of a head in the L2.  Never 0, and at most the heads of an XCD.
-inline int head_group(int D, bool ft, int BH, int Ti) {
-  const int slots = 32 * (D == 128 ? 1 : ft ? 2 : 3), h8 = BH >> 3;
-  const int g = (slots + Ti - 1) / Ti;
+inline int head_group_of(int slots, int BH, int Ti) {
+  const int h8 = BH >> 3, g = (slots + Ti - 1) / Ti;
   return g < h8 ? g : h8 > 0 ? h8 : 1;
 }
+inline int head_group(int D, bool ft, int BH, int Ti) { return head_group_of(32 * (D == 128 ? 1 : ft ? 2 : 3), BH, Ti); }
 
 typedef void (*kernel_fn)(const KArgs);
 

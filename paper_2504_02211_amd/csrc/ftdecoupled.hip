@@ -676,7 +676,7 @@ extern "C" int ftdec_forward(ftdec_ctx* c, const void* q, const void* k, const v
     a.events = c->g_events + (size_t)slot * c->ring_n;
     a.cursor = c->cursors + slot;
     a.ring_mask = c->ring_n - 1;
-    const int per_head = which ? ftgemm::gemm_slots(N, d, plan2) : ftgemm::gemm_slots(N, N, plan1);
+    const int per_head = which ? ftgemm::gemm_slots(N, d, plan2) : ftgemm::gemm_slots(N, N, plan1, e.causal && !n_g);
     a.n_slots = &c->stat->slots[which];
     a.slots = c->g_slots + (which ? (size_t)BH * c->slots1 : 0) + (size_t)bh * per_head;
     if (!n_g) { a.bs_events = c->ring_n; a.bs_slots = per_head; }

@@ -92,7 +92,8 @@ hipError_t gemm_launch_encode_w(const uint16_t* w, uint16_t* wc, int n, int k, b
   return hipGetLastError();
 }
 
-int gemm_slots(long long m, long long n, GPlan plan) {
+int gemm_slots(long long m, long long n, GPlan plan, bool skip_upper) {
+  if (skip_upper) return lower_tiles((int)((m + TILES[plan.tile].bm - 1) / TILES[plan.tile].bm), TILES[plan.tile].bm);
   const int bm = plan.parts > 1 ? TileFinish::BM : TILES[plan.tile].bm;
   return (int)((m + bm - 1) / bm * ((n + GBN - 1) / GBN));
 }
@@ -149,7 +150,14 @@ hipError_t gemm_launch(GArgs a, bool ft, bool inject, bool bf16, GPlan plan, hip
   a.Tn = (a.N + GBN - 1) / GBN;
   a.parts = plan.parts;
   a.ws_tokens = ws_tokens_of(a.M, plan);
-  hipLaunchKernelGGL(tile_kernel(plan.tile, ft, inject, bf16), dim3(a.Tm * a.Tn, batch, plan.parts), dim3(ti.threads), ti.lds[ft], st, a);
+  a.tiles = a.head_group = 0;
+  dim3 grid(a.Tm * a.Tn, batch, plan.parts);
+  if (a.skip_upper || a.k_lower) {       // (never split)
+    a.tiles = a.skip_upper ? lower_tiles(a.Tm, ti.bm) : a.Tm;
+    a.head_group = ftattn::head_group_of(32 * ti.per_cu, batch, a.Tm);
+    grid = dim3(a.tiles * batch);
+  }
+  hipLaunchKernelGGL(tile_kernel(plan.tile, ft, inject, bf16), grid, dim3(ti.threads), ti.lds[ft], st, a);
   hipError_t he = hipGetLastError();
   if (he != hipSuccess || plan.parts <= 1) return he;
   hipLaunchKernelGGL((bf16 ? finish_kernel_bf16 : finish_kernel_f16)(ft), dim3((a.M + TileFinish::BM - 1) / TileFinish::BM * a.Tn),

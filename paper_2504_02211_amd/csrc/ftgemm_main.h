@@ -106,9 +106,11 @@ struct GArgs {
   // wc, the event rings and the slots, byte stride of y; one cursor per problem.  All zero for a single product.
   long long bs_x, bs_w, bs_wc, bs_y_bytes, bs_events, bs_slots;
   int32_t skip_upper;      // 1: output tiles that lie entirely above the diagonal (first feature > last token) are
-                           // not computed and not written (the score matrix of a causal attention: nobody reads them)
+                           // not launched (the score matrix of a causal attention: nobody reads them)
   int32_t k_lower;         // 1: x is lower-triangular (the weights of a causal attention): contraction steps beyond the
-                           // last token of the tile multiply zeros and are skipped
+                           // last token of the tile multiply zeros and are skipped.  One feature block only
+  int32_t tiles;           // with one of these two the batch is in blockIdx.x as well: tiles launched per problem ...
+  int32_t head_group;      // ... and (k_lower) problems whose tiles are issued together (causal_row_tile)
   int32_t parts;           // > 1: the K dimension is split over blockIdx.z, the shares go to ws
   float4v* ws;             // [part][16-token block][feature block of 256][WS_BLOCKS][lane]
   int32_t ws_tokens;       // 16-token blocks per part
@@ -209,7 +211,20 @@ using TileSlim2 = GTile<128, 64, 2, 4, 64, 2, 2>;
 
 __device__ __forceinline__ void write_slot(const GArgs& a, int logical, const GSlot& s) {
   a.slots[logical] = s;
-  if (logical == 0) *a.n_slots = (int32_t)gridDim.x;
+  if (logical == 0) *a.n_slots = a.tiles ? a.tiles : (int32_t)gridDim.x;
+}
+
+// Tiles on or below the diagonal: a block row of 256 tokens, the b-th, has b + 1 feature blocks for each of its token tiles.
+__host__ __device__ __forceinline__ int lower_tiles(int Tm, int bm) {
+  const int per = GBN / bm, b = Tm / per;
+  return per * (b * (b + 1) / 2) + (Tm - b * per) * (b + 1);
+}
+__device__ __forceinline__ void lower_tile(int t, int bm, int& tm, int& tn) {
+  const int per = GBN / bm;
+  int b = 0;
+  while (t >= per * (b + 1)) { t -= per * (b + 1); ++b; }
+  tm = b * per + t / (b + 1);
+  tn = t % (b + 1);
 }
 
 __device__ __forceinline__ void log_gemm_event(const GArgs& a, uint32_t at, int row, int col, float res, int action) {
@@ -515,8 +530,36 @@ __device__ __forceinline__ void finish_tile(const GArgs& a, char* smem, float4v 
 template <class T, bool FT, bool INJ, bool BF>
 __global__ __launch_bounds__(T::NW * 64, T::PER_CU * T::NW / 4 > 8 / T::NW ? T::PER_CU * T::NW / 4 : 8 / T::NW) void ftgemm_main(const GArgs a0) {
   GArgs a = a0;
+  // ---- workgroup -> problem of the batch, output tile.  Workgroup ids go round-robin over the 8 XCDs; each XCD gets a
+  // contiguous range of tiles, and tiles are numbered in groups of 8 token tiles x all feature
+  // tiles, feature-major inside a group, so that the workgroups an XCD runs together share
+  // weight rows and token rows in its L2.
+  int by, tm, tn, logical;
+  if (a.k_lower) {
+    // tiles of unequal length (tile t has t + 1 times as many steps as tile 0): longest first
+    const ftattn::RowTile rt = ftattn::causal_row_tile((int)blockIdx.x, (int)gridDim.x, a.tiles, a.head_group);
+    by = rt.bh; tm = logical = rt.ti; tn = 0;
+  } else {
+    const int id = blockIdx.x, total = gridDim.x, xcd = id & 7, slot = id >> 3, qn = total >> 3, rn = total & 7;
+    logical = xcd * qn + (xcd < rn ? xcd : rn) + slot;
+    if (a.skip_upper) {
+      by = logical / a.tiles;
+      logical -= by * a.tiles;
+      lower_tile(logical, T::BM, tm, tn);
+    } else {
+      by = blockIdx.y;
+      constexpr int GM = 8;
+      const int gsz = GM * a.Tn, g = logical / gsz, first = g * GM;
+      const int gm = a.Tm - first < GM ? a.Tm - first : GM;
+      const int in_g = logical - g * gsz;
+      tm = first + in_g % gm;
+      tn = in_g / gm;
+    }
+  }
+  // (divisions leave the vector unit; everything here is the same in all lanes)
+  by = __builtin_amdgcn_readfirstlane(by); tm = __builtin_amdgcn_readfirstlane(tm);
+  tn = __builtin_amdgcn_readfirstlane(tn); logical = __builtin_amdgcn_readfirstlane(logical);
   {
-    const size_t by = blockIdx.y;          // problem of the batch
     a.x += by * a0.bs_x; a.w += by * a0.bs_w; a.wc += by * a0.bs_wc;
     a.y = reinterpret_cast<char*>(a0.y) + by * a0.bs_y_bytes;
     a.events += by * a0.bs_events; a.cursor += by; a.slots += by * a0.bs_slots;
@@ -527,38 +570,11 @@ __global__ __launch_bounds__(T::NW * 64, T::PER_CU * T::NW / 4 > 8 / T::NW ? T::
   constexpr int NKS = BK / 32;           // k-steps of 32 per stage
   extern __shared__ __attribute__((aligned(1024))) char smem[];
 
-  // ---- workgroup -> output tile.  Workgroup ids go round-robin over the 8 XCDs; each XCD gets a
-  // contiguous range of tiles, and tiles are numbered in groups of 8 token tiles x all feature
-  // tiles, feature-major inside a group, so that the workgroups an XCD runs together share
-  // weight rows and token rows in its L2.
-  const int total = gridDim.x;
-  int logical;
-  {
-    int id = blockIdx.x, xcd = id & 7, slot = id >> 3, qn = total >> 3, rn = total & 7;
-    // (in a batch the ranges move on by one XCD per problem: with skip_upper or k_lower they hold unequal
-    // work, and the XCD of the longest one ran twice as long as the average.  32 products of a causal
-    // attention of 2048 x 128: scores 144 -> 110 us, weights times values 79 -> 65)
-    if (rn == 0) xcd = (xcd + blockIdx.y) & 7;
-    logical = xcd * qn + (xcd < rn ? xcd : rn) + slot;
-  }
-  int tm, tn;
-  {
-    constexpr int GM = 8;
-    const int gsz = GM * a.Tn, g = logical / gsz, first = g * GM;
-    const int gm = a.Tm - first < GM ? a.Tm - first : GM;
-    const int in_g = logical - g * gsz;
-    tm = first + in_g % gm;
-    tn = in_g / gm;
-  }
   const int tid = threadIdx.x, lane = tid & 63, lq = lane & 15, lg = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wt = wave / NWF, wf = wave % NWF;         // the wave's place along tokens and features
   const int M = a.M, N = a.N, K = a.K;
   const int m0 = tm * T::BM, n0 = tn * GBN;
-  if (a.skip_upper && n0 > m0 + T::BM - 1) {          // (the whole workgroup, before any barrier)
-    if (tid == 0) write_slot(a, logical, GSlot{0u, 0, 0.f});
-    return;
-  }
   int nkb = (K + BK - 1) / BK;
   const int krem = K - (nkb - 1) * BK;      // columns of the last K step (BK unless K is ragged; K is a multiple of 8)
   int kb_ragged = krem < BK ? nkb - 1 : -1;
@@ -850,7 +866,7 @@ hipError_t gemm_launch_encode_w(const uint16_t* w, uint16_t* wc, int n, int k, b
 struct GPlan { int tile, parts; };
 GPlan gemm_plan(long long m, long long n, long long k, int batch, bool inject, bool may_split);
 hipError_t gemm_allow_lds(GPlan plan, bool ft, bool bf16);       // once, before the launches of a plan
-int gemm_slots(long long m, long long n, GPlan plan);           // report slots of one problem
+int gemm_slots(long long m, long long n, GPlan plan, bool skip_upper = false);      // report slots of one problem
 size_t gemm_workspace(long long m, long long n, GPlan plan);    // bytes of GArgs::ws (0: not split)
 hipError_t gemm_launch(GArgs a, bool ft, bool inject, bool bf16, GPlan plan, hipStream_t st, int batch = 1);
 // What the slots of one call (host copies) say: the events logged and the largest passing statistic.

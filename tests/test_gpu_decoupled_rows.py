@@ -108,3 +108,27 @@ def test_weights_do_not_depend_on_the_fault_list(seq):
         ctx.close()
         outs.append(o)
     assert torch.equal(outs[0], outs[1])
+
+
+@pytest.mark.parametrize("batch,heads,seq,head_dim", [(1, 11, 257, 64), (1, 3, 1025, 128), (2, 8, 512, 64), (1, 9, 300, 136), (3, 17, 130, 128), (1, 1, 2049, 64)])
+def test_causal_tiles_of_all_heads(batch, heads, seq, head_dim):
+    """Causal products launch the tiles on and below the diagonal only, and the longest tiles of all heads first: numbers of
+    heads that 8 does not divide, last rows of tiles one token long, one and several tiles to a row of 256 tokens."""
+    print(f"[decoupled tiles] {batch} x {heads} x {seq} x {head_dim}", flush=True)
+    shape = (batch, heads, seq, head_dim)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seq)
+    q, k, v = (torch.randn(shape, generator=g, device="cuda").half() for _ in range(3))
+    s = torch.matmul(q.double(), k.double().transpose(-1, -2).contiguous()) * head_dim ** -0.5
+    s.masked_fill_(~torch.ones((seq, seq), dtype=torch.bool, device="cuda").tril(), float("-inf"))
+    want = torch.matmul(torch.softmax(s, -1), v.double())
+    o = torch.full(shape, float("nan"), dtype=torch.float32, device="cuda")
+    ctx = ftdecoupled.FtDecoupled(*shape, 0, True)
+    for _ in range(2):
+        o.fill_(float("nan"))
+        ctx.forward(q, k, v, o, None, torch.cuda.current_stream().cuda_stream)
+        rep = ctx.report()
+        assert rep.n_events == 0 and rep.n_events_dropped == 0 and rep.retried_rows == 0
+        diff = o.double() - want
+        assert float(diff.abs().max()) <= 2e-3 and float(diff.norm() / want.norm()) <= 1e-3
+    ctx.close()
