@@ -16,6 +16,9 @@
 
 namespace ftdec {
 
+using ftattn::as_f;
+using ftattn::as_u;
+
 struct SFault { int32_t key, col, bit, stage; };   // key = bh * seq + row; sorted by key
 
 struct SArgs {
@@ -173,26 +176,35 @@ __global__ __launch_bounds__(256) void ftdec_softmax(const SArgs a) {
 // registers from the one read of S to the one write of P.  Lane l holds the scores 256 c + 4 l .. + 3
 // of chunk c; chunks beyond the row's last valid score are skipped (wave-uniform), so a causal row
 // pays for its own length only.  S has rows of N floats, 16 bytes at a time from any multiple of 4 bytes.
-// Bound: memory (S once, P once; 268 + 134 MB for the lower half of 32 x 2048 x 2048).  There a workgroup
-// per row with eight barriers and four passes over LDS took 232 us, this takes 114.  Rows beyond 4096
+// Bound: memory (S once, P once; 268 + 151 MB for the lower half of 32 x 2048 x 2048, at 4.5 TB/s).  There a workgroup
+// per row with eight barriers and four passes over LDS took 232 us, a wave per row whose loads waited for one another
+// and whose reductions went through LDS 109, this takes 94.  Rows beyond 4096
 // scores do not fit a wave's registers and keep the workgroup-per-row kernel.
 typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
 typedef _Float16 half4 __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v = __builtin_fmaxf(v, __shfl_xor(v, off));
-  return v;
+template <int I> struct index_t { static constexpr int value = I; };
+
+// op over the 64 lanes, in every lane: register moves within rows of 16 lanes, then between rows.  (As six LDS permutes, each
+// waiting for the one before, four of these were 3100 cycles of a row's time.)
+template <class F> __device__ __forceinline__ float wave_reduce(float v, const F& op) {
+  auto moved = [&](auto ctrl) __attribute__((always_inline)) -> float {
+    return as_f((uint32_t)__builtin_amdgcn_update_dpp(0, (int)as_u(v), decltype(ctrl)::value, 0xF, 0xF, true));
+  };
+  v = op(v, moved(index_t<0xB1>{}));         // quads: 1 0 3 2, 2 3 0 1
+  v = op(v, moved(index_t<0x4E>{}));
+  v = op(v, moved(index_t<0x141>{}));        // mirrored in 8, in 16 lanes
+  v = op(v, moved(index_t<0x140>{}));
+  const auto r = __builtin_amdgcn_permlane16_swap(as_u(v), as_u(v), false, false);
+  v = op(as_f(r[0]), as_f(r[1]));
+  const auto q = __builtin_amdgcn_permlane32_swap(as_u(v), as_u(v), false, false);
+  return op(as_f(q[0]), as_f(q[1]));
 }
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off);
-  return v;
-}
+__device__ __forceinline__ float wave_max(float v) { return wave_reduce(v, [](float x, float y) { return __builtin_fmaxf(x, y); }); }
+__device__ __forceinline__ float wave_sum(float v) { return wave_reduce(v, [](float x, float y) { return x + y; }); }
 
 // f(0) .. f(E - 1) with the index as a constant from the start.  (Loops over the registers of a row are
 // unrolled only after the row has become one wide vector, which is then copied whole around every load.)
-template <int I> struct index_t { static constexpr int value = I; };
 template <int E, int I = 0, class F> __device__ __forceinline__ void each(const F& f) {
   if constexpr (I < E) {
     f(index_t<I>{});
@@ -201,9 +213,11 @@ template <int E, int I = 0, class F> __device__ __forceinline__ void each(const 
 }
 
 template <bool FT, bool INJ, int CH>
-__global__ __launch_bounds__(256) void ftdec_softmax_wave(const SArgs a) {
+__global__ __launch_bounds__(256, INJ ? 1 : CH <= 4 ? 8 : CH == 8 ? 7 : 4) void ftdec_softmax_wave(const SArgs a) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int N = a.N, row = blockIdx.x * 4 + wave, bh = blockIdx.y;
+  // (the heads whose scores were written last come first: they are still in the memory-side cache; 2 x 16 x 2048 x 128 without a
+  // mask 437 -> 425 us)
+  const int N = a.N, row = blockIdx.x * 4 + wave, bh = gridDim.y - 1 - blockIdx.y;
   if (row >= N) return;
   const int nvalid = a.causal ? row + 1 : N;
   const float* src = a.S + ((size_t)bh * N + row) * N + 4 * lane;
@@ -221,7 +235,7 @@ __global__ __launch_bounds__(256) void ftdec_softmax_wave(const SArgs a) {
   // (causal: GEMM II stops at the last query of the row's 256-query tile; the weights beyond are never read)
   const int jend = a.causal && (row / 256 + 1) * 256 < a.Np ? (row / 256 + 1) * 256 : a.Np;
   for (int attempt = 0; attempt < 3; ++attempt) {
-    float s[CH][4];
+    float4u s[CH];            // (chunks beyond the row's last valid score are never written, nor read)
     // the lane's scores of chunk c are valid below left - 256 c (formed here: the masks of all chunks would
     // otherwise be kept in scalar registers across the attempts, more than there are)
     int left = nvalid - 4 * lane;
@@ -234,31 +248,39 @@ __global__ __launch_bounds__(256) void ftdec_softmax_wave(const SArgs a) {
       return v;
     };
     // ---- the row, and its maximum, twice
+    // All loads first, in registers that stay where they are: with the choice between a whole chunk and the last
+    // one made around each load, its values were moved together behind it, and every load waited for the one before.
     each<CH>([&](auto ci) __attribute__((always_inline)) {
       constexpr int c = decltype(ci)::value;
-      float4u q = (float4u)(-__builtin_inff());
-      if (256 * c + 256 <= nvalid) q = *reinterpret_cast<const float4u*>(src + 256 * c);
-      else if (256 * c < nvalid) {
-        // (in place of a score beyond the last valid one that one is read again)
-#pragma unroll
-        for (int x = 0; x < 4; ++x) {
-          const bool ok = left > 256 * c + x;
-          const float t = src[ok ? 256 * c + x : left - 1];
-          q[x] = ok ? t : -__builtin_inff();
-        }
-      }
-      s[c][0] = q[0]; s[c][1] = q[1]; s[c][2] = q[2]; s[c][3] = q[3];
+      // (up to three scores beyond the last valid one are read with it, and not used: S ends in 16 bytes more)
+      if (256 * c < nvalid && left > 256 * c) s[c] = *reinterpret_cast<const float4u*>(src + 256 * c);
     });
-    float ma = -__builtin_inff(), mb = -__builtin_inff();
     each<CH>([&](auto ci) __attribute__((always_inline)) {
       constexpr int c = decltype(ci)::value;
-      if (256 * c < nvalid)
+      if (256 * c < nvalid && 256 * c + 256 > nvalid)
         each<4>([&](auto xi) __attribute__((always_inline)) {
-          const float v = s[c][decltype(xi)::value];
-          ma = __builtin_fmaxf(ma, v);
-          if (FT) mb = __builtin_fmaxf(mb, opaque(v));
+          constexpr int x = decltype(xi)::value;
+          s[c][x] = left > 256 * c + x ? s[c][x] : -__builtin_inff();
         });
     });
+    // The second evaluations are made on the registers of the first, renewed: the compiler cannot merge them, and keeps
+    // no copy for it.
+    auto renew = [&](float4u& v) __attribute__((always_inline)) { asm volatile("" : "+v"(v)); };
+    float ma = -__builtin_inff(), mb = -__builtin_inff();
+    auto row_max = [&](float& m) __attribute__((always_inline)) {
+      each<CH>([&](auto ci) __attribute__((always_inline)) {
+        constexpr int c = decltype(ci)::value;
+        if (256 * c < nvalid) each<4>([&](auto xi) __attribute__((always_inline)) { m = __builtin_fmaxf(m, s[c][decltype(xi)::value]); });
+      });
+    };
+    row_max(ma);
+    if (FT) {
+      each<CH>([&](auto ci) __attribute__((always_inline)) {
+        constexpr int c = decltype(ci)::value;
+        if (256 * c < nvalid) renew(s[c]);
+      });
+      row_max(mb);
+    }
     ma = wave_max(ma);
     if (FT) mb = wave_max(mb);
     const float na = -ma * sl2, nb = -mb * sl2;
@@ -269,19 +291,35 @@ __global__ __launch_bounds__(256) void ftdec_softmax_wave(const SArgs a) {
     each<CH>([&](auto ci) __attribute__((always_inline)) {
       constexpr int c = decltype(ci)::value;
       if (256 * c < nvalid) {
+        float4u e;
+        float d[4];
         each<4>([&](auto xi) __attribute__((always_inline)) {
           constexpr int x = decltype(xi)::value;
-          const float v = s[c][x];
-          float e = inject(FTDEC_ST_EXP, 256 * c + 4 * lane + x, ex2(__builtin_fmaf(v, sl2, na)));
-          if (FT) {
-            const float eb = ex2(__builtin_fmaf(opaque(v), sl2, nb));
-            bad[c / 8] |= __builtin_fabsf(e - eb) < a.eps ? 0u : 1u << (4 * (c % 8) + x);
-            e = 0.5f * (e + eb);
-          }
-          sum += e;
-          s[c][x] = e;
+          e[x] = inject(FTDEC_ST_EXP, 256 * c + 4 * lane + x, ex2(__builtin_fmaf(s[c][x], sl2, na)));
         });
-        if (FT) asm volatile("" : "+v"(bad[c / 8]));
+        if (FT) {
+          renew(s[c]);
+          each<4>([&](auto xi) __attribute__((always_inline)) {
+            constexpr int x = decltype(xi)::value;
+            const float eb = ex2(__builtin_fmaf(s[c][x], sl2, nb));
+            d[x] = e[x] - eb;
+            e[x] = 0.5f * (e[x] + eb);
+          });
+          // the largest difference of the four (a NaN stays one); which ones it was only where one is too large
+          float m;
+          asm("v_maximum3_f32 %0, |%1|, |%2|, |%3|" : "=v"(m) : "v"(d[0]), "v"(d[1]), "v"(d[2]));
+          asm("v_maximum3_f32 %0, %0, %0, |%1|" : "+v"(m) : "v"(d[3]));
+          if (__builtin_amdgcn_ballot_w64(!(m < a.eps)) != 0ull)
+            each<4>([&](auto xi) __attribute__((always_inline)) {
+              constexpr int x = decltype(xi)::value;
+              bad[c / 8] |= __builtin_fabsf(d[x]) < a.eps ? 0u : 1u << (4 * (c % 8) + x);
+            });
+        }
+        each<4>([&](auto xi) __attribute__((always_inline)) {
+          constexpr int x = decltype(xi)::value;
+          sum += e[x];
+        });
+        s[c] = e;
       }
     });
     uint32_t any = 0u;
@@ -301,7 +339,7 @@ __global__ __launch_bounds__(256) void ftdec_softmax_wave(const SArgs a) {
     // ---- normalised weights; eq. (12).  The weight that is summed and the one that is stored are one value:
     // without `opaque` the product is contracted into the sum and into the conversion, each with a
     // multiplication of its own, and the sum says nothing of what is stored (the lower half of 32 x 2048 x
-    // 2048: 112 us contracted, 114 like this).
+    // 2048: 2 us).
     float psum = 0.f;
     each<CH>([&](auto ci) __attribute__((always_inline)) {
       constexpr int c = decltype(ci)::value;
@@ -564,7 +602,7 @@ extern "C" int ftdec_create(const ftdec_config* cfg, ftdec_ctx** out) {
   size_t at = 0;
   for (auto& al : allocs) {
     if (al.sp) {
-      if (const int rc = allocate(al.p, al.bytes)) return rc;
+      if (const int rc = allocate(al.p, al.bytes + 16)) return rc;      // (the softmax reads up to three scores past a row)
       c->bytes_sp += (int64_t)al.bytes;
     } else {
       *al.p = static_cast<char*>(c->scratch) + at;
