@@ -272,16 +272,28 @@ __device__ __forceinline__ void finish_tile(const GArgs& a, char* smem, float4v 
       }
     }
   }
-  // Exchange area, in floats: [token block of the tile][value][wave along the features][lane % 32]; values
-  // 0..3 fold sums of the classes, 4..7 sums of magnitudes, 8..11 first checksum products.  Behind it a
+  // Exchange area, in floats: [token block of the tile][kind][wave along the features][lane][2]; kinds: fold sums of the classes,
+  // sums of magnitudes, first checksum products.  A class r = 0..3 of lane % 32 stands with lane % 32 + 32 (r % 2), entry r / 2:
+  // where it is after the two halves of two classes were added up in one exchange of lanes (pair_sums).  Behind it a
   // staging area per wave, through which the results go out in whole rows.
-  constexpr int EX_BYTES = FT ? T::BM / 16 * 12 * NWF * 32 * 4 : 0, SHARED_BYTES = 64;
+  constexpr int EX_BYTES = FT ? T::BM / 16 * 3 * NWF * 64 * 8 : 0, SHARED_BYTES = 64;
   constexpr int OUT_PITCH = 16 * WF * 4 + 16, OUT_PITCH_T = 16 * WT * 4 + 16;
   constexpr int OUT_BYTES = 16 * (OUT_PITCH > OUT_PITCH_T ? OUT_PITCH : OUT_PITCH_T);
   constexpr int TAIL_BYTES = T::NW * OUT_BYTES > EX_BYTES ? T::NW * OUT_BYTES : EX_BYTES;      // staging, or a second exchange area
   static_assert(EX_BYTES + SHARED_BYTES + TAIL_BYTES <= T::template lds<FT>(), "exchange and staging areas fit the ring");
-  auto ex = [&](int t, int val, int f) __attribute__((always_inline)) -> float& {
-    return reinterpret_cast<float*>(smem)[(((WT * wt + block_of(t)) * 12 + val) * NWF + f) * 32 + (lane & 31)];
+  typedef float float2v __attribute__((ext_vector_type(2)));
+  auto ex_pair = [&](int block, int kind, int f) __attribute__((always_inline)) -> float2v& {
+    return reinterpret_cast<float2v*>(smem)[((block * 3 + kind) * NWF + f) * 64 + lane];
+  };
+  auto ex = [&](int t, int val, int f) __attribute__((always_inline)) -> float& {       // val: 4 * kind + class
+    const int at = (((WT * wt + block_of(t)) * 3 + (val >> 2)) * NWF + f) * 64 + (lane & 31) + 32 * (val & 1);
+    return reinterpret_cast<float*>(smem)[2 * at + ((val >> 1) & 1)];
+  };
+  // sums of lane and lane^32 of four values: of the first and third in the lower half of the lanes, of the others in the upper half
+  auto pair_sums = [&](const float (&v)[4]) __attribute__((always_inline)) -> float2v {
+    const auto x = __builtin_amdgcn_permlane32_swap(as_u(v[0]), as_u(v[1]), false, false);
+    const auto y = __builtin_amdgcn_permlane32_swap(as_u(v[2]), as_u(v[3]), false, false);
+    return float2v{as_f(x[0]) + as_f(x[1]), as_f(y[0]) + as_f(y[1])};
   };
   auto ex2 = [&](int t, int val, int f) __attribute__((always_inline)) -> float& {
     return *reinterpret_cast<float*>(reinterpret_cast<char*>(&ex(t, val, f)) + EX_BYTES + SHARED_BYTES);
@@ -318,10 +330,12 @@ __device__ __forceinline__ void finish_tile(const GArgs& a, char* smem, float4v 
       }
     }
     if (FT) {
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        ex(t, r, wf) = sum32(sum1[r]); ex(t, 4 + r, wf) = sum32(mag[r]);
-        if (t < CB && check_wave) ex(t, 8 + r, 0) = sum32(sc[t][0][r]);
+      const int b = WT * wt + block_of(t);
+      ex_pair(b, 0, wf) = pair_sums(sum1);
+      ex_pair(b, 1, wf) = pair_sums(mag);
+      if (t < CB && check_wave) {
+        const float4v c = sc[t < CB ? t : 0][0];
+        ex_pair(b, 2, 0) = pair_sums({c[0], c[1], c[2], c[3]});
       }
     }
     if (a.transposed) return;
@@ -398,8 +412,9 @@ __device__ __forceinline__ void finish_tile(const GArgs& a, char* smem, float4v 
 
   if (FT) {
     __syncthreads();
-    // fold of the results of each class against the first checksum product (eq. (15)); every wave of a
-    // token range forms the same sums in the same order, and so comes to the same verdict
+    // fold of the results of each class against the first checksum product (eq. (15)).  The waves of a token range
+    // divide its token blocks; a lane has the two classes whose sums it finds at its own place.  (With every wave forming the
+    // verdicts of all blocks, this took 1.7 us of the 3.2 that follow the last product of the smallest tile; now 0.6.)
     auto total = [&](int t, int val, int n) __attribute__((always_inline)) -> float {
       float v = ex(t, val, 0);
 #pragma unroll
@@ -407,25 +422,41 @@ __device__ __forceinline__ void finish_tile(const GArgs& a, char* smem, float4v 
       return v;
     };
     float stat_max = 0.f;
-    uint32_t det = 0u;
+    bool any = false;
 #pragma unroll
-    for (int t = 0; t < WT; ++t)
+    for (int u = 0; u < (WT + NWF - 1) / NWF; ++u) {
+      const int in_range = wf + u * NWF;
+      if (WT % NWF != 0 && in_range >= WT) break;
+      const int b = WT * wt + in_range;
+      float2v fold = ex_pair(b, 0, 0), mag = ex_pair(b, 1, 0);
+      const float2v chk = ex_pair(b, 2, 0);
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const float R = ex(t, 8 + r, 0) - total(t, r, NWF);
-        const float thr = a.tau_abs + a.tau_rel * total(t, 4 + r, NWF);
-        const bool real = row_of(t) < M;
+      for (int f = 1; f < NWF; ++f) { fold += ex_pair(b, 0, f); mag += ex_pair(b, 1, f); }
+      const bool real = m0 + 16 * b + lq < M;
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const float R = chk[h] - fold[h], thr = a.tau_abs + a.tau_rel * mag[h];
         const bool d = real && (!(__builtin_fabsf(R) <= thr) || !finitef(R));
-        if (d) det |= 1u << (4 * t + r);
+        any |= d;
         if (!d && real && thr > 0.f) stat_max = fmax2(stat_max, __builtin_fabsf(R) / thr);
       }
-    if (det) shared_n[0] = 1;
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) stat_max = fmax2(stat_max, __shfl_xor(stat_max, o));
-    if (lane == 0) shared_stat[wave] = stat_max;
+    }
+    if (any) shared_n[0] = 1;
+    const uint32_t stat = ftattn::wave_max_u32(as_u(stat_max));        // (not negative: ordered like its bits)
+    if (lane == 63) shared_stat[wave] = as_f(stat);
     __syncthreads();
     if (shared_n[0]) {
-      // ---- rare: locate with the second checksum, restore from the first, one token block after the
+      // ---- rare: the verdicts again, of all blocks of its token range by every wave, in the same order and so alike
+      uint32_t det = 0u;
+#pragma unroll
+      for (int t = 0; t < WT; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const float R = ex(t, 8 + r, 0) - total(t, r, NWF);
+          const float thr = a.tau_abs + a.tau_rel * total(t, 4 + r, NWF);
+          if (row_of(t) < M && (!(__builtin_fabsf(R) <= thr) || !finitef(R))) det |= 1u << (4 * t + r);
+        }
+      // Locate with the second checksum, restore from the first, one token block after the
       // other.  The workgroup's run of the event ring is counted by the waves that log (one per token
       // range).  The results are in Y already: a restored one is stored over the faulty one.
       if (wf == 0 && lane < 32 && det) atomicAdd(&shared_n[1], __popc(det));
@@ -579,9 +610,12 @@ __global__ __launch_bounds__(T::NW * 64, T::PER_CU * T::NW / 4 > 8 / T::NW ? T::
   const int krem = K - (nkb - 1) * BK;      // columns of the last K step (BK unless K is ragged; K is a multiple of 8)
   int kb_ragged = krem < BK ? nkb - 1 : -1;
   if (a.k_lower) { const int lim = (m0 + T::BM + BK - 1) / BK; nkb = lim < nkb ? lim : nkb; }
-  const int kb0 = (int)((long long)nkb * blockIdx.z / a.parts);      // first K step of this workgroup's share
-  nkb = (int)((long long)nkb * (blockIdx.z + 1) / a.parts) - kb0;
-  kb_ragged -= kb0;
+  int kb0 = 0;                              // first K step of this workgroup's share
+  if (a.parts > 1) {
+    kb0 = nkb * (int)blockIdx.z / a.parts;  // (at most 2^16 steps)
+    nkb = nkb * ((int)blockIdx.z + 1) / a.parts - kb0;
+    kb_ragged -= kb0;
+  }
   const uint32_t smem_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
 
   // ---- per-lane source offsets of this wave's load instructions.  Piece p of an operand tile is its
@@ -603,25 +637,31 @@ __global__ __launch_bounds__(T::NW * 64, T::PER_CU * T::NW / 4 > 8 / T::NW ? T::
   const uint16_t* xb = a.x + (size_t)m0 * K + kb0 * BK;
   const uint16_t* wb = a.w + (size_t)n0 * K + kb0 * BK;
   const uint16_t* cb = (FT ? a.wc + (size_t)tn * GCK * K : a.w) + kb0 * BK;
-  auto piece_lds = [&](int i, int st) __attribute__((always_inline)) -> uint32_t {
-    const int base = i < T::XW ? 0 : i < T::XW + T::WW ? T::XP : T::XP + T::WP;
-    return smem_base + (uint32_t)(st * STAGE + (base + piece_of(i)) * 1024);
+  // Steps are requested in their order: the sources move on by one step behind each (next_step), and a piece's place
+  // is its stage's base plus what does not change over the steps.
+  const uint32_t wave_at = smem_base + (uint32_t)wave * 1024u;
+  const uint32_t x_at = T::XP % T::NW ? (uint32_t)(wave % T::XP - wave) * 1024u : 0u;      // (pieces that are fetched twice)
+  const uint32_t c_at = T::CP % T::NW ? (uint32_t)(wave % T::CP - wave) * 1024u : 0u;
+  auto piece_lds = [&](int i, uint32_t stage) __attribute__((always_inline)) -> uint32_t {
+    if (i < T::XW) return wave_at + stage + x_at + (uint32_t)(T::NW * i * 1024);
+    if (i < T::XW + T::WW) return wave_at + stage + (uint32_t)((T::XP + T::NW * (i - T::XW)) * 1024);
+    return wave_at + stage + c_at + (uint32_t)((T::XP + T::WP) * 1024);
   };
-  auto issue_piece = [&](int i, int kb, int st) __attribute__((always_inline)) {
-    const uint16_t* src = i < T::XW ? xb : i < T::XW + T::WW ? wb : cb;
-    gload_lds16_off(src + (size_t)kb * BK, off[i], piece_lds(i, st));
+  auto issue_piece = [&](int i, uint32_t stage) __attribute__((always_inline)) {
+    gload_lds16_off(i < T::XW ? xb : i < T::XW + T::WW ? wb : cb, off[i], piece_lds(i, stage));
   };
+  auto next_step = [&]() __attribute__((always_inline)) { xb += BK; wb += BK; cb += BK; };
   // the last K step of a ragged K: the chunks beyond column K are filled with zeros instead
   // (a wave without a piece of the checksum rows has one load less; fetching another wave's piece once more to keep the
   // counts alike made the steps of the 64-token tile, whose 48 pieces include 4 such, 10 % longer where rows are not
   // multiples of a cache line: 1733 x 539 x 6344)
   const bool has_c = FT && (!T::C_SPARE || wave < T::CP);
-  auto issue_ragged = [&](int kb, int st) {
+  auto issue_ragged = [&](uint32_t stage) {
 #pragma unroll
     for (int i = 0; i < NLOAD; ++i) {
       if (i == T::XW + T::WW && !has_c) continue;
-      if (chunk * 8 < krem) issue_piece(i, kb, st);
-      else *reinterpret_cast<__attribute__((address_space(3))) half8*>((uintptr_t)(piece_lds(i, st) + 16u * lane)) = (half8)(_Float16)0.f;
+      if (chunk * 8 < krem) issue_piece(i, stage);
+      else *reinterpret_cast<__attribute__((address_space(3))) half8*>((uintptr_t)(piece_lds(i, stage) + 16u * lane)) = (half8)(_Float16)0.f;
     }
   };
 
@@ -683,12 +723,13 @@ __global__ __launch_bounds__(T::NW * 64, T::PER_CU * T::NW / 4 > 8 / T::NW ? T::
 #pragma unroll
   for (int st = 0; st < NST; ++st)
     if (st < nkb) {
-      if (st == kb_ragged) issue_ragged(st, st);
+      if (st == kb_ragged) issue_ragged((uint32_t)(st * STAGE));
       else {
 #pragma unroll
         for (int i = 0; i < NLOAD; ++i)
-          if (i < T::XW + T::WW || has_c) issue_piece(i, st, st);
+          if (i < T::XW + T::WW || has_c) issue_piece(i, (uint32_t)(st * STAGE));
       }
+      next_step();
     }
   if (nkb < NST) wait_vmcnt<0>();
   else if (has_c) wait_vmcnt<(NST - 1) * NLOAD>();
@@ -700,11 +741,11 @@ __global__ __launch_bounds__(T::NW * 64, T::PER_CU * T::NW / 4 > 8 / T::NW ? T::
     constexpr bool CHK = decltype(chk_tag)::value;
     constexpr int NL = T::XW + T::WW + (decltype(c_tag)::value ? 1 : 0);      // loads per step of this wave
     constexpr int NCHK = CHK ? 2 * CB : 0;
-    int st = 0;
+    uint32_t stage = 0;                      // base of the stage in use
     // Row y of k-step ks: its products, and the LDS reads behind them.  `tail`: the last AHEAD rows of a
     // stage, behind its barrier, which read the next stage's first operands (after the last stage: what the
     // ring still holds, in bounds and unused) and request (LD) the stage that takes this one's place.
-    auto row_step = [&](auto row_tag, uint32_t stage, uint32_t next, int kb_ld, auto ld_tag) __attribute__((always_inline)) {
+    auto row_step = [&](auto row_tag, uint32_t stage, uint32_t next, auto ld_tag) __attribute__((always_inline)) {
       constexpr bool LD = decltype(ld_tag)::value;
       constexpr int ks = decltype(row_tag)::value / WF, y = decltype(row_tag)::value % WF;
       constexpr bool last = ks == NKS - 1, tail = last && y >= WF - AHEAD;
@@ -731,7 +772,7 @@ __global__ __launch_bounds__(T::NW * 64, T::PER_CU * T::NW / 4 > 8 / T::NW ? T::
         if (LD && tail) {
           const int q = (y - (WF - AHEAD)) * WT + m;
 #pragma unroll
-          for (int i = NL * q / TAILP; i < NL * (q + 1) / TAILP; ++i) issue_piece(i, kb_ld, st);
+          for (int i = NL * q / TAILP; i < NL * (q + 1) / TAILP; ++i) issue_piece(i, stage);
         }
       }
 #pragma unroll
@@ -739,20 +780,19 @@ __global__ __launch_bounds__(T::NW * 64, T::PER_CU * T::NW / 4 > 8 / T::NW ? T::
     };
     auto stage_step = [&](int kb, auto ld_tag) __attribute__((always_inline)) {
       constexpr bool LD = decltype(ld_tag)::value;
-      const uint32_t stage = (uint32_t)(st * STAGE);
-      const int st_next = st + 1 == NST ? 0 : st + 1;
-      const uint32_t next = (uint32_t)(st_next * STAGE);
-      for_each_index<NKS * WF - AHEAD>([&](auto row) __attribute__((always_inline)) { row_step(row, stage, next, kb + NST, ld_tag); });
+      const uint32_t next = stage == (uint32_t)((NST - 1) * STAGE) ? 0u : stage + (uint32_t)STAGE;
+      for_each_index<NKS * WF - AHEAD>([&](auto row) __attribute__((always_inline)) { row_step(row, stage, next, ld_tag); });
       wait_lds();                            // the operands of the last rows are in registers: this wave is done with the stage
       // the next stage has landed; up to NST-2 younger ones may be in flight
       if (LD || kb + NST - 1 < nkb) wait_vmcnt<(NST - 2) * NL>();
       else wait_vmcnt<0>();
       phase_barrier();                       // everyone's pieces of the next stage have landed, and everyone is done with this one
-      if (!LD && kb + NST < nkb) issue_ragged(kb + NST, st);
+      if (!LD && kb + NST < nkb) issue_ragged(stage);
       for_each_index<AHEAD>([&](auto row) __attribute__((always_inline)) {
-        row_step(std::integral_constant<int, NKS * WF - AHEAD + decltype(row)::value>{}, stage, next, kb + NST, ld_tag);
+        row_step(std::integral_constant<int, NKS * WF - AHEAD + decltype(row)::value>{}, stage, next, ld_tag);
       });
-      st = st_next;
+      if (LD) next_step();
+      stage = next;
     };
 #pragma unroll
     for (int t = 0; t < WT; ++t) read_x(0, t, 0u);
