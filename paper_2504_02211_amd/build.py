@@ -10,7 +10,7 @@ ROOT = os.path.dirname(PKG)
 LIB = os.path.join(PKG, "libftattn.so")
 SOURCES = [os.path.join(PKG, "csrc", "ftattn.hip"), os.path.join(PKG, "csrc", "ftattn_perstep.hip"),
            os.path.join(PKG, "csrc", "ftattn_elementwide.hip"), os.path.join(PKG, "csrc", "ftattn_lazy.hip"),
-           os.path.join(PKG, "csrc", "ftattn_split.hip"),
+           os.path.join(PKG, "csrc", "ftattn_split.hip"), os.path.join(PKG, "csrc", "ftattn_self.hip"),
            os.path.join(PKG, "csrc", "ftgemm.hip"), os.path.join(PKG, "csrc", "ftgemm_f16.hip"),
            os.path.join(PKG, "csrc", "ftgemm_bf16.hip"), os.path.join(PKG, "csrc", "ftdecoupled.hip")]
 HEADERS = [os.path.join(PKG, "csrc", "ftattn_device.h"), os.path.join(PKG, "csrc", "ftattn_main.h"),

@@ -37,6 +37,7 @@ struct Buffers {
   unsigned long long* recheck = nullptr;
   uint32_t* resmax = nullptr;
   float* ws = nullptr;                // state of split row tiles (null: no row tile is split)
+  unsigned char* work = nullptr;      // STAT_WORK
   uint32_t* range = nullptr;          // the word this call sets
   uint32_t* range_next = nullptr;     // the word the next call sets: cleared by this call
 };
@@ -44,7 +45,8 @@ struct Buffers {
 // Offsets in the block a report reads: event count, recheck count, two range words used in turn by
 // consecutive calls, residual maxima.  One block, so that a report is one copy behind one wait:
 // a pass over 2 x 3 x 333 x 128 with its report takes 53 us, and took 98 with a blocking copy for each.
-constexpr size_t STAT_EVENTS = 0, STAT_RECHECK = 8, STAT_RANGE = 16, STAT_RESMAX = 256;
+// (STAT_WORK: what calls in one launch count in, zero between them: event count, range word, recheck count, workgroups that have ended.)
+constexpr size_t STAT_EVENTS = 0, STAT_RECHECK = 8, STAT_RANGE = 16, STAT_WORK = 64, STAT_RESMAX = 256;
 
 struct ftattn_ctx {
   ftattn_config cfg;          // effective configuration
@@ -119,6 +121,7 @@ void (*select_perstep(int D, bool causal, bool inject, int mode))(const KArgs);
 void (*select_elementwide(int D, bool causal, bool inject))(const KArgs);
 void (*select_lazy(int D, bool ft, bool causal, bool inject))(const KArgs);
 kernel_fn select_split(int D, bool ft, bool causal);
+kernel_fn select_self(int D, bool ft, bool causal);
 kernel_fn select_finish(int D, bool ft, bool causal);
 }
 
@@ -245,6 +248,11 @@ static int resolve_config(const ftattn_config* cfg, ftattn_config& e, Geometry& 
   return FTATTN_OK;
 }
 
+// Whether a call without a fault list is one launch.
+static bool in_one_launch(const ftattn_config& e, const Geometry& g) {
+  return self_encodes(e.head_dim, g.Ti, g.Tj) && e.per_step == 0 && e.stride == 8 && !(e.rescale_margin > 0.f);
+}
+
 // For the tests, and no part of the interface: how a call without a fault list is split.  out: number of the first row
 // tile that is split (all row tiles: none is), key tiles of a share at most, shares, bytes of their state.
 extern "C" int ftattn_split_of(const ftattn_config* cfg, int64_t out[4]) {
@@ -259,14 +267,16 @@ extern "C" int ftattn_split_of(const ftattn_config* cfg, int64_t out[4]) {
 // Lets the kernels that a configuration runs, with a fault list or without one, use their dynamic LDS.  Needs the
 // device current.  (Only those: a call to the runtime for each takes about 10 us of the 110 to 300 that creating a
 // context takes.)
-static hipError_t allow_lds(const ftattn_config& e, bool split, const char*& why) {
+static hipError_t allow_lds(const ftattn_config& e, bool split, bool self, const char*& why) {
   const int D = e.head_dim;
   const bool ft = e.ft_mode != FTATTN_FT_OFF, causal = e.causal != 0, lazy = e.rescale_margin > 0.f;
   const int bytes = (int)lds_bytes(D, ft);
   why = "no kernel for this tile shape";
-  for (int v = 0; v < (split ? 3 : 2); ++v) {
+  for (int v = 0; v < 4; ++v) {
     const bool inject = v == 1;
+    if (v == 2 ? !split : v == 3 ? !self : false) continue;
     main_fn f = v == 2 ? select_split(D, ft, causal)
+                : v == 3 ? select_self(D, ft, causal)
                 : e.per_step ? select_perstep(D, causal, inject, e.per_step)
                 : e.stride == 1 ? select_elementwide(D, causal, inject)
                 : lazy ? select_lazy(D, ft, causal, inject)
@@ -342,7 +352,7 @@ extern "C" int ftattn_create(const ftattn_config* cfg, ftattn_ctx** out) {
   CREATE_TRY(hipMemset(c->kc, 0, tiles_bytes));
   if (!vt_joined) CREATE_TRY(hipMemset(c->vt, 0, vt_bytes));
   {
-    hipError_t le = allow_lds(e, g.n_ws != 0, why);
+    hipError_t le = allow_lds(e, g.n_ws != 0, in_one_launch(e, g), why);
     if (le != hipSuccess) {
       int rc = fail(nullptr, le == hipErrorInvalidValue ? FTATTN_EUNSUPPORTED : FTATTN_EHIP, std::string(why) + ": " + hipGetErrorString(le));
       release(c);
@@ -370,11 +380,14 @@ static hipError_t launch_pass(const ftattn_config& e, const Geometry& g, const B
   const bool ft = e.ft_mode != FTATTN_FT_OFF;
   const int n_resmax = g.BH * g.Ti * 4;
   hipError_t he;
+  // (a timed call keeps the launch of the encode, which has a time of its own)
+  const bool self = !inject && !timing && in_one_launch(e, g);
   if (timing && (he = hipEventRecord(timing[0], st)) != hipSuccess) return he;
   dim3 eg(g.Tj, g.BH, 2);
   const int bf = e.in_dtype == FTATTN_BF16 ? 1 : 0;
   const int kchk = ft ? 1 : 0, vchk = ft ? 1 + e.rowsum_fold : 0;
-  if (D == 128)
+  if (self) {}
+  else if (D == 128)
     ftattn_prepare<128><<<eg, 256, 0, st>>>(k, v, bf, b.kc, b.vt, N, g.Tj, kchk, vchk, b.ev_count, b.recheck, b.resmax, n_resmax, b.range, b.range_next);
   else
     ftattn_prepare<64><<<eg, 256, 0, st>>>(k, v, bf, b.kc, b.vt, N, g.Tj, kchk, vchk, b.ev_count, b.recheck, b.resmax, n_resmax, b.range, b.range_next);
@@ -400,10 +413,17 @@ static hipError_t launch_pass(const ftattn_config& e, const Geometry& g, const B
   a.fault_off = inject ? b.fault_off : nullptr;
   a.events = b.events; a.ev_count = b.ev_count; a.max_events = e.max_events;
   a.resmax = b.resmax; a.recheck = b.recheck; a.range = b.range;
+  a.k = k; a.v = v;
+  a.last = {};
+  if (self) {
+    a.last = {(uint32_t*)(b.work + 16), b.ev_count, b.recheck, b.range, b.range_next};
+    a.ev_count = (int32_t*)b.work; a.range = (uint32_t*)(b.work + 4); a.recheck = (unsigned long long*)(b.work + 8);
+  }
   main_fn f = e.per_step ? select_perstep(D, e.causal != 0, inject, e.per_step)
               : e.stride == 1 ? select_elementwide(D, e.causal != 0, inject)
               : e.rescale_margin > 0.f ? select_lazy(D, ft, e.causal != 0, inject)
               : split ? select_split(D, ft, e.causal != 0)
+              : self ? select_self(D, ft, e.causal != 0)
                               : select_kernel(D, ft, e.causal != 0, inject);
   if (timing && (he = hipEventRecord(timing[1], st)) != hipSuccess) return he;
   const int n_split = a.n_tiles - a.first_split;
@@ -471,6 +491,7 @@ extern "C" int ftattn_forward(ftattn_ctx* c, const void* q, const void* k, const
   bufs.ev_count = (int32_t*)(c->d_stat + STAT_EVENTS);
   bufs.recheck = (unsigned long long*)(c->d_stat + STAT_RECHECK);
   bufs.resmax = (uint32_t*)(c->d_stat + STAT_RESMAX);
+  bufs.work = c->d_stat + STAT_WORK;
   uint32_t* range = (uint32_t*)(c->d_stat + STAT_RANGE);
   bufs.range = range + (c->calls & 1u); bufs.range_next = range + ((c->calls + 1u) & 1u);
   hipError_t le = launch_pass(e, c->geo, bufs, q, k, v, o, n_faults > 0, st, c->timing ? c->ev : nullptr);
@@ -638,7 +659,7 @@ extern "C" int ftattn_forward_static(const ftattn_config* cfg, const void* q, co
     }
     const int di = (e.head_dim == 128 ? 4 : 0) + (e.ft_mode != FTATTN_FT_OFF ? 2 : 0) + (e.causal != 0 ? 1 : 0);
     if (!g_static_lds[e.device][di]) {
-      he = allow_lds(e, true, why);
+      he = allow_lds(e, true, true, why);
       if (he != hipSuccess) return static_fail(FTATTN_EHIP, why, he);
       g_static_lds[e.device][di] = true;
     }
@@ -649,6 +670,7 @@ extern "C" int ftattn_forward_static(const ftattn_config* cfg, const void* q, co
   Buffers bufs;
   bufs.ev_count = n_events_dev ? n_events_dev : (int32_t*)base;
   bufs.recheck = (unsigned long long*)(base + 8);
+  bufs.work = base + STAT_WORK;
   bufs.range = (uint32_t*)(base + 16) + (calls & 1u);
   bufs.range_next = (uint32_t*)(base + 16) + ((calls + 1u) & 1u);
   bufs.resmax = (uint32_t*)(base + off_resmax);

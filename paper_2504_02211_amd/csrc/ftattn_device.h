@@ -72,6 +72,11 @@ struct KArgs {
   uint32_t* resmax;        // [BH][Ti][4], float bits of non-negative values
   unsigned long long* recheck;
   uint32_t* range;         // FTATTN_RANGE_* bits of this call (operands that do not survive the conversion to fp16)
+  // Calls in one launch (SELF in ftattn_main.h).  events, recheck and range then point at words that are zero between calls;
+  // the workgroup that ends last moves them to where a report reads them.
+  const void* k;           // the caller's, [BH][N][D] like q
+  const void* v;
+  struct { uint32_t* done; int32_t* ev_count; unsigned long long* recheck; uint32_t* range; uint32_t* range_next; } last;
 };
 
 // ------------------------------------------------------------------ small helpers
@@ -199,17 +204,14 @@ __device__ __forceinline__ half8 to_half8(uint4v raw, bool bf16) {
   return r;
 }
 
-// Key tile j of head bh by the first D threads of a workgroup, one thread per (checksum class,
-// 16-byte chunk of a row): the thread converts the 8 rows of its class to fp16 and forms, in fp32
-// registers, the four checksum words of check1[c,:] = sum_l K[c+8l,:] and
-// check2[c,:] = sum_l (l+1) K[c+8l,:]  (eq. (13), (14)).
-template <int D>
-__device__ __forceinline__ void encode_k_tile(const void* __restrict__ k, int bf16, _Float16* __restrict__ kc,
-                                              int N, int Tj, int with_checksums, int j, int bh, int tid, uint32_t* range) {
+// Key tile j of head bh, one thread per (checksum class, 16-byte chunk of a row), `id` of D: the thread converts the 8 rows
+// of its class to fp16 and forms, in fp32 registers, the four checksum words of check1[c,:] = sum_l K[c+8l,:] and
+// check2[c,:] = sum_l (l+1) K[c+8l,:]  (eq. (13), (14)).  put(row, chunk, values) stores 16 bytes of the tile.  Returns FTATTN_RANGE_* bits.
+template <int D, class PUT>
+__device__ __forceinline__ uint32_t encode_k_tile(const void* __restrict__ k, int bf16, int N, int with_checksums, int j, int bh, int id, const PUT& put) {
   constexpr int KCH = D / 8;
-  const int cls = tid / KCH, ch = tid % KCH;
+  const int cls = id / KCH, ch = id % KCH;
   const uint16_t* src = reinterpret_cast<const uint16_t*>(k) + (size_t)bh * N * D + ch * 8;
-  _Float16* out = kc + ((size_t)bh * Tj + j) * ((BN + CKR) * D) + ch * 8;
   float c1[8], c2[8];
   RangeCheck operands;
 #pragma unroll
@@ -221,7 +223,7 @@ __device__ __forceinline__ void encode_k_tile(const void* __restrict__ k, int bf
     if (key < N) raw = *reinterpret_cast<const uint4v*>(src + (size_t)key * D);
     if (bf16) operands.add(raw);
     const half8 h = to_half8(raw, bf16 != 0);
-    *reinterpret_cast<half8*>(out + r * D) = h;
+    put(r, ch, h);
 #pragma unroll
     for (int x = 0; x < 8; ++x) {
       const float v = (float)h[x];
@@ -230,10 +232,7 @@ __device__ __forceinline__ void encode_k_tile(const void* __restrict__ k, int bf
     }
   }
   uint32_t rbits = operands.bits();
-  if (!with_checksums) {
-    if (rbits) atomicOr(range, rbits);
-    return;
-  }
+  if (!with_checksums) return rbits;
   half8 w0, w1, w2, w3;
 #pragma unroll
   for (int x = 0; x < 8; ++x) {
@@ -242,11 +241,11 @@ __device__ __forceinline__ void encode_k_tile(const void* __restrict__ k, int bf
     // a checksum beyond the fp16 range (the second one reaches 36 times the largest key value)
     if ((finitef(c1[x]) && !finitef((float)w0[x])) || (finitef(c2[x]) && !finitef((float)w2[x]))) rbits |= FTATTN_RANGE_CHECKSUM_OVERFLOW;
   }
-  if (rbits) atomicOr(range, rbits);
-  *reinterpret_cast<half8*>(out + (BN + cls) * D) = w0;
-  *reinterpret_cast<half8*>(out + (BN + 8 + cls) * D) = w1;
-  *reinterpret_cast<half8*>(out + (BN + 16 + cls) * D) = w2;
-  *reinterpret_cast<half8*>(out + (BN + 24 + cls) * D) = w3;
+  put(BN + cls, ch, w0);
+  put(BN + 8 + cls, ch, w1);
+  put(BN + 16 + cls, ch, w2);
+  put(BN + 24 + cls, ch, w3);
+  return rbits;
 }
 
 // position of key kl (0..63) inside the permuted key axis of the V^T tile
@@ -317,6 +316,51 @@ __device__ __forceinline__ void encode_v_tile(const void* __restrict__ v, int bf
   if (rbits) atomicOr(range, rbits);
 }
 
+// The same by one wave, into LDS as the fused kernel reads it (`tile`: its value tile): a lane takes the row of one key, whose
+// features and checksum classes are then all in its registers; 2-byte stores transpose.  Returns FTATTN_RANGE_* bits.
+template <int D, bool FT>
+__device__ __forceinline__ uint32_t encode_v_rows(const void* __restrict__ v, int bf16, int N, bool ones, int j, int bh, int lane, char* tile) {
+  const int key = j * BN + lane, p = vt_pos(lane);
+  const uint16_t* src = reinterpret_cast<const uint16_t*>(v) + ((size_t)bh * N + (key < N ? key : 0)) * D;
+  auto put = [&](const int row, const _Float16 x) __attribute__((always_inline)) {
+    *reinterpret_cast<_Float16*>(tile + row * (BN * 2) + (((p >> 3) ^ swz_v(row)) << 4) + (p & 7) * 2) = x;
+  };
+  RangeCheck operands;
+  half8 h[D / 8];
+#pragma unroll
+  for (int c = 0; c < D / 8; ++c) {
+    uint4v raw = *reinterpret_cast<const uint4v*>(src + 8 * c);
+    if (key >= N) raw = (uint4v)0u;
+    if (bf16) operands.add(raw);
+    h[c] = to_half8(raw, bf16 != 0);
+  }
+#pragma unroll
+  for (int c = 0; c < D / 8; ++c)
+#pragma unroll
+    for (int x = 0; x < 8; ++x) put(8 * c + x, h[c][x]);
+  uint32_t rbits = operands.bits();
+  if (FT) {
+#pragma unroll
+    for (int cls = 0; cls < 8; ++cls) {
+      float c1 = 0.f, c2 = 0.f;
+#pragma unroll
+      for (int l = 0; l < D / 8; ++l) {
+        const float x = (float)h[l][cls];
+        c1 += x;
+        c2 += (float)(l + 1) * x;
+      }
+      if (ones && cls == 0 && key < N) { c1 += 1.0f; c2 += (float)(D / 8 + 1); }
+      const _Float16 h1 = (_Float16)c1, h2 = (_Float16)c2;
+      if ((finitef(c1) && !finitef((float)h1)) || (finitef(c2) && !finitef((float)h2))) rbits |= FTATTN_RANGE_CHECKSUM_OVERFLOW;
+      put(D + cls, h1);
+      put(D + 8 + cls, (_Float16)(c1 - (float)h1));
+      put(D + 16 + cls, h2);
+      put(D + 24 + cls, (_Float16)(c2 - (float)h2));
+    }
+  }
+  return rbits;
+}
+
 // Everything the fused pass needs before it starts, in one launch (Algorithm 1: "Encode tensor
 // checksum"): grid (key tiles, heads, 2); the workgroups with blockIdx.z == 0 encode the value tiles
 // and clear the event counter, the recheck counter and the residual maxima (a store per thread
@@ -337,7 +381,11 @@ __global__ __launch_bounds__(256) void ftattn_prepare(const void* __restrict__ k
     if (i < n_resmax) resmax[i] = 0u;
     encode_v_tile<D>(v, bf16, vt, N, Tj, v_checksums, j, bh, tid, range);
   } else if (tid < D) {
-    encode_k_tile<D>(k, bf16, kc, N, Tj, k_checksums, j, bh, tid, range);
+    _Float16* out = kc + ((size_t)bh * Tj + j) * ((BN + CKR) * D);
+    const uint32_t rbits = encode_k_tile<D>(k, bf16, N, k_checksums, j, bh, tid, [&](const int row, const int ch, const half8& h) __attribute__((always_inline)) {
+      *reinterpret_cast<half8*>(out + row * D + ch * 8) = h;
+    });
+    if (rbits) atomicOr(range, rbits);
   }
 }
 

@@ -334,10 +334,10 @@ __device__ __forceinline__ void note_statistics(const KArgs& a, const int bh, co
 
 // What follows the last key tile of 32 query rows whose state a wave holds: row-sum range check, normalisation,
 // sum-form check, store, statistics.
-template <int D, bool FT, bool CAUSAL, int PS>
+template <int D, bool FT, bool CAUSAL, int PS, class NOTE>
 __device__ __forceinline__ void finish_rows(const KArgs& a, float16v (&o)[D / 32], float16v& oc, const int bh, const int ti, const int row,
                                             const int lane, const float l_part, const float l_low, const float m_run, const float m_true,
-                                            const float dev_max, const unsigned rechecks) {
+                                            const float dev_max, const NOTE& note) {
   constexpr int NFB = D / 32, NFOLD_V = D / 8;
   constexpr bool DMR = PS == 2, LAZY = PS == 4;
   const int N = a.N, hi = lane >> 5;
@@ -443,7 +443,7 @@ __device__ __forceinline__ void finish_rows(const KArgs& a, float16v (&o)[D / 32
   }
   if (FT) {
     const float vals[4] = {dev_max, rmax_o, rmax_u, rmax_l};
-    note_statistics(a, bh, ti, lane, vals, rechecks);
+    note(vals);
   }
 }
 
@@ -556,7 +556,8 @@ __global__ __launch_bounds__(D * 2) void ftattn_finish(const KArgs a) {
       const float4 t = block[fb - 1][q][lane];
       o[fb][4 * q] = t.x; o[fb][4 * q + 1] = t.y; o[fb][4 * q + 2] = t.z; o[fb][4 * q + 3] = t.w;
     }
-  finish_rows<D, FT, CAUSAL, 0>(a, o, oc, sh.rt.bh, sh.rt.ti, row0 + (lane & 31), lane, l, l_low, m, m, 0.f, 0u);
+  finish_rows<D, FT, CAUSAL, 0>(a, o, oc, sh.rt.bh, sh.rt.ti, row0 + (lane & 31), lane, l, l_low, m, m, 0.f,
+                                [&](const float (&vals)[4]) __attribute__((always_inline)) { note_statistics(a, sh.rt.bh, sh.rt.ti, lane, vals, 0u); });
 }
 
 // PS >= 1: verification after every step (the paper's EFTA before the unified verification of
@@ -571,9 +572,14 @@ __global__ __launch_bounds__(D * 2) void ftattn_finish(const KArgs a) {
 // classes of the same encoded tiles (c1 = sum_c c1_c, c2 = sum_c 8 c2_c + (c - 7) c1_c), so the
 // matrix work is the same; what changes is that a row has one residual per key tile, formed by
 // the two lanes of a query together, and can name one element of 64 (of D for the output).
-template <int D, bool FT, bool CAUSAL, bool INJ, int PS = 0, bool SPLIT = false>
+// SELF: the whole call in one launch, for heads of one row tile whose key and value tiles fit the ring (see self_encodes):
+// the workgroup encodes them into LDS itself, each by one wave, in place of a launch that does so in memory.  Nothing else
+// reads them, and what the first launch clears is written whole instead, or cleared by the workgroup that ends last.
+// Measured, in two launches and in one: 1 x 1 x 128 x 64 12.4 and 9.3 us, 4 x 8 x 100 x 64 causal 15.4 and 12.2, 16 x 32 x 128 x 64
+// 26.0 and 20.3, 16 x 32 x 192 x 128 causal 75.5 and 56.0, 2 x 3 x 150 x 128 causal 24.1 and 23.5.
+template <int D, bool FT, bool CAUSAL, bool INJ, int PS = 0, bool SPLIT = false, bool SELF = false>
 __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : FT ? 2 : 3) void ftattn_main(const KArgs a) {
-  static_assert(!SPLIT || (PS == 0 && !INJ), "split calls run the default verification scheme without a fault list");
+  static_assert(!(SPLIT || SELF) || (PS == 0 && !INJ && SPLIT != SELF), "these run the default verification scheme without a fault list");
   static_assert(FT || PS == 0 || PS == 4, "the verification modes are modes of the protected kernel");
   constexpr bool DMR = PS == 2;
   constexpr bool STEP = PS == 1 || PS == 2;
@@ -668,6 +674,41 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : FT ? 2 : 3
   const DevFault* __restrict__ F = a.faults;
   if (INJ && a.fault_off != nullptr) { fcur = a.fault_off[bh * a.Ti + ti]; fend = a.fault_off[bh * a.Ti + ti + 1]; }
 
+  half8 qf[NSLAB];
+  if constexpr (SELF) {
+    // (queries requested first, converted last)
+    const uint16_t* qp = reinterpret_cast<const uint16_t*>(a.q) + ((size_t)bh * N + (row < N ? row : 0)) * D + 8 * hi;
+    uint4v raw[D / 16];
+#pragma unroll
+    for (int sl = 0; sl < D / 16; ++sl) raw[sl] = *reinterpret_cast<const uint4v*>(qp + 16 * sl);
+    __builtin_amdgcn_sched_barrier(0);
+    uint32_t rbits = 0u;
+    // (a key tile is as many tasks as it has lanes' worth of work, 2.3 us each; a value tile is one, of 3.5 us at head_dim 64.  Value
+    // tiles in two or three tasks gain nothing: 2 x 3 x 100 x 128 18.0 and 18.7 us, 1 x 1 x 16 x 64 8.7 and 8.9.)
+    constexpr int KTASKS = D / 64;
+    for (int task = wave; task < (KTASKS + 1) * nj; task += NWAVE) {
+      if (task >= KTASKS * nj) {
+        const int j = task - KTASKS * nj;
+        rbits |= encode_v_rows<D, FT>(a.v, a.q_bf16, N, a.rowsum_fold != 0, j, bh, lane, smem + (j + 1) % NSTAGE * U::BYTES + U::KBYTES);
+      } else {
+        const int j = task / KTASKS;
+        char* tile = smem + j % NSTAGE * U::BYTES;
+        rbits |= encode_k_tile<D>(a.k, a.q_bf16, N, FT, j, bh, lane + 64 * (task % KTASKS), [&](const int r, const int ch, const half8& h) __attribute__((always_inline)) {
+          *reinterpret_cast<half8*>(tile + r * (D * 2) + ((ch ^ swz_k<D>(r)) << 4)) = h;
+        });
+      }
+    }
+    RangeCheck operands;
+#pragma unroll
+    for (int sl = 0; sl < D / 16; ++sl) {
+      if (row >= N) raw[sl] = (uint4v)0u;
+      if (a.q_bf16) operands.add(raw[sl]);
+      qf[sl] = to_half8(raw[sl], a.q_bf16 != 0);
+    }
+    rbits |= operands.bits();
+    if (rbits) atomicOr(a.range, rbits);
+    __syncthreads();
+  } else {
   // The first key tile alone, then the queries, and the other units only when both are there: loads are waited for
   // in their order, and GEMM I of the first tile needs nothing else.  (With the queries behind three units of
   // tiles a workgroup's start took 5.5-11 us at head_dim 128 and 3-5 us at head_dim 64, now 5-9 and 2.8-4.)
@@ -678,7 +719,6 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : FT ? 2 : 3
 
   // ---- Q_i^T as MFMA B operand: lane (query lq, half hi) holds Q[row][16*slab + 8*hi .. +7]
   // (bf16 queries are converted here: exact for magnitudes in the fp16 normal range)
-  half8 qf[NSLAB];
   {
     const uint16_t* qp = reinterpret_cast<const uint16_t*>(a.q) + ((size_t)bh * N + (row < N ? row : 0)) * D + 8 * hi;
     RangeCheck operands;
@@ -694,6 +734,7 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : FT ? 2 : 3
   wait_vmcnt<0>();
   issue_unit();
   if (ALT) issue_unit();
+  }
 
   float16v o[NFB], oc, s[2], sc;
   half8 ph[2][2];             // P^T in fp16, B operand of GEMM II: [key block][8-key half]
@@ -1259,12 +1300,12 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : FT ? 2 : 3
     __builtin_amdgcn_s_setprio(1);
     // (after a wave's last key tile GEMM I runs on a tile it does not need: same code, result unused)
     if (DMR) l_prev = l_part;
-    if (on) matrix_stream(stage + (uint32_t)U::KBYTES, stage, yes{}, yes{}, yes{});
-    else {
+    if (on) matrix_stream(stage + (uint32_t)U::KBYTES, stage, yes{}, yes{}, std::conditional_t<SELF, no, yes>{});
+    else if (!SELF) {
 #pragma unroll
       for (int n = 0; n < U::NLOAD; ++n) issue_piece(n);
     }
-    next_unit();
+    if (!SELF) next_unit();
     __builtin_amdgcn_s_setprio(0);
 
     // ---- injection point: row-sum (right after the update of this iteration)
@@ -1350,10 +1391,49 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : FT ? 2 : 3
   wait_vmcnt<0>();          // (the units after the last key tile: LDS is given back at the end)
 
   const int lane_e = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));      // (not kept through the loop)
+  if constexpr (SELF) {
+    // the statistics of the row tile are those of this workgroup's waves: written whole, through LDS (nobody reads the ring any more)
+    __syncthreads();
+    uint32_t* of_waves = reinterpret_cast<uint32_t*>(smem);
+    finish_rows<D, FT, CAUSAL, PS>(a, o, oc, bh, ti, row0_w + (lane_e & 31), lane_e, l_part, l_low, m_run, m_true, dev_max, [&](const float (&vals)[4]) __attribute__((always_inline)) {
+#pragma unroll
+      for (int x = 0; x < 4; ++x) {
+        const uint32_t v = wave_max_u32(as_u(vals[x]));
+        if (lane_e == 63) of_waves[x * NWAVE + wave] = v;
+      }
+      if (lane_e == 0 && rechecks) atomicAdd(a.recheck, (unsigned long long)rechecks);
+    });
+    wait_vmcnt<0>();          // (this wave's counts and events are in memory)
+    __syncthreads();
+    if (wave == 0) {
+      if (lane_e < 4) {
+        uint32_t v = 0u;
+        if (FT)
+          for (int w = 0; w < NWAVE; ++w) v = of_waves[lane_e * NWAVE + w] > v ? of_waves[lane_e * NWAVE + w] : v;
+        a.resmax[(size_t)bh * 4 + lane_e] = v;
+      }
+      if (lane_e == 0 && (gridDim.x == 1 || atomicInc(a.last.done, gridDim.x - 1) == gridDim.x - 1)) {      // (and is zero again)
+        const int32_t events = atomicExch(a.ev_count, 0);
+        const unsigned long long rechecked = atomicExch(a.recheck, 0ull);
+        const uint32_t bits = atomicExch(a.range, 0u);
+        __builtin_amdgcn_sched_barrier(0);
+        *a.last.ev_count = events;
+        *a.last.recheck = rechecked;
+        *a.last.range = bits;
+        *a.last.range_next = 0u;
+      }
+    }
+    return;
+  }
   if (!SPLIT || sh.nparts == 1)
-    finish_rows<D, FT, CAUSAL, PS>(a, o, oc, bh, ti, row0_w + (lane_e & 31), lane_e, l_part, l_low, m_run, m_true, dev_max, rechecks);
+    finish_rows<D, FT, CAUSAL, PS>(a, o, oc, bh, ti, row0_w + (lane_e & 31), lane_e, l_part, l_low, m_run, m_true, dev_max,
+                                   [&](const float (&vals)[4]) __attribute__((always_inline)) { note_statistics(a, bh, ti, lane_e, vals, rechecks); });
   else
     store_part<D, FT>(a, o, oc, sh, wave, lane_e, l_part, l_low, m_run, dev_max, rechecks);
 }
+
+// A head of one row tile whose tiles the ring holds all at once: unit u stands in stage (u + 1) mod NSTAGE, and with
+// at most NSTAGE key tiles none takes the place of another.
+inline bool self_encodes(int D, int Ti, int Tj) { return Ti == 1 && Tj <= nstage_of(D); }
 
 }  // namespace ftattn
