@@ -68,7 +68,7 @@ namespace ftgemm {
 template <class T> static constexpr TileInfo info_of() { return TileInfo{T::BM, T::NW * 64, T::PER_CU, {T::template lds<false>(), T::template lds<true>()}}; }
 static constexpr TileInfo TILES[N_TILES] = {info_of<TileWide>(), info_of<TileHalf>(), info_of<TileQuarter>(),
                                             info_of<TileStrip>(), info_of<TileNarrow>(), info_of<TileSlim>(),
-                                            info_of<TileNarrow2>(), info_of<TileSlim2>()};
+                                            info_of<TileNarrow2>(), info_of<TileSlim2>(), info_of<TileLow>()};
 
 static gemm_fn tile_kernel(int tile, bool ft, bool inject, bool bf16) {
   return bf16 ? tile_kernel_bf16(tile, ft, inject) : tile_kernel_f16(tile, ft, inject);
@@ -120,6 +120,11 @@ size_t gemm_workspace(long long m, long long n, GPlan plan) {
 // high ones, 99 with the low and 126 with 32-token tiles of 256 features, 16384 x 100 x 512 18.0 / 12.9 / 23, 1000 x 100 x
 // 1000 21.4 / 14.4 / 16.0; with K split the 32-token tiles take 18.9 for 37 x 100 x 8192 (69 / 46 unsplit), 20.4 for
 // 2000 x 128 x 4096 (38 / 26) and 20.9 for 2000 x 64 x 4096 (44 / 27).
+// A K of one or two steps is nearly all start and store: from a little more than one tile per CU on, tiles that keep one stage and run two
+// to a CU beat those with a ring, whose workgroup does one after the other: 16384 x 4096 x 64 69.7 -> 54.5 us, 4096 x 2560 x 64 (320
+// tiles) 21.8 -> 12.5, 16384 x 8192 x 128 131 -> 115, 2400 x 4000 x 128 (304) 14.3 -> 14.1, Q K^T of 4 x 1501 x 64 (288) 66.6 -> 58.7 for the
+// whole scheme.  Below that they lose (2048 x 2048 x 128, 128 tiles: 8.1 and 10.8; 8 x 1000 x 64, 256: 37.4 and 38.8), as with four steps
+// (16384 x 2048 x 256 37.5 and 38.5).
 GPlan gemm_plan(long long m, long long n, long long k, int batch, bool inject, bool may_split) {
   if (inject) return {TILE_QUARTER, 1};
   static constexpr struct { int tile, max_n; double fixed, step, load; } COST[] = {
@@ -128,6 +133,7 @@ GPlan gemm_plan(long long m, long long n, long long k, int batch, bool inject, b
   constexpr double CUS = 256.0, LAUNCH = 4.5, MEMORY = 5e6;           // bytes per microsecond
   const long long steps = (k + 63) / 64, tn = (n + GBN - 1) / GBN;
   const int max_n = n <= 64 ? 64 : n <= 128 ? 128 : 0;
+  if (max_n == 0 && steps <= 2 && (m + TILES[TILE_LOW].bm - 1) / TILES[TILE_LOW].bm * tn * batch >= (batch > 1 ? 288 : 300)) return {TILE_LOW, 1};
   GPlan best{TILE_WIDE, 1};
   double best_us = 0.0;
   for (const auto& c : COST) {

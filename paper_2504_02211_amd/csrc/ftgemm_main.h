@@ -167,8 +167,9 @@ __global__ __launch_bounds__(256) void ftgemm_encode_w(const uint16_t* __restric
   encode_weight_rows<BF>(w + (size_t)blockIdx.z * bs_w, wc + (size_t)blockIdx.z * bs_wc, N, K, blockIdx.x, blockIdx.y);      // z: matrix of a batch
 }
 
-// Tile shape: BM tokens x BF features, a wave takes WT x WF blocks of 16 x 16, ring of NST stages, PER_CU workgroups per CU.
-template <int BM_, int BF_, int WT_, int WF_, int BK_, int NST_, int PER_CU_ = 1> struct GTile {
+// Tile shape: BM tokens x BF features, a wave takes WT x WF blocks of 16 x 16, ring of NST stages, PER_CU workgroups per CU
+// (whose epilogue may need more LDS than the ring: EPILOGUE).
+template <int BM_, int BF_, int WT_, int WF_, int BK_, int NST_, int PER_CU_ = 1, int EPILOGUE_ = 0> struct GTile {
   static constexpr int PER_CU = PER_CU_;
   static constexpr int BM = BM_, BF = BF_, WT = WT_, WF = WF_, BK = BK_, NST = NST_;
   static constexpr int NWT = BM / (16 * WT), NWF = BF / (16 * WF);   // waves along the tokens / along the features
@@ -191,9 +192,9 @@ template <int BM_, int BF_, int WT_, int WF_, int BK_, int NST_, int PER_CU_ = 1
   static_assert((XP % NW == 0 || XP < NW) && (WP % NW == 0) && CP <= NW, "pieces split evenly");
   template <bool FT> static constexpr int nload() { return XW + WW + (FT ? CW : 0); }
   template <bool FT> static constexpr int bytes() { return (BM + BF + (FT ? GCK : 0)) * ROWB; }
-  template <bool FT> static constexpr int lds() { return NST * bytes<FT>(); }
+  template <bool FT> static constexpr int lds() { return FT && EPILOGUE_ > NST * bytes<FT>() ? EPILOGUE_ : NST * bytes<FT>(); }
   static_assert((NST - 1) * (XW + WW + CW) <= 63, "counted waits use a 6-bit immediate");
-  static_assert(PER_CU * NST * (BM + BF + GCK) * ROWB <= 160 * 1024 && NST <= 3, "LDS; the waits of the last stages");
+  static_assert(PER_CU * NST * (BM + BF + GCK) * ROWB <= 160 * 1024 && PER_CU * EPILOGUE_ <= 160 * 1024 && NST <= 3, "LDS; the waits of the last stages");
 };
 
 // The tile shapes in use (see gemm_plan in ftgemm.hip for when).  The tiles of 128 and 64 tokens are spread over eight waves,
@@ -208,6 +209,9 @@ using TileFinish = GTile<16, 256, 1, 4, 64, 1>;      // epilogue only
 using TileSlim = GTile<256, 64, 4, 4, 64, 3>;
 using TileNarrow2 = GTile<64, 128, 2, 4, 64, 2, 2>;
 using TileSlim2 = GTile<128, 64, 2, 4, 64, 2, 2>;
+// Short contractions with large results: a stage at a time, two workgroups to a CU, so that one loads and multiplies while the
+// other's results are on their way out.
+using TileLow = GTile<128, 256, 4, 8, 64, 1, 2, 58 * 1024>;
 
 __device__ __forceinline__ void write_slot(const GArgs& a, int logical, const GSlot& s) {
   a.slots[logical] = s;
@@ -760,14 +764,14 @@ __global__ __launch_bounds__(T::NW * 64, T::PER_CU * T::NW / 4 > 8 / T::NW ? T::
         if (m < WT) mma(wr[(ks * WF + y) & 3], xr[ks & 1][m], acc[y][m]);
         else mma(cr[(m - WT) / CB], xr[ks & 1][(m - WT) % CB], sc[(m - WT) % CB][(m - WT) / CB]);
         int n = 0;
-        if (m == 0) {
-          const int p = ks * WF + y + AHEAD;
+        const int p = ks * WF + y + AHEAD;
+        if (m == 0 && (NST > 1 || p < NKS * WF)) {
           read_w(p % (NKS * WF), p < NKS * WF ? stage : next);
           ++n;
         }
         if (CHK && y == 0 && m == 1) { read_c(ks, 0, stage); read_c(ks, 1, stage); n += 2; }     // (ahead of the barrier of the last k-step)
         // one token operand behind every product but the first
-        if (m >= 1 && x0 + m - 1 < x1) { read_x((ks + 1) % NKS, x0 + m - 1, last ? next : stage); ++n; }
+        if (m >= 1 && x0 + m - 1 < x1 && (NST > 1 || !last)) { read_x((ks + 1) % NKS, x0 + m - 1, last ? next : stage); ++n; }
         nread[m] = n;
         if (LD && tail) {
           const int q = (y - (WF - AHEAD)) * WT + m;
@@ -778,14 +782,22 @@ __global__ __launch_bounds__(T::NW * 64, T::PER_CU * T::NW / 4 > 8 / T::NW ? T::
 #pragma unroll
       for (int m = 0; m < np; ++m) pin(nread[m]);
     };
+    auto first_operands = [&]() __attribute__((always_inline)) {
+#pragma unroll
+      for (int t = 0; t < WT; ++t) read_x(0, t, 0u);
+#pragma unroll
+      for (int p = 0; p < AHEAD; ++p) read_w(p, 0u);
+    };
     auto stage_step = [&](int kb, auto ld_tag) __attribute__((always_inline)) {
       constexpr bool LD = decltype(ld_tag)::value;
       const uint32_t next = stage == (uint32_t)((NST - 1) * STAGE) ? 0u : stage + (uint32_t)STAGE;
       for_each_index<NKS * WF - AHEAD>([&](auto row) __attribute__((always_inline)) { row_step(row, stage, next, ld_tag); });
       wait_lds();                            // the operands of the last rows are in registers: this wave is done with the stage
       // the next stage has landed; up to NST-2 younger ones may be in flight
-      if (LD || kb + NST - 1 < nkb) wait_vmcnt<(NST - 2) * NL>();
-      else wait_vmcnt<0>();
+      if constexpr (NST > 1) {
+        if (LD || kb + NST - 1 < nkb) wait_vmcnt<(NST - 2) * NL>();
+        else wait_vmcnt<0>();
+      }
       phase_barrier();                       // everyone's pieces of the next stage have landed, and everyone is done with this one
       if (!LD && kb + NST < nkb) issue_ragged(stage);
       for_each_index<AHEAD>([&](auto row) __attribute__((always_inline)) {
@@ -793,11 +805,16 @@ __global__ __launch_bounds__(T::NW * 64, T::PER_CU * T::NW / 4 > 8 / T::NW ? T::
       });
       if (LD) next_step();
       stage = next;
+      if constexpr (NST == 1) {
+        if (kb + 1 < nkb) {                  // the one stage again, once everyone's pieces have landed
+          wait_vmcnt<0>();
+          wait_lds();
+          phase_barrier();
+          first_operands();
+        }
+      }
     };
-#pragma unroll
-    for (int t = 0; t < WT; ++t) read_x(0, t, 0u);
-#pragma unroll
-    for (int p = 0; p < AHEAD; ++p) read_w(p, 0u);
+    first_operands();
     int kb = 0;
     for (; kb + NST < nfull; ++kb) stage_step(kb, ftattn::yes{});
     for (; kb < nkb; ++kb) stage_step(kb, ftattn::no{});
@@ -874,7 +891,7 @@ __global__ __launch_bounds__(256) void ftgemm_finish(const GArgs a) {
 }
 
 typedef void (*gemm_fn)(const GArgs);
-enum TileId { TILE_WIDE, TILE_HALF, TILE_QUARTER, TILE_STRIP, TILE_NARROW, TILE_SLIM, TILE_NARROW2, TILE_SLIM2, N_TILES };
+enum TileId { TILE_WIDE, TILE_HALF, TILE_QUARTER, TILE_STRIP, TILE_NARROW, TILE_SLIM, TILE_NARROW2, TILE_SLIM2, TILE_LOW, N_TILES };
 struct TileInfo { int bm, threads, per_cu, lds[2]; };       // lds: dynamic LDS bytes without / with the checksum rows
 
 // kernel of one tile shape, instantiated per type (ftgemm_f16.hip, ftgemm_bf16.hip); the fault
@@ -892,6 +909,7 @@ template <bool BF> gemm_fn tile_kernel_of(int tile, bool ft, bool inject) {
     case TILE_STRIP: return ft ? ftgemm_main<TileStrip, true, false, BF> : ftgemm_main<TileStrip, false, false, BF>;
     case TILE_NARROW2: return ft ? ftgemm_main<TileNarrow2, true, false, BF> : ftgemm_main<TileNarrow2, false, false, BF>;
     case TILE_SLIM2: return ft ? ftgemm_main<TileSlim2, true, false, BF> : ftgemm_main<TileSlim2, false, false, BF>;
+    case TILE_LOW: return ft ? ftgemm_main<TileLow, true, false, BF> : ftgemm_main<TileLow, false, false, BF>;
     case TILE_NARROW: return ft ? ftgemm_main<TileNarrow, true, false, BF> : ftgemm_main<TileNarrow, false, false, BF>;
     default: return ft ? ftgemm_main<TileSlim, true, false, BF> : ftgemm_main<TileSlim, false, false, BF>;
   }
