@@ -147,6 +147,41 @@ __device__ __forceinline__ void gload_lds16_off(const void* base, uint32_t byte_
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(byte_off), "s"(base), "s"(lds_addr) : "m0");
 }
 
+// The queries of a lane (NQ times 16 bytes, 32 bytes apart), then the pieces of a unit (KPW of the key tile, VPW of the value tile, all but the last
+// a fixed distance apart in memory and in LDS), then the wait for everything but these.
+#define FTATTN_LOAD_Q(r, off) "global_load_dwordx4 %" #r ", %[q], off offset:" #off "\n\t"
+#define FTATTN_PIECE(m, v, b) "s_mov_b32 m0, %[" #m "]\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %[" #v "], %[" #b "]\n\t"
+template <int NQ, int KPW, int VPW>
+__device__ __forceinline__ void queries_and_unit(const void* q, uint4v (&r)[NQ], uint32_t koff, uint32_t voff, const _Float16* k, const _Float16* v, int step,
+                                                 uint32_t lds, uint32_t lds_step, const _Float16* last_v, uint32_t last_v_lds, uint32_t vbase) {
+  static_assert((NQ == 4 || NQ == 8) && ((KPW == 2 && VPW == 2) || (KPW == 3 && VPW == 3)), "the shapes of Unit");
+#define FTATTN_Q4 FTATTN_LOAD_Q(0, 0) FTATTN_LOAD_Q(1, 32) FTATTN_LOAD_Q(2, 64) FTATTN_LOAD_Q(3, 96)
+#define FTATTN_Q8 FTATTN_Q4 FTATTN_LOAD_Q(4, 128) FTATTN_LOAD_Q(5, 160) FTATTN_LOAD_Q(6, 192) FTATTN_LOAD_Q(7, 224)
+#define FTATTN_U2 FTATTN_PIECE(m0, ko, k0) FTATTN_PIECE(m1, ko, k1) FTATTN_PIECE(n0, vo, v0) FTATTN_PIECE(nl, vo, vl) "s_waitcnt vmcnt(4)"
+#define FTATTN_U3 FTATTN_PIECE(m0, ko, k0) FTATTN_PIECE(m1, ko, k1) FTATTN_PIECE(m2, ko, k2) FTATTN_PIECE(n0, vo, v0) FTATTN_PIECE(n1, vo, v1) FTATTN_PIECE(nl, vo, vl) "s_waitcnt vmcnt(6)"
+#define FTATTN_IN2 [q] "v"(q), [ko] "v"(koff), [vo] "v"(voff), [k0] "s"(k), [k1] "s"(k + step), [v0] "s"(v), [vl] "s"(last_v), \
+                   [m0] "s"(lds), [m1] "s"(lds + lds_step), [n0] "s"(lds + vbase), [nl] "s"(last_v_lds)
+#define FTATTN_IN3 FTATTN_IN2, [k2] "s"(k + 2 * step), [v1] "s"(v + step), [m2] "s"(lds + 2 * lds_step), [n1] "s"(lds + vbase + lds_step)
+  if constexpr (NQ == 4 && KPW == 2)
+    asm volatile(FTATTN_Q4 FTATTN_U2 : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3]) : FTATTN_IN2 : "m0", "memory");
+  else if constexpr (NQ == 4)
+    asm volatile(FTATTN_Q4 FTATTN_U3 : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3]) : FTATTN_IN3 : "m0", "memory");
+  else if constexpr (KPW == 2)
+    asm volatile(FTATTN_Q8 FTATTN_U2 : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3]), "=&v"(r[4 % NQ]), "=&v"(r[5 % NQ]), "=&v"(r[6 % NQ]), "=&v"(r[7 % NQ])
+                 : FTATTN_IN2 : "m0", "memory");
+  else
+    asm volatile(FTATTN_Q8 FTATTN_U3 : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3]), "=&v"(r[4 % NQ]), "=&v"(r[5 % NQ]), "=&v"(r[6 % NQ]), "=&v"(r[7 % NQ])
+                 : FTATTN_IN3 : "m0", "memory");
+#undef FTATTN_Q4
+#undef FTATTN_Q8
+#undef FTATTN_U2
+#undef FTATTN_U3
+#undef FTATTN_IN2
+#undef FTATTN_IN3
+}
+#undef FTATTN_LOAD_Q
+#undef FTATTN_PIECE
+
 struct yes { static constexpr bool value = true; };
 struct no { static constexpr bool value = false; };
 
@@ -709,9 +744,15 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : FT ? 2 : 3
     if (rbits) atomicOr(a.range, rbits);
     __syncthreads();
   } else {
-  // The first key tile alone, then the queries, and the other units only when both are there: loads are waited for
-  // in their order, and GEMM I of the first tile needs nothing else.  (With the queries behind three units of
-  // tiles a workgroup's start took 5.5-11 us at head_dim 128 and 3-5 us at head_dim 64, now 5-9 and 2.8-4.)
+  // The first key tile and the queries are waited for, unit 0 is not: GEMM I of the first tile needs nothing else.  Where
+  // workgroups follow one another on a CU, unit 0 is requested right behind them, and its latency no longer stands between
+  // the first two key tiles: 16 x 12 x 512 x 64 48.9 -> 45.7 us, 4 x 16 x 1000 x 64 causal 38.9 -> 37.6, 8 x 32 x 512 x 128 causal 97.8 -> 95.2,
+  // 1 x 32 x 16384 x 128 causal 2845 -> 2818.  (Loads are waited for in their order, and the compiler, which counts the queries
+  // only, would wait for unit 0 as well: so the queries are loaded, unit 0 requested and the wait made in one block.)  Elsewhere
+  // it is requested when the queries are there: the first workgroup of every CU at once would only get its queries
+  // later (2 x 8 x 300 x 128 27.6 and 28.0 us), and beside a second workgroup with many key tiles nothing is gained (8 x 16 x 2048 x 64
+  // causal 183.7 and 186.2).
+  const bool early = a.n_tiles >= 256 && (D == 128 || a.Tj <= 24);
 #pragma unroll
   for (int n = 0; n < U::KPW; ++n) issue_piece(n);
   next_unit();
@@ -722,17 +763,27 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : FT ? 2 : 3
   {
     const uint16_t* qp = reinterpret_cast<const uint16_t*>(a.q) + ((size_t)bh * N + (row < N ? row : 0)) * D + 8 * hi;
     RangeCheck operands;
-#pragma unroll
-    for (int sl = 0; sl < NSLAB; ++sl) {
-      uint4v raw = *reinterpret_cast<const uint4v*>(qp + 16 * sl);
+    auto take = [&](const int sl, uint4v raw) __attribute__((always_inline)) {
       if (row >= N) raw = (uint4v)0u;
       if (a.q_bf16) operands.add(raw);
       qf[sl] = to_half8(raw, a.q_bf16 != 0);
+    };
+    if (early) {
+      uint4v raw[NSLAB];
+      queries_and_unit<NSLAB, U::KPW, U::VPW>(qp, raw, koff0, voff0, ld_kt, ld_vt, PIECE_STEP, ld_lds, (uint32_t)(NWAVE * 1024),
+                                              ld_vt + last_v_src, ld_lds + last_v_lds, (uint32_t)U::KBYTES);
+      next_unit();
+#pragma unroll
+      for (int sl = 0; sl < NSLAB; ++sl) take(sl, raw[sl]);
+      if (const uint32_t qbits = operands.bits()) atomicOr(a.range, qbits);
+    } else {
+#pragma unroll
+      for (int sl = 0; sl < NSLAB; ++sl) take(sl, *reinterpret_cast<const uint4v*>(qp + 16 * sl));
+      if (const uint32_t qbits = operands.bits()) atomicOr(a.range, qbits);
+      wait_vmcnt<0>();
+      issue_unit();
     }
-    if (const uint32_t qbits = operands.bits()) atomicOr(a.range, qbits);
   }
-  wait_vmcnt<0>();
-  issue_unit();
   if (ALT) issue_unit();
   }
 
