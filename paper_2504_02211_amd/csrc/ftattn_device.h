@@ -7,7 +7,7 @@
 //                    stored as an fp16 high word and an fp16 low word);
 //                    V -> per key tile: V^T in fp16 (feature-major, keys permuted to the order in
 //                    which the MFMA accumulator of GEMM I hands out scores) followed by 32
-//                    checksum rows of V.
+//                    checksum rows of V.  (Heads of one row tile and few keys have no such launch: the main kernel encodes.)
 //   main kernel      one workgroup per (batch, head, row tile); loop over key tiles:
 //                    GEMM I (+checksum block) -> max -> exp -> product-form check -> row-sum ->
 //                    GEMM II with rescale (+checksum block); after the loop: row-sum range check,

@@ -375,8 +375,8 @@ __global__ __launch_bounds__(256, INJ ? 1 : CH <= 4 ? 8 : CH == 8 ? 7 : 4) void 
 // Role 1: the checksum rows of K.
 // Bound: memory, one read of K and V and one write of V^T; for short sequences the launches.  Three launches (V^T with
 // 16 bytes per lane, the checksums of K, those of V^T read back) took 23 us for 2 x 16 x 2048 x 128, this takes 14; for 2 x 5 x 151 x 128 they took 15.
-// The second product gives that back at the larger size (76 us, 69 with three launches): it reads V^T from memory, which the
-// launch that read V^T back had just brought into the caches.
+// The second product gave that back at the larger size (76 us, 69 with three launches; 59 since its longest tiles come first): it reads
+// V^T from memory, which the launch that read V^T back had just brought into the caches.
 template <bool FT, bool BF>
 __global__ __launch_bounds__(256) void ftdec_prepare(const uint16_t* __restrict__ k, const uint16_t* __restrict__ v, uint16_t* __restrict__ wc1,
                                                      _Float16* __restrict__ vt, _Float16* __restrict__ wc2, int N, int Np, int d, int Tn1,

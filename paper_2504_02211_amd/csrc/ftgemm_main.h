@@ -25,7 +25,7 @@
 // ahead of their products, also across the stage boundary: the barrier of a stage sits AHEAD rows before
 // its end, where the last operands of the stage are in registers, so that no wave waits for LDS after it.
 //
-// Measured (16384 tokens, 4096 -> 16384 features, fp16): 1860 us protected, 1660 us with the checks
+// Measured (16384 tokens, 4096 -> 16384 features, fp16): 1810-1870 us protected, 1660 us with the checks
 // compiled out, against 2250 / 1930 us for one 32-token row of 32x32x16 blocks per wave.  Four waves of 8 x 8
 // blocks would read a third less LDS, but their 288 accumulators do not fit next to the operands without
 // register copies in the loop.
