@@ -184,10 +184,14 @@ int ftattn_forward(ftattn_ctx* ctx, const void* q, const void* k, const void* v,
 /* Waits for the last forward of this context and exposes its flags, residuals and events. */
 int ftattn_report(ftattn_ctx* ctx, ftattn_report_view* out);
 /* Kernel timing for benchmarks.  After ftattn_set_timing(ctx, 1) every forward brackets its
- * encode kernel and its fused kernel with HIP events on the stream it launches on;
+ * encode kernel and its fused kernel with HIP events on the stream it launches on (with the kernel that
+ * puts divided keys together, where the call has one);
  * ftattn_get_timing waits for the last forward and returns the two durations in milliseconds:
  * ms[0] = encode (Algorithm 1, "Encode tensor checksum", plus operand conversion / transposition),
- * ms[1] = fused attention kernel (all other steps of Algorithm 1). */
+ * ms[1] = fused attention kernel (all other steps of Algorithm 1).
+ * A head of at most 128 (head_dim 64) or 192 keys (head_dim 128) in the default scheme is one launch, whose fused
+ * kernel encodes by itself; while timing is enabled such a call is two launches like any other, with the same result, so
+ * that ms[0] and ms[1] are not the time of the call without timing. */
 int ftattn_set_timing(ftattn_ctx* ctx, int32_t enabled);
 int ftattn_get_timing(ftattn_ctx* ctx, float ms[2]);
 int ftattn_destroy(ftattn_ctx* ctx);
@@ -201,9 +205,11 @@ const char* ftattn_last_error(const ftattn_ctx* ctx);
  * type), without a context: the encoded key / value tiles, the counters and the event log live in
  * one array of FTATTN_STATIC_SCRATCH_MIB MiB that is part of the library's device code and that
  * every GPU the library runs on holds until the process ends.  The call allocates and frees
- * nothing, on the host or on the device, and is two kernel launches on `hip_stream` (three where a call has
- * so few row tiles that their keys are split over several workgroups and the array has room for their state;
- * where it has none the call runs unsplit, and its result is that of ftattn_forward to within rounding instead of bit for bit).
+ * nothing, on the host or on the device, and is two kernel launches on `hip_stream` (one where a head
+ * has at most 128 keys at head_dim 64, 192 at head_dim 128; three where a call has so few row tiles
+ * that their keys are split over several workgroups and the array has room for their state; where it
+ * has none the call runs unsplit, and its result is that of ftattn_forward to within rounding instead
+ * of bit for bit).
  *   cfg           host pointer, as for ftattn_create (defaults resolved the same way; max_events is
  *                 capped at 4096).  A shape whose encoded tiles do not fit the array fails with
  *                 FTATTN_EUNSUPPORTED and a message that names both sizes; nothing is launched.
@@ -211,9 +217,10 @@ const char* ftattn_last_error(const ftattn_ctx* ctx);
  *   n_events_dev  device pointer to one int32 owned by the caller, or NULL: when the pass has run
  *                 it holds the number of events the checks raised (0 on a fault-free pass).
  * No fault list: the injector needs staging buffers.  All calls on one GPU share that GPU's
- * array, which keeps the previous call's contents; every part a pass reads is rewritten by its
- * own encode launch first, so calls may follow each other on one stream in any order of shapes,
- * but calls that overlap in time on one GPU (different streams, different threads) race.
+ * array, which keeps the previous call's contents.  A pass writes every part that it reads first, but
+ * for the counters of calls in one launch, which are zero between calls; so calls may follow each
+ * other on one stream in any order of shapes.  Calls that overlap in time on one GPU (different
+ * streams, different threads) race: their results and counts are not defined, those of later calls are.
  * On failure returns a negative code; ftattn_static_last_error() then returns the calling
  * thread's message (a fixed buffer, never allocated). */
 #define FTATTN_STATIC_SCRATCH_MIB 64

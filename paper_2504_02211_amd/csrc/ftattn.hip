@@ -38,6 +38,7 @@ struct Buffers {
   uint32_t* resmax = nullptr;
   float* ws = nullptr;                // state of split row tiles (null: no row tile is split)
   unsigned char* work = nullptr;      // STAT_WORK
+  uint32_t* ended = nullptr;          // where workgroups of calls in one launch count that they have ended
   uint32_t* range = nullptr;          // the word this call sets
   uint32_t* range_next = nullptr;     // the word the next call sets: cleared by this call
 };
@@ -45,7 +46,10 @@ struct Buffers {
 // Offsets in the block a report reads: event count, recheck count, two range words used in turn by
 // consecutive calls, residual maxima.  One block, so that a report is one copy behind one wait:
 // a pass over 2 x 3 x 333 x 128 with its report takes 53 us, and took 98 with a blocking copy for each.
-// (STAT_WORK: what calls in one launch count in, zero between them: event count, range word, recheck count, workgroups that have ended.)
+// STAT_WORK: what calls in one launch count in, zero between them: event count, range word, recheck count, workgroups that have ended.
+// Nothing clears these first, so they must come back to zero by themselves also where calls overlapped (which spoils the reports of
+// those calls): the last word is counted by calls of one number of heads only, each of which adds that number and takes it off again,
+// and the workgroup that ends last of all is the last one of its own call and finds everything that was counted.
 constexpr size_t STAT_EVENTS = 0, STAT_RECHECK = 8, STAT_RANGE = 16, STAT_WORK = 64, STAT_RESMAX = 256;
 
 struct ftattn_ctx {
@@ -371,8 +375,9 @@ extern "C" int ftattn_get_config(const ftattn_ctx* ctx, ftattn_config* effective
   return FTATTN_OK;
 }
 
-// The two launches of one pass on `st`: encode (Algorithm 1: "Encode tensor checksum"), once per key
-// tile for all row tiles, which also clears the counters of the report; then the fused pass.
+// The launches of one pass on `st`: encode (Algorithm 1: "Encode tensor checksum"), once per key tile for all row tiles, which
+// also clears the counters of the report; then the fused pass; then, where row tiles are split by their keys, what puts their shares
+// together.  The fused pass alone where in_one_launch says so.
 // Allocates nothing.  `timing`: three events recorded before, between and after the launches, or null.
 static hipError_t launch_pass(const ftattn_config& e, const Geometry& g, const Buffers& b, const void* q, const void* k,
                               const void* v, void* o, bool inject, hipStream_t st, hipEvent_t* timing) {
@@ -416,7 +421,7 @@ static hipError_t launch_pass(const ftattn_config& e, const Geometry& g, const B
   a.k = k; a.v = v;
   a.last = {};
   if (self) {
-    a.last = {(uint32_t*)(b.work + 16), b.ev_count, b.recheck, b.range, b.range_next};
+    a.last = {b.ended, b.ev_count, b.recheck, b.range, b.range_next};
     a.ev_count = (int32_t*)b.work; a.range = (uint32_t*)(b.work + 4); a.recheck = (unsigned long long*)(b.work + 8);
   }
   main_fn f = e.per_step ? select_perstep(D, e.causal != 0, inject, e.per_step)
@@ -492,6 +497,7 @@ extern "C" int ftattn_forward(ftattn_ctx* c, const void* q, const void* k, const
   bufs.recheck = (unsigned long long*)(c->d_stat + STAT_RECHECK);
   bufs.resmax = (uint32_t*)(c->d_stat + STAT_RESMAX);
   bufs.work = c->d_stat + STAT_WORK;
+  bufs.ended = (uint32_t*)(bufs.work + 16);
   uint32_t* range = (uint32_t*)(c->d_stat + STAT_RANGE);
   bufs.range = range + (c->calls & 1u); bufs.range_next = range + ((c->calls + 1u) & 1u);
   hipError_t le = launch_pass(e, c->geo, bufs, q, k, v, o, n_faults > 0, st, c->timing ? c->ev : nullptr);
@@ -598,8 +604,11 @@ extern "C" const char* ftattn_last_error(const ftattn_ctx* c) {
 constexpr size_t STATIC_SCRATCH_BYTES = (size_t)FTATTN_STATIC_SCRATCH_MIB << 20;
 constexpr int STATIC_MAX_EVENTS = 4096;
 constexpr int STATIC_MAX_DEVICES = 64;
-// (behind it what a workgroup may read past the last encoded tile)
-static __device__ __align__(256) unsigned char scratch[STATIC_SCRATCH_BYTES + tiles_beyond(128)];
+// Behind what a workgroup may read past the last encoded tile: Buffers::ended, a word for each number of heads that a call may have
+// (a head takes at least one key and one value tile of head_dim 64).
+constexpr size_t STATIC_ENDED = STATIC_SCRATCH_BYTES + tiles_beyond(128);
+constexpr size_t STATIC_MAX_HEADS = STATIC_SCRATCH_BYTES / (2 * (BN + CKR) * 64 * 2);
+static __device__ __align__(256) unsigned char scratch[STATIC_ENDED + (STATIC_MAX_HEADS + 1) * sizeof(uint32_t)];
 
 static std::mutex g_static_mu;
 static unsigned char* g_static_ptr[STATIC_MAX_DEVICES];      // per device, null until set up
@@ -671,6 +680,7 @@ extern "C" int ftattn_forward_static(const ftattn_config* cfg, const void* q, co
   bufs.ev_count = n_events_dev ? n_events_dev : (int32_t*)base;
   bufs.recheck = (unsigned long long*)(base + 8);
   bufs.work = base + STAT_WORK;
+  bufs.ended = (uint32_t*)(base + STATIC_ENDED) + ((size_t)g.BH <= STATIC_MAX_HEADS ? g.BH : 0);
   bufs.range = (uint32_t*)(base + 16) + (calls & 1u);
   bufs.range_next = (uint32_t*)(base + 16) + ((calls + 1u) & 1u);
   bufs.resmax = (uint32_t*)(base + off_resmax);

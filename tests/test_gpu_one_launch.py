@@ -1,6 +1,8 @@
 """Calls in one launch: heads of one row tile whose key and value tiles fit the ring of the fused kernel (128 keys at head_dim 64,
 192 at head_dim 128) are encoded by its workgroups.  At the edges of tiles and of that rule: the output, bit for bit, and the
 report are those of a timed call, which keeps the launch that encodes; a report is of its own call, whatever the one before counted."""
+import ctypes as C
+
 import numpy as np
 import pytest
 
@@ -125,3 +127,38 @@ def test_static_entry_point_in_one_launch():
         want, _ = _call(ctx, q, k, v, torch.float32, True)
         ctx.close()
         assert torch.equal(o, want) and int(events) == 0
+
+
+def test_static_calls_that_overlap_leave_nothing_behind():
+    """Calls of different numbers of heads that overlap in time, on three streams, may spoil their own counts: those of every call after
+    them are its own.  (All checks fire, so that each workgroup has something to count.)"""
+    lib = ftattn.load_library()
+    def call(x, n_events, stream):
+        cfg = ftattn.Config(struct_size=C.sizeof(ftattn.Config), batch=x.shape[0], heads=x.shape[1], seq=x.shape[2], head_dim=x.shape[3], in_dtype=synth.F16,
+                            out_dtype=ftattn.F32, causal=1, ft_mode=ftattn.FT_DETECT, eps1=1e-7, tau_o=1e-9, max_events=4096)
+        o = outs[tuple(x.shape)]
+        assert lib.ftattn_forward_static(C.byref(cfg), x.data_ptr(), x.data_ptr(), x.data_ptr(), o.data_ptr(), n_events.data_ptr(), C.c_void_p(stream)) == 0
+    shapes = [(1, 3, 64, 64), (20, 16, 128, 64), (2, 35, 70, 64), (3, 100, 150, 128)]
+    data = {s: _tensors(s, synth.F16, s[1])[0] for s in shapes}
+    outs = {s: torch.empty(s, dtype=torch.float32, device="cuda") for s in shapes}
+    want = {}
+    for s, x in data.items():
+        ctx = ftattn.FtAttn(*s, synth.F16, True, ft_mode=ftattn.FT_DETECT, eps1=1e-7, tau_o=1e-9)
+        ctx.forward(x, x, x, outs[s], None, torch.cuda.current_stream().cuda_stream)
+        rep = ctx.report()
+        want[s] = rep.n_events + rep.n_events_dropped
+        ctx.close()
+        assert want[s] > s[0] * s[1]
+    streams = [torch.cuda.Stream() for _ in range(3)]
+    spoilt = torch.zeros(3, dtype=torch.int32, device="cuda")
+    torch.cuda.synchronize()
+    for round_ in range(20):
+        for i, st in enumerate(streams):
+            call(data[shapes[(round_ + i) % len(shapes)]], spoilt[i:i + 1], st.cuda_stream)
+    torch.cuda.synchronize()
+    n = torch.full((1,), -1, dtype=torch.int32, device="cuda")
+    for s in shapes * 3:
+        print(f"[one launch after an overlap] {s}", flush=True)
+        n.fill_(-1)
+        call(data[s], n, torch.cuda.current_stream().cuda_stream)
+        assert int(n) == want[s]
