@@ -610,8 +610,9 @@ __global__ __launch_bounds__(D * 2) void ftattn_finish(const KArgs a) {
 // SELF: the whole call in one launch, for heads of one row tile whose key and value tiles fit the ring (see self_encodes):
 // the workgroup encodes them into LDS itself, each by one wave, in place of a launch that does so in memory.  Nothing else
 // reads them, and what the first launch clears is written whole instead, or cleared by the workgroup that ends last.
-// Measured, in two launches and in one: 1 x 1 x 128 x 64 12.4 and 9.3 us, 4 x 8 x 100 x 64 causal 15.4 and 12.2, 16 x 32 x 128 x 64
-// 26.0 and 20.3, 16 x 32 x 192 x 128 causal 75.5 and 56.0, 2 x 3 x 150 x 128 causal 24.1 and 23.5.
+// Measured, in two launches and in one: 1 x 1 x 128 x 64 12.5 and 9.3 us, 9 x 31 x 128 x 64 causal 22.6 and 16.7, 1 x 4 x 64 x 128 12.6
+// and 10.9, 2 x 3 x 100 x 128 17.1 and 16.1, 2 x 3 x 150 x 128 causal 23.5 and 21.7, 9 x 31 x 64 x 128 25.7 and 23.2 (without checks 19.2
+// and 17.4), 16 x 32 x 192 x 128 70 and 50.
 template <int D, bool FT, bool CAUSAL, bool INJ, int PS = 0, bool SPLIT = false, bool SELF = false>
 __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : FT ? 2 : 3) void ftattn_main(const KArgs a) {
   static_assert(!(SPLIT || SELF) || (PS == 0 && !INJ && SPLIT != SELF), "these run the default verification scheme without a fault list");
@@ -711,7 +712,7 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : FT ? 2 : 3
 
   half8 qf[NSLAB];
   if constexpr (SELF) {
-    // (queries requested first, converted last)
+    // (queries requested first, converted last; registers for both and no more: see encode_v_rows)
     const uint16_t* qp = reinterpret_cast<const uint16_t*>(a.q) + ((size_t)bh * N + (row < N ? row : 0)) * D + 8 * hi;
     uint4v raw[D / 16];
 #pragma unroll
