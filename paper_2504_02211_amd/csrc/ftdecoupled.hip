@@ -212,6 +212,9 @@ template <int E, int I = 0, class F> __device__ __forceinline__ void each(const 
   }
 }
 
+// (Waves per SIMD: the most whose registers hold a row, but for rows of more than 2048 scores with their second evaluations, where four waves
+// spill 5 values and three none: with a causal mask four are the faster ones, without it three: 1 x 4 x 4096 x 64 causal 144.2 and 146.5 us for the
+// whole pass, 1 x 3 x 2500 x 64 causal 66.6 and 67.3, 1 x 2 x 4001 x 64 140.2 and 137.7, 1 x 7 x 2900 x 128 221.9 and 219.6.)
 template <bool FT, bool INJ, int CH>
 __global__ __launch_bounds__(256, INJ ? 1 : CH <= 4 ? 8 : CH == 8 ? 7 : 4) void ftdec_softmax_wave(const SArgs a) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
