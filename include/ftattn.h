@@ -144,7 +144,8 @@ typedef struct {
   int32_t b, h, check;    /* FTATTN_CHECK_* */
   int32_t kv_tile;        /* key-tile iteration (S, EXP); -1 for the post-loop checks (L, O) */
   int32_t row;            /* global query index */
-  int32_t col;            /* S, EXP: global key index; O: feature index; L: 0; -1 = not locatable */
+  int32_t col;            /* S, EXP: global key index (EXP: also of a masked key whose weight is not 0, up to
+                             the end of the key tile); O: feature index; L: 0; -1 = not locatable */
   float residual;         /* S, EXP: log-ratio statistic; L: the offending row-sum; O: sum residual */
   int32_t action;         /* 1 corrected, 0 detected only */
 } ftattn_event;

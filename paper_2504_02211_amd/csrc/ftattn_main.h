@@ -1084,16 +1084,18 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : FT ? 2 : 3
           else if (EW) dev_max = fmax2(dev_max, __builtin_fabsf(dv[0]));
           else if (!DMR) dev_max = dev;
         }
-        else if (!INJ && (PS == 0 || LAZY) && (CAUSAL || D == 128)) {
+        else if (!INJ && (PS == 0 || LAZY) && (CAUSAL || D == 128 || SELF)) {
           // ============ masked tile: is there anything for the exact re-evaluation below to report?  With
-          // every exponential equal to its second evaluation its lambda is -sigma*R1, so the tile passes
+          // every exponential equal to its second evaluation, and every masked weight 0, its lambda is -sigma*R1, so the tile passes
           // there exactly if it passes here.  (Every row tile ends in masked key tiles when causal; the
           // exact path costs about four times as many instructions, with a branch per element: 8 x 16 x 2048 x 64
           // took 201 us with it on every masked tile and 195 with this filter, 4 x 32 x 4096 x 128 976 and 938.
           // The kernels with the injection code have no registers left for it and take the exact path.
           // Without a causal mask only the last key tile can be masked, and at head_dim 64 the filter's registers
-          // and code cost the others more than that tile gains: 8 x 16 x 2048 x 64 takes 286 us without it and 291
-          // with it, 2047 keys 292 and 295, 16 x 12 x 512 x 64 54.2 and 55.4, 333 keys 41.1 and 40.7.)
+          // and code cost the others more than that tile gains where there are many: 8 x 16 x 2048 x 64 takes 278.7 us without it and
+          // 281.3 with it, 16 x 12 x 512 x 64 44.1 and 44.6, 333 keys 18.0 and 17.2.  Calls in one launch have two tiles at
+          // most: 9 x 31 x 100 x 64 15.1 and 14.0.  The choice by the mask compiles to a branch around an exponential that no lane
+          // needs: with all of them evaluated 2 x 3 x 333 x 128 causal takes 27.3 us, like this 25.7.)
           bool bad = false;
           uint32_t diff = 0u;
           n_ok = opaque(n_ok);      // (the 32 comparisons are made again: kept, they would take 64 scalar registers)
@@ -1105,10 +1107,9 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : FT ? 2 : 3
 #pragma unroll
               for (int gg = 0; gg < 4; ++gg) {
                 const int v = 4 * gg + r;
-                const bool ok = valid(kb, v);
                 sum1 += s[kb][v];
                 const uint32_t pe = as_u(ex2(__builtin_fmaf(opaque(s[kb][v]), sl2, negm)));
-                diff |= ok ? pe ^ as_u(p[kb][v]) : 0u;
+                diff |= (valid(kb, v) ? pe : 0u) ^ as_u(p[kb][v]);       // (a masked weight is 0)
               }
             bad |= !(a.scale * __builtin_fabsf((sc[r] + sc[4 + r]) - sum1) <= a.eps1);
           }
@@ -1119,6 +1120,20 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : FT ? 2 : 3
           // lambda = ln prod P - (sigma*check1_eff - n_valid*m) = sum_l (ln P_l - x_l) - sigma*R1.
           bool lin_fixed = false, logged = false;
           n_ok = opaque(n_ok);
+          // (hi, formed again: nothing of this path is kept in registers outside it)
+          const int half = __builtin_amdgcn_mbcnt_hi((uint32_t)opaque(-1), __builtin_amdgcn_mbcnt_lo((uint32_t)opaque(-1), 0u)) >> 5;
+          auto exponent = [&](const int kb, const int v) __attribute__((always_inline)) -> float {      // (-inf where masked: the weight is 0)
+            return __builtin_fmaf(valid(kb, v) ? s[kb][v] : -__builtin_inff(), sl2, negm);
+          };
+          // Weights of masked scores are in no sum: they are 0 (or NaN, where the row has no finite maximum).
+          uint32_t masked = 0u;
+          if (g_mask)
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+              for (int v = 0; v < 16; ++v) masked |= valid(kb, v) ? 0u : as_u(p[kb][v]);
+          const bool stray = masked != 0u && ex2(__builtin_fmaf(-__builtin_inff(), sl2, negm)) == 0.f;
+          n_ok = opaque(n_ok);      // (comparisons made again, as above)
           if (EW) {
             // the whole tile row as one class (fold index = position of the key in the tile): every
             // sum is the lane's half plus its partner's, formed by all lanes alike (the exchanges
@@ -1129,13 +1144,13 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : FT ? 2 : 3
             for (int r = 0; r < 4; ++r) {
               const float c1 = sc[r] + sc[4 + r];
               chk1 += c1;
-              chk2 += 8.0f * (sc[8 + r] + sc[12 + r]) + (float)(4 * hi + r - 7) * c1;
+              chk2 += 8.0f * (sc[8 + r] + sc[12 + r]) + (float)(4 * half + r - 7) * c1;
             }
 #pragma unroll
             for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
               for (int v = 0; v < 16; ++v) {
-                const int l = key_of(kb, v, hi);
+                const int l = key_of(kb, v, half);
                 const bool ok = valid(kb, v);
                 const float sv = s[kb][v];
                 sum1 += sv;
@@ -1150,10 +1165,10 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : FT ? 2 : 3
                 }
               }
             sum1 = sum32(sum1); sum2 = sum32(sum2); E = sum32(E); chk1 = sum32(chk1); chk2 = sum32(chk2);
-            nvalid += (int)xchg32((float)nvalid, hi);
+            nvalid += (int)xchg32((float)nvalid, half);
             {
-              const float bigp = xchg32(big, hi);
-              const int lp = (int)xchg32((float)l_big, hi);
+              const float bigp = xchg32(big, half);
+              const int lp = (int)xchg32((float)l_big, half);
               if (bigp > big) l_big = lp; else if (bigp == big) l_big = -1;
             }
             const float R1 = chk1 - sum1;
@@ -1176,20 +1191,20 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : FT ? 2 : 3
             for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
               for (int v = 0; v < 16; ++v)
-                if (key_of(kb, v, hi) != lstar) rest += s[kb][v];
+                if (key_of(kb, v, half) != lstar) rest += s[kb][v];
             rest = sum32(rest);
-            if (det) {
+            if (det || stray) {
               logged = true;
-              if (linear) {
+              if (det && linear) {
                 const bool fix = a.correct && lstar >= 0;
-                if (hi == 0) log_event(a, bh, FTATTN_CHECK_S, j0 + i, row, lstar >= 0 ? k0 + lstar : -1, lam, fix ? 1 : 0);
+                if (half == 0) log_event(a, bh, FTATTN_CHECK_S, j0 + i, row, lstar >= 0 ? k0 + lstar : -1, lam, fix ? 1 : 0);
                 if (fix) {
                   const float val = chk1 - rest;
 #pragma unroll
                   for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
                     for (int v = 0; v < 16; ++v)
-                      if (key_of(kb, v, hi) == lstar) s[kb][v] = val;
+                      if (key_of(kb, v, half) == lstar) s[kb][v] = val;
                   lin_fixed = true;
                 }
               } else {
@@ -1197,10 +1212,9 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : FT ? 2 : 3
                 for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
                   for (int v = 0; v < 16; ++v) {
-                    const int key = k0 + key_of(kb, v, hi);
-                    const bool ok = valid(kb, v);
-                    const float pe = ex2(__builtin_fmaf(s[kb][v], sl2, negm));
-                    if (ok && as_u(pe) != as_u(p[kb][v])) {
+                    const int key = k0 + key_of(kb, v, half);
+                    const float pe = ex2(exponent(kb, v));
+                    if (as_u(pe) != as_u(p[kb][v])) {
                       log_event(a, bh, FTATTN_CHECK_EXP, j0 + i, row, key, lam, a.correct ? 1 : 0);
                       if (a.correct) p[kb][v] = pe;
                     }
@@ -1231,11 +1245,11 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : FT ? 2 : 3
               }
             float R1 = chk1 - sum1;
             float lam = LN2 * E - a.scale * R1;
-            const bool linear = !(a.scale * __builtin_fabsf(R1) <= 0.5f * a.eps1);
+            const bool linear = !(a.scale * __builtin_fabsf(R1) * 2.0f <= a.eps1);
             bool det = nvalid > 0 && (DMR ? (linear || differs) : (!(__builtin_fabsf(lam) <= a.eps1) || (STEP && linear)));
-            if (det) {
+            if (det || stray) {
               logged = true;
-              if (linear) {
+              if (det && linear) {
                 float chk2 = sc[8 + r] + sc[12 + r];
                 float sum2 = 0.f, big = -1.f;
                 int l_big = -1;
@@ -1256,7 +1270,7 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : FT ? 2 : 3
                 } else {
                   lstar = l_big;   // residuals left the fp32 range: the fold of overwhelming size
                 }
-                int col = lstar >= 0 ? k0 + 32 * (lstar >> 2) + 8 * (lstar & 3) + 4 * hi + r : -1;
+                int col = lstar >= 0 ? k0 + 32 * (lstar >> 2) + 8 * (lstar & 3) + 4 * half + r : -1;
                 bool fix = a.correct && lstar >= 0;
                 log_event(a, bh, FTATTN_CHECK_S, j0 + i, row, col, lam, fix ? 1 : 0);
                 if (fix) {
@@ -1279,10 +1293,9 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : FT ? 2 : 3
                 for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
                   for (int gg = 0; gg < 4; ++gg) {
-                    int v = 4 * gg + r, key = k0 + key_of(kb, v, hi);
-                    bool ok = valid(kb, v);
-                    float pe = ex2(__builtin_fmaf(s[kb][v], sl2, negm));
-                    if (ok && as_u(pe) != as_u(p[kb][v])) {
+                    int v = 4 * gg + r, key = k0 + key_of(kb, v, half);
+                    float pe = ex2(exponent(kb, v));
+                    if (as_u(pe) != as_u(p[kb][v])) {
                       log_event(a, bh, FTATTN_CHECK_EXP, j0 + i, row, key, lam, a.correct ? 1 : 0);
                       if (a.correct) p[kb][v] = pe;
                     }
@@ -1294,7 +1307,7 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : FT ? 2 : 3
           if (wave_any(logged)) wait_vmcnt<0>();
           // a repaired score changes the row's maximum and exponentials: recompute the row
           // (the exchange is a wave-wide operation: evaluate it outside any per-lane short circuit)
-          const float partner_fixed = xchg32(lin_fixed ? 1.f : 0.f, hi);
+          const float partner_fixed = xchg32(lin_fixed ? 1.f : 0.f, half);
           bool redo = lin_fixed | (partner_fixed != 0.f);
           if (wave_any(redo)) {
             float mx2 = -__builtin_inff();
