@@ -269,6 +269,15 @@ extern "C" int ftattn_split_of(const ftattn_config* cfg, int64_t out[4]) {
   return FTATTN_OK;
 }
 
+// For the tests, and no part of the interface: 1 where a call without a fault list is one launch.
+extern "C" int ftattn_in_one_launch(const ftattn_config* cfg) {
+  ftattn_config e;
+  Geometry g;
+  const char* why;
+  if (int rc = resolve_config(cfg, e, g, why)) return rc;
+  return in_one_launch(e, g);
+}
+
 // Lets the kernels that a configuration runs, with a fault list or without one, use their dynamic LDS.  Needs the
 // device current.  (Only those: a call to the runtime for each takes about 10 us of the 110 to 300 that creating a
 // context takes.)

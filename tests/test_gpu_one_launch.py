@@ -59,6 +59,31 @@ def test_one_launch_gives_what_two_give(shape, causal):
         ctx.close()
 
 
+@pytest.mark.parametrize("shape", [(1, 6, 128, 64), (1, 6, 90, 64), (1, 6, 192, 128), (1, 6, 70, 128)])
+@pytest.mark.parametrize("dtype", [synth.F16, synth.BF16])
+@pytest.mark.parametrize("causal", [False, True])
+def test_infinities_and_nan(shape, dtype, causal):
+    """One head each with an infinity or NaN in an operand, with the type's lowest value, and with keys whose scores are all -inf (in bf16
+    by the conversion to fp16): outputs and reports of one launch and of two."""
+    print(f"[one launch, not finite] {shape} dtype {dtype} causal {causal}", flush=True)
+    q, k, v = _tensors(shape, dtype, shape[2])
+    n = shape[2]
+    q[0, 0, n // 2, 3] = float("inf")
+    k[0, 1, n - 1, 5] = float("-inf")
+    v[0, 2, 0, 7] = float("nan")
+    k[0, 3, n // 3] = torch.finfo(k.dtype).min
+    q[0, 4, :, 0], q[0, 4, :, 1:], k[0, 4, :, 0] = 1.0, 0.0, float("-inf")
+    v[0, 5, n // 2, 1] = float("inf")
+    for mode in (ftattn.FT_CORRECT, ftattn.FT_DETECT, ftattn.FT_OFF):
+        ctx = ftattn.FtAttn(*shape, dtype, causal, ft_mode=mode, max_events=1 << 20)
+        one, r1 = _call(ctx, q, k, v, torch.float32, False)
+        two, r2 = _call(ctx, q, k, v, torch.float32, True)
+        _same(one, two, r1, r2)
+        assert not r1.event_set() ^ r2.event_set() and (mode == ftattn.FT_OFF or r1.n_events > 0)
+        assert bool(torch.isnan(one[0, 0, n // 2]).all()) and bool(torch.isnan(one[0, 2, n - 1, 7])) and bool(torch.isfinite(one[0, 2, :, 8:]).all())
+        ctx.close()
+
+
 @pytest.mark.parametrize("shape", [(2, 3, 127, 64), (1, 300, 70, 64), (2, 5, 192, 128)])
 def test_reports_are_of_their_own_call(shape):
     """Thresholds far below rounding make every check fire; values that fp16 cannot hold set range flags.  Calls in one and

@@ -9,17 +9,23 @@ pytest.importorskip("torch")
 from paper_2504_02211_amd import ftattn
 import test_gpu_gemm_narrow as narrow
 import test_gpu_gemm_tiles as tiles
+import test_gpu_one_launch as one_launch
 import test_gpu_report_after_replay as replay
 import test_gpu_split_keys as split_keys
+import test_short_contractions as short
 
-TILES = ["wide", "half", "quarter", "strip", "narrow", "slim", "narrow2", "slim2"]
+TILES = ["wide", "half", "quarter", "strip", "narrow", "slim", "narrow2", "slim2", "low"]
 
 
-def split_of(batch, heads, seq, head_dim, causal, **options):
+def config(batch, heads, seq, head_dim, causal, **options):
+    return ftattn.Config(struct_size=C.sizeof(ftattn.Config), batch=batch, heads=heads, seq=seq, head_dim=head_dim, in_dtype=0, out_dtype=2,
+                         causal=int(causal), **{"ft_mode": ftattn.FT_CORRECT, **options})
+
+
+def split_of(*shape, **options):
     """(row tiles that are not split, shares of the longest row tile that is, or 1, key tiles of a share at most, bytes of state)"""
     lib = ftattn.load_library()
-    cfg = ftattn.Config(struct_size=C.sizeof(ftattn.Config), batch=batch, heads=heads, seq=seq, head_dim=head_dim, in_dtype=0, out_dtype=2,
-                        causal=int(causal), ft_mode=ftattn.FT_CORRECT, **options)
+    cfg, seq = config(*shape, **options), shape[2]
     out = (C.c_int64 * 4)()
     assert lib.ftattn_split_of(C.byref(cfg), out) == 0
     first, piece, shares, state = out
@@ -55,10 +61,23 @@ def test_ablation_modes_are_not_divided(options):
     assert split_of(1, 1, 1024, 128, False, **options)[1] == 1
 
 
+def test_the_calls_that_are_one_launch():
+    lib = ftattn.load_library()
+    for shape in one_launch.SHAPES:
+        for causal in (False, True):
+            for options in ({}, dict(ft_mode=ftattn.FT_OFF), dict(ft_mode=ftattn.FT_DETECT), dict(rowsum_fold=1)):
+                one = lib.ftattn_in_one_launch(C.byref(config(*shape, causal, **options)))
+                assert one == (shape[2] <= {64: 128, 128: 192}[shape[3]]), (shape, causal, options)
+            for options in (dict(per_step=1), dict(per_step=2), dict(stride=1), dict(rescale_margin=4.0)):
+                assert lib.ftattn_in_one_launch(C.byref(config(*shape, causal, **options))) == 0
+    assert {lib.ftattn_in_one_launch(C.byref(config(*shape, True))) for shape in one_launch.SHAPES} == {0, 1}
+
+
 def test_tile_shapes_of_the_linear_layer_are_what_the_tests_of_them_say():
     assert {s: (gemm_plan_of(*s), gemm_plan_of(s[1], s[0], s[2])) for s in tiles.PLANS} == tiles.PLANS
     assert {s: gemm_plan_of(*s) for s in narrow.PLANS} == narrow.PLANS
-    seen = [plan for pair in tiles.PLANS.values() for plan in pair] + list(narrow.PLANS.values())
+    seen = [plan for pair in tiles.PLANS.values() for plan in pair] + list(narrow.PLANS.values()) + [gemm_plan_of(*s) for s, low in short.SHAPES.items() if low]
+    assert TILES[short.LOW] == "low"
     assert {tile for tile, _ in seen} == set(TILES) and {parts for _, parts in seen} == {1, 2, 4, 8, 16}
 
 
