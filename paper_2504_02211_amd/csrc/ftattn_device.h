@@ -93,7 +93,8 @@ __device__ __forceinline__ float xchg32(float x, int hi) {
   auto r = __builtin_amdgcn_permlane32_swap(as_u(x), as_u(x), false, false);
   return as_f(hi ? r[0] : r[1]);
 }
-// (as an instruction: the compiler would first quieten both values, which come out of a maximum already)
+// (as an instruction: the compiler would first quieten both values, which come out of a maximum already; it does quieten the result, and
+// the running maximum, before it compares the two)
 __device__ __forceinline__ float max32(float x) {
   auto r = __builtin_amdgcn_permlane32_swap(as_u(x), as_u(x), false, false);
   float m;

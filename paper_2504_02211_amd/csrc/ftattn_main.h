@@ -745,14 +745,15 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : FT ? 2 : 3
     if (rbits) atomicOr(a.range, rbits);
     __syncthreads();
   } else {
-  // The first key tile and the queries are waited for, unit 0 is not: GEMM I of the first tile needs nothing else.  Where
-  // workgroups follow one another on a CU, unit 0 is requested right behind them, and its latency no longer stands between
+  // The first key tile and the queries are waited for, unit 0 is not: GEMM I of the first tile needs nothing else.  From one
+  // workgroup per CU on, unit 0 is requested right behind them, and its latency no longer stands between
   // the first two key tiles: 16 x 12 x 512 x 64 48.9 -> 45.7 us, 4 x 16 x 1000 x 64 causal 38.9 -> 37.6, 8 x 32 x 512 x 128 causal 97.8 -> 95.2,
   // 1 x 32 x 16384 x 128 causal 2845 -> 2818.  (Loads are waited for in their order, and the compiler, which counts the queries
   // only, would wait for unit 0 as well: so the queries are loaded, unit 0 requested and the wait made in one block.)  Elsewhere
   // it is requested when the queries are there: the first workgroup of every CU at once would only get its queries
   // later (2 x 8 x 300 x 128 27.6 and 28.0 us), and beside a second workgroup with many key tiles nothing is gained (8 x 16 x 2048 x 64
-  // causal 183.7 and 186.2).
+  // causal 183.7 and 186.2; 16 key tiles still gain, 32 lose; where two share a CU and 256 row tiles fill half of their places it gains
+  // or loses 1 %: 4 x 16 x 512 x 64 23.5 and 23.6, 4 x 8 x 1000 x 64 34.8 and 34.7, 3 x 8 x 1500 x 64 causal 42.2 and 42.6).
   const bool early = a.n_tiles >= 256 && (D == 128 || a.Tj <= 24);
 #pragma unroll
   for (int n = 0; n < U::KPW; ++n) issue_piece(n);

@@ -123,8 +123,12 @@ size_t gemm_workspace(long long m, long long n, GPlan plan) {
 // A K of one or two steps is nearly all start and store: from a little more than one tile per CU on, tiles that keep one stage and run two
 // to a CU beat those with a ring, whose workgroup does one after the other: 16384 x 4096 x 64 69.7 -> 54.5 us, 4096 x 2560 x 64 (320
 // tiles) 21.8 -> 12.5, 16384 x 8192 x 128 131 -> 115, 2400 x 4000 x 128 (304) 14.3 -> 14.1, Q K^T of 4 x 1501 x 64 (288) 66.6 -> 58.7 for the
-// whole scheme.  Below that they lose (2048 x 2048 x 128, 128 tiles: 8.1 and 10.8; 8 x 1000 x 64, 256: 37.4 and 38.8), as with four steps
-// (16384 x 2048 x 256 37.5 and 38.5).
+// whole scheme.  Below that they lose (2048 x 2048 x 128, 128 tiles: 8.1 and 10.8; 2000 x 3400 x 64, 224: 9.7 and 10.4; 2300 x 3500 x 128, 252: 14.0
+// and 22.2; 8 x 1000 x 64, 256: 40.8 and 41.2), as with four steps (16384 x 2048 x 256 37.5 and 38.5).  In between it goes either way (2300 x 3800 x 64,
+// 270 tiles: 21.5 and 12.8; 2300 x 4000 x 128, 288: 14.2 and 14.1; 4352 x 1900 x 64, 272: 30.8 and 21.9), so each line stands below
+// the smallest count at which nothing measured lost.  Tiles are counted above the diagonal too, which a causal Q K^T does not launch: of 288 to 400 it launches
+// 168 to 290, and still gains (the whole scheme, 3 x 3 x 1024 x 128, 180 launched: 39.1 -> 37.6 us, 4 x 9 x 512 x 64, 216: 42.3 -> 34.4, 1 x 2 x 2560 x 64, 220:
+// 59.1 -> 56.3) or loses nothing (4 x 1501 x 64, 168: 52.1 and 52.9).
 GPlan gemm_plan(long long m, long long n, long long k, int batch, bool inject, bool may_split) {
   if (inject) return {TILE_QUARTER, 1};
   static constexpr struct { int tile, max_n; double fixed, step, load; } COST[] = {
