@@ -625,6 +625,10 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : FT ? 2 : 3
   // one and the rescale of the output falls away.  Exponentials then reach e^margin; every identity of
   // Algorithm 1 holds with the reference in place of the maximum (Section 3.4, case 1).
   constexpr bool LAZY = PS == 4;
+  // What becomes of a masked tile (see there): FILTER, looked through for anything to re-evaluate exactly; else always re-evaluated.  CONSTANT: the
+  // weights of its masked keys are chosen to be 0 behind their exponentials, so that none of those is used; else they are checked like any other.
+  constexpr bool FILTER = FT && !INJ && (PS == 0 || LAZY) && (CAUSAL || D == 128 || SELF);
+  constexpr bool CONSTANT = FT && !INJ && (PS == 0 || LAZY) && !FILTER && !SPLIT;
   using U = Unit<D, FT>;
   constexpr int NWAVE = U::NWAVE, BM = NWAVE * 32, NSTAGE = U::NSTAGE;
   constexpr bool ALT = NWAVE == 8;      // two wave groups alternating between the phases (else: free-running waves)
@@ -993,6 +997,11 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : FT ? 2 : 3
         for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
           for (int v = 0; v < 16; ++v) p[kb][v] = ex2(__builtin_fmaf(p[kb][v], sl2, negm));
+        if (CONSTANT)
+#pragma unroll
+          for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) p[kb][v] = valid(kb, v) ? p[kb][v] : 0.f;
       }
 
       // ---- injection point: exponentials
@@ -1085,7 +1094,7 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : FT ? 2 : 3
           else if (EW) dev_max = fmax2(dev_max, __builtin_fabsf(dv[0]));
           else if (!DMR) dev_max = dev;
         }
-        else if (!INJ && (PS == 0 || LAZY) && (CAUSAL || D == 128 || SELF)) {
+        else if (FILTER) {
           // ============ masked tile: is there anything for the exact re-evaluation below to report?  With
           // every exponential equal to its second evaluation, and every masked weight 0, its lambda is -sigma*R1, so the tile passes
           // there exactly if it passes here.  (Every row tile ends in masked key tiles when causal; the
@@ -1094,8 +1103,10 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : FT ? 2 : 3
           // The kernels with the injection code have no registers left for it and take the exact path.
           // Without a causal mask only the last key tile can be masked, and at head_dim 64 the filter's registers
           // and code cost the others more than that tile gains where there are many: 8 x 16 x 2048 x 64 takes 278.7 us without it and
-          // 281.3 with it, 16 x 12 x 512 x 64 44.1 and 44.6, 333 keys 18.0 and 17.2.  Calls in one launch have two tiles at
-          // most: 9 x 31 x 100 x 64 15.1 and 14.0.  The choice by the mask compiles to a branch around an exponential that no lane
+          // 281.3 with it, 16 x 12 x 512 x 64 44.1 and 44.6, 333 keys 18.0 and 17.2.  (There choosing masked weights costs 0.1 us, their
+          // check 0.4 to 0.7 of the exact path: 2 x 3 x 333 x 64 17.6 and 18.0, 4 x 3 x 891 x 64 29.1 and 29.6; where keys are divided the choice
+          // made the loop longer instead, also without a masked tile: 1 x 5 x 3008 x 64 47.9 and 46.0.)  Calls in one launch have two
+          // tiles at most: 9 x 31 x 100 x 64 15.1 and 14.0.  The choice by the mask compiles to a branch around an exponential that no lane
           // needs: with all of them evaluated 2 x 3 x 333 x 128 causal takes 27.3 us, like this 25.7.)
           bool bad = false;
           uint32_t diff = 0u;
@@ -1123,17 +1134,15 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : FT ? 2 : 3
           n_ok = opaque(n_ok);
           // (hi, formed again: nothing of this path is kept in registers outside it)
           const int half = __builtin_amdgcn_mbcnt_hi((uint32_t)opaque(-1), __builtin_amdgcn_mbcnt_lo((uint32_t)opaque(-1), 0u)) >> 5;
-          auto exponent = [&](const int kb, const int v) __attribute__((always_inline)) -> float {      // (-inf where masked: the weight is 0)
-            return __builtin_fmaf(valid(kb, v) ? s[kb][v] : -__builtin_inff(), sl2, negm);
-          };
-          // Weights of masked scores are in no sum: they are 0 (or NaN, where the row has no finite maximum).
+          // Weights of masked scores are in no sum: they are 0 (or NaN, where the row has no finite maximum).  One that is not, is replaced below.
           uint32_t masked = 0u;
-          if (g_mask)
+          if (g_mask && !CONSTANT)
 #pragma unroll
             for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
               for (int v = 0; v < 16; ++v) masked |= valid(kb, v) ? 0u : as_u(p[kb][v]);
-          const bool stray = masked != 0u && ex2(__builtin_fmaf(-__builtin_inff(), sl2, negm)) == 0.f;
+          const float none = CONSTANT ? 0.f : ex2(__builtin_fmaf(-__builtin_inff(), sl2, negm));
+          const bool stray = masked != 0u && none == 0.f;
           n_ok = opaque(n_ok);      // (comparisons made again, as above)
           if (EW) {
             // the whole tile row as one class (fold index = position of the key in the tile): every
@@ -1214,7 +1223,7 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : FT ? 2 : 3
 #pragma unroll
                   for (int v = 0; v < 16; ++v) {
                     const int key = k0 + key_of(kb, v, half);
-                    const float pe = ex2(exponent(kb, v));
+                    const float pe = valid(kb, v) ? ex2(__builtin_fmaf(s[kb][v], sl2, negm)) : none;
                     if (as_u(pe) != as_u(p[kb][v])) {
                       log_event(a, bh, FTATTN_CHECK_EXP, j0 + i, row, key, lam, a.correct ? 1 : 0);
                       if (a.correct) p[kb][v] = pe;
@@ -1295,7 +1304,7 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : FT ? 2 : 3
 #pragma unroll
                   for (int gg = 0; gg < 4; ++gg) {
                     int v = 4 * gg + r, key = k0 + key_of(kb, v, half);
-                    float pe = ex2(exponent(kb, v));
+                    float pe = valid(kb, v) ? ex2(__builtin_fmaf(s[kb][v], sl2, negm)) : none;
                     if (as_u(pe) != as_u(p[kb][v])) {
                       log_event(a, bh, FTATTN_CHECK_EXP, j0 + i, row, key, lam, a.correct ? 1 : 0);
                       if (a.correct) p[kb][v] = pe;
