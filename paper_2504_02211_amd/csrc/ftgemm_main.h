@@ -26,9 +26,9 @@
 // its end, where the last operands of the stage are in registers, so that no wave waits for LDS after it.
 //
 // Measured (16384 tokens, 4096 -> 16384 features, fp16): 1810-1950 us protected (by the clock that a card's power allows; 1859 where the
-// epilogue in which every wave formed all verdicts took 1884), 1660-1700 us with the checks compiled out, against 2250 / 1930 us for one 32-token row of 32x32x16 blocks per wave.  Four waves of 8 x 8
-// blocks would read a third less LDS, but their 288 accumulators do not fit next to the operands without
-// register copies in the loop.
+// epilogue in which every wave formed all verdicts took 1884), 1660-1700 us with the checks compiled out, against
+// 2250 / 1930 us for one 32-token row of 32x32x16 blocks per wave.  Four waves of 8 x 8 blocks would read a third less
+// LDS, but their 288 accumulators do not fit next to the operands without register copies in the loop.
 #pragma once
 #include "ftattn_main.h"
 #include "ftgemm.h"
