@@ -1106,8 +1106,8 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : FT ? 2 : 3
           // 281.3 with it, 16 x 12 x 512 x 64 44.1 and 44.6, 333 keys 18.0 and 17.2.  (There choosing masked weights costs 0.1 us, their
           // check 0.4 to 0.7 of the exact path: 2 x 3 x 333 x 64 17.6 and 18.0, 4 x 3 x 891 x 64 29.1 and 29.6; where keys are divided the choice
           // made the loop longer instead, also without a masked tile: 1 x 5 x 3008 x 64 47.9 and 46.0.)  Calls in one launch have two
-          // tiles at most: 9 x 31 x 100 x 64 15.1 and 14.0.  The choice by the mask compiles to a branch around an exponential that no lane
-          // needs: with all of them evaluated 2 x 3 x 333 x 128 causal takes 27.3 us, like this 25.7.)
+          // tiles at most: 9 x 31 x 100 x 64 15.1 and 14.0.  The second evaluation is chosen to be 0 where masked, not skipped there: skipped, it
+          // compiled to 32 regions with an execution mask of their own, 2 x 3 x 333 x 128 causal 26.1 us, like this 25.7.)
           bool bad = false;
           uint32_t diff = 0u;
           n_ok = opaque(n_ok);      // (the 32 comparisons are made again: kept, they would take 64 scalar registers)
@@ -1134,6 +1134,9 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : FT ? 2 : 3
           n_ok = opaque(n_ok);
           // (hi, formed again: nothing of this path is kept in registers outside it)
           const int half = __builtin_amdgcn_mbcnt_hi((uint32_t)opaque(-1), __builtin_amdgcn_mbcnt_lo((uint32_t)opaque(-1), 0u)) >> 5;
+          auto exponent = [&](const int kb, const int v) __attribute__((always_inline)) -> float {      // (-inf where masked: the weight is 0)
+            return __builtin_fmaf(valid(kb, v) ? s[kb][v] : -__builtin_inff(), sl2, negm);
+          };
           // Weights of masked scores are in no sum: they are 0 (or NaN, where the row has no finite maximum).  One that is not, is replaced below.
           uint32_t masked = 0u;
           if (g_mask && !CONSTANT)
@@ -1141,8 +1144,8 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : FT ? 2 : 3
             for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
               for (int v = 0; v < 16; ++v) masked |= valid(kb, v) ? 0u : as_u(p[kb][v]);
-          const float none = CONSTANT ? 0.f : ex2(__builtin_fmaf(-__builtin_inff(), sl2, negm));
-          const bool stray = masked != 0u && none == 0.f;
+          auto none = [&]() __attribute__((always_inline)) -> float { return ex2(__builtin_fmaf(-__builtin_inff(), sl2, negm)); };
+          const bool stray = !CONSTANT && masked != 0u && none() == 0.f;
           n_ok = opaque(n_ok);      // (comparisons made again, as above)
           if (EW) {
             // the whole tile row as one class (fold index = position of the key in the tile): every
@@ -1223,7 +1226,7 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : FT ? 2 : 3
 #pragma unroll
                   for (int v = 0; v < 16; ++v) {
                     const int key = k0 + key_of(kb, v, half);
-                    const float pe = valid(kb, v) ? ex2(__builtin_fmaf(s[kb][v], sl2, negm)) : none;
+                    const float pe = ex2(exponent(kb, v));
                     if (as_u(pe) != as_u(p[kb][v])) {
                       log_event(a, bh, FTATTN_CHECK_EXP, j0 + i, row, key, lam, a.correct ? 1 : 0);
                       if (a.correct) p[kb][v] = pe;
@@ -1304,7 +1307,8 @@ __global__ __launch_bounds__(nwave_of(D) * 64, nwave_of(D) == 8 ? 1 : FT ? 2 : 3
 #pragma unroll
                   for (int gg = 0; gg < 4; ++gg) {
                     int v = 4 * gg + r, key = k0 + key_of(kb, v, half);
-                    float pe = valid(kb, v) ? ex2(__builtin_fmaf(s[kb][v], sl2, negm)) : none;
+                    // (a masked weight by the same choice as its first evaluation)
+                    float pe = !CONSTANT ? ex2(exponent(kb, v)) : valid(kb, v) ? ex2(__builtin_fmaf(s[kb][v], sl2, negm)) : none();
                     if (as_u(pe) != as_u(p[kb][v])) {
                       log_event(a, bh, FTATTN_CHECK_EXP, j0 + i, row, key, lam, a.correct ? 1 : 0);
                       if (a.correct) p[kb][v] = pe;
