@@ -177,9 +177,9 @@ def test_static_calls_that_overlap_leave_nothing_behind():
     streams = [torch.cuda.Stream() for _ in range(3)]
     spoilt = torch.zeros(3, dtype=torch.int32, device="cuda")
     torch.cuda.synchronize()
-    for round_ in range(20):
+    for turn in range(20):
         for i, st in enumerate(streams):
-            call(data[shapes[(round_ + i) % len(shapes)]], spoilt[i:i + 1], st.cuda_stream)
+            call(data[shapes[(turn + i) % len(shapes)]], spoilt[i:i + 1], st.cuda_stream)
     torch.cuda.synchronize()
     n = torch.full((1,), -1, dtype=torch.int32, device="cuda")
     for s in shapes * 3:
